@@ -497,7 +497,7 @@ int neat_distance(const neat_dims *d, const float *nodes, const float *conns, in
     if (d->P == 0 || Q == 0) return NEAT_OK;
     if (!nodes || !rnodes || !out || (d->C_max > 0 && (!conns || !rconns)))
         return fail(NEAT_E_INVALID, "nodes, conns, rnodes, rconns or out is NULL");
-    const size_t lds = neat::distance_lds_bytes(d->N_max, d->C_max);
+    const size_t lds = neat::gene_tables_lds_bytes(d->N_max, d->C_max);
     if (lds > max_lds_bytes())
         return fail(NEAT_E_TOO_LARGE,
                     "distance with N_max=%d, C_max=%d needs %zu B of LDS, device allows %zu",
@@ -506,7 +506,7 @@ int neat_distance(const neat_dims *d, const float *nodes, const float *conns, in
     L.nodes = nodes, L.conns = conns, L.rnodes = rnodes, L.rconns = rconns, L.out = out;
     L.P = d->P, L.Q = Q, L.N = d->N_max, L.C = d->C_max;
     L.cd = c_disjoint, L.ch = c_homologous;
-    hipError_t e = neat::distance_launch(L, (hipStream_t)stream);
+    hipError_t e = neat::distance_launch(L, max_lds_bytes(), (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "distance launch");
     return NEAT_OK;
 }

@@ -10,8 +10,10 @@
 namespace neat {
 
 // out [P][Q] = distance of genome p (nodes/conns [P][N][5] / [P][C][4]) to
-// representative q (rnodes/rconns [Q][N][5] / [Q][C][4]); hn, hc are set by
-// distance_launch (hash table sizes).
+// representative q (rnodes/rconns [Q][N][5] / [Q][C][4]).  The fields from hn
+// on are set by distance_launch: hash table sizes, representatives per group,
+// genomes per workgroup, workgroups per group, and whether the connection
+// tensors are 16-byte aligned.
 struct DistLaunch {
     const float *nodes;
     const float *conns;
@@ -20,13 +22,14 @@ struct DistLaunch {
     float *out;
     int P, Q, N, C;
     float cd, ch;
-    int hn, hc;
+    int hn, hc, hn_log2, hc_log2;
+    int rq, per_block, blocks_per_group, vec;
 };
 
-size_t distance_lds_bytes(int N, int C);
-// LDS of the two gene hash tables alone (what crossover uses)
+// LDS of the two gene hash tables of one genome (what crossover uses, and
+// the distance for the largest genomes)
 size_t gene_tables_lds_bytes(int N, int C);
-hipError_t distance_launch(DistLaunch L, hipStream_t stream);
+hipError_t distance_launch(DistLaunch L, size_t max_lds, hipStream_t stream);
 
 // children cn/cc [Pc][N][5] / [Pc][C][4] of the parent pairs [Pc][2] of
 // nodes/conns [P][N][5] / [P][C][4], with uniform numbers rn [Pc][N], rc

@@ -15,13 +15,15 @@
 //   per kind (cd (|A| + |B| - 2 h) + ch sum) / max(|A|, |B|), 0 when both
 //   are empty; the distance is the node part plus the connection part.
 //
-// A workgroup takes eight genomes (two per wave) and loops over the
-// representatives: B's genes go into LDS hash tables (key bits -> first
-// row, by atomic min), built once for the eight, then every lane probes the
-// tables with its A genes and each wave sums counts and attribute
-// distances.  Keys are compared as floats: -0 is folded into +0
-// before hashing, and a connection whose out key is NaN never matches.
+// Two kernels: distance_dict_kernel (a dictionary of the keys of up to 16
+// representatives in LDS, one lookup per gene for all of them), and
+// distance_kernel (a table per representative) where not even one
+// representative's dictionary fits.  Keys are compared as floats: -0 is
+// folded into +0 before hashing, and a connection whose out key is NaN
+// never matches.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "genes.h"
 
@@ -102,16 +104,6 @@ __device__ __forceinline__ void insert(unsigned long long *hk, int *hr, int H,
     }
 }
 
-__device__ __forceinline__ int lookup_from(const unsigned long long *hk, const int *hr, int H,
-                                           unsigned long long key, unsigned s) {
-    for (;;) {
-        const unsigned long long k = hk[s];
-        if (k == key) return hr[s];
-        if (k == EMPTY64) return -1;
-        s = (s + 1) & (unsigned)(H - 1);
-    }
-}
-
 __device__ __forceinline__ int lookup(const unsigned long long *hk, const int *hr, int H,
                                       unsigned long long key) {
     unsigned s = mix(key, H);
@@ -123,21 +115,358 @@ __device__ __forceinline__ int lookup(const unsigned long long *hk, const int *h
     }
 }
 
-// DIST_WAVES waves per workgroup, DIST_PER_WAVE genomes per wave: a
-// representative's tables are built once for DIST_WAVES * DIST_PER_WAVE
-// genomes.
+// ---- distance by dictionary.
+//
+// A workgroup takes up to R representatives and a run of genomes.  Every
+// distinct key of its representatives gets one entry in an LDS hash table
+// that holds, beside the key, the row each representative has the gene at
+// (16 bytes: R row numbers of W bytes, all ones where it has none); the
+// representatives' attributes are copied into LDS by row.  A wave then takes
+// a genome at a time: each lane looks its genes up once (one node row and
+// four connection rows per round) and, representative by representative,
+// reads the partner's attributes directly.  Counts of homologous genes are
+// ballots; the 2 R sums of attribute distances are folded over the lanes
+// together (each step halves the values a lane holds), so lane l ends with
+// one of them.
+//
+// What bounds it: vector issue (74 instructions per pair of a genome and a
+// representative at N = 50, C = 200; the vector pipe 68 % busy).  The table
+// lookups, whose probe loops run as long as the longest chain of any lane,
+// are paid once per genome and group of representatives instead of once per
+// pair, and the tables are built once per workgroup instead of once per
+// eight genomes.  Measured against a table per representative: P = 10000,
+// N = 50, C = 200, Q = 64: 465 -> 104 us; Q = 1: 21.8 -> 16.1 us; P = 1250,
+// N = 400, C = 1600, Q = 64: 3460 -> 445 us.
+// R: representatives of a group (at most 16 / W), RB: those that one test of
+// the group's size covers.
+template <int W, int R_, int RB_>
+struct DictShape {
+    static constexpr int R = R_, RB = RB_;
+    static constexpr unsigned NONE = W == 1 ? 0xffu : 0xffffu;
+    static constexpr int LN = WAVE / (2 * R);    // lanes per folded sum
+    // the attribute row to read for row number j: one-byte numbers are read
+    // as they are (the attributes are followed by 256 rows of LDS), the
+    // result of an absent gene is dropped
+    static __device__ __forceinline__ int index(unsigned j, bool hit) {
+        return W == 1 || hit ? (int)j : 0;
+    }
+};
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ unsigned dict_slot(unsigned a, unsigned b, int shift) {
+    unsigned h = (a ^ (a >> 13)) * 0x9e3779b1u + (b ^ (b >> 11)) * 0x85ebca77u;
+    h ^= h >> 15;
+    h *= 0x2c1b3c6du;
+    return h >> shift;
+}
+
+// Row number of representative r in an entry's 16 bytes.
+template <int W>
+__device__ __forceinline__ unsigned dict_row(const u32x4 &e, int r) {
+    return (e[r * W / 4] >> (8 * (r * W % 4))) & (W == 1 ? 0xffu : 0xffffu);
+}
+
+// Put row into representative r's place of entry s; true when the
+// representative had the key already (the place then needs the repair).
+template <int W>
+__device__ __forceinline__ bool dict_put(unsigned *rows, unsigned s, int r, int row) {
+    const int sh = 8 * (r * W % 4);
+    const unsigned none = W == 1 ? 0xffu : 0xffffu;
+    const unsigned old =
+        atomicAnd(rows + 4 * s + r * W / 4, ~(none << sh) | ((unsigned)row << sh));
+    return ((old >> sh) & none) != none;
+}
+template <int W>
+__device__ __forceinline__ void dict_set(unsigned *rows, unsigned s, int r, int row) {
+    if constexpr (W == 1) ((unsigned char *)(rows + 4 * s))[r] = (unsigned char)row;
+    else ((unsigned short *)(rows + 4 * s))[r] = (unsigned short)row;
+}
+
+// One connection row (four floats) of a tensor that need not be 16-byte
+// aligned.
+__device__ __forceinline__ float4 conn_row(const float *p, bool vec) {
+    if (vec) return *reinterpret_cast<const float4 *>(p);
+    return make_float4(p[0], p[1], p[2], p[3]);
+}
+
+// a's and b's sums over the lanes that differ in one lane bit, a's in the
+// lanes where the bit is 0 and b's where it is 1.
+__device__ __forceinline__ float fold32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// x is needed as loaded (a select on a fresh load would become a branch
+// around it, and the loads one wait each)
+__device__ __forceinline__ void keep(float &x) { asm volatile("" : "+v"(x)); }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_sum(float a) {
+    return a + __int_as_float(
+                   __builtin_amdgcn_update_dpp(0, __float_as_int(a), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ float fold_dpp(float a, float b, bool hi) {
+    const float x = dpp_sum<CTRL>(a), y = dpp_sum<CTRL>(b);
+    return hi ? y : x;
+}
+constexpr int DPP_ROR8 = 0x128;
+
+template <int W, int R, int RB>
+__global__ __launch_bounds__(1024) void distance_dict_kernel(DistLaunch L) {
+    using D = DictShape<W, R, RB>;
+    extern __shared__ __align__(16) unsigned char dict_lds[];
+    const int N = L.N, C = L.C, HN = L.hn, HC = L.hc, rq = L.rq;
+    const int ra = (rq + RB - 1) / RB * RB;  // attribute rows of whole guards
+    unsigned *crow = (unsigned *)dict_lds;                       // [HC][4] rows by representative
+    unsigned *nrow = crow + 4 * (size_t)HC;                      // [HN][4]
+    float4 *nattr = (float4 *)(nrow + 4 * (size_t)HN);           // [ra][N] bias, resp, act, agg
+    unsigned long long *ckey = (unsigned long long *)(nattr + (size_t)ra * N);  // [HC] in, out
+    float2 *cattr = (float2 *)(ckey + HC);                       // [ra][C] enabled, weight
+    unsigned *nkey = (unsigned *)(cattr + (size_t)ra * C);       // [HN]
+    int *cnt = (int *)(nkey + HN);                               // [3][R] nodes, connections, repeats
+    const int t = (int)threadIdx.x, T = (int)blockDim.x;
+    const int lane = t & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(t / WAVE), waves = T / WAVE;
+    const int group = (int)blockIdx.x / L.blocks_per_group;
+    const int part = (int)blockIdx.x - group * L.blocks_per_group;
+    const int q0 = group * rq, nq = min(rq, L.Q - q0);
+    const int sn = 32 - L.hn_log2, sc = 32 - L.hc_log2;  // hash shifts
+    const bool vec = L.vec != 0;
+
+    // ---- the dictionary of representatives q0 .. q0 + nq - 1
+    for (int s = t; s < HC; s += T) {
+        ckey[s] = EMPTY64;
+        ((u32x4 *)crow)[s] = u32x4{~0u, ~0u, ~0u, ~0u};
+    }
+    for (int s = t; s < HN; s += T) {
+        nkey[s] = ~0u;
+        ((u32x4 *)nrow)[s] = u32x4{~0u, ~0u, ~0u, ~0u};
+    }
+    if (t < 3 * R) cnt[t] = 0;
+    __syncthreads();
+    for (int i = t; i < nq * N; i += T) {
+        const int r = i / N, row = i - r * N;
+        const float *y = L.rnodes + (size_t)(q0 + r) * N * 5 + (size_t)row * 5;
+        const float key = y[0];
+        nattr[i] = make_float4(y[1], y[2], y[3], y[4]);
+        if (isnan(key)) continue;
+        atomicAdd(&cnt[r], 1);
+        const unsigned k = key_bits(key);
+        unsigned s = dict_slot(k, 0u, sn);
+        for (;;) {
+            const unsigned prev = atomicCAS(nkey + s, ~0u, k);
+            if (prev == ~0u || prev == k) break;
+            s = (s + 1) & (unsigned)(HN - 1);
+        }
+        if (dict_put<W>(nrow, s, r, row)) cnt[2 * R + r] = 1;
+    }
+    for (int i = t; i < nq * C; i += T) {
+        const int r = i / C, row = i - r * C;
+        const float4 y = conn_row(L.rconns + (size_t)(q0 + r) * C * 4 + (size_t)row * 4, vec);
+        cattr[i] = make_float2(y.z, y.w);
+        if (isnan(y.x)) continue;
+        atomicAdd(&cnt[R + r], 1);
+        if (isnan(y.y)) continue;  // can never match
+        const unsigned a = key_bits(y.x), b = key_bits(y.y);
+        const unsigned long long k = ((unsigned long long)a << 32) | b;
+        unsigned s = dict_slot(a, b, sc);
+        for (;;) {
+            const unsigned long long prev = atomicCAS(ckey + s, EMPTY64, k);
+            if (prev == EMPTY64 || prev == k) break;
+            s = (s + 1) & (unsigned)(HC - 1);
+        }
+        if (dict_put<W>(crow, s, r, row)) cnt[2 * R + r] = 1;
+    }
+    __syncthreads();
+    // a representative with a repeated key: one lane sets its rows again from
+    // the last to the first, so that the first one stays
+    bool repeats = false;
+    for (int r = 0; r < nq; ++r) repeats |= cnt[2 * R + r] != 0;
+    if (repeats) {  // uniform
+        for (int r = wave; r < nq; r += waves) {
+            if (cnt[2 * R + r] == 0 || lane != 0) continue;
+            for (int row = N - 1; row >= 0; --row) {
+                const float key = L.rnodes[(size_t)(q0 + r) * N * 5 + (size_t)row * 5];
+                if (isnan(key)) continue;
+                const unsigned k = key_bits(key);
+                unsigned s = dict_slot(k, 0u, sn);
+                while (nkey[s] != k) s = (s + 1) & (unsigned)(HN - 1);
+                dict_set<W>(nrow, s, r, row);
+            }
+            for (int row = C - 1; row >= 0; --row) {
+                const float *y = L.rconns + (size_t)(q0 + r) * C * 4 + (size_t)row * 4;
+                if (isnan(y[0]) || isnan(y[1])) continue;
+                const unsigned a = key_bits(y[0]), b = key_bits(y[1]);
+                const unsigned long long k = ((unsigned long long)a << 32) | b;
+                unsigned s = dict_slot(a, b, sc);
+                while (ckey[s] != k) s = (s + 1) & (unsigned)(HC - 1);
+                dict_set<W>(crow, s, r, row);
+            }
+        }
+        __syncthreads();
+    }
+    // this lane's folded sum: its representative, kind and gene count
+    const int my_r = (lane & 31) / D::LN;
+    const bool conn_half = lane >= 32;
+    const int my_b = cnt[(conn_half ? R : 0) + my_r];
+
+    // ---- genomes, one per wave
+    const int g1 = min(L.P, (part + 1) * L.per_block);
+    for (int g = part * L.per_block + wave; g < g1; g += waves) {
+        const float *An = L.nodes + (size_t)g * N * 5;
+        const float *Ac = L.conns + (size_t)g * C * 4;
+        int na = 0, ca = 0;
+        unsigned hun[R], huc[R];  // homologous genes and, 16 bits up, their unlike codes
+        // opaque copies: what is derived from them for each representative is
+        // computed where it is used (kept across genomes, it would spill)
+        int Ns = N, Cs = C, lane_now = lane;
+        asm volatile("" : "+s"(Ns), "+s"(Cs), "+v"(lane_now));
+        float v[2 * R];  // attribute distances: nodes, connections
+#pragma unroll
+        for (int r = 0; r < R; ++r) hun[r] = huc[r] = 0u, v[r] = v[R + r] = 0.0f;
+        for (int n0 = 0; n0 < N; n0 += WAVE) {
+            const int row = n0 + lane;
+            float x[5];
+#pragma unroll
+            for (int f = 0; f < 5; ++f)
+                x[f] = row < N ? An[(size_t)row * 5 + f] : __builtin_nanf("");
+            const bool have = !isnan(x[0]);
+            na += __popcll(__ballot(have));
+            u32x4 e = {~0u, ~0u, ~0u, ~0u};
+            if (have) {
+                const unsigned k = key_bits(x[0]);
+                for (unsigned s = dict_slot(k, 0u, sn);; s = (s + 1) & (unsigned)(HN - 1)) {
+                    const unsigned kk = nkey[s];
+                    if (kk == k) {
+                        e = ((const u32x4 *)nrow)[s];
+                        break;
+                    }
+                    if (kk == ~0u) break;
+                }
+            }
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += RB) {
+                if (r0 >= nq) continue;  // uniform; places past nq are empty
+#pragma unroll
+                for (int r = r0; r < r0 + RB; ++r) {
+                    const unsigned j = dict_row<W>(e, r);
+                    const bool hit = j != D::NONE;
+                    const unsigned long long hm = __ballot(hit);
+                    float4 y = nattr[r * Ns + D::index(j, hit)];
+                    keep(y.x), keep(y.y);
+                    hun[r] += __popcll(hm) + ((__popcll(hm & __ballot(x[3] != y.z)) +
+                                               __popcll(hm & __ballot(x[4] != y.w))) << 16);
+                    const float d = fabsf(x[1] - y.x) + fabsf(x[2] - y.y);
+                    v[r] += hit ? d : 0.0f;
+                }
+            }
+        }
+        constexpr int CR = 4;  // connection rows of a lane in one round
+        for (int c0 = 0; c0 < C; c0 += CR * WAVE) {
+            float en[CR], w[CR];
+            unsigned k0[CR], k1[CR], s[CR];
+            unsigned long long kk[CR];
+            bool go[CR];
+            u32x4 e[CR];
+#pragma unroll
+            for (int m = 0; m < CR; ++m) {
+                const int row = c0 + m * WAVE + lane;
+                const float nan = __builtin_nanf("");
+                float4 x = make_float4(nan, nan, nan, nan);
+                if (row < C) x = conn_row(Ac + (size_t)row * 4, vec);
+                ca += __popcll(__ballot(!isnan(x.x)));
+                en[m] = x.z, w[m] = x.w;
+                go[m] = !isnan(x.x) && !isnan(x.y);
+                k0[m] = key_bits(x.x), k1[m] = key_bits(x.y);
+                s[m] = dict_slot(k0[m], k1[m], sc);
+            }
+            // first probes together, then the further ones row by row
+#pragma unroll
+            for (int m = 0; m < CR; ++m) kk[m] = ckey[s[m]];
+#pragma unroll
+            for (int m = 0; m < CR; ++m) {
+                const unsigned long long k = ((unsigned long long)k0[m] << 32) | k1[m];
+                while (go[m] && kk[m] != k && kk[m] != EMPTY64) {
+                    s[m] = (s[m] + 1) & (unsigned)(HC - 1);
+                    kk[m] = ckey[s[m]];
+                }
+                e[m] = u32x4{~0u, ~0u, ~0u, ~0u};
+                if (go[m] && kk[m] == k) e[m] = ((const u32x4 *)crow)[s[m]];
+            }
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += RB) {
+                if (r0 >= nq) continue;
+#pragma unroll
+                for (int r = r0; r < r0 + RB; ++r) {
+                    const float2 *attr = cattr + r * Cs;
+                    float2 y[CR];
+                    bool hit[CR];
+                    unsigned like = 0, unlike = 0;
+#pragma unroll
+                    for (int m = 0; m < CR; ++m) {
+                        const unsigned j = dict_row<W>(e[m], r);
+                        hit[m] = j != D::NONE;
+                        like += __popcll(__ballot(hit[m]));
+                        y[m] = attr[D::index(j, hit[m])];
+                    }
+#pragma unroll
+                    for (int m = 0; m < CR; ++m) {
+                        keep(y[m].y);
+                        unlike += __popcll(__ballot(hit[m]) & __ballot(en[m] != y[m].x));
+                        v[R + r] += hit[m] ? fabsf(w[m] - y[m].y) : 0.0f;
+                    }
+                    huc[r] += like + (unlike << 16);
+                }
+            }
+        }
+        // fold the 2 R sums over the lanes: value i ends in lanes LN i ..
+#pragma unroll
+        for (int i = 0; i < R; ++i) v[i] = fold32(v[i], v[i + R]);
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) v[i] = fold16(v[i], v[i + R / 2]);
+#pragma unroll
+        for (int i = 0; i < R / 4; ++i) v[i] = fold_dpp<DPP_ROR8>(v[i], v[i + R / 4], lane & 8);
+        float sum = v[0];
+        if constexpr (R >= 8) {
+#pragma unroll
+            for (int i = 0; i < R / 8; ++i)
+                v[i] = fold_dpp<DPP_HALF_MIRROR>(v[i], v[i + R / 8], lane & 4);
+            sum = R == 16 ? fold_dpp<DPP_SWAP2>(v[0], v[1], lane & 2) : dpp_sum<DPP_SWAP2>(v[0]);
+        } else {
+            sum = dpp_sum<DPP_SWAP2>(dpp_sum<DPP_HALF_MIRROR>(sum));
+        }
+        sum = dpp_sum<DPP_SWAP1>(sum);
+        // the counts of this lane's sum
+        unsigned hu = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            hu = lane_now / D::LN == r ? hun[r] : hu;
+            hu = lane_now / D::LN == R + r ? huc[r] : hu;
+        }
+        const int h = (int)(hu & 0xffffu);
+        sum += (float)(hu >> 16);
+        const int a = conn_half ? ca : na, m = max(a, my_b);
+        const float d =
+            m ? (L.cd * (float)(a + my_b - 2 * h) + L.ch * sum) / (float)m : 0.0f;
+        const float other = __shfl_xor(d, 32);
+        if (!conn_half && (lane & (D::LN - 1)) == 0 && my_r < nq)
+            L.out[(size_t)g * L.Q + q0 + my_r] = d + other;
+    }
+}
+
+// ---- distance by a table per representative, for shapes whose dictionary
+// does not fit in LDS.  DIST_WAVES waves per workgroup, DIST_PER_WAVE
+// genomes per wave: a representative's tables are built once for
+// DIST_WAVES * DIST_PER_WAVE genomes.
 constexpr int DIST_WAVES = 4, DIST_PER_WAVE = 2;
 constexpr int DIST_GENOMES = DIST_WAVES * DIST_PER_WAVE;
 
-// SMALL (N_max <= 64, C_max <= 256): every lane keeps its genes' keys,
-// attributes and first hash slots in registers for the whole loop over the
-// representatives (one node row and up to four connection rows per genome),
-// B's rows are copied into LDS beside the tables (a partner's attributes
-// are an LDS read away, not a cache round trip), and the per-pair sums run
-// on the DPP lane network.
-constexpr int SMALL_CONN_ROWS = 4;
-
-template <bool SMALL>
 __global__ __launch_bounds__(WAVE *DIST_WAVES) void distance_kernel(DistLaunch L) {
     extern __shared__ unsigned long long dsm[];
     const int N = L.N, C = L.C, HN = L.hn, HC = L.hc;
@@ -146,19 +475,12 @@ __global__ __launch_bounds__(WAVE *DIST_WAVES) void distance_kernel(DistLaunch L
     int *nr = (int *)(ck + HC);              // rows [HN]
     int *cr = nr + HN;                       // rows [HC]
     int *bcount = cr + HC;                   // B's node and connection genes
-    float *bn_s = (float *)(bcount + 2);     // SMALL: B's rows [N][5], [C][4]
-    float *bc_s = bn_s + (SMALL ? N * 5 : 0);
     const int t = (int)threadIdx.x, lane = t & (WAVE - 1), wave = t / WAVE;
     const int T = WAVE * DIST_WAVES;
 
     // this wave's genomes and their gene counts (once)
     long long gs[DIST_PER_WAVE];
     int na[DIST_PER_WAVE], ca[DIST_PER_WAVE];
-    // SMALL: the lane's genes (node row lane, connection rows lane + 64 m)
-    float xn[DIST_PER_WAVE][5];
-    unsigned xns[DIST_PER_WAVE];
-    float xc[DIST_PER_WAVE][SMALL_CONN_ROWS][4];
-    unsigned xcs[DIST_PER_WAVE][SMALL_CONN_ROWS];
 #pragma unroll
     for (int i = 0; i < DIST_PER_WAVE; ++i) {
         gs[i] = (long long)blockIdx.x * DIST_GENOMES + wave * DIST_PER_WAVE + i;
@@ -168,23 +490,6 @@ __global__ __launch_bounds__(WAVE *DIST_WAVES) void distance_kernel(DistLaunch L
             const float *Ac = L.conns + (size_t)gs[i] * C * 4;
             for (int r = lane; r < N; r += WAVE) a += !isnan(An[(size_t)r * 5]);
             for (int r = lane; r < C; r += WAVE) c += !isnan(Ac[(size_t)r * 4]);
-            if constexpr (SMALL) {
-                const bool in = lane < N;
-#pragma unroll
-                for (int f = 0; f < 5; ++f)
-                    xn[i][f] = in ? An[(size_t)lane * 5 + f] : __builtin_nanf("");
-                xns[i] = mix(key_bits(xn[i][0]), HN);
-#pragma unroll
-                for (int m = 0; m < SMALL_CONN_ROWS; ++m) {
-                    const int r = lane + WAVE * m;
-#pragma unroll
-                    for (int f = 0; f < 4; ++f)
-                        xc[i][m][f] = r < C ? Ac[(size_t)r * 4 + f] : __builtin_nanf("");
-                    xcs[i][m] = mix(((unsigned long long)key_bits(xc[i][m][0]) << 32) |
-                                        key_bits(xc[i][m][1]),
-                                    HC);
-                }
-            }
         }
         na[i] = wave_sum(a);
         ca[i] = wave_sum(c);
@@ -200,20 +505,12 @@ __global__ __launch_bounds__(WAVE *DIST_WAVES) void distance_kernel(DistLaunch L
         int nb = 0, cb = 0;
         for (int r = t; r < N; r += T) {
             const float k = Bn[(size_t)r * 5];
-            if constexpr (SMALL) {
-#pragma unroll
-                for (int f = 0; f < 5; ++f) bn_s[r * 5 + f] = Bn[(size_t)r * 5 + f];
-            }
             if (isnan(k)) continue;
             ++nb;
             insert(nk, nr, HN, key_bits(k), r);
         }
         for (int r = t; r < C; r += T) {
             const float ki = Bc[(size_t)r * 4], ko = Bc[(size_t)r * 4 + 1];
-            if constexpr (SMALL) {
-#pragma unroll
-                for (int f = 0; f < 4; ++f) bc_s[r * 4 + f] = Bc[(size_t)r * 4 + f];
-            }
             if (isnan(ki)) continue;
             ++cb;
             if (isnan(ko)) continue;  // can never match
@@ -235,50 +532,25 @@ __global__ __launch_bounds__(WAVE *DIST_WAVES) void distance_kernel(DistLaunch L
             const float *Ac = L.conns + (size_t)gs[i] * C * 4;
             int hn = 0, hc = 0;
             float sn = 0.0f, sc = 0.0f;
-            if constexpr (SMALL) {
-                const float *x = xn[i];
-                if (!isnan(x[0])) {
-                    const int j = lookup_from(nk, nr, HN, key_bits(x[0]), xns[i]);
-                    if (j >= 0) {
-                        const float *y = bn_s + j * 5;
-                        ++hn;
-                        sn += fabsf(x[1] - y[1]) + fabsf(x[2] - y[2]) + (float)(x[3] != y[3]) +
-                              (float)(x[4] != y[4]);
-                    }
-                }
-#pragma unroll
-                for (int m = 0; m < SMALL_CONN_ROWS; ++m) {
-                    const float *xm = xc[i][m];
-                    if (isnan(xm[0]) || isnan(xm[1])) continue;
-                    const int j = lookup_from(
-                        ck, cr, HC, ((unsigned long long)key_bits(xm[0]) << 32) | key_bits(xm[1]),
-                        xcs[i][m]);
-                    if (j < 0) continue;
-                    const float *y = bc_s + j * 4;
-                    ++hc;
-                    sc += fabsf(xm[3] - y[3]) + (float)(xm[2] != y[2]);
-                }
-            } else {
-                for (int r = lane; r < N; r += WAVE) {
-                    const float *x = An + (size_t)r * 5;
-                    if (isnan(x[0])) continue;
-                    const int j = lookup(nk, nr, HN, key_bits(x[0]));
-                    if (j < 0) continue;
-                    const float *y = Bn + (size_t)j * 5;
-                    ++hn;
-                    sn += fabsf(x[1] - y[1]) + fabsf(x[2] - y[2]) + (float)(x[3] != y[3]) +
-                          (float)(x[4] != y[4]);
-                }
-                for (int r = lane; r < C; r += WAVE) {
-                    const float *x = Ac + (size_t)r * 4;
-                    if (isnan(x[0]) || isnan(x[1])) continue;
-                    const int j = lookup(ck, cr, HC,
-                                         ((unsigned long long)key_bits(x[0]) << 32) | key_bits(x[1]));
-                    if (j < 0) continue;
-                    const float *y = Bc + (size_t)j * 4;
-                    ++hc;
-                    sc += fabsf(x[3] - y[3]) + (float)(x[2] != y[2]);
-                }
+            for (int r = lane; r < N; r += WAVE) {
+                const float *x = An + (size_t)r * 5;
+                if (isnan(x[0])) continue;
+                const int j = lookup(nk, nr, HN, key_bits(x[0]));
+                if (j < 0) continue;
+                const float *y = Bn + (size_t)j * 5;
+                ++hn;
+                sn += fabsf(x[1] - y[1]) + fabsf(x[2] - y[2]) + (float)(x[3] != y[3]) +
+                      (float)(x[4] != y[4]);
+            }
+            for (int r = lane; r < C; r += WAVE) {
+                const float *x = Ac + (size_t)r * 4;
+                if (isnan(x[0]) || isnan(x[1])) continue;
+                const int j = lookup(ck, cr, HC,
+                                     ((unsigned long long)key_bits(x[0]) << 32) | key_bits(x[1]));
+                if (j < 0) continue;
+                const float *y = Bc + (size_t)j * 4;
+                ++hc;
+                sc += fabsf(x[3] - y[3]) + (float)(x[2] != y[2]);
             }
             hn = wave_total(hn);
             hc = wave_total(hc);
@@ -511,13 +783,6 @@ size_t gene_tables_lds_bytes(int N, int C) {
     return (size_t)(hn + hc) * (sizeof(unsigned long long) + sizeof(int)) + 2 * sizeof(int);
 }
 
-static bool distance_small(int N, int C) { return N <= WAVE && C <= WAVE * SMALL_CONN_ROWS; }
-
-size_t distance_lds_bytes(int N, int C) {
-    return gene_tables_lds_bytes(N, C) +
-           (distance_small(N, C) ? sizeof(float) * (size_t)(5 * N + 4 * C) : 0);
-}
-
 hipError_t crossover_launch(CrossLaunch L, hipStream_t stream) {
     L.hn = pow2_at_least(2 * L.N);
     L.hc = pow2_at_least(2 * L.C);
@@ -542,17 +807,70 @@ hipError_t edit_launch(EditLaunch L, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t distance_launch(DistLaunch L, hipStream_t stream) {
-    L.hn = pow2_at_least(2 * L.N);
-    L.hc = pow2_at_least(2 * L.C);
+// The dictionary's shape for groups of rq representatives, and its LDS
+// bytes: tables a quarter larger than the keys they can have to hold (rows
+// that are absent and keys that representatives share leave them emptier).
+static size_t dict_shape(int N, int C, int rq, int row_bytes, int *hn, int *hc) {
+    const int rb = rq <= 4 ? 1 : 4, ra = (rq + rb - 1) / rb * rb;
+    *hn = pow2_at_least((5 * rq * N + 3) / 4);
+    *hc = pow2_at_least((5 * rq * C + 3) / 4);
+    return (size_t)*hc * 24 + (size_t)*hn * 20 + (size_t)ra * ((size_t)16 * N + (size_t)8 * C) +
+           3 * sizeof(int) * (16 / row_bytes) + (row_bytes == 1 ? 256 * sizeof(float4) : 0);
+}
+
+static int log2_of(int x) {
+    int l = 0;
+    while ((1 << l) < x) ++l;
+    return l;
+}
+
+hipError_t distance_launch(DistLaunch L, size_t max_lds, hipStream_t stream) {
     if (L.P == 0 || L.Q == 0) return hipSuccess;
-    const dim3 grid((unsigned)((L.P + DIST_GENOMES - 1) / DIST_GENOMES)), block(WAVE * DIST_WAVES);
-    if (distance_small(L.N, L.C))
-        hipLaunchKernelGGL(distance_kernel<true>, grid, block, distance_lds_bytes(L.N, L.C), stream,
-                           L);
-    else
-        hipLaunchKernelGGL(distance_kernel<false>, grid, block, distance_lds_bytes(L.N, L.C),
-                           stream, L);
+    // Rows are numbered in one byte (16 representatives per group) while
+    // every row number is below 255, else in two (8).  A group takes as many
+    // representatives as their dictionary fits in LDS (none: the kernel with a
+    // table per representative).  With few genomes it takes fewer, so that
+    // the groups reach every CU (P = 100, Q = 64: 10.5 us in groups of 16,
+    // 9.5 us in groups of 4).  Groups of up to 4 have a kernel that folds 8
+    // sums instead of 32 (P = 10000, Q = 1: 24.5 us with 32, 16.1 us with 8).
+    const int row_bytes = std::max(L.N, L.C) <= 255 ? 1 : 2;
+    int rq = std::min(L.Q, 16 / row_bytes);
+    while (rq > 0 && dict_shape(L.N, L.C, rq, row_bytes, &L.hn, &L.hc) > max_lds) --rq;
+    if (rq == 0) {
+        L.hn = pow2_at_least(2 * L.N);
+        L.hc = pow2_at_least(2 * L.C);
+        const dim3 grid((unsigned)((L.P + DIST_GENOMES - 1) / DIST_GENOMES));
+        hipLaunchKernelGGL(distance_kernel, grid, dim3(WAVE * DIST_WAVES),
+                           gene_tables_lds_bytes(L.N, L.C), stream, L);
+        return hipGetLastError();
+    }
+    constexpr int CUS = 256;
+    while (rq > 4 && (long long)((L.Q + rq - 1) / rq) * ((L.P + 15) / 16) < CUS) rq = (rq + 1) / 2;
+    const int groups = (L.Q + rq - 1) / rq;
+    L.rq = (L.Q + groups - 1) / groups;
+    const size_t lds = dict_shape(L.N, L.C, L.rq, row_bytes, &L.hn, &L.hc);
+    L.hn_log2 = log2_of(L.hn), L.hc_log2 = log2_of(L.hc);
+    L.vec = ((uintptr_t)L.conns % 16) == 0 && ((uintptr_t)L.rconns % 16) == 0;
+    // one workgroup of 16 waves per CU, or two of eight (four for the small
+    // groups, whose kernels hold fewer registers)
+    const bool small = L.rq <= 4;
+    const int waves = 2 * lds > max_lds ? 16 : 8;
+    const int per_cu = waves == 16 ? 1 : (int)std::min<size_t>(small ? 4 : 2, max_lds / lds);
+    const int target = std::max(1, CUS * per_cu / groups);  // workgroups per group
+    const int least = (L.P + target - 1) / target;
+    L.per_block = (least + waves - 1) / waves * waves;
+    L.blocks_per_group = (L.P + L.per_block - 1) / L.per_block;
+    const dim3 grid((unsigned)(groups * L.blocks_per_group)), block((unsigned)(WAVE * waves));
+#define NEAT_DICT(W, R, RB)                                                                 \
+    hipLaunchKernelGGL((distance_dict_kernel<W, R, RB>), grid, block, lds, stream, L)
+    if (row_bytes == 1) {
+        if (small) NEAT_DICT(1, 4, 1);
+        else NEAT_DICT(1, 16, 4);
+    } else {
+        if (small) NEAT_DICT(2, 4, 1);
+        else NEAT_DICT(2, 8, 4);
+    }
+#undef NEAT_DICT
     return hipGetLastError();
 }
 

@@ -55,6 +55,35 @@ def test_distance_parity(P, Q, N, C):
     _check(_gpu(pop.nodes, pop.conns, rn, rc), pop.nodes, pop.conns, rn, rc)
 
 
+# (P, Q, N, C): one more than a full group of representatives, groups of one
+# and two, the last row numbers that fit one byte and the first that need two,
+# rows beyond a lane's first round, more than one genome per wave, and a shape
+# whose dictionary does not fit (a table per representative)
+@pytest.mark.parametrize("P,Q,N,C", [(33, 17, 50, 200), (5, 1, 64, 255), (6, 2, 254, 255),
+                                     (6, 9, 256, 256), (300, 65, 20, 70), (4099, 64, 10, 33),
+                                     (3, 2, 40, 4000)])
+def test_distance_dictionary_groups(P, Q, N, C):
+    print("case", P, Q, N, C, flush=True)
+    rng = np.random.default_rng(P + 7 * C)
+    pop = synth.make_population(rng, min(P, 40), N, C, 3, 2, N - 5, synth._k_uniform(C),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    who = rng.integers(0, pop.P, P)
+    nodes, conns = pop.nodes[who].copy(), pop.conns[who].copy()
+    nodes[:, :, 1] += rng.normal(0, 0.3, nodes.shape[:2]).astype(np.float32)
+    pick = rng.integers(0, pop.P, Q)
+    rn, rc = pop.nodes[pick].copy(), pop.conns[pick].copy()
+    # a repeated node key and a repeated connection in some representatives and
+    # genomes: the partner is the first row that has it
+    for n, c in ((rn, rc), (nodes, conns)):
+        for q in range(0, n.shape[0], 3):
+            rows = np.flatnonzero(~np.isnan(n[q, :, 0]))
+            n[q, rows[-1], 0] = n[q, rows[0], 0]
+            rows = np.flatnonzero(~np.isnan(c[q, :, 0]))
+            if rows.size > 1:
+                c[q, rows[-1], :2] = c[q, rows[0], :2]
+    _check(_gpu(nodes, conns, rn, rc), nodes, conns, rn, rc)
+
+
 def test_distance_hand_pair_and_special_keys():
     """The oracle's hand-computed pair, plus -0 against +0 keys and NaN out
     keys (which never match), planted in a second pair."""
