@@ -163,7 +163,11 @@ int neat_forward(const neat_dims *dims, const void *program, const float *inputs
  * simultaneously live values (<= 62, <= 126, <= 222 values in registers,
  * more in LDS rows); NEAT_FWD_AUTO runs each class's genomes with that
  * class's kernel, two samples per lane for the smallest class when B > 64.
- * The others exist for tuning and testing. */
+ * A call over one population that can need more than the smallest class may
+ * run every class in one launch instead (NEAT_FWD_AUTO, _REG and _REG2;
+ * genomes past the register classes then as by NEAT_FWD_LVL), and
+ * NEAT_FWD_AUTO takes NEAT_FWD_LVL for few samples: by P, B and N_max, with
+ * the same bits.  The others exist for tuning and testing. */
 #define NEAT_FWD_AUTO 0
 #define NEAT_FWD_REG 1  /* registers, one sample per lane (LDS rows for the LDS class) */
 #define NEAT_FWD_LDS 2  /* every genome in LDS rows */

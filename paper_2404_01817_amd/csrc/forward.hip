@@ -358,16 +358,13 @@ __device__ __forceinline__ void fill_nan(float *out_g, int first, int end, int O
     for (int e = first * O + lane; e < end * O; e += WAVE) out_g[e] = __builtin_nanf("");
 }
 
-// The waves of one unit with a register store: genome g, this wave's tiles.
-// area: the wave's LDS (input staging TS x I floats, then output staging
+// One unit with a register store: tiles [t0, t1) of genome g.  area: the wave's LDS (input staging TS x I floats, then output staging
 // TS x O floats).
 template <int K, bool GRID>
-__device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int chunk, float *area,
+__device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int t1, float *area,
                                                  int stage_floats) {
     constexpr int SPL = AsmTile<K>::SPL;
     constexpr int TS = WAVE * SPL;  // samples per tile
-    int t0, t1;
-    if (!wave_tiles(it, chunk, &t0, &t1)) return;
     const unsigned lane = threadIdx.x & (WAVE - 1);
     const int N = it->N, I = it->I, O = it->O, B = it->B, side = GRID ? it->side : 0;
     cprog_t *prog = (cprog_t *)(it->prog + (size_t)g * it->prog_words);
@@ -443,14 +440,12 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int chunk, 
     flush_outputs(ostage, out_g + (size_t)(t1 - 1) * TS * O, (min(B, t1 * TS) - (t1 - 1) * TS) * O);
 }
 
-// The waves of one unit with the LDS store.  stage: the wave's input
+// One unit with the LDS store: tiles [t0, t1) of genome g.  stage: the wave's input
 // staging area (TS x I floats; unused for grid items).
 template <bool GRID, int LD>
-__device__ __forceinline__ void forward_unit_lds(citem_t *it, int g, int chunk, float *stage,
-                                                 LdsStoreT<LD> &v) {
+__device__ __forceinline__ void forward_unit_lds(citem_t *it, int g, int t0, int t1,
+                                                 float *stage, LdsStoreT<LD> &v) {
     constexpr int TS = LD;
-    int t0, t1;
-    if (!wave_tiles(it, chunk, &t0, &t1)) return;
     const int lane = (int)(threadIdx.x & (WAVE - 1));
     // half-wave tiles: lanes LD.. take no sample (their columns would alias)
     const bool active = LD == WAVE || lane < LD;
@@ -594,9 +589,8 @@ __device__ __forceinline__ void lvl_step(const i32x16 &r, int e, bool active, gi
     if (slot >= 0) v[(slot << sh) + j] = y;
 }
 
-__device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int chunk, float *v) {
-    int t0, t1;
-    if (!wave_tiles(it, chunk, &t0, &t1)) return;
+// Tiles [t0, t1) of BW samples.
+__device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int t0, int t1, float *v) {
     const int lane = (int)(threadIdx.x & (WAVE - 1));
     const int sh = it->lvl_sh, BW = 1 << sh;
     const int N = it->N, C = it->C, I = it->I, O = it->O, B = it->B;
@@ -699,9 +693,7 @@ __device__ __forceinline__ int wave_excl_scan(int v, int *total) {
     return x - v;
 }
 
-__device__ __forceinline__ void forward_unit_seg(citem_t *it, int g, int chunk, float *v) {
-    int t0, t1;
-    if (!wave_tiles(it, chunk, &t0, &t1)) return;
+__device__ __forceinline__ void forward_unit_seg(citem_t *it, int g, int t0, int t1, float *v) {
     const int lane = (int)(threadIdx.x & (WAVE - 1));
     const int sh = it->lvl_sh, BW = 1 << sh, R = WAVE >> sh;
     const int N = it->N, C = it->C, I = it->I, O = it->O, B = it->B;
@@ -891,6 +883,46 @@ __device__ __forceinline__ const __attribute__((address_space(4))) FwdLaunch *la
         __builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// ---------------------------------------------------------------- any class
+// Mapping "any class" (KIND_ANY): every genome of a population in one
+// launch, each wave with the register store of its genome's class, and the
+// level mapping for genomes past the register classes.
+//
+// What it replaces: a launch per class, one after another on the caller's
+// stream, each of them as long as its largest genome's chain of nodes (some
+// 260 cycles per node for a wave alone on its SIMD) although a population
+// of a few hundred genomes fills none of them.  Here the chains of all
+// classes run side by side.  The price: the kernel's registers are those of
+// its largest class (two waves per SIMD for all).  Measured, launch per
+// class against this kernel, in us (I / O rows and 4 N connections):
+//   N = 365, P = 500, B = 24: 93 / 34.6; P = 1500, B = 300: 272 / 109
+//   N = 222, P = 500, B = 24: 45.5 / 22.0; P = 3000, B = 300: 188 / 127
+//   N = 140, P = 2000, B = 300: 58.9 / 60.4; P = 4000, B = 300: 91 / 110
+//   N = 80, P = 2000, B = 48: 12.1 / 10.0; P = 4000, B = 48: 15.8 / 18.3
+// Tiles are of 64 samples, or of 128 (it->lvl_rows) that a genome of the
+// smallest class runs two to a lane and the others as two tiles of 64.
+__device__ __forceinline__ void run_any(citem_t *it, int g, int t0, int t1, float *area,
+                                        int stage_floats) {
+    const int c = ((cprog_t *)(it->prog + (size_t)g * it->prog_words))[HDR_CLASS];
+    const int wide = it->lvl_rows == 2 * WAVE ? 2 : 1;
+    if (c == CLS_R64 && wide == 2) {
+        forward_unit_reg<KIND_R64X2, false>(it, g, t0, t1, area, stage_floats);
+        return;
+    }
+    t0 *= wide;
+    t1 = min((it->B + WAVE - 1) / WAVE, t1 * wide);
+    if (c == CLS_R64) {
+        forward_unit_reg<KIND_R64, false>(it, g, t0, t1, area, stage_floats);
+    } else if (c == CLS_R128) {
+        forward_unit_reg<KIND_R128, false>(it, g, t0, t1, area, stage_floats);
+    } else if (c == CLS_R224) {
+        forward_unit_reg<KIND_R224, false>(it, g, t0, t1, area, stage_floats);
+    } else {
+        const int per = WAVE >> it->lvl_sh, all = (it->B + (1 << it->lvl_sh) - 1) >> it->lvl_sh;
+        forward_unit_lvl(it, g, t0 * per, min(all, t1 * per), area);
+    }
+}
+
 // One unit: find its item and genome, then run the unit's waves with a
 // fresh value store (nothing carries over from one unit to the next).
 template <int K, bool GRID>
@@ -907,20 +939,24 @@ __device__ __forceinline__ void run_unit(long long u, float *wave_area) {
         if (i >= pop[POP_COUNT + cls]) return;
         g = pop[POP_IDS + pop[POP_BEGIN + cls] + i];
     }
+    int t0, t1;
+    if (!wave_tiles(it, chunk, &t0, &t1)) return;
     if constexpr (K == KIND_LVL) {
-        forward_unit_lvl(it, g, chunk, wave_area);
+        forward_unit_lvl(it, g, t0, t1, wave_area);
     } else if constexpr (K == KIND_SEG) {
-        forward_unit_seg(it, g, chunk, wave_area);
+        forward_unit_seg(it, g, t0, t1, wave_area);
+    } else if constexpr (K == KIND_ANY) {
+        run_any(it, g, t0, t1, wave_area, L->stage_floats);
     } else if constexpr (K == KIND_LDS) {
         LdsStore v;
         v.col = wave_area + L->stage_floats + (threadIdx.x & (WAVE - 1));
-        forward_unit_lds<GRID, WAVE>(it, g, chunk, wave_area, v);
+        forward_unit_lds<GRID, WAVE>(it, g, t0, t1, wave_area, v);
     } else if constexpr (K == KIND_LDS32) {
         LdsStoreT<WAVE / 2> v;
         v.col = wave_area + L->stage_floats + (threadIdx.x & (WAVE / 2 - 1));
-        forward_unit_lds<GRID, WAVE / 2>(it, g, chunk, wave_area, v);
+        forward_unit_lds<GRID, WAVE / 2>(it, g, t0, t1, wave_area, v);
     } else {
-        forward_unit_reg<K, GRID>(it, g, chunk, wave_area, L->stage_floats);
+        forward_unit_reg<K, GRID>(it, g, t0, t1, wave_area, L->stage_floats);
     }
 }
 
@@ -1025,7 +1061,8 @@ bool lds_kind(int kind) { return kind == KIND_LDS || kind == KIND_LDS32; }
 // kernel of class c under a variant
 int kind_of(int variant, int cls, int B) {
     if (variant == FWD_LDS) return KIND_LDS;
-    if (variant == FWD_LVL || variant == FWD_SEG) variant = FWD_AUTO;  // grid, recurrent items
+    if (variant == FWD_LVL || variant == FWD_SEG || variant == FWD_ANY)
+        variant = FWD_AUTO;  // grid, recurrent items
     switch (cls) {
     case CLS_R64:
         if (variant == FWD_REG2 || (variant == FWD_AUTO && B > WAVE)) return KIND_R64X2;
@@ -1040,8 +1077,57 @@ int kind_of(int variant, int cls, int B) {
 
 const char *kind_name(int kind) {
     static const char *names[] = {"r64", "r64x2", "r128", "r224", "lds", "r64rec", "lds32",
-                                  "lvl", "seg"};
+                                  "lvl", "seg", "any"};
     return kind >= 0 && kind < N_KINDS ? names[kind] : "?";
+}
+
+// Level and segment mappings: the widest power-of-two tile of samples (<= 64,
+// <= B rounded up) whose values, rows of them, fit a wave's LDS budget beside
+// extra bytes (log2).
+static int level_tile(int rows, int B, size_t extra) {
+    int sh = 0;
+    while (sh < 6 && (1 << sh) < B &&
+           sizeof(float) * (size_t)rows * (2u << sh) + extra <= lvl_wave_bytes())
+        ++sh;
+    return sh;
+}
+
+// Samples of one KIND_ANY tile: 64 while the GPU holds every 64-sample tile
+// at once (2048 waves of that kernel), else 128, which the smallest class
+// runs at half the scalar work per sample.
+static int any_tile(const FwdJob &J) {
+    return J.B > WAVE && (long long)J.P * ((J.B + WAVE - 1) / WAVE) > 2048 ? 2 * WAVE : WAVE;
+}
+
+// The mapping of a call's only population of more than 62 node rows where
+// the caller left it open (FWD_AUTO, or registers of either kind).
+static int resolve_variant(const FwdJob &J, int variant, int n_jobs, size_t max_lds) {
+    const int top = max_class(J.N);
+    if (n_jobs != 1 || J.side || J.recurrent || top == CLS_R64) return variant;
+    // a call that the launches per class refuse stays refused
+    const size_t stage = sizeof(float) * (size_t)(2 * WAVE) * (J.I + J.O);
+    const size_t lds32 = sizeof(float) * (size_t)(WAVE / 2) * (J.I + class_slots(top, J.N));
+    if (stage > max_lds || (top == CLS_LDS && lds32 > max_lds)) return variant;
+    const long long units = (long long)J.P * ((J.B + WAVE - 1) / WAVE);
+    if (variant == FWD_AUTO) {
+        // Few samples: the level mapping, whose lanes share a genome's nodes,
+        // has the shorter chain while its waves fit the GPU (N = 300, P =
+        // 700: 24.5 us against 28.9 at B = 18, 37.6 against 28.9 at B = 48),
+        // and past 2048 genomes up to 8 samples (N = 160, P = 4000: 19.9 us
+        // against 32.0 at B = 4, 38.4 against 31.7 at B = 12).  Below 127 rows
+        // the chains are short and only the second holds (N = 126, P = 200,
+        // B = 12: 13.3 us against 12.8).
+        if (J.P > 2048 ? J.B <= 8 : J.N > 126 && (long long)J.P * J.B <= 16384) return FWD_LVL;
+    }
+    if (variant == FWD_AUTO || variant == FWD_REG || variant == FWD_REG2) {
+        // One launch for every class (figures at run_any): up to 126 rows while
+        // every wave is resident at once, up to 150 rows for four times as
+        // many, and always past that, where the launches per class leave the
+        // two largest at two waves per SIMD anyway.
+        const long long most = J.N <= 126 ? 2048 : (J.N <= 150 ? 8192 : units);
+        if (units <= most) return FWD_ANY;
+    }
+    return variant;
 }
 
 int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
@@ -1061,21 +1147,21 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
     for (int j = 0; j < n; ++j) {
         const FwdJob &J = jobs[j];
         if (J.P == 0 || J.B == 0) continue;
-        const int variant = J.variant >= 0 ? J.variant : plan_variant;
         const int top = max_class(J.N);
+        const int variant = resolve_variant(J, J.variant >= 0 ? J.variant : plan_variant, n, max_lds);
         if ((variant == FWD_LVL || variant == FWD_SEG) && !J.side && !J.recurrent) {
             // the level and segment mappings: every genome, one launch per
-            // mapping over all items; the widest power-of-two tile of
-            // samples (<= 64, <= B rounded up) whose values fit a wave's
-            // LDS budget (the segment mapping also keeps N_max + 1 edge
-            // offsets)
+            // mapping over all items (the segment mapping also keeps N_max + 1
+            // edge offsets)
             const bool seg = variant == FWD_SEG;
             const int rows = class_slots(top, J.N);
-            const size_t extra = seg ? sizeof(int) * (size_t)(J.N + 1) : 0;
-            int sh = 0;
-            while (sh < 6 && (1 << sh) < J.B &&
-                   sizeof(float) * (size_t)rows * (2u << sh) + extra <= lvl_wave_bytes())
-                ++sh;
+            int sh = level_tile(rows, J.B, seg ? sizeof(int) * (size_t)(J.N + 1) : 0);
+            // a population alone: narrower tiles, so more of a level's nodes
+            // side by side, while the GPU holds every wave at once (N = 300,
+            // P = 100, B = 24: 22 -> 19 us)
+            if (n == 1)
+                while (sh > 0 && (long long)J.P * ((J.B + (1 << (sh - 1)) - 1) >> (sh - 1)) <= 4096)
+                    --sh;
             FwdItem it{};
             it.prog = J.prog;
             it.inputs = J.inputs;
@@ -1095,11 +1181,15 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         }
         // FWD_LDS takes every genome in one pass over all genomes; the other
         // variants take class c's genomes with class c's kernel; a recurrent
-        // job (N_max <= 62) takes every genome with the recurrent kernel
-        const int c_lo = (variant == FWD_LDS || J.recurrent) ? -1 : 0;
-        const int c_hi = (variant == FWD_LDS || J.recurrent) ? -1 : top;
+        // job (N_max <= 62) takes every genome with the recurrent kernel;
+        // FWD_ANY takes every genome with the kernel that holds all classes
+        const bool any = variant == FWD_ANY && !J.side && !J.recurrent && top != CLS_R64;
+        const bool whole = variant == FWD_LDS || J.recurrent || any;
+        const int c_lo = whole ? -1 : 0, c_hi = whole ? -1 : top;
         for (int c = c_lo; c <= c_hi; ++c) {
-            int kind = J.recurrent ? KIND_R64REC : kind_of(variant, c < 0 ? CLS_LDS : c, J.B);
+            int kind = J.recurrent ? KIND_R64REC
+                       : any       ? KIND_ANY
+                                   : kind_of(variant, c < 0 ? CLS_LDS : c, J.B);
             // LDS rows too large for 64 columns per wave: half-wave tiles
             if (kind == KIND_LDS &&
                 sizeof(float) * (size_t)WAVE * (J.I + class_slots(top, J.N)) > max_lds)
@@ -1117,7 +1207,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             it.side = J.side;
             it.prog_words = prog_words(J.N, J.C, J.O);
             it.sweeps = J.recurrent ? J.sweeps : 0;
-            const int TS = tile_samples(kind);
+            const int TS = kind == KIND_ANY ? any_tile(J) : tile_samples(kind);
             it.tiles = (J.B + TS - 1) / TS;
             it.vec4 = (!J.side && ((uintptr_t)J.inputs % 16 == 0) && (J.gstride % 4 == 0)) ? 1 : 0;
             const int x = 2 * kind + (J.side ? 1 : 0);
@@ -1127,6 +1217,13 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             if (!J.side || !lds_kind(kind))
                 stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE : 0));
             if (!lds_kind(kind)) ostage_max[x] = std::max(ostage_max[x], TS * J.O);
+            if (kind == KIND_ANY) {
+                // the values of a genome past the register classes, in the same area
+                const int rows = class_slots(top, J.N), sh = level_tile(rows, J.B, 0);
+                k[x].items.back().lvl_sh = sh;
+                k[x].items.back().lvl_rows = TS;
+                rows_max[x] = std::max(rows_max[x], rows << sh);
+            }
             if (lds_kind(kind)) rows_max[x] = std::max(rows_max[x], class_slots(top, J.N));
         }
     }
@@ -1137,7 +1234,8 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const size_t rows = (kind == KIND_LVL || kind == KIND_SEG) ? (size_t)rows_max[x]
                             : lds_kind(kind) ? (size_t)rows_max[x] * tile_samples(kind)
                                              : (size_t)ostage_max[x];
-        const size_t wave_floats = (size_t)stage_max[x] + rows;
+        size_t wave_floats = (size_t)stage_max[x] + rows;
+        if (kind == KIND_ANY) wave_floats = std::max(wave_floats, (size_t)rows_max[x]);
         const size_t wave_bytes = wave_floats * sizeof(float);
         int waves = FWD_MAX_WAVES;
         while (waves > 1 && wave_bytes * waves > max_lds) --waves;
@@ -1252,6 +1350,10 @@ hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hi
     case KIND_LDS32: NEAT_LAUNCH(KIND_LDS32) break;
     case KIND_LVL: NEAT_LAUNCH2(KIND_LVL, false) break;
     case KIND_SEG: NEAT_LAUNCH2(KIND_SEG, false) break;
+    case KIND_ANY:  // never persistent (its grid has no cap)
+        hipLaunchKernelGGL((forward_kernel<KIND_ANY, false, false>), dim3(k.grid), dim3(k.block),
+                           k.lds, stream, L);
+        break;
     default: NEAT_LAUNCH(KIND_LDS) break;
     }
 #undef NEAT_LAUNCH

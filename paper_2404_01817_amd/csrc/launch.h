@@ -50,6 +50,7 @@ constexpr int FWD_LDS = 2;   // every genome in LDS rows
 constexpr int FWD_REG2 = 3;  // as FWD_REG, R64 genomes two samples per lane
 constexpr int FWD_LVL = 5;   // lanes over a level's nodes x a tile of samples (values in LDS)
 constexpr int FWD_SEG = 6;   // lanes over a level's in-edges x a tile, segmented reduction
+constexpr int FWD_ANY = 7;   // one launch, each wave by its genome's class (internal)
 
 // Forward kernels, one per value store.
 // KIND_R64REC: the recurrent calculation (K synchronous sweeps) with the
@@ -57,10 +58,12 @@ constexpr int FWD_SEG = 6;   // lanes over a level's in-edges x a tile, segmente
 // LDS-row store with half-wave tiles (32 samples), for genomes whose rows
 // do not fit in LDS with 64 columns.
 // KIND_LVL / KIND_SEG: the level and segment mappings (FWD_LVL, FWD_SEG),
-// every genome of an item, tiles of 2^lvl_sh samples.
+// every genome of an item, tiles of 2^lvl_sh samples.  KIND_ANY: every
+// genome of an item, each wave with the register store of its genome's class
+// (the level mapping past the register classes).
 enum FwdKind {
     KIND_R64 = 0, KIND_R64X2, KIND_R128, KIND_R224, KIND_LDS, KIND_R64REC, KIND_LDS32, KIND_LVL,
-    KIND_SEG, N_KINDS
+    KIND_SEG, KIND_ANY, N_KINDS
 };
 constexpr int FWD_MAX_WAVES = 4;  // waves per workgroup
 
@@ -93,7 +96,8 @@ struct FwdItem {
     int sweeps;  // recurrent kernel: sweeps per sample
     int C;         // C_max (program layout)
     int lvl_sh;    // level and segment mappings: log2 of the samples per tile
-    int lvl_rows;  // segment mapping: value rows before the edge offsets
+    int lvl_rows;  // segment mapping: value rows before the edge offsets; any class: samples
+                   // per tile
 };
 
 // Kernel argument: one item inline, or a device table of items.

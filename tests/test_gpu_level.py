@@ -192,3 +192,31 @@ def test_segment_mapping_long_in_edge_lists():
     y64, beta = oracle.forward(pop.nodes, pop.conns, pop.inputs, pop.I, pop.O)
     assert_parity(ys, y64, beta, "seg wide levels")
     assert_parity(_run(pop, neat.FWD_LVL), y64, beta, "lvl wide levels")
+
+
+# (P, N_max, B) on both sides of the rules that choose one population's
+# mapping: one launch for every class in tiles of 64 samples (up to 2048
+# waves) and of 128, the level mapping, and the launches per class; 223 and
+# 400 rows reach the class past the registers, B leaves ragged tiles
+CHOICES = [(5, 63, 65), (2049, 63, 8), (2049, 64, 64), (33, 126, 129), (700, 127, 200),
+           (90, 127, 181), (91, 127, 181), (1100, 151, 130), (40, 223, 70), (300, 223, 70),
+           (250, 400, 129), (700, 400, 200), (2731, 150, 130)]
+
+
+@pytest.mark.parametrize("P,N,B", CHOICES, ids=["P%dN%dB%d" % s for s in CHOICES])
+def test_one_population_mappings_agree_bitwise(P, N, B):
+    neat = _neat()
+    print("case P=%d N_max=%d B=%d" % (P, N, B), flush=True)
+    rng = np.random.default_rng(P + N + B)
+    base = synth.uneven_population(rng, (24, 24), (N, N), (1, 1), with_inputs=False)
+    who = rng.integers(0, base.P, P)
+    who[:base.P] = np.arange(base.P)[:P]
+    pop = synth.Population(base.nodes[who].copy(), base.conns[who].copy(), base.I, base.O)
+    pop.nodes[P // 2, :, 3] = 99.0  # a rejected genome: NaN outputs
+    pop.inputs = rng.standard_normal((P, B, base.I), dtype=np.float32)
+    ref = _run(pop, neat.FWD_LDS)
+    for variant in (neat.FWD_AUTO, neat.FWD_REG, neat.FWD_REG2):
+        assert _same_bits(_run(pop, variant), ref), variant
+    few = min(P, 12)
+    y64, beta = oracle.forward(pop.nodes[:few], pop.conns[:few], pop.inputs[:few], pop.I, pop.O)
+    assert_parity(ref[:few], y64, beta, "P%d N%d B%d" % (P, N, B))
