@@ -1,7 +1,7 @@
 """Build the HIP library ``libneat.so`` for gfx950 (MI355X) in-tree.
 
-``csrc/node_loop_asm.h`` is regenerated by ``csrc/gen_node_loop.py`` and
-checked by ``csrc/check_node_loop.py`` (wait states, load completion,
+``csrc/node_loop_asm.h`` and ``csrc/node_loop_wide.h`` are regenerated by
+``csrc/gen_node_loop.py`` and checked by ``csrc/check_node_loop.py`` (wait states, load completion,
 GPR-index mode, clobbers), then every ``csrc/*.hip`` file is compiled by hipcc into an object under
 ``paper_2404_01817_amd/_build/`` (in parallel), then linked into
 ``paper_2404_01817_amd/libneat.so``.  Packed fp32 instructions are disabled
@@ -57,7 +57,7 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run([sys.executable, os.path.join(CSRC, "check_node_loop.py")],
                        capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("node_loop_asm.h fails its hazard checks:\n" + r.stdout)
+        raise RuntimeError("the node loop fails its hazard checks:\n" + r.stdout)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(_compile, srcs))

@@ -50,7 +50,7 @@ Registers:
            those registers are not overwritten in between
 
 ``check_text(header_text)`` returns the violations (empty when clean) for
-every variant; ``main`` prints them for node_loop_asm.h and exits non-zero
+every variant; ``main`` prints them for the generated headers and exits non-zero
 when there are any.
 """
 from __future__ import annotations
@@ -227,11 +227,12 @@ def parse_header(text):
 
 
 # Record words the node loop jumps on (program.h): the code word (field =
-# activation slot 0..6, or 7 = end of the loop for the sentinel) and the
-# pair-count word (field = aggregation entry 8..20, or 7 for the sentinel).
+# activation slot 0..6, the same with a unit response 21..27, or 7 = end of
+# the loop for the sentinel) and the pair-count word (field = aggregation
+# entry 8..20, or 7 for the sentinel).
 JUMP_WORDS = {"s40": "act", "s56": "act", "s43": "agg", "s59": "agg"}
 TABLE_OF_BASE = {"s92": "A", "s94": "B"}
-N_ACT_SLOTS, END_SLOT, N_SLOTS = 7, 7, 21
+N_ACT_SLOTS, END_SLOT, UNIT_ACT0, N_SLOTS = 7, 7, 21, 28
 
 
 def build_cfg(insts):
@@ -269,8 +270,8 @@ def build_cfg(insts):
             assert shr.op == "s_lshr_b32" and add.op == "s_add_u32", ins.text
             kind = JUMP_WORDS[shr.args[1]]
             slots = tables[TABLE_OF_BASE[add.args[2]]]
-            pick = (list(range(N_ACT_SLOTS)) + [END_SLOT] if kind == "act"
-                    else [END_SLOT] + list(range(END_SLOT + 1, N_SLOTS)))
+            pick = (list(range(N_ACT_SLOTS)) + [END_SLOT] + list(range(UNIT_ACT0, N_SLOTS))
+                    if kind == "act" else list(range(END_SLOT, UNIT_ACT0)))
             succ[k].update(slots[j] for j in pick)
         else:
             succ[k].add(k + 1 if k + 1 <= n else n)
@@ -494,7 +495,8 @@ def check_registers(insts, succ, clobbers):
 
 
 VALUE_SLOTS = {"S1_64": {0: 64}, "S2_64": {0: 64, 64: 64}, "S1_128": {0: 128},
-               "S1_224": {0: 224}, "S1_64R": {0: 64, 64: 64}}
+               "S1_224": {0: 224}, "S1_64R": {0: 64, 64: 64},
+               "S4_32": {0: 32, 32: 32, 64: 32, 96: 32}}
 
 
 def check_variant(name, body, clobbers, scratch):
@@ -517,8 +519,8 @@ def check_text(text):
 
 def main(argv):
     here = os.path.dirname(os.path.abspath(__file__))
-    path = argv[1] if len(argv) > 1 else os.path.join(here, "node_loop_asm.h")
-    v = check_text(open(path).read())
+    paths = argv[1:] or [os.path.join(here, f) for f in ("node_loop_asm.h", "node_loop_wide.h")]
+    v = [line for path in paths for line in check_text(open(path).read())]
     for line in v:
         print(line)
     print("%d violation(s)" % len(v))

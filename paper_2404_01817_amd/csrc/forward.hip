@@ -11,6 +11,7 @@
 // in program.h), one kernel per store:
 //   R64    v0..v63, one sample per lane            (class R64)
 //   R64X2  v0..v63 and v64..v127, two samples       (class R64)
+//   R32X4  v0..v31 ... v96..v127, four samples      (class R64, N_max <= 30)
 //   R128   v0..v127, one sample                     (class R128)
 //   R224   v0..v223, one sample                     (class R224)
 //   LDS    one LDS row of 64 lanes per slot         (class LDS; any class
@@ -47,6 +48,7 @@
 #include "launch.h"
 #include "neat.h"
 #include "node_loop_asm.h"
+#include "node_loop_wide.h"
 #include "program.h"
 
 namespace neat {
@@ -142,6 +144,11 @@ struct AsmTile<KIND_R224> {
     NEAT_TILE_FN(NEAT_TILE_S1_224, NEAT_CLOB_S1_224, )
 };
 template <>
+struct AsmTile<KIND_R32X4> {
+    static constexpr int SPL = 4;
+    NEAT_TILE_FN(NEAT_TILE_S4_32, NEAT_CLOB_S4_32, )
+};
+template <>
 struct AsmTile<KIND_R64REC> {
     static constexpr int SPL = 1;
     NEAT_TILE_FN(NEAT_TILE_S1_64R, NEAT_CLOB_S1_64R, NEAT_NSW_OPERAND)
@@ -224,7 +231,7 @@ __device__ __forceinline__ void run_program(cprog_t *prog, int N, int O, int I, 
         const unsigned code = (unsigned)r[REC_CODE], np = (unsigned)r[REC_NPAIRS];
         const int pairs = (int)(np & (unsigned)REC_NPAIRS_MASK);
         const int acls = slot_class((int)(np >> REC_FIELD_SHIFT));
-        const int act = (int)(code >> REC_FIELD_SHIFT);
+        const int act = rec_act(code);
         const int slot = (int)(code & (unsigned)REC_DST_MASK);
         const float bias = fbits(r[REC_BIAS]), resp = fbits(r[REC_RESP]);
         // next record (the record array has room for N records)
@@ -382,12 +389,29 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
     const float *in_g = GRID ? nullptr : it->inputs + (size_t)g * it->gstride;
     const int vec4 = it->vec4;
     if (!GRID) dma_inputs(in_g + (size_t)t0 * TS * I, istage, min(TS, B - t0 * TS) * I, vec4);
-    // grid queries: the side coordinates, once per unit, after the staging
+    // grid queries: the side coordinates and every sample's offset in the
+    // tile as digits (x, y, points past them), once per unit, after the staging
     float *ctab = istage + TS * I;
-    const unsigned pts = (unsigned)(side * side);
+    unsigned *otab = (unsigned *)(ctab + GRID_MAX_SIDE);
+    const unsigned uside = (unsigned)side, pts = uside * uside;
     const float rside = GRID ? 1.0f / (float)side : 0.0f;
+    // digits of the tile's first query (points p1, p2) and of a tile's length
+    unsigned x1_0 = 0, y1_0 = 0, x2_0 = 0, y2_0 = 0, tx = 0, ty = 0, tk = 0;
     if (GRID) {
         for (int i = (int)lane; i < side; i += WAVE) ctab[i] = grid_coord(i, side);
+        for (int h = 0; h < SPL; ++h) {
+            const unsigned o = (unsigned)(h * WAVE) + lane, k = o / pts;
+            unsigned oy, ox;
+            divmod_small(o - k * pts, uside, rside, &oy, &ox);
+            otab[o] = ox | (oy << 8) | (k << 16);
+            istage[o * 5 + 4] = 1.0f;
+        }
+        const unsigned q0 = (unsigned)(it->first + (long long)t0 * TS);
+        const unsigned p1 = q0 / pts, p2 = q0 - p1 * pts;
+        y1_0 = p1 / uside, x1_0 = p1 - y1_0 * uside;
+        y2_0 = p2 / uside, x2_0 = p2 - y2_0 * uside;
+        tk = (unsigned)TS / pts;
+        ty = (unsigned)TS % pts / uside, tx = (unsigned)TS % pts % uside;
         __builtin_amdgcn_wave_barrier();
     }
     // the records and overflow edges the node loop will read, in one burst
@@ -398,30 +422,38 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
 
     for (int t = t0; t < t1; ++t) {
         if (GRID) {
-            // grid queries: the five inputs of each of the lane's samples.
-            // Queries are below side^4 <= 2^32; the tile's first one is split
-            // into its two points once, each lane adds its offset (< 128)
-            const unsigned q0 = (unsigned)(it->first + (long long)t * TS);
-            const unsigned p1_0 = q0 / pts, p2_0 = q0 - p1_0 * pts;
+            // grid queries: the inputs of each of the lane's samples (the
+            // fifth, 1, stays), by adding the sample's offset to the tile's
+            // first query digit by digit.  Where whole rows of targets fit the
+            // tile (tx = ty = 0) the target point stays from tile to tile.
+            const bool target = t == t0 || (tx | ty) != 0;
             for (int h = 0; h < SPL; ++h) {
-                unsigned p1 = p1_0, p2 = p2_0 + (unsigned)(h * WAVE) + lane;
-                if (pts >= (unsigned)TS) {
-                    if (p2 >= pts) p2 -= pts, ++p1;
-                } else {
-                    p1 += p2 / pts;
-                    p2 %= pts;
-                }
-                unsigned y1, x1, y2, x2;
-                divmod_small(p1, (unsigned)side, rside, &y1, &x1);
-                divmod_small(p2, (unsigned)side, rside, &y2, &x2);
-                y1 = min(y1, (unsigned)side - 1u);  // lanes past the last query
                 float *x = istage + (h * WAVE + lane) * 5;
+                const unsigned o = otab[h * WAVE + lane];
+                unsigned x2 = x2_0 + (o & 0xffu), y2 = y2_0 + ((o >> 8) & 0xffu);
+                unsigned x1 = x1_0 + (o >> 16), y1 = y1_0;
+                if (x2 >= uside) x2 -= uside, ++y2;
+                if (y2 >= uside) y2 -= uside, ++x1;
+                if (pts >= (unsigned)TS) {
+                    if (x1 >= uside) x1 -= uside, ++y1;
+                } else {
+                    unsigned c;
+                    divmod_small(x1, uside, rside, &c, &x1);
+                    y1 += c;
+                }
+                y1 = min(y1, uside - 1u);  // lanes past the last query
                 x[0] = ctab[x1];
                 x[1] = ctab[y1];
-                x[2] = ctab[x2];
-                x[3] = ctab[y2];
-                x[4] = 1.0f;
+                if (target) {
+                    x[2] = ctab[x2];
+                    x[3] = ctab[y2];
+                }
             }
+            // the next tile's first query
+            x2_0 += tx, y2_0 += ty, x1_0 += tk;
+            if (x2_0 >= uside) x2_0 -= uside, ++y2_0;
+            if (y2_0 >= uside) y2_0 -= uside, ++x1_0;
+            while (x1_0 >= uside) x1_0 -= uside, ++y1_0;
         } else {
             wait_dma();
         }
@@ -559,7 +591,7 @@ __device__ __forceinline__ void lvl_step(const i32x16 &r, int e, bool active, gi
         const unsigned code = (unsigned)r[REC_CODE], np = (unsigned)r[REC_NPAIRS];
         const int pairs = (int)(np & (unsigned)REC_NPAIRS_MASK);
         const int acls = slot_class((int)(np >> REC_FIELD_SHIFT));
-        const int act = (int)(code >> REC_FIELD_SHIFT);
+        const int act = rec_act(code);
         slot = (int)(code & (unsigned)REC_DST_MASK);
         // the six inline sources at once (unused inline edges name the
         // constant slot with weight 0)
@@ -795,7 +827,7 @@ __device__ __forceinline__ void forward_unit_seg(citem_t *it, int g, int t0, int
                 const bool tail = active && q == ec - 1;
                 float yv = 0.0f;
                 if (tail)
-                    yv = activation((int)(code >> REC_FIELD_SHIFT), fmaf(resp, xv, bias));
+                    yv = activation(rec_act(code), fmaf(resp, xv, bias));
                 // every lane of the step has read its sources
                 wave_lds_sync();
                 if (tail) v[((int)(code & (unsigned)REC_DST_MASK) << sh) + j] = yv;
@@ -960,10 +992,19 @@ __device__ __forceinline__ void run_unit(long long u, float *wave_area) {
     }
 }
 
+// Waves per SIMD that a register kernel's tile block leaves room for: what
+// the compiler adds around it must not cost one.
+constexpr int min_waves(int kind) {
+    return kind == KIND_R64 ? 5
+           : (kind == KIND_R64X2 || kind == KIND_R32X4 || kind == KIND_R128 || kind == KIND_R64REC)
+               ? 3
+               : (kind == KIND_R224 || kind == KIND_ANY) ? 2 : 1;
+}
+
 // PERSIST: a grid smaller than the unit count, each workgroup looping.
 // GRID: CPPN grid queries generated in the kernel instead of read inputs.
 template <int K, bool PERSIST, bool GRID>
-__global__ __launch_bounds__(WAVE *FWD_MAX_WAVES) void forward_kernel(FwdLaunch L) {
+__global__ __launch_bounds__(WAVE *FWD_MAX_WAVES, min_waves(K)) void forward_kernel(FwdLaunch L) {
     extern __shared__ float smem[];
     float *wave_area = smem + (size_t)(threadIdx.x / WAVE) * L.wave_floats;
     // the wave index is uniform; say so, so everything derived stays scalar
@@ -1053,7 +1094,9 @@ int launch_tiles_per_wave(const std::vector<FwdItem> &items) {
 
 // samples of one tile
 int tile_samples(int kind) {
-    return kind == KIND_R64X2 ? 2 * WAVE : (kind == KIND_LDS32 ? WAVE / 2 : WAVE);
+    return kind == KIND_R32X4   ? 4 * WAVE
+           : kind == KIND_R64X2 ? 2 * WAVE
+                                : (kind == KIND_LDS32 ? WAVE / 2 : WAVE);
 }
 
 bool lds_kind(int kind) { return kind == KIND_LDS || kind == KIND_LDS32; }
@@ -1077,7 +1120,7 @@ int kind_of(int variant, int cls, int B) {
 
 const char *kind_name(int kind) {
     static const char *names[] = {"r64", "r64x2", "r128", "r224", "lds", "r64rec", "lds32",
-                                  "lvl", "seg", "any"};
+                                  "lvl", "seg", "any", "r32x4"};
     return kind >= 0 && kind < N_KINDS ? names[kind] : "?";
 }
 
@@ -1097,6 +1140,19 @@ static int level_tile(int rows, int B, size_t extra) {
 // runs at half the scalar work per sample.
 static int any_tile(const FwdJob &J) {
     return J.B > WAVE && (long long)J.P * ((J.B + WAVE - 1) / WAVE) > 2048 ? 2 * WAVE : WAVE;
+}
+
+// Four samples per lane for the smallest class: where every value has one of
+// 32 slots, two-sample tiles fill the GPU (3072 waves of that kernel) and
+// 256 staged samples leave room for 12 waves per CU.  The node loop's scalar
+// work is shared by twice the samples, and the register file holds as many
+// samples per SIMD as with two per lane and 64 slots: CPPN grid queries, P =
+// 1000, N = 30, 65536 queries: 508 us with two samples per lane and 64 slots,
+// 414 us with two and 32 slots (five waves per SIMD instead of three), 395 us
+// with four (the vector pipe 79 % busy).
+static bool four_samples(const FwdJob &J) {
+    return J.N <= SMALL_ROWS && J.I + J.O <= 12 && J.B > 2 * WAVE &&
+           (long long)J.P * ((J.B + 2 * WAVE - 1) / (2 * WAVE)) > 3072;
 }
 
 // The mapping of a call's only population of more than 62 node rows where
@@ -1190,6 +1246,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             int kind = J.recurrent ? KIND_R64REC
                        : any       ? KIND_ANY
                                    : kind_of(variant, c < 0 ? CLS_LDS : c, J.B);
+            if (kind == KIND_R64X2 && variant == FWD_AUTO && four_samples(J)) kind = KIND_R32X4;
             // LDS rows too large for 64 columns per wave: half-wave tiles
             if (kind == KIND_LDS &&
                 sizeof(float) * (size_t)WAVE * (J.I + class_slots(top, J.N)) > max_lds)
@@ -1212,10 +1269,10 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             it.vec4 = (!J.side && ((uintptr_t)J.inputs % 16 == 0) && (J.gstride % 4 == 0)) ? 1 : 0;
             const int x = 2 * kind + (J.side ? 1 : 0);
             k[x].items.push_back(it);
-            // register kernels on grid queries keep the coordinates after
-            // the staged inputs
+            // register kernels on grid queries keep the coordinates and the
+            // samples' offsets after the staged inputs
             if (!J.side || !lds_kind(kind))
-                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE : 0));
+                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE + TS : 0));
             if (!lds_kind(kind)) ostage_max[x] = std::max(ostage_max[x], TS * J.O);
             if (kind == KIND_ANY) {
                 // the values of a genome past the register classes, in the same area
@@ -1256,7 +1313,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         // keep each item's own target: their short-B items are latency-bound
         // and gain from spreading tiles over waves (a launch-wide target made
         // the uneven batch's calculation up to 32 % slower).
-        const int shared_tpw = kind == KIND_R64X2 && K.items.size() > 1
+        const int shared_tpw = (kind == KIND_R64X2 || kind == KIND_R32X4) && K.items.size() > 1
                                    ? launch_tiles_per_wave(K.items) : 0;
         long long units = 0;
         for (FwdItem &it : K.items) {
@@ -1328,36 +1385,39 @@ hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hi
         L.items = dev_items;
         L.n_items = (int)k.items.size();
     }
+    // register kernels are never persistent (their grids have no cap)
+#define NEAT_LAUNCH1(KIND, PERSIST, GRID)                                                  \
+    hipLaunchKernelGGL((forward_kernel<KIND, PERSIST, GRID>), dim3(k.grid), dim3(k.block), \
+                       k.lds, stream, L)
+#define NEAT_LAUNCH_REG(KIND)                                                              \
+    if (k.grid_mode) NEAT_LAUNCH1(KIND, false, true);                                      \
+    else NEAT_LAUNCH1(KIND, false, false);
 #define NEAT_LAUNCH2(KIND, GRID)                                                           \
-    if (L.persistent)                                                                      \
-        hipLaunchKernelGGL((forward_kernel<KIND, true, GRID>), dim3(k.grid), dim3(k.block),   \
-                           k.lds, stream, L);                                              \
-    else                                                                                   \
-        hipLaunchKernelGGL((forward_kernel<KIND, false, GRID>), dim3(k.grid), dim3(k.block),  \
-                           k.lds, stream, L);
-#define NEAT_LAUNCH(KIND)                                                                  \
+    if (L.persistent) NEAT_LAUNCH1(KIND, true, GRID);                                      \
+    else NEAT_LAUNCH1(KIND, false, GRID);
+#define NEAT_LAUNCH_LDS(KIND)                                                              \
     if (k.grid_mode) {                                                                     \
         NEAT_LAUNCH2(KIND, true)                                                           \
     } else {                                                                               \
         NEAT_LAUNCH2(KIND, false)                                                          \
     }
     switch (k.kind) {
-    case KIND_R64: NEAT_LAUNCH(KIND_R64) break;
-    case KIND_R64X2: NEAT_LAUNCH(KIND_R64X2) break;
-    case KIND_R128: NEAT_LAUNCH(KIND_R128) break;
-    case KIND_R224: NEAT_LAUNCH(KIND_R224) break;
-    case KIND_R64REC: NEAT_LAUNCH2(KIND_R64REC, false) break;
-    case KIND_LDS32: NEAT_LAUNCH(KIND_LDS32) break;
+    case KIND_R64: NEAT_LAUNCH_REG(KIND_R64) break;
+    case KIND_R64X2: NEAT_LAUNCH_REG(KIND_R64X2) break;
+    case KIND_R32X4: NEAT_LAUNCH_REG(KIND_R32X4) break;
+    case KIND_R128: NEAT_LAUNCH_REG(KIND_R128) break;
+    case KIND_R224: NEAT_LAUNCH_REG(KIND_R224) break;
+    case KIND_R64REC: NEAT_LAUNCH1(KIND_R64REC, false, false); break;
+    case KIND_LDS32: NEAT_LAUNCH_LDS(KIND_LDS32) break;
     case KIND_LVL: NEAT_LAUNCH2(KIND_LVL, false) break;
     case KIND_SEG: NEAT_LAUNCH2(KIND_SEG, false) break;
-    case KIND_ANY:  // never persistent (its grid has no cap)
-        hipLaunchKernelGGL((forward_kernel<KIND_ANY, false, false>), dim3(k.grid), dim3(k.block),
-                           k.lds, stream, L);
-        break;
-    default: NEAT_LAUNCH(KIND_LDS) break;
+    case KIND_ANY: NEAT_LAUNCH1(KIND_ANY, false, false); break;
+    default: NEAT_LAUNCH_LDS(KIND_LDS) break;
     }
-#undef NEAT_LAUNCH
+#undef NEAT_LAUNCH_LDS
 #undef NEAT_LAUNCH2
+#undef NEAT_LAUNCH_REG
+#undef NEAT_LAUNCH1
     return hipGetLastError();
 }
 

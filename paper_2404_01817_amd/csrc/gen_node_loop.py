@@ -1,6 +1,6 @@
 #!/usr/bin/env python3
-"""Generate node_loop_asm.h: the forward kernels' node loop in gfx950
-assembly, one variant per value-vector shape.
+"""Generate node_loop_asm.h and node_loop_wide.h: the forward kernels' node
+loop in gfx950 assembly, one variant per value-vector shape.
 
 The node loop evaluates, for every computed node of a genome in topological
 order, v[dst] = act(bias + response * agg(w * v[src])) (the calculation
@@ -22,10 +22,12 @@ Variants (name: samples per lane, value slots, VGPRs of the value vectors):
   S1_224  1 sample, 224 slots,  v0..v223
   S1_64R  1 sample,  64 slots,  v0..v63 read and v64..v127 written: the
           recurrent calculation, %[nsw] synchronous sweeps of the node loop
+and in node_loop_wide.h, for populations of few node rows:
+  S4_32   4 samples, 32 slots,  v0..v31, v32..v63, v64..v95, v96..v127
 Scratch VGPRs follow the value vectors.
 
-Run as ``python gen_node_loop.py`` to rewrite node_loop_asm.h next to it;
-the build does this before compiling, so the header always matches.
+Run as ``python gen_node_loop.py`` to rewrite the two headers next to it;
+the build does this before compiling, so they always match.
 """
 from __future__ import annotations
 
@@ -42,6 +44,11 @@ VARIANTS = [
     ("S1_64R", 1, (0,), 128, (64,)),
 ]
 
+# the variants of node_loop_wide.h, and the input buffers per sample
+VARIANTS_WIDE = [
+    ("S4_32", 4, (0, 32, 64, 96), 128, None, 4),
+]
+
 # scalar register map (shared by all variants)
 # record buffers: code, bias, response', pair count, three edge pairs
 REC_A = tuple("s%d" % i for i in range(40, 56))
@@ -54,7 +61,8 @@ INLINE_PAIRS = 3
 # table slot at bit 24.  Table (per copy of the node loop, one stride per
 # slot): activation blocks 0..6, the end of the loop at 7, then the
 # aggregation entries, one per (class, pairs): sum with 0..3 pairs and with
-# overflow, product and max with 1..3 pairs and with overflow.
+# overflow, product and max with 1..3 pairs and with overflow; then the
+# activation blocks of nodes whose response' is 1.
 FIELD_SHIFT = 24
 NP_MASK = "0x3fff"
 TAB_END = 7
@@ -97,6 +105,7 @@ class Regs:
 
     def __init__(self, spl, bases, scratch, wbases=None, group=8):
         self.spl = spl
+        self.unit_response = False  # set while those blocks are generated
         self.bases = ["v%d" % b for b in bases]
         # recurrent: reads from v[bases], writes to v[wbases]
         self.rec = wbases is not None
@@ -187,9 +196,19 @@ def pair(R, cls, first, s0, w0, s1, w1):
 
 
 def inline_pairs(R, cls, rec, k):
-    """The first k (<= 3) of the node's pairs, from its record."""
+    """The first k (<= 3) of the node's pairs, from its record.  A sum's
+    edges all read v[slot] as src0, so they stay in one span of indexed
+    mode."""
     p = rec[4:16]
     out = []
+    if cls == "sum":
+        for e in range(2 * k):
+            slot, w = p[2 * e], p[2 * e + 1]
+            out += ["s_set_gpr_idx_idx %s" % slot if e else
+                    "s_set_gpr_idx_on %s, gpr_idx(SRC0)" % slot]
+            out += per_sample(R, ("v_fmac_f32_e64 {acc}, {val}, " if e else
+                                  "v_mul_f32_e64 {acc}, {val}, ") + w)
+        return out + (["s_set_gpr_idx_off"] if k else [])
     for j in range(k):
         out += pair(R, cls, j == 0, *p[4 * j:4 * j + 4])
     return out
@@ -234,9 +253,8 @@ def jump(word, base, shift):
 
 
 def to_activation(R, rec, base, shift):
-    """z = bias (the activation block finishes z), then the jump to the
-    node's activation block."""
-    return seq(R, "v_mov_b32_e32 {z}, " + rec[1]) + jump(rec[0], base, shift)
+    """The jump to the node's activation block."""
+    return jump(rec[0], base, shift)
 
 
 def agg_entry(R, X, cls, k, rec, pref, base, shift):
@@ -257,19 +275,22 @@ def agg_entry(R, X, cls, k, rec, pref, base, shift):
 
 
 # --------------------------------------------------------------- activation
-# Activation blocks, one per code of the encoding (ACT_*).  On entry z holds
-# the bias and acc the aggregate; every block returns (body, y): body
+# Activation blocks, one per code of the encoding (ACT_*).  On entry acc
+# holds the aggregate; every block returns (body, y): body
 # computes y = act(z) into the scratch register named y, which a plain move
 # with the destination indexed then writes to v[dst].  Only moves run with
 # destination indexing; the arithmetic stays outside it, and two wait states
 # separate a transcendental (v_exp, v_rcp, which completes after later
 # instructions have issued) from the switch into indexed mode.
-# z = fma(response', acc, bias) is the first step of every block.
+# The first step of every block is z = fma(response', acc, bias), or z = acc
+# + bias, the same bits in one instruction less, where response' is 1.
 TRANS_GAP = "s_nop 1"
 
 
 def z_of(R):
-    return seq(R, "v_fmac_f32_e64 {z}, " + "%(resp)s" + ", {acc}")
+    if R.unit_response:
+        return seq(R, "v_add_f32_e32 {z}, %(bias)s, {acc}")
+    return seq(R, "v_mov_b32_e32 {z}, %(bias)s", "v_fmac_f32_e64 {z}, %(resp)s, {acc}")
 
 
 def act_identity(R):
@@ -370,11 +391,11 @@ def act_blocks(R, rec, orec, obase, shift):
     """The activation blocks of the copy of the node loop with record buffer
     rec, each with the write of v[dst] and the jump into the next node's
     aggregation entry (record orec, the other copy's table at obase)."""
-    CODE, RESP = rec[0], rec[2]
+    CODE, BIAS, RESP = rec[0], rec[1], rec[2]
     blocks = []
     for fn in ACTS:
         body, y = fn(R)
-        body = [l % {"resp": RESP} for l in body]
+        body = [l % {"resp": RESP, "bias": BIAS} for l in body]
         # v[dst] = y (GPR-index mode uses the low 8 bits of the code word:
         # the destination slot); next node, once its record is in
         body += ["s_set_gpr_idx_on %s, gpr_idx(DST)" % CODE]
@@ -391,6 +412,9 @@ def table(R, X, rec, pref, base, orec, obase, shift):
     slots.append(["s_branch Ldone%="])
     for cls, k in AGG_ENTRIES:
         slots.append(agg_entry(R, X, cls, k, rec, pref, base, shift))
+    R.unit_response = True
+    slots += act_blocks(R, rec, orec, obase, shift)
+    R.unit_response = False
     return slots
 
 
@@ -456,39 +480,41 @@ def node_loop(R):
 
 
 def place_inputs(R):
-    """v[i] = staged input i of the lane's sample(s), i < %[ni], eight at a
-    time (ds_read2 pairs, one index setting per eight moves).  The last
-    group may write up to seven slots past the inputs: those belong to
+    """v[i] = staged input i of the lane's sample(s), i < %[ni], a group (8,
+    or 4) at a time (ds_read2 pairs, one index setting per group's moves).
+    The last group may write slots past the inputs: those belong to
     computed nodes (written before any read) or the constants (set after),
     and the reads past the lane's inputs stay inside the staging areas."""
-    # lane l's first input: %[dm0] + 4 l ni (+ 256 ni for the second sample)
+    G = R.group
+    # lane l's first input: %[dm0] + 4 l ni (+ 256 ni for each further sample)
     out = ["s_lshl_b32 s41, %[ni], 2",
            "v_mul_u32_u24_e32 %s, s41, %%[lane]" % R.addr[0],
            "v_add_u32_e32 %s, %%[dm0], %s" % (R.addr[0], R.addr[0])]
-    if R.spl == 2:
-        out += ["s_lshl_b32 s41, %[ni], 8",
-                "v_add_u32_e32 %s, s41, %s" % (R.addr[1], R.addr[0])]
+    if R.spl > 1:
+        out += ["s_lshl_b32 s41, %[ni], 8"]
+        out += ["v_add_u32_e32 %s, s41, %s" % (R.addr[h], R.addr[h - 1])
+                for h in range(1, R.spl)]
     out += ["s_mov_b32 s40, 0",
             "s_cmp_eq_u32 %[ni], 0",
             "s_cbranch_scc1 Lpl_done%=",
             "Lpl%=:"]
     for h in range(R.spl):
         b = R.buf[h]
-        for k in range(0, 8, 2):
+        for k in range(0, G, 2):
             lo, hi = int(b[k][1:]), int(b[k + 1][1:])
             out.append("ds_read2_b32 v[%d:%d], %s offset0:%d offset1:%d"
                        % (lo, hi, R.addr[h], k, k + 1))
     for h in range(R.spl):
-        out.append("v_add_u32_e32 %s, 32, %s" % (R.addr[h], R.addr[h]))
+        out.append("v_add_u32_e32 %s, %d, %s" % (R.addr[h], 4 * G, R.addr[h]))
     out += ["s_waitcnt lgkmcnt(0)",
             "s_set_gpr_idx_on s40, gpr_idx(DST)"]
     for h in range(R.spl):
         for vb in sorted(set([R.bases[h], R.wbases[h]])):
             base = int(vb[1:])
-            for k in range(8):
+            for k in range(G):
                 out.append("v_mov_b32_e32 v%d, %s" % (base + k, R.buf[h][k]))
     out += ["s_set_gpr_idx_off",
-            "s_add_u32 s40, s40, 8",
+            "s_add_u32 s40, s40, %d" % G,
             "s_cmp_lt_u32 s40, %[ni]",
             "s_cbranch_scc1 Lpl%=",
             "Lpl_done%=:",
@@ -545,26 +571,27 @@ def dma_next(R):
 
 def write_outputs(R):
     """Output j of the lane's sample(s) -> LDS output area %[om0] + 4 (l O
-    + j) for lane l (+ 256 O for the second sample), slots from %[outs],
+    + j) for lane l (+ 256 O for each further sample), slots from %[outs],
     O = %[no]."""
     out = ["s_mov_b64 s[44:45], %[outs]",
            "s_mov_b32 s40, 0",
            "s_lshl_b32 s41, %[no], 2",
            "v_mul_u32_u24_e32 %s, s41, %%[lane]" % R.addr[0],
            "v_add_u32_e32 %s, %%[om0], %s" % (R.addr[0], R.addr[0])]
-    if R.spl == 2:
-        out += ["s_lshl_b32 s41, %[no], 8",
-                "v_add_u32_e32 %s, s41, %s" % (R.addr[1], R.addr[0])]
+    if R.spl > 1:
+        out += ["s_lshl_b32 s41, %[no], 8"]
+        out += ["v_add_u32_e32 %s, s41, %s" % (R.addr[h], R.addr[h - 1])
+                for h in range(1, R.spl)]
     out += ["Lout%=:",
             "s_load_dwordx8 s[48:55], s[44:45], 0x0",
             "s_waitcnt lgkmcnt(0)"]
     for k in range(8):
         out += ["s_set_gpr_idx_on s%d, gpr_idx(SRC0)" % (48 + k)]
         for h in range(R.spl):
-            out += ["v_mov_b32_e32 %s, %s" % (R.buf[h][k], R.bases[h])]
+            out += ["v_mov_b32_e32 %s, %s" % (R.buf[h][k % R.group], R.bases[h])]
         out += ["s_set_gpr_idx_off"]
         for h in range(R.spl):
-            out += ["ds_write_b32 %s, %s offset:%d" % (R.addr[h], R.buf[h][k], 4 * k)]
+            out += ["ds_write_b32 %s, %s offset:%d" % (R.addr[h], R.buf[h][k % R.group], 4 * k)]
         out += ["s_add_u32 s40, s40, 1",
                 "s_cmp_ge_u32 s40, %[no]",
                 "s_cbranch_scc1 Lout_done%="]
@@ -639,7 +666,7 @@ HEADER = """\
 // A tile block (NEAT_TILE_<variant>) does, in order:
 //   1. v[i] = input i of the lane's sample(s), i < %[ni], from the LDS
 //      staging area at byte address %[dm0] (sample s's inputs at + 4 s ni;
-//      lane l holds samples l and, with two per lane, 64 + l); then the
+//      lane l holds samples l, 64 + l, ...: one per sample of the lane); then the
 //      constants 0 and 1 at slots %[zs], %[zs] + 1;
 //   2. the DMA of the next tile's inputs into the staging area: %[dn]
 //      pieces of 16 bytes (%[dvec] = 1) or 4 bytes (%[dvec] = 0) from the
@@ -693,31 +720,55 @@ def c_string(lines_):
                      for l in lines_)
 
 
+WIDE_HEADER = """\
+// node_loop_wide.h -- GENERATED by gen_node_loop.py; edit that script.
+//
+// Tile blocks as in node_loop_asm.h (which describes them) for populations
+// of few node rows, with more samples per lane or fewer value registers.
+#pragma once
+"""
+
+
+def variant_text(name, spl, bases, scratch, wbases, group=8):
+    R = Regs(spl, bases, scratch, wbases, group)
+    body = tile(R)
+    parts = ["// %s: %d sample(s) per lane, value vectors at %s, scratch v%d..v%d\n"
+             % (name, spl, ", ".join("v%d" % b for b in bases), scratch, R.last)]
+    parts.append("#define NEAT_TILE_%s \\\n%s\n" % (name, " \\\n".join(
+        c_string([l]) for l in body)))
+    vclob = ['"v%d"' % i for i in range(0, R.last + 1)]
+    clob = vclob + ['"%s"' % s for s in SGPR_CLOBBERS] + ['"vcc"', '"scc"']
+    rows = [", ".join(clob[i:i + 12]) for i in range(0, len(clob), 12)]
+    parts.append("#define NEAT_CLOB_%s \\\n    %s\n" % (name, ", \\\n    ".join(rows)))
+    parts.append("#define NEAT_SCRATCH_%s %d\n\n" % (name, scratch))
+    return parts
+
+
 def generate():
     parts = [HEADER]
-    for name, spl, bases, scratch, wbases in VARIANTS:
-        R = Regs(spl, bases, scratch, wbases)
-        body = tile(R)
-        parts.append("// %s: %d sample(s) per lane, value vectors at %s, scratch v%d..v%d\n"
-                     % (name, spl, ", ".join("v%d" % b for b in bases), scratch, R.last))
-        parts.append("#define NEAT_TILE_%s \\\n%s\n" % (name, " \\\n".join(
-            c_string([l]) for l in body)))
-        vclob = ['"v%d"' % i for i in range(0, R.last + 1)]
-        clob = vclob + ['"%s"' % s for s in SGPR_CLOBBERS] + ['"vcc"', '"scc"']
-        rows = [", ".join(clob[i:i + 12]) for i in range(0, len(clob), 12)]
-        parts.append("#define NEAT_CLOB_%s \\\n    %s\n" % (name, ", \\\n    ".join(rows)))
-        parts.append("#define NEAT_SCRATCH_%s %d\n\n" % (name, scratch))
+    for v in VARIANTS:
+        parts += variant_text(*v)
     return "\n".join(parts)
 
 
-def main(argv):
-    here = os.path.dirname(os.path.abspath(__file__))
-    path = argv[1] if len(argv) > 1 else os.path.join(here, "node_loop_asm.h")
-    text = generate()
+def generate_wide():
+    parts = [WIDE_HEADER]
+    for v in VARIANTS_WIDE:
+        parts += variant_text(*v)
+    return "\n".join(parts)
+
+
+def write(path, text):
     old = open(path).read() if os.path.exists(path) else None
     if old != text:
         with open(path, "w") as f:
             f.write(text)
+
+
+def main(argv):
+    here = os.path.dirname(os.path.abspath(__file__))
+    write(argv[1] if len(argv) > 1 else os.path.join(here, "node_loop_asm.h"), generate())
+    write(argv[2] if len(argv) > 2 else os.path.join(here, "node_loop_wide.h"), generate_wide())
 
 
 if __name__ == "__main__":

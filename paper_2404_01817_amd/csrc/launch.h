@@ -57,13 +57,14 @@ constexpr int FWD_ANY = 7;   // one launch, each wave by its genome's class (int
 // 64-slot register store, for populations of N_max <= 62.  KIND_LDS32: the
 // LDS-row store with half-wave tiles (32 samples), for genomes whose rows
 // do not fit in LDS with 64 columns.
+// KIND_R32X4: four samples per lane, for populations of N_max <= 30.
 // KIND_LVL / KIND_SEG: the level and segment mappings (FWD_LVL, FWD_SEG),
 // every genome of an item, tiles of 2^lvl_sh samples.  KIND_ANY: every
 // genome of an item, each wave with the register store of its genome's class
 // (the level mapping past the register classes).
 enum FwdKind {
     KIND_R64 = 0, KIND_R64X2, KIND_R128, KIND_R224, KIND_LDS, KIND_R64REC, KIND_LDS32, KIND_LVL,
-    KIND_SEG, KIND_ANY, N_KINDS
+    KIND_SEG, KIND_ANY, KIND_R32X4, N_KINDS
 };
 constexpr int FWD_MAX_WAVES = 4;  // waves per workgroup
 

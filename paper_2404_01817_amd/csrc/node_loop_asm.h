@@ -7,7 +7,7 @@
 // A tile block (NEAT_TILE_<variant>) does, in order:
 //   1. v[i] = input i of the lane's sample(s), i < %[ni], from the LDS
 //      staging area at byte address %[dm0] (sample s's inputs at + 4 s ni;
-//      lane l holds samples l and, with two per lane, 64 + l); then the
+//      lane l holds samples l, 64 + l, ...: one per sample of the lane); then the
 //      constants 0 and 1 at slots %[zs], %[zs] + 1;
 //   2. the DMA of the next tile's inputs into the staging area: %[dn]
 //      pieces of 16 bytes (%[dvec] = 1) or 4 bytes (%[dvec] = 0) from the
@@ -149,6 +149,7 @@
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v67\n" \
@@ -159,6 +160,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_mul_f32_e32 v65, 0x4038aa3b, v67\n" \
     "  v_exp_f32_e32 v65, v65\n" \
@@ -176,6 +178,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_mul_f32_e32 v65, 0xbfb8aa3b, v67\n" \
     "  v_exp_f32_e32 v65, v65\n" \
@@ -192,6 +195,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_maximum3_f32 v65, v67, 0, 0\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -203,6 +207,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_mul_f32_e32 v66, 0x3ea2f983, v67\n" \
     "  v_rndne_f32_e32 v66, v66\n" \
@@ -227,6 +232,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_mul_f32_e32 v65, v67, v67\n" \
     "  v_mul_f32_e32 v65, 0xbfb8aa3b, v65\n" \
@@ -241,6 +247,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s41\n" \
     "  v_fmac_f32_e64 v67, s42, v64\n" \
     "  v_maximum3_f32 v65, v67, -v67, -v67\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -257,7 +264,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
     "  v_mov_b32_e32 v64, 0\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -270,7 +276,6 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v64, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -282,13 +287,11 @@
     "  v_mul_f32_e64 v64, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v64, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v64, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v64, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -300,18 +303,15 @@
     "  v_mul_f32_e64 v64, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v64, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v64, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v64, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v64, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v64, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -324,13 +324,11 @@
     "  v_mul_f32_e64 v64, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v64, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v64, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v64, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v64, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v64, v0, s55\n" \
@@ -345,7 +343,6 @@
     "  v_mul_f32_e64 v66, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -366,7 +363,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v65\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -394,7 +390,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v65\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -433,7 +428,6 @@
     "  v_mul_f32_e64 v66, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v65, v66, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -453,7 +447,6 @@
     "  v_mul_f32_e64 v66, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -479,7 +472,6 @@
     "  v_mul_f32_e64 v66, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -507,6 +499,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
     "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_mul_f32_e32 v65, 0x4038aa3b, v67\n" \
+    "  v_exp_f32_e32 v65, v65\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v66, 1.0, v65\n" \
+    "  v_rcp_f32_e32 v66, v66\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v65, v66, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_mul_f32_e32 v65, 0xbfb8aa3b, v67\n" \
+    "  v_exp_f32_e32 v65, v65\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v66, 1.0, v65\n" \
+    "  v_rcp_f32_e32 v65, v66\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_maximum3_f32 v65, v67, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_mul_f32_e32 v66, 0x3ea2f983, v67\n" \
+    "  v_rndne_f32_e32 v66, v66\n" \
+    "  v_fmamk_f32 v64, v66, 0xc0490fdb, v67\n" \
+    "  v_fmac_f32_e32 v64, 0x33bbbd2e, v66\n" \
+    "  v_cvt_i32_f32_e32 v66, v66\n" \
+    "  v_mul_f32_e32 v67, v64, v64\n" \
+    "  v_fmaak_f32 v69, v67, v68, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0xb9500d01\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0x3c088889\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v65, v64, v67\n" \
+    "  v_fmac_f32_e32 v64, v65, v69\n" \
+    "  v_lshl_add_u32 v65, v66, 31, v64\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_mul_f32_e32 v65, v67, v67\n" \
+    "  v_mul_f32_e32 v65, 0xbfb8aa3b, v65\n" \
+    "  v_exp_f32_e32 v66, v65\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v66\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s41, v64\n" \
+    "  v_maximum3_f32 v65, v67, -v67, -v67\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_A%=:\n" \
     "  s_and_b32 s87, s43, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -536,7 +631,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_A%=\n" \
     "Lovds_A%=:\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -574,7 +668,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_A%=\n" \
     "Lovdp_A%=:\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -610,13 +703,13 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_A%=\n" \
     "Lovdm_A%=:\n" \
-    "  v_mov_b32_e32 v67, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v67\n" \
@@ -627,6 +720,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_mul_f32_e32 v65, 0x4038aa3b, v67\n" \
     "  v_exp_f32_e32 v65, v65\n" \
@@ -644,6 +738,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_mul_f32_e32 v65, 0xbfb8aa3b, v67\n" \
     "  v_exp_f32_e32 v65, v65\n" \
@@ -660,6 +755,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_maximum3_f32 v65, v67, 0, 0\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -671,6 +767,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_mul_f32_e32 v66, 0x3ea2f983, v67\n" \
     "  v_rndne_f32_e32 v66, v66\n" \
@@ -695,6 +792,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_mul_f32_e32 v65, v67, v67\n" \
     "  v_mul_f32_e32 v65, 0xbfb8aa3b, v65\n" \
@@ -709,6 +807,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v67, s57\n" \
     "  v_fmac_f32_e64 v67, s58, v64\n" \
     "  v_maximum3_f32 v65, v67, -v67, -v67\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -725,7 +824,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
     "  v_mov_b32_e32 v64, 0\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -738,7 +836,6 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v64, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -750,13 +847,11 @@
     "  v_mul_f32_e64 v64, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v64, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v64, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v64, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -768,18 +863,15 @@
     "  v_mul_f32_e64 v64, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v64, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v64, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v64, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v64, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v64, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -792,13 +884,11 @@
     "  v_mul_f32_e64 v64, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v64, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v64, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v64, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v64, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v64, v0, s71\n" \
@@ -813,7 +903,6 @@
     "  v_mul_f32_e64 v66, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -834,7 +923,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v65\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -862,7 +950,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v64, v64, v65\n" \
     "  v_mul_f32_e32 v64, v64, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -901,7 +988,6 @@
     "  v_mul_f32_e64 v66, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v65, v66, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -921,7 +1007,6 @@
     "  v_mul_f32_e64 v66, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -947,7 +1032,6 @@
     "  v_mul_f32_e64 v66, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -975,6 +1059,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v64, v64, v65, v66\n" \
     "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_mul_f32_e32 v65, 0x4038aa3b, v67\n" \
+    "  v_exp_f32_e32 v65, v65\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v66, 1.0, v65\n" \
+    "  v_rcp_f32_e32 v66, v66\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v65, v66, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_mul_f32_e32 v65, 0xbfb8aa3b, v67\n" \
+    "  v_exp_f32_e32 v65, v65\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v66, 1.0, v65\n" \
+    "  v_rcp_f32_e32 v65, v66\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_maximum3_f32 v65, v67, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_mul_f32_e32 v66, 0x3ea2f983, v67\n" \
+    "  v_rndne_f32_e32 v66, v66\n" \
+    "  v_fmamk_f32 v64, v66, 0xc0490fdb, v67\n" \
+    "  v_fmac_f32_e32 v64, 0x33bbbd2e, v66\n" \
+    "  v_cvt_i32_f32_e32 v66, v66\n" \
+    "  v_mul_f32_e32 v67, v64, v64\n" \
+    "  v_fmaak_f32 v69, v67, v68, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0xb9500d01\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0x3c088889\n" \
+    "  v_fmaak_f32 v69, v67, v69, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v65, v64, v67\n" \
+    "  v_fmac_f32_e32 v64, v65, v69\n" \
+    "  v_lshl_add_u32 v65, v66, 31, v64\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_mul_f32_e32 v65, v67, v67\n" \
+    "  v_mul_f32_e32 v65, 0xbfb8aa3b, v65\n" \
+    "  v_exp_f32_e32 v66, v65\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v66\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v67, s57, v64\n" \
+    "  v_maximum3_f32 v65, v67, -v67, -v67\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v65\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_B%=:\n" \
     "  s_and_b32 s87, s59, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -1004,7 +1191,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_B%=\n" \
     "Lovds_B%=:\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -1042,7 +1228,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_B%=\n" \
     "Lovdp_B%=:\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -1078,7 +1263,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_B%=\n" \
     "Lovdm_B%=:\n" \
-    "  v_mov_b32_e32 v67, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -1285,6 +1469,8 @@
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -1297,6 +1483,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
@@ -1319,6 +1507,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
@@ -1340,6 +1530,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_maximum3_f32 v130, v134, 0, 0\n" \
@@ -1354,6 +1546,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
@@ -1394,6 +1588,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_mul_f32_e32 v130, v134, v134\n" \
@@ -1413,6 +1609,8 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
     "  v_fmac_f32_e64 v134, s42, v128\n" \
     "  v_fmac_f32_e64 v135, s42, v129\n" \
     "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
@@ -1433,8 +1631,6 @@
     "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
     "  v_mov_b32_e32 v129, 0\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1449,8 +1645,6 @@
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  v_fmac_f32_e64 v129, v64, s47\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1464,16 +1658,13 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  v_fmac_f32_e64 v129, v64, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  v_fmac_f32_e64 v129, v64, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
     "  v_fmac_f32_e64 v129, v64, s51\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1487,23 +1678,19 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  v_fmac_f32_e64 v129, v64, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  v_fmac_f32_e64 v129, v64, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
     "  v_fmac_f32_e64 v129, v64, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  v_fmac_f32_e64 v129, v64, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v128, v0, s55\n" \
     "  v_fmac_f32_e64 v129, v64, s55\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1518,15 +1705,13 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  v_fmac_f32_e64 v129, v64, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  v_fmac_f32_e64 v129, v64, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
     "  v_fmac_f32_e64 v129, v64, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  v_fmac_f32_e64 v129, v64, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
@@ -1546,8 +1731,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1575,8 +1758,6 @@
     "  v_mul_f32_e32 v129, v129, v131\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1615,8 +1796,6 @@
     "  v_mul_f32_e32 v129, v129, v131\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1669,8 +1848,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v130, v132, v132\n" \
     "  v_maximum3_f32 v129, v131, v133, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1696,8 +1873,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1732,8 +1907,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1770,6 +1943,148 @@
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
     "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v134\n" \
+    "  v_mov_b32_e32 v64, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v132\n" \
+    "  v_mov_b32_e32 v64, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_A%=:\n" \
     "  s_and_b32 s87, s43, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -1803,8 +2118,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_A%=\n" \
     "Lovds_A%=:\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1850,8 +2163,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_A%=\n" \
     "Lovdp_A%=:\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -1893,14 +2204,14 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_A%=\n" \
     "Lovdm_A%=:\n" \
-    "  v_mov_b32_e32 v134, s41\n" \
-    "  v_mov_b32_e32 v135, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -1913,6 +2224,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
@@ -1935,6 +2248,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
@@ -1956,6 +2271,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_maximum3_f32 v130, v134, 0, 0\n" \
@@ -1970,6 +2287,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
@@ -2010,6 +2329,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_mul_f32_e32 v130, v134, v134\n" \
@@ -2029,6 +2350,8 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
     "  v_fmac_f32_e64 v134, s58, v128\n" \
     "  v_fmac_f32_e64 v135, s58, v129\n" \
     "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
@@ -2049,8 +2372,6 @@
     "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
     "  v_mov_b32_e32 v129, 0\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2065,8 +2386,6 @@
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  v_fmac_f32_e64 v129, v64, s63\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2080,16 +2399,13 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  v_fmac_f32_e64 v129, v64, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  v_fmac_f32_e64 v129, v64, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
     "  v_fmac_f32_e64 v129, v64, s67\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2103,23 +2419,19 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  v_fmac_f32_e64 v129, v64, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  v_fmac_f32_e64 v129, v64, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
     "  v_fmac_f32_e64 v129, v64, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  v_fmac_f32_e64 v129, v64, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v128, v0, s71\n" \
     "  v_fmac_f32_e64 v129, v64, s71\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2134,15 +2446,13 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  v_fmac_f32_e64 v129, v64, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  v_fmac_f32_e64 v129, v64, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
     "  v_fmac_f32_e64 v129, v64, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  v_fmac_f32_e64 v129, v64, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
@@ -2162,8 +2472,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2191,8 +2499,6 @@
     "  v_mul_f32_e32 v129, v129, v131\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2231,8 +2537,6 @@
     "  v_mul_f32_e32 v129, v129, v131\n" \
     "  v_mul_f32_e32 v128, v128, v132\n" \
     "  v_mul_f32_e32 v129, v129, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2285,8 +2589,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v130, v132, v132\n" \
     "  v_maximum3_f32 v129, v131, v133, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2312,8 +2614,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2348,8 +2648,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2386,6 +2684,148 @@
     "  v_maximum3_f32 v128, v128, v130, v132\n" \
     "  v_maximum3_f32 v129, v129, v131, v133\n" \
     "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v134\n" \
+    "  v_mov_b32_e32 v64, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v132\n" \
+    "  v_mov_b32_e32 v64, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_B%=:\n" \
     "  s_and_b32 s87, s59, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -2419,8 +2859,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_B%=\n" \
     "Lovds_B%=:\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2466,8 +2904,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_B%=\n" \
     "Lovdp_B%=:\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2509,8 +2945,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_B%=\n" \
     "Lovdm_B%=:\n" \
-    "  v_mov_b32_e32 v134, s57\n" \
-    "  v_mov_b32_e32 v135, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -2725,6 +3159,7 @@
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v131\n" \
@@ -2735,6 +3170,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -2752,6 +3188,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -2768,6 +3205,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_maximum3_f32 v129, v131, 0, 0\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -2779,6 +3217,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
     "  v_rndne_f32_e32 v130, v130\n" \
@@ -2803,6 +3242,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, v131, v131\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
@@ -2817,6 +3257,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -2833,7 +3274,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2846,7 +3286,6 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2858,13 +3297,11 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2876,18 +3313,15 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v128, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2900,13 +3334,11 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v128, v0, s55\n" \
@@ -2921,7 +3353,6 @@
     "  v_mul_f32_e64 v130, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2942,7 +3373,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -2970,7 +3400,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3009,7 +3438,6 @@
     "  v_mul_f32_e64 v130, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v129, v130, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3029,7 +3457,6 @@
     "  v_mul_f32_e64 v130, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3055,7 +3482,6 @@
     "  v_mul_f32_e64 v130, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3083,6 +3509,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
     "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v130, v130\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v129, v130, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v129, v130\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_maximum3_f32 v129, v131, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
+    "  v_rndne_f32_e32 v130, v130\n" \
+    "  v_fmamk_f32 v128, v130, 0xc0490fdb, v131\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v130\n" \
+    "  v_cvt_i32_f32_e32 v130, v130\n" \
+    "  v_mul_f32_e32 v131, v128, v128\n" \
+    "  v_fmaak_f32 v133, v131, v132, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xb9500d01\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3c088889\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v129, v128, v131\n" \
+    "  v_fmac_f32_e32 v128, v129, v133\n" \
+    "  v_lshl_add_u32 v129, v130, 31, v128\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, v131, v131\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
+    "  v_exp_f32_e32 v130, v129\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_A%=:\n" \
     "  s_and_b32 s87, s43, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -3112,7 +3641,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_A%=\n" \
     "Lovds_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3150,7 +3678,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_A%=\n" \
     "Lovdp_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3186,13 +3713,13 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_A%=\n" \
     "Lovdm_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v131\n" \
@@ -3203,6 +3730,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -3220,6 +3748,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -3236,6 +3765,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_maximum3_f32 v129, v131, 0, 0\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -3247,6 +3777,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
     "  v_rndne_f32_e32 v130, v130\n" \
@@ -3271,6 +3802,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, v131, v131\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
@@ -3285,6 +3817,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -3301,7 +3834,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3314,7 +3846,6 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3326,13 +3857,11 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3344,18 +3873,15 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v128, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3368,13 +3894,11 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v128, v0, s71\n" \
@@ -3389,7 +3913,6 @@
     "  v_mul_f32_e64 v130, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3410,7 +3933,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3438,7 +3960,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3477,7 +3998,6 @@
     "  v_mul_f32_e64 v130, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v129, v130, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3497,7 +4017,6 @@
     "  v_mul_f32_e64 v130, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3523,7 +4042,6 @@
     "  v_mul_f32_e64 v130, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3551,6 +4069,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
     "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v130, v130\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v129, v130, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v129, v130\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_maximum3_f32 v129, v131, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
+    "  v_rndne_f32_e32 v130, v130\n" \
+    "  v_fmamk_f32 v128, v130, 0xc0490fdb, v131\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v130\n" \
+    "  v_cvt_i32_f32_e32 v130, v130\n" \
+    "  v_mul_f32_e32 v131, v128, v128\n" \
+    "  v_fmaak_f32 v133, v131, v132, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xb9500d01\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3c088889\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v129, v128, v131\n" \
+    "  v_fmac_f32_e32 v128, v129, v133\n" \
+    "  v_lshl_add_u32 v129, v130, 31, v128\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, v131, v131\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
+    "  v_exp_f32_e32 v130, v129\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v130\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_B%=:\n" \
     "  s_and_b32 s87, s59, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -3580,7 +4201,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_B%=\n" \
     "Lovds_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3618,7 +4238,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_B%=\n" \
     "Lovdp_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3654,7 +4273,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_B%=\n" \
     "Lovdm_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -3849,6 +4467,7 @@
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v227\n" \
@@ -3859,6 +4478,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_mul_f32_e32 v225, 0x4038aa3b, v227\n" \
     "  v_exp_f32_e32 v225, v225\n" \
@@ -3876,6 +4496,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_mul_f32_e32 v225, 0xbfb8aa3b, v227\n" \
     "  v_exp_f32_e32 v225, v225\n" \
@@ -3892,6 +4513,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_maximum3_f32 v225, v227, 0, 0\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -3903,6 +4525,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_mul_f32_e32 v226, 0x3ea2f983, v227\n" \
     "  v_rndne_f32_e32 v226, v226\n" \
@@ -3927,6 +4550,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_mul_f32_e32 v225, v227, v227\n" \
     "  v_mul_f32_e32 v225, 0xbfb8aa3b, v225\n" \
@@ -3941,6 +4565,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s41\n" \
     "  v_fmac_f32_e64 v227, s42, v224\n" \
     "  v_maximum3_f32 v225, v227, -v227, -v227\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -3957,7 +4582,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
     "  v_mov_b32_e32 v224, 0\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3970,7 +4594,6 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v224, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -3982,13 +4605,11 @@
     "  v_mul_f32_e64 v224, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v224, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v224, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v224, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4000,18 +4621,15 @@
     "  v_mul_f32_e64 v224, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v224, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v224, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v224, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v224, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v224, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4024,13 +4642,11 @@
     "  v_mul_f32_e64 v224, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v224, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v224, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v224, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v224, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v224, v0, s55\n" \
@@ -4045,7 +4661,6 @@
     "  v_mul_f32_e64 v226, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4066,7 +4681,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v225\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4094,7 +4708,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v225\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4133,7 +4746,6 @@
     "  v_mul_f32_e64 v226, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v225, v226, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4153,7 +4765,6 @@
     "  v_mul_f32_e64 v226, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4179,7 +4790,6 @@
     "  v_mul_f32_e64 v226, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4207,6 +4817,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
     "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v227\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_mul_f32_e32 v225, 0x4038aa3b, v227\n" \
+    "  v_exp_f32_e32 v225, v225\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v226, 1.0, v225\n" \
+    "  v_rcp_f32_e32 v226, v226\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v225, v226, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_mul_f32_e32 v225, 0xbfb8aa3b, v227\n" \
+    "  v_exp_f32_e32 v225, v225\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v226, 1.0, v225\n" \
+    "  v_rcp_f32_e32 v225, v226\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_maximum3_f32 v225, v227, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_mul_f32_e32 v226, 0x3ea2f983, v227\n" \
+    "  v_rndne_f32_e32 v226, v226\n" \
+    "  v_fmamk_f32 v224, v226, 0xc0490fdb, v227\n" \
+    "  v_fmac_f32_e32 v224, 0x33bbbd2e, v226\n" \
+    "  v_cvt_i32_f32_e32 v226, v226\n" \
+    "  v_mul_f32_e32 v227, v224, v224\n" \
+    "  v_fmaak_f32 v229, v227, v228, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0xb9500d01\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0x3c088889\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v225, v224, v227\n" \
+    "  v_fmac_f32_e32 v224, v225, v229\n" \
+    "  v_lshl_add_u32 v225, v226, 31, v224\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_mul_f32_e32 v225, v227, v227\n" \
+    "  v_mul_f32_e32 v225, 0xbfb8aa3b, v225\n" \
+    "  v_exp_f32_e32 v226, v225\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v226\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s41, v224\n" \
+    "  v_maximum3_f32 v225, v227, -v227, -v227\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_A%=:\n" \
     "  s_and_b32 s87, s43, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -4236,7 +4949,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_A%=\n" \
     "Lovds_A%=:\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4274,7 +4986,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_A%=\n" \
     "Lovdp_A%=:\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -4310,13 +5021,13 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_A%=\n" \
     "Lovdm_A%=:\n" \
-    "  v_mov_b32_e32 v227, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, v227\n" \
@@ -4327,6 +5038,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_mul_f32_e32 v225, 0x4038aa3b, v227\n" \
     "  v_exp_f32_e32 v225, v225\n" \
@@ -4344,6 +5056,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_mul_f32_e32 v225, 0xbfb8aa3b, v227\n" \
     "  v_exp_f32_e32 v225, v225\n" \
@@ -4360,6 +5073,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_maximum3_f32 v225, v227, 0, 0\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -4371,6 +5085,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_mul_f32_e32 v226, 0x3ea2f983, v227\n" \
     "  v_rndne_f32_e32 v226, v226\n" \
@@ -4395,6 +5110,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_mul_f32_e32 v225, v227, v227\n" \
     "  v_mul_f32_e32 v225, 0xbfb8aa3b, v225\n" \
@@ -4409,6 +5125,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v227, s57\n" \
     "  v_fmac_f32_e64 v227, s58, v224\n" \
     "  v_maximum3_f32 v225, v227, -v227, -v227\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -4425,7 +5142,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
     "  v_mov_b32_e32 v224, 0\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4438,7 +5154,6 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v224, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4450,13 +5165,11 @@
     "  v_mul_f32_e64 v224, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v224, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v224, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v224, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4468,18 +5181,15 @@
     "  v_mul_f32_e64 v224, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v224, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v224, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v224, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v224, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v224, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4492,13 +5202,11 @@
     "  v_mul_f32_e64 v224, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v224, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v224, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v224, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v224, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v224, v0, s71\n" \
@@ -4513,7 +5221,6 @@
     "  v_mul_f32_e64 v226, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4534,7 +5241,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v225\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4562,7 +5268,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v224, v224, v225\n" \
     "  v_mul_f32_e32 v224, v224, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4601,7 +5306,6 @@
     "  v_mul_f32_e64 v226, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v225, v226, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4621,7 +5325,6 @@
     "  v_mul_f32_e64 v226, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4647,7 +5350,6 @@
     "  v_mul_f32_e64 v226, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4675,6 +5377,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v224, v224, v225, v226\n" \
     "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v227\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_mul_f32_e32 v225, 0x4038aa3b, v227\n" \
+    "  v_exp_f32_e32 v225, v225\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v226, 1.0, v225\n" \
+    "  v_rcp_f32_e32 v226, v226\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v225, v226, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_mul_f32_e32 v225, 0xbfb8aa3b, v227\n" \
+    "  v_exp_f32_e32 v225, v225\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v226, 1.0, v225\n" \
+    "  v_rcp_f32_e32 v225, v226\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_maximum3_f32 v225, v227, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_mul_f32_e32 v226, 0x3ea2f983, v227\n" \
+    "  v_rndne_f32_e32 v226, v226\n" \
+    "  v_fmamk_f32 v224, v226, 0xc0490fdb, v227\n" \
+    "  v_fmac_f32_e32 v224, 0x33bbbd2e, v226\n" \
+    "  v_cvt_i32_f32_e32 v226, v226\n" \
+    "  v_mul_f32_e32 v227, v224, v224\n" \
+    "  v_fmaak_f32 v229, v227, v228, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0xb9500d01\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0x3c088889\n" \
+    "  v_fmaak_f32 v229, v227, v229, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v225, v224, v227\n" \
+    "  v_fmac_f32_e32 v224, v225, v229\n" \
+    "  v_lshl_add_u32 v225, v226, 31, v224\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_mul_f32_e32 v225, v227, v227\n" \
+    "  v_mul_f32_e32 v225, 0xbfb8aa3b, v225\n" \
+    "  v_exp_f32_e32 v226, v225\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v226\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v227, s57, v224\n" \
+    "  v_maximum3_f32 v225, v227, -v227, -v227\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v225\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_B%=:\n" \
     "  s_and_b32 s87, s59, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -4704,7 +5509,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_B%=\n" \
     "Lovds_B%=:\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4742,7 +5546,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_B%=\n" \
     "Lovdp_B%=:\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -4778,7 +5581,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_B%=\n" \
     "Lovdm_B%=:\n" \
-    "  v_mov_b32_e32 v227, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5069,6 +5871,7 @@
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v64, v131\n" \
@@ -5079,6 +5882,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -5096,6 +5900,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -5112,6 +5917,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_maximum3_f32 v129, v131, 0, 0\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -5123,6 +5929,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
     "  v_rndne_f32_e32 v130, v130\n" \
@@ -5147,6 +5954,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_mul_f32_e32 v129, v131, v131\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
@@ -5161,6 +5969,7 @@
     "  s_addc_u32 s89, s95, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s41\n" \
     "  v_fmac_f32_e64 v131, s42, v128\n" \
     "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
     "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
@@ -5177,7 +5986,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5190,7 +5998,6 @@
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5202,13 +6009,11 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5220,18 +6025,15 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v128, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5244,13 +6046,11 @@
     "  v_mul_f32_e64 v128, v0, s45\n" \
     "  s_set_gpr_idx_idx s46\n" \
     "  v_fmac_f32_e64 v128, v0, s47\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s48\n" \
     "  v_fmac_f32_e64 v128, v0, s49\n" \
     "  s_set_gpr_idx_idx s50\n" \
     "  v_fmac_f32_e64 v128, v0, s51\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s52\n" \
     "  v_fmac_f32_e64 v128, v0, s53\n" \
     "  s_set_gpr_idx_idx s54\n" \
     "  v_fmac_f32_e64 v128, v0, s55\n" \
@@ -5265,7 +6065,6 @@
     "  v_mul_f32_e64 v130, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5286,7 +6085,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5314,7 +6112,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5353,7 +6150,6 @@
     "  v_mul_f32_e64 v130, v0, s47\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v129, v130, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5373,7 +6169,6 @@
     "  v_mul_f32_e64 v130, v0, s51\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5399,7 +6194,6 @@
     "  v_mul_f32_e64 v130, v0, s55\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5427,6 +6221,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
     "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v130, v130\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v129, v130, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v129, v130\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_maximum3_f32 v129, v131, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
+    "  v_rndne_f32_e32 v130, v130\n" \
+    "  v_fmamk_f32 v128, v130, 0xc0490fdb, v131\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v130\n" \
+    "  v_cvt_i32_f32_e32 v130, v130\n" \
+    "  v_mul_f32_e32 v131, v128, v128\n" \
+    "  v_fmaak_f32 v133, v131, v132, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xb9500d01\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3c088889\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v129, v128, v131\n" \
+    "  v_fmac_f32_e32 v128, v129, v133\n" \
+    "  v_lshl_add_u32 v129, v130, 31, v128\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_mul_f32_e32 v129, v131, v131\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
+    "  v_exp_f32_e32 v130, v129\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s41, v128\n" \
+    "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_A%=:\n" \
     "  s_and_b32 s87, s43, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -5456,7 +6353,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_A%=\n" \
     "Lovds_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5494,7 +6390,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_A%=\n" \
     "Lovdp_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
@@ -5530,13 +6425,13 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_A%=\n" \
     "Lovdm_A%=:\n" \
-    "  v_mov_b32_e32 v131, s41\n" \
     "  s_lshr_b32 s88, s40, 16\n" \
     "  s_add_u32 s88, s88, s92\n" \
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
     "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v64, v131\n" \
@@ -5547,6 +6442,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -5564,6 +6460,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
     "  v_exp_f32_e32 v129, v129\n" \
@@ -5580,6 +6477,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_maximum3_f32 v129, v131, 0, 0\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -5591,6 +6489,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
     "  v_rndne_f32_e32 v130, v130\n" \
@@ -5615,6 +6514,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_mul_f32_e32 v129, v131, v131\n" \
     "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
@@ -5629,6 +6529,7 @@
     "  s_addc_u32 s89, s93, 0\n" \
     "  s_setpc_b64 s[88:89]\n" \
     "  .p2align 8\n" \
+    "  v_mov_b32_e32 v131, s57\n" \
     "  v_fmac_f32_e64 v131, s58, v128\n" \
     "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
     "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
@@ -5645,7 +6546,6 @@
     "  s_add_u32 s86, s86, 64\n" \
     "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
     "  v_mov_b32_e32 v128, 0\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5658,7 +6558,6 @@
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5670,13 +6569,11 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5688,18 +6585,15 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v128, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5712,13 +6606,11 @@
     "  v_mul_f32_e64 v128, v0, s61\n" \
     "  s_set_gpr_idx_idx s62\n" \
     "  v_fmac_f32_e64 v128, v0, s63\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s64\n" \
     "  v_fmac_f32_e64 v128, v0, s65\n" \
     "  s_set_gpr_idx_idx s66\n" \
     "  v_fmac_f32_e64 v128, v0, s67\n" \
-    "  s_set_gpr_idx_off\n" \
-    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_idx s68\n" \
     "  v_fmac_f32_e64 v128, v0, s69\n" \
     "  s_set_gpr_idx_idx s70\n" \
     "  v_fmac_f32_e64 v128, v0, s71\n" \
@@ -5733,7 +6625,6 @@
     "  v_mul_f32_e64 v130, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5754,7 +6645,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5782,7 +6672,6 @@
     "  s_set_gpr_idx_off\n" \
     "  v_mul_f32_e32 v128, v128, v129\n" \
     "  v_mul_f32_e32 v128, v128, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5821,7 +6710,6 @@
     "  v_mul_f32_e64 v130, v0, s63\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v129, v130, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5841,7 +6729,6 @@
     "  v_mul_f32_e64 v130, v0, s67\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5867,7 +6754,6 @@
     "  v_mul_f32_e64 v130, v0, s71\n" \
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5895,6 +6781,109 @@
     "  s_set_gpr_idx_off\n" \
     "  v_maximum3_f32 v128, v128, v129, v130\n" \
     "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, 0x4038aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v130, v130\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v129, v130, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v129, v129\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v130, 1.0, v129\n" \
+    "  v_rcp_f32_e32 v129, v130\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_maximum3_f32 v129, v131, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v130, 0x3ea2f983, v131\n" \
+    "  v_rndne_f32_e32 v130, v130\n" \
+    "  v_fmamk_f32 v128, v130, 0xc0490fdb, v131\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v130\n" \
+    "  v_cvt_i32_f32_e32 v130, v130\n" \
+    "  v_mul_f32_e32 v131, v128, v128\n" \
+    "  v_fmaak_f32 v133, v131, v132, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xb9500d01\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0x3c088889\n" \
+    "  v_fmaak_f32 v133, v131, v133, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v129, v128, v131\n" \
+    "  v_fmac_f32_e32 v128, v129, v133\n" \
+    "  v_lshl_add_u32 v129, v130, 31, v128\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_mul_f32_e32 v129, v131, v131\n" \
+    "  v_mul_f32_e32 v129, 0xbfb8aa3b, v129\n" \
+    "  v_exp_f32_e32 v130, v129\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v131, s57, v128\n" \
+    "  v_maximum3_f32 v129, v131, -v131, -v131\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v129\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
     "Lovs_B%=:\n" \
     "  s_and_b32 s87, s59, 0x3fff\n" \
     "  s_sub_u32 s87, s87, 3\n" \
@@ -5924,7 +6913,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Los_B%=\n" \
     "Lovds_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5962,7 +6950,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lop_B%=\n" \
     "Lovdp_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \
@@ -5998,7 +6985,6 @@
     "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
     "  s_branch Lom_B%=\n" \
     "Lovdm_B%=:\n" \
-    "  v_mov_b32_e32 v131, s57\n" \
     "  s_lshr_b32 s88, s56, 16\n" \
     "  s_add_u32 s88, s88, s94\n" \
     "  s_addc_u32 s89, s95, 0\n" \

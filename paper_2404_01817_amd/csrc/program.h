@@ -15,7 +15,8 @@
 // of slots at the largest number of simultaneously live values.  Inputs
 // hold slots 0..I-1; outputs are never freed.  That number decides the
 // genome's SLOT CLASS and where the two constant slots (0 and 1) sit:
-//   R64   <= 62 values: 64 register slots, constants at 62 and 63;
+//   R64   <= 62 values: 64 register slots, constants at 62 and 63 (at 30 and
+//         31 for N_max <= 30, whose values all fit 32 slots);
 //   R128  <= 126 values: 128 register slots, constants at 126 and 127;
 //   R224  <= 222 values: 224 register slots, constants at 222 and 223;
 //   LDS   otherwise: N_max + 2 LDS rows, constants at N_max and N_max + 1.
@@ -66,19 +67,24 @@ __host__ __device__ constexpr int class_slots(int cls, int N) {
     return cls == CLS_R64 ? 64 : (cls == CLS_R128 ? 128 : (cls == CLS_R224 ? 224 : N + 2));
 }
 // slot of the constant 0 (the constant 1 is the next slot)
-__host__ __device__ constexpr int zero_slot(int cls, int N) { return class_slots(cls, N) - 2; }
+constexpr int SMALL_ROWS = 30;  // N_max of the populations that fit 32 slots
+__host__ __device__ constexpr int zero_slot(int cls, int N) {
+    return cls == CLS_R64 && N <= SMALL_ROWS ? SMALL_ROWS : class_slots(cls, N) - 2;
+}
 
 // node record (16 words), record k describes position I + k:
-//   code: dst slot | activation << 24 (the register kernels index with
-//   the low 8 bits of the code word, and every register slot is below 256);
+//   code: dst slot | activation << 11 | activation block << 24 (the
+//   register kernels index with the low 8 bits of the code word, and every
+//   register slot is below 256);
 //   bias, response', pairs: pair count | aggregation entry << 24, then the
 //   node's first three edge pairs.
 // The register kernels jump on the fields at bit 24: each copy of their
 // node loop has a table with one slot per activation code (0..6), the end
 // of the loop (TAB_END) and one aggregation entry per (class, pair count):
 // sum with 0..3 pairs or more (overflow), product and max with 1..3 pairs
-// or more.  After the last node a sentinel record (code ACT_END, entry
-// TAB_END, no pairs) ends the loop.
+// or more; then the activation blocks of nodes whose response' is 1 (the
+// usual one: bias + agg in one instruction).  After the last node a sentinel
+// record (block and entry TAB_END, no pairs) ends the loop.
 // Aggregation classes: SUM (sum, mean, and any node without incoming
 // edges), PROD, MAX (max; min is stored as max over negated weights with
 // the response negated, since min(t) = -max(-t) exactly);
@@ -93,14 +99,15 @@ constexpr int REC_PAIRS = 4;  // the node's first three edge pairs (12 words)
 constexpr int REC_WORDS = 16;
 constexpr int REC_INLINE_PAIRS = 3;
 constexpr int REC_DST_MASK = 0x7ff;
+constexpr int REC_ACT_SHIFT = 11;
+constexpr int REC_ACT_MASK = 7;
 constexpr int REC_FIELD_SHIFT = 24;
 constexpr int REC_NPAIRS_MASK = 0x3fff;
-constexpr int ACT_END = 7;    // sentinel activation code
 enum AggClass { ACLS_SUM = 0, ACLS_PROD = 1, ACLS_MAX = 2 };
 // table slots
 constexpr int TAB_END = 7;
 constexpr int TAB_AGG0 = 8;   // first aggregation entry: sum with 0 pairs
-constexpr int TAB_SLOTS = TAB_AGG0 + 13;
+constexpr int TAB_UNIT0 = TAB_AGG0 + 13;  // first activation block with a unit response
 __host__ __device__ constexpr int agg_slot(int acls, int pairs) {
     return TAB_AGG0 + (acls == ACLS_SUM ? (pairs < 4 ? pairs : 4)
                                         : 4 * acls + (pairs < 4 ? pairs : 4));
@@ -108,13 +115,17 @@ __host__ __device__ constexpr int agg_slot(int acls, int pairs) {
 __host__ __device__ constexpr int slot_class(int slot) {
     return slot < TAB_AGG0 + 5 ? ACLS_SUM : (slot < TAB_AGG0 + 9 ? ACLS_PROD : ACLS_MAX);
 }
-__host__ __device__ constexpr uint32_t rec_code(int act, int dst) {
-    return (uint32_t)dst | ((uint32_t)act << REC_FIELD_SHIFT);
+__host__ __device__ constexpr uint32_t rec_code(int act, int dst, bool unit_response) {
+    return (uint32_t)dst | ((uint32_t)act << REC_ACT_SHIFT) |
+           ((uint32_t)(unit_response ? TAB_UNIT0 + act : act) << REC_FIELD_SHIFT);
+}
+__host__ __device__ constexpr int rec_act(uint32_t code) {
+    return (int)(code >> REC_ACT_SHIFT) & REC_ACT_MASK;
 }
 __host__ __device__ constexpr uint32_t rec_npairs(int acls, int pairs) {
     return (uint32_t)pairs | ((uint32_t)agg_slot(acls, pairs) << REC_FIELD_SHIFT);
 }
-constexpr uint32_t REC_SENTINEL_CODE = (uint32_t)ACT_END << REC_FIELD_SHIFT;
+constexpr uint32_t REC_SENTINEL_CODE = (uint32_t)TAB_END << REC_FIELD_SHIFT;
 constexpr uint32_t REC_SENTINEL_NPAIRS = (uint32_t)TAB_END << REC_FIELD_SHIFT;
 // edge (2 words): source slot, weight
 constexpr int EDGE_WORDS = 2;

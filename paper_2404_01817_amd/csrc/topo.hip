@@ -990,7 +990,7 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
         const float rp = deg == 0 ? resp
                                   : (agg == AGG_MEAN ? resp * (1.0f / (float)deg)
                                                      : (agg == AGG_MIN ? -resp : resp));
-        prog[r0 + REC_CODE] = (int32_t)rec_code(act, s_slot[t]);
+        prog[r0 + REC_CODE] = (int32_t)rec_code(act, s_slot[t], rp == 1.0f);
         progf[r0 + REC_BIAS] = bias;
         progf[r0 + REC_RESP] = rp;
         prog[r0 + REC_NPAIRS] = (int32_t)rec_npairs(acls, pairs);

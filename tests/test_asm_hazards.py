@@ -134,3 +134,11 @@ def test_rejected_register_placement_is_clean_too():
         gen.Regs = saved
     assert text != _text()
     assert check.check_text(text) == []
+
+
+def test_wide_header_is_current_and_clean():
+    text = open(os.path.join(CSRC, "node_loop_wide.h")).read()
+    assert gen.generate_wide() == text, "node_loop_wide.h differs from gen_node_loop.py's output"
+    v = check.check_text(text)
+    assert v == [], "\n".join(v)
+    assert set(check.parse_header(text)) == {n[0] for n in gen.VARIANTS_WIDE}
