@@ -496,7 +496,9 @@ def check_registers(insts, succ, clobbers):
 
 VALUE_SLOTS = {"S1_64": {0: 64}, "S2_64": {0: 64, 64: 64}, "S1_128": {0: 128},
                "S1_224": {0: 224}, "S1_64R": {0: 64, 64: 64},
-               "S4_32": {0: 32, 32: 32, 64: 32, 96: 32}}
+               "S4_32": {0: 32, 32: 32, 64: 32, 96: 32},
+               "S2_32R": {0: 32, 32: 32, 64: 32, 96: 32},
+               "S1_52R": {0: 52, 52: 52}}
 
 
 def check_variant(name, body, clobbers, scratch):

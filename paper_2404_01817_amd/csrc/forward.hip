@@ -153,6 +153,16 @@ struct AsmTile<KIND_R64REC> {
     static constexpr int SPL = 1;
     NEAT_TILE_FN(NEAT_TILE_S1_64R, NEAT_CLOB_S1_64R, NEAT_NSW_OPERAND)
 };
+template <>
+struct AsmTile<KIND_R32REC> {
+    static constexpr int SPL = 2;
+    NEAT_TILE_FN(NEAT_TILE_S2_32R, NEAT_CLOB_S2_32R, NEAT_NSW_OPERAND)
+};
+template <>
+struct AsmTile<KIND_R52REC> {
+    static constexpr int SPL = 1;
+    NEAT_TILE_FN(NEAT_TILE_S1_52R, NEAT_CLOB_S1_52R, NEAT_NSW_OPERAND)
+};
 
 // ---------------------------------------------------------------- nodes (C++)
 // The LDS store's node loop: the operations of node_loop_asm.h in the same
@@ -996,9 +1006,12 @@ __device__ __forceinline__ void run_unit(long long u, float *wave_area) {
 // the compiler adds around it must not cost one.
 constexpr int min_waves(int kind) {
     return kind == KIND_R64 ? 5
-           : (kind == KIND_R64X2 || kind == KIND_R32X4 || kind == KIND_R128 || kind == KIND_R64REC)
+           : (kind == KIND_R64X2 || kind == KIND_R32X4 || kind == KIND_R128 ||
+              kind == KIND_R64REC || kind == KIND_R32REC)
                ? 3
-               : (kind == KIND_R224 || kind == KIND_ANY) ? 2 : 1;
+           : kind == KIND_R52REC                     ? 4
+           : kind == KIND_R224 || kind == KIND_ANY ? 2
+                                                   : 1;
 }
 
 // PERSIST: a grid smaller than the unit count, each workgroup looping.
@@ -1095,7 +1108,7 @@ int launch_tiles_per_wave(const std::vector<FwdItem> &items) {
 // samples of one tile
 int tile_samples(int kind) {
     return kind == KIND_R32X4   ? 4 * WAVE
-           : kind == KIND_R64X2 ? 2 * WAVE
+           : kind == KIND_R64X2 || kind == KIND_R32REC ? 2 * WAVE
                                 : (kind == KIND_LDS32 ? WAVE / 2 : WAVE);
 }
 
@@ -1120,7 +1133,7 @@ int kind_of(int variant, int cls, int B) {
 
 const char *kind_name(int kind) {
     static const char *names[] = {"r64", "r64x2", "r128", "r224", "lds", "r64rec", "lds32",
-                                  "lvl", "seg", "any", "r32x4"};
+                                  "lvl", "seg", "any", "r32x4", "r32rec", "r52rec"};
     return kind >= 0 && kind < N_KINDS ? names[kind] : "?";
 }
 
@@ -1140,6 +1153,22 @@ static int level_tile(int rows, int B, size_t extra) {
 // runs at half the scalar work per sample.
 static int any_tile(const FwdJob &J) {
     return J.B > WAVE && (long long)J.P * ((J.B + WAVE - 1) / WAVE) > 2048 ? 2 * WAVE : WAVE;
+}
+
+// The recurrent register store by rows: waves per SIMD count most, since a
+// wave's chain of short dependent instructions leaves most issue slots empty.
+// Both vectors of 52 slots leave room for four (64 slots: three), and of 32
+// slots for three with two samples per lane, taken when one per lane would
+// fill the GPU (3072 waves) anyway.  Calculation alone, 17 inputs, 6 outputs,
+// B = 500, K = 4, 64 slots and one sample against this: N = 50, P = 5000: 184
+// / 165 us (52 slots and two samples at two waves per SIMD: 170); N = 30, P =
+// 10000: 213 / 145 us.
+static int recurrent_kind(const FwdJob &J) {
+    if (J.N > MEDIUM_ROWS) return KIND_R64REC;
+    if (J.N <= SMALL_ROWS && J.B > WAVE &&
+        (long long)J.P * ((J.B + WAVE - 1) / WAVE) > 3072)
+        return KIND_R32REC;
+    return KIND_R52REC;
 }
 
 // Four samples per lane for the smallest class: where every value has one of
@@ -1243,7 +1272,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const bool whole = variant == FWD_LDS || J.recurrent || any;
         const int c_lo = whole ? -1 : 0, c_hi = whole ? -1 : top;
         for (int c = c_lo; c <= c_hi; ++c) {
-            int kind = J.recurrent ? KIND_R64REC
+            int kind = J.recurrent ? recurrent_kind(J)
                        : any       ? KIND_ANY
                                    : kind_of(variant, c < 0 ? CLS_LDS : c, J.B);
             if (kind == KIND_R64X2 && variant == FWD_AUTO && four_samples(J)) kind = KIND_R32X4;
@@ -1408,6 +1437,8 @@ hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hi
     case KIND_R128: NEAT_LAUNCH_REG(KIND_R128) break;
     case KIND_R224: NEAT_LAUNCH_REG(KIND_R224) break;
     case KIND_R64REC: NEAT_LAUNCH1(KIND_R64REC, false, false); break;
+    case KIND_R32REC: NEAT_LAUNCH1(KIND_R32REC, false, false); break;
+    case KIND_R52REC: NEAT_LAUNCH1(KIND_R52REC, false, false); break;
     case KIND_LDS32: NEAT_LAUNCH_LDS(KIND_LDS32) break;
     case KIND_LVL: NEAT_LAUNCH2(KIND_LVL, false) break;
     case KIND_SEG: NEAT_LAUNCH2(KIND_SEG, false) break;

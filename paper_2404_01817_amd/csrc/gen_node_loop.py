@@ -24,6 +24,8 @@ Variants (name: samples per lane, value slots, VGPRs of the value vectors):
           recurrent calculation, %[nsw] synchronous sweeps of the node loop
 and in node_loop_wide.h, for populations of few node rows:
   S4_32   4 samples, 32 slots,  v0..v31, v32..v63, v64..v95, v96..v127
+  S2_32R  2 samples, 32 slots, recurrent: v0..v63 read, v64..v127 written
+  S1_52R  1 sample, 52 slots, recurrent: v0..v51 read, v52..v103 written
 Scratch VGPRs follow the value vectors.
 
 Run as ``python gen_node_loop.py`` to rewrite the two headers next to it;
@@ -47,6 +49,8 @@ VARIANTS = [
 # the variants of node_loop_wide.h, and the input buffers per sample
 VARIANTS_WIDE = [
     ("S4_32", 4, (0, 32, 64, 96), 128, None, 4),
+    ("S2_32R", 2, (0, 32), 128, (64, 96), 4),
+    ("S1_52R", 1, (0,), 104, (52,), 4),
 ]
 
 # scalar register map (shared by all variants)
@@ -109,6 +113,7 @@ class Regs:
         self.bases = ["v%d" % b for b in bases]
         # recurrent: reads from v[bases], writes to v[wbases]
         self.rec = wbases is not None
+        self.slots = (bases[1] if spl > 1 else wbases[0]) - bases[0] if self.rec else None
         self.wbases = ["v%d" % b for b in (wbases if self.rec else bases)]
         self.names = {}
         for k, role in enumerate(self.ROLES[:4]):
@@ -588,7 +593,7 @@ def write_outputs(R):
     for k in range(8):
         out += ["s_set_gpr_idx_on s%d, gpr_idx(SRC0)" % (48 + k)]
         for h in range(R.spl):
-            out += ["v_mov_b32_e32 %s, %s" % (R.buf[h][k % R.group], R.bases[h])]
+            out += ["v_mov_b32_e32 %s, %s" % (R.buf[h][k % R.group], R.wbases[h])]
         out += ["s_set_gpr_idx_off"]
         for h in range(R.spl):
             out += ["ds_write_b32 %s, %s offset:%d" % (R.addr[h], R.buf[h][k % R.group], 4 * k)]
@@ -604,46 +609,65 @@ def write_outputs(R):
     return out
 
 
+def vector_blocks(R, tag, line):
+    """line(h, k) for every sample h and slot k below %[n] + %[ni] (rounded up
+    to a block of eight): the slots that the genome's nodes hold.  s40, s41 are
+    scratch."""
+    out = ["s_add_u32 s41, %[n], %[ni]"]
+    for k0 in range(0, R.slots, 8):
+        if k0:
+            out += ["s_cmp_le_u32 s41, %d" % k0,
+                    "s_cbranch_scc1 L%s%%=" % tag]
+        out += [line(h, k) for k in range(k0, min(R.slots, k0 + 8)) for h in range(R.spl)]
+    return out + ["L%s%%=:" % tag]
+
+
 def zero_values(R):
-    """Recurrent variant: v0 = 0 at every slot of the read vector (the inputs
-    and constants are placed after)."""
-    base = int(R.bases[0][1:])
-    return ["v_mov_b32_e32 v%d, 0" % (base + k) for k in range(64)]
+    """Recurrent variants: v0 = 0 at every node's slot of the read vectors
+    (the inputs and constants are placed after); of the written ones too when
+    there is no sweep, since the outputs are read from those."""
+    def zero(bases):
+        return lambda h, k: "v_mov_b32_e32 v%d, 0" % (int(bases[h][1:]) + k)
+    return (vector_blocks(R, "zr", zero(R.bases)) +
+            ["s_cmp_lg_u32 %[nsw], 0",
+             "s_cbranch_scc1 Lzw%="] + vector_blocks(R, "zw", zero(R.wbases)))
 
 
 def sweeps(R):
-    """Recurrent variant: %[nsw] sweeps of the node loop, each reading the
-    previous sweep's values (read vector) and writing the write vector, then
-    copying the write vector into the read vector (inputs and constants are
-    in both, so the copy keeps them)."""
-    rb, wb = int(R.bases[0][1:]), int(R.wbases[0][1:])
+    """Recurrent variants: %[nsw] sweeps of the node loop, each reading the
+    previous sweep's values (read vectors) and writing the write vectors; all
+    but the last then copy the nodes' slots back (inputs and constants are in
+    both, so the copy keeps them)."""
     out = ["s_mov_b32 s91, %[nsw]",
            "Lsw%=:",
            "s_cmp_eq_u32 s91, 0",
            "s_cbranch_scc1 Lsw_done%="]
     out += node_loop(R)
-    out += ["v_mov_b32_e32 v%d, v%d" % (rb + k, wb + k) for k in range(64)]
     out += ["s_sub_u32 s91, s91, 1",
-            "s_branch Lsw%=",
+            "s_cmp_eq_u32 s91, 0",
+            "s_cbranch_scc1 Lsw_done%="]
+    out += vector_blocks(R, "cp", lambda h, k: "v_mov_b32_e32 v%d, v%d"
+                         % (int(R.bases[h][1:]) + k, int(R.wbases[h][1:]) + k))
+    out += ["s_branch Lsw%=",
             "Lsw_done%=:"]
     return out
 
 
 def clear_past_inputs(R):
-    """Recurrent variant: place_inputs writes whole groups of eight, so the
-    read vector's slots from %[ni] up to the next multiple of eight (below
-    64) hold staging words; set them back to 0 (before the constants)."""
-    base = int(R.bases[0][1:])
-    return ["s_mov_b32 s41, %[ni]",
-            "Lcl%=:",
-            "s_and_b32 s40, s41, 7",
-            "s_cbranch_scc0 Lcl_done%=",
-            "s_set_gpr_idx_on s41, gpr_idx(DST)",
-            "v_mov_b32_e32 v%d, 0" % base,
-            "s_set_gpr_idx_off",
-            "s_add_u32 s41, s41, 1",
-            "s_branch Lcl%=",
-            "Lcl_done%=:"]
+    """Recurrent variants: place_inputs writes whole groups, so the slots from
+    %[ni] up to the next multiple of the group hold staging words in both
+    vectors; set them back to 0 (before the constants)."""
+    out = ["s_mov_b32 s41, %[ni]",
+           "Lcl%=:",
+           "s_and_b32 s40, s41, " + str(R.group - 1),
+           "s_cbranch_scc0 Lcl_done%=",
+           "s_set_gpr_idx_on s41, gpr_idx(DST)"]
+    for b in R.bases + R.wbases:
+        out += ["v_mov_b32_e32 %s, 0" % b]
+    return out + ["s_set_gpr_idx_off",
+                  "s_add_u32 s41, s41, 1",
+                  "s_branch Lcl%=",
+                  "Lcl_done%=:"]
 
 
 def tile(R):
@@ -706,7 +730,8 @@ HEADER = """\
 // The recurrent block (NEAT_TILE_S1_64R) zeroes the read vector v0..v63,
 // places the inputs and constants in it and in the write vector v64..v127,
 // then runs the node loop %[nsw] times: every sweep reads v0.. and writes
-// v64.., and 64 moves copy the write vector back (s91 counts the sweeps).
+// v64.., and all but the last copy the %[n] + %[ni] nodes' slots back (s91
+// counts the sweeps); the outputs are read from v64...
 //
 // Hazards: a transcendental's result is read no sooner than one instruction
 // later (with two samples the other sample's instruction sits between); a

@@ -54,7 +54,9 @@ constexpr int FWD_ANY = 7;   // one launch, each wave by its genome's class (int
 
 // Forward kernels, one per value store.
 // KIND_R64REC: the recurrent calculation (K synchronous sweeps) with the
-// 64-slot register store, for populations of N_max <= 62.  KIND_LDS32: the
+// 64-slot register store, for populations of N_max <= 62; KIND_R52REC the
+// same with 52 slots (N_max <= 50), KIND_R32REC with 32 slots and two samples
+// per lane (N_max <= 30).  KIND_LDS32: the
 // LDS-row store with half-wave tiles (32 samples), for genomes whose rows
 // do not fit in LDS with 64 columns.
 // KIND_R32X4: four samples per lane, for populations of N_max <= 30.
@@ -64,7 +66,7 @@ constexpr int FWD_ANY = 7;   // one launch, each wave by its genome's class (int
 // (the level mapping past the register classes).
 enum FwdKind {
     KIND_R64 = 0, KIND_R64X2, KIND_R128, KIND_R224, KIND_LDS, KIND_R64REC, KIND_LDS32, KIND_LVL,
-    KIND_SEG, KIND_ANY, KIND_R32X4, N_KINDS
+    KIND_SEG, KIND_ANY, KIND_R32X4, KIND_R32REC, KIND_R52REC, N_KINDS
 };
 constexpr int FWD_MAX_WAVES = 4;  // waves per workgroup
 

@@ -47,7 +47,8 @@
 // The recurrent block (NEAT_TILE_S1_64R) zeroes the read vector v0..v63,
 // places the inputs and constants in it and in the write vector v64..v127,
 // then runs the node loop %[nsw] times: every sweep reads v0.. and writes
-// v64.., and 64 moves copy the write vector back (s91 counts the sweeps).
+// v64.., and all but the last copy the %[n] + %[ni] nodes' slots back (s91
+// counts the sweeps); the outputs are read from v64...
 //
 // Hazards: a transcendental's result is read no sooner than one instruction
 // later (with two samples the other sample's instruction sits between); a
@@ -5692,6 +5693,7 @@
 
 #define NEAT_TILE_S1_64R \
     "  s_mov_b32 s90, m0\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
     "  v_mov_b32_e32 v0, 0\n" \
     "  v_mov_b32_e32 v1, 0\n" \
     "  v_mov_b32_e32 v2, 0\n" \
@@ -5700,6 +5702,8 @@
     "  v_mov_b32_e32 v5, 0\n" \
     "  v_mov_b32_e32 v6, 0\n" \
     "  v_mov_b32_e32 v7, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v8, 0\n" \
     "  v_mov_b32_e32 v9, 0\n" \
     "  v_mov_b32_e32 v10, 0\n" \
@@ -5708,6 +5712,8 @@
     "  v_mov_b32_e32 v13, 0\n" \
     "  v_mov_b32_e32 v14, 0\n" \
     "  v_mov_b32_e32 v15, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v16, 0\n" \
     "  v_mov_b32_e32 v17, 0\n" \
     "  v_mov_b32_e32 v18, 0\n" \
@@ -5716,6 +5722,8 @@
     "  v_mov_b32_e32 v21, 0\n" \
     "  v_mov_b32_e32 v22, 0\n" \
     "  v_mov_b32_e32 v23, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v24, 0\n" \
     "  v_mov_b32_e32 v25, 0\n" \
     "  v_mov_b32_e32 v26, 0\n" \
@@ -5724,6 +5732,8 @@
     "  v_mov_b32_e32 v29, 0\n" \
     "  v_mov_b32_e32 v30, 0\n" \
     "  v_mov_b32_e32 v31, 0\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v32, 0\n" \
     "  v_mov_b32_e32 v33, 0\n" \
     "  v_mov_b32_e32 v34, 0\n" \
@@ -5732,6 +5742,8 @@
     "  v_mov_b32_e32 v37, 0\n" \
     "  v_mov_b32_e32 v38, 0\n" \
     "  v_mov_b32_e32 v39, 0\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v40, 0\n" \
     "  v_mov_b32_e32 v41, 0\n" \
     "  v_mov_b32_e32 v42, 0\n" \
@@ -5740,6 +5752,8 @@
     "  v_mov_b32_e32 v45, 0\n" \
     "  v_mov_b32_e32 v46, 0\n" \
     "  v_mov_b32_e32 v47, 0\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v48, 0\n" \
     "  v_mov_b32_e32 v49, 0\n" \
     "  v_mov_b32_e32 v50, 0\n" \
@@ -5748,6 +5762,8 @@
     "  v_mov_b32_e32 v53, 0\n" \
     "  v_mov_b32_e32 v54, 0\n" \
     "  v_mov_b32_e32 v55, 0\n" \
+    "  s_cmp_le_u32 s41, 56\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
     "  v_mov_b32_e32 v56, 0\n" \
     "  v_mov_b32_e32 v57, 0\n" \
     "  v_mov_b32_e32 v58, 0\n" \
@@ -5756,6 +5772,89 @@
     "  v_mov_b32_e32 v61, 0\n" \
     "  v_mov_b32_e32 v62, 0\n" \
     "  v_mov_b32_e32 v63, 0\n" \
+    "Lzr%=:\n" \
+    "  s_cmp_lg_u32 %[nsw], 0\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
+    "  v_mov_b32_e32 v65, 0\n" \
+    "  v_mov_b32_e32 v66, 0\n" \
+    "  v_mov_b32_e32 v67, 0\n" \
+    "  v_mov_b32_e32 v68, 0\n" \
+    "  v_mov_b32_e32 v69, 0\n" \
+    "  v_mov_b32_e32 v70, 0\n" \
+    "  v_mov_b32_e32 v71, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v72, 0\n" \
+    "  v_mov_b32_e32 v73, 0\n" \
+    "  v_mov_b32_e32 v74, 0\n" \
+    "  v_mov_b32_e32 v75, 0\n" \
+    "  v_mov_b32_e32 v76, 0\n" \
+    "  v_mov_b32_e32 v77, 0\n" \
+    "  v_mov_b32_e32 v78, 0\n" \
+    "  v_mov_b32_e32 v79, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v80, 0\n" \
+    "  v_mov_b32_e32 v81, 0\n" \
+    "  v_mov_b32_e32 v82, 0\n" \
+    "  v_mov_b32_e32 v83, 0\n" \
+    "  v_mov_b32_e32 v84, 0\n" \
+    "  v_mov_b32_e32 v85, 0\n" \
+    "  v_mov_b32_e32 v86, 0\n" \
+    "  v_mov_b32_e32 v87, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v88, 0\n" \
+    "  v_mov_b32_e32 v89, 0\n" \
+    "  v_mov_b32_e32 v90, 0\n" \
+    "  v_mov_b32_e32 v91, 0\n" \
+    "  v_mov_b32_e32 v92, 0\n" \
+    "  v_mov_b32_e32 v93, 0\n" \
+    "  v_mov_b32_e32 v94, 0\n" \
+    "  v_mov_b32_e32 v95, 0\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v96, 0\n" \
+    "  v_mov_b32_e32 v97, 0\n" \
+    "  v_mov_b32_e32 v98, 0\n" \
+    "  v_mov_b32_e32 v99, 0\n" \
+    "  v_mov_b32_e32 v100, 0\n" \
+    "  v_mov_b32_e32 v101, 0\n" \
+    "  v_mov_b32_e32 v102, 0\n" \
+    "  v_mov_b32_e32 v103, 0\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v104, 0\n" \
+    "  v_mov_b32_e32 v105, 0\n" \
+    "  v_mov_b32_e32 v106, 0\n" \
+    "  v_mov_b32_e32 v107, 0\n" \
+    "  v_mov_b32_e32 v108, 0\n" \
+    "  v_mov_b32_e32 v109, 0\n" \
+    "  v_mov_b32_e32 v110, 0\n" \
+    "  v_mov_b32_e32 v111, 0\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v112, 0\n" \
+    "  v_mov_b32_e32 v113, 0\n" \
+    "  v_mov_b32_e32 v114, 0\n" \
+    "  v_mov_b32_e32 v115, 0\n" \
+    "  v_mov_b32_e32 v116, 0\n" \
+    "  v_mov_b32_e32 v117, 0\n" \
+    "  v_mov_b32_e32 v118, 0\n" \
+    "  v_mov_b32_e32 v119, 0\n" \
+    "  s_cmp_le_u32 s41, 56\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v120, 0\n" \
+    "  v_mov_b32_e32 v121, 0\n" \
+    "  v_mov_b32_e32 v122, 0\n" \
+    "  v_mov_b32_e32 v123, 0\n" \
+    "  v_mov_b32_e32 v124, 0\n" \
+    "  v_mov_b32_e32 v125, 0\n" \
+    "  v_mov_b32_e32 v126, 0\n" \
+    "  v_mov_b32_e32 v127, 0\n" \
+    "Lzw%=:\n" \
     "  s_lshl_b32 s41, %[ni], 2\n" \
     "  v_mul_u32_u24_e32 v136, s41, %[lane]\n" \
     "  v_add_u32_e32 v136, %[dm0], v136\n" \
@@ -5797,6 +5896,7 @@
     "  s_cbranch_scc0 Lcl_done%=\n" \
     "  s_set_gpr_idx_on s41, gpr_idx(DST)\n" \
     "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
     "  s_set_gpr_idx_off\n" \
     "  s_add_u32 s41, s41, 1\n" \
     "  s_branch Lcl%=\n" \
@@ -6991,6 +7091,10 @@
     "  s_setpc_b64 s[88:89]\n" \
     "Ldone%=:\n" \
     "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_sub_u32 s91, s91, 1\n" \
+    "  s_cmp_eq_u32 s91, 0\n" \
+    "  s_cbranch_scc1 Lsw_done%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
     "  v_mov_b32_e32 v0, v64\n" \
     "  v_mov_b32_e32 v1, v65\n" \
     "  v_mov_b32_e32 v2, v66\n" \
@@ -6999,6 +7103,8 @@
     "  v_mov_b32_e32 v5, v69\n" \
     "  v_mov_b32_e32 v6, v70\n" \
     "  v_mov_b32_e32 v7, v71\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v8, v72\n" \
     "  v_mov_b32_e32 v9, v73\n" \
     "  v_mov_b32_e32 v10, v74\n" \
@@ -7007,6 +7113,8 @@
     "  v_mov_b32_e32 v13, v77\n" \
     "  v_mov_b32_e32 v14, v78\n" \
     "  v_mov_b32_e32 v15, v79\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v16, v80\n" \
     "  v_mov_b32_e32 v17, v81\n" \
     "  v_mov_b32_e32 v18, v82\n" \
@@ -7015,6 +7123,8 @@
     "  v_mov_b32_e32 v21, v85\n" \
     "  v_mov_b32_e32 v22, v86\n" \
     "  v_mov_b32_e32 v23, v87\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v24, v88\n" \
     "  v_mov_b32_e32 v25, v89\n" \
     "  v_mov_b32_e32 v26, v90\n" \
@@ -7023,6 +7133,8 @@
     "  v_mov_b32_e32 v29, v93\n" \
     "  v_mov_b32_e32 v30, v94\n" \
     "  v_mov_b32_e32 v31, v95\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v32, v96\n" \
     "  v_mov_b32_e32 v33, v97\n" \
     "  v_mov_b32_e32 v34, v98\n" \
@@ -7031,6 +7143,8 @@
     "  v_mov_b32_e32 v37, v101\n" \
     "  v_mov_b32_e32 v38, v102\n" \
     "  v_mov_b32_e32 v39, v103\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v40, v104\n" \
     "  v_mov_b32_e32 v41, v105\n" \
     "  v_mov_b32_e32 v42, v106\n" \
@@ -7039,6 +7153,8 @@
     "  v_mov_b32_e32 v45, v109\n" \
     "  v_mov_b32_e32 v46, v110\n" \
     "  v_mov_b32_e32 v47, v111\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v48, v112\n" \
     "  v_mov_b32_e32 v49, v113\n" \
     "  v_mov_b32_e32 v50, v114\n" \
@@ -7047,6 +7163,8 @@
     "  v_mov_b32_e32 v53, v117\n" \
     "  v_mov_b32_e32 v54, v118\n" \
     "  v_mov_b32_e32 v55, v119\n" \
+    "  s_cmp_le_u32 s41, 56\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
     "  v_mov_b32_e32 v56, v120\n" \
     "  v_mov_b32_e32 v57, v121\n" \
     "  v_mov_b32_e32 v58, v122\n" \
@@ -7055,7 +7173,7 @@
     "  v_mov_b32_e32 v61, v125\n" \
     "  v_mov_b32_e32 v62, v126\n" \
     "  v_mov_b32_e32 v63, v127\n" \
-    "  s_sub_u32 s91, s91, 1\n" \
+    "Lcp%=:\n" \
     "  s_branch Lsw%=\n" \
     "Lsw_done%=:\n" \
     "  s_mov_b64 s[44:45], %[outs]\n" \
@@ -7067,56 +7185,56 @@
     "  s_load_dwordx8 s[48:55], s[44:45], 0x0\n" \
     "  s_waitcnt lgkmcnt(0)\n" \
     "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v128, v0\n" \
+    "  v_mov_b32_e32 v128, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v128 offset:0\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s49, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v129, v0\n" \
+    "  v_mov_b32_e32 v129, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v129 offset:4\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s50, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v130, v0\n" \
+    "  v_mov_b32_e32 v130, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v130 offset:8\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s51, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v131, v0\n" \
+    "  v_mov_b32_e32 v131, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v131 offset:12\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v132, v0\n" \
+    "  v_mov_b32_e32 v132, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v132 offset:16\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s53, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v133, v0\n" \
+    "  v_mov_b32_e32 v133, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v133 offset:20\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s54, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v134, v0\n" \
+    "  v_mov_b32_e32 v134, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v134 offset:24\n" \
     "  s_add_u32 s40, s40, 1\n" \
     "  s_cmp_ge_u32 s40, %[no]\n" \
     "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s55, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v135, v0\n" \
+    "  v_mov_b32_e32 v135, v64\n" \
     "  s_set_gpr_idx_off\n" \
     "  ds_write_b32 v136, v135 offset:28\n" \
     "  s_add_u32 s40, s40, 1\n" \

@@ -2502,3 +2502,3475 @@
 
 #define NEAT_SCRATCH_S4_32 128
 
+
+// S2_32R: 2 sample(s) per lane, value vectors at v0, v32, scratch v128..v139
+
+#define NEAT_TILE_S2_32R \
+    "  s_mov_b32 s90, m0\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v32, 0\n" \
+    "  v_mov_b32_e32 v1, 0\n" \
+    "  v_mov_b32_e32 v33, 0\n" \
+    "  v_mov_b32_e32 v2, 0\n" \
+    "  v_mov_b32_e32 v34, 0\n" \
+    "  v_mov_b32_e32 v3, 0\n" \
+    "  v_mov_b32_e32 v35, 0\n" \
+    "  v_mov_b32_e32 v4, 0\n" \
+    "  v_mov_b32_e32 v36, 0\n" \
+    "  v_mov_b32_e32 v5, 0\n" \
+    "  v_mov_b32_e32 v37, 0\n" \
+    "  v_mov_b32_e32 v6, 0\n" \
+    "  v_mov_b32_e32 v38, 0\n" \
+    "  v_mov_b32_e32 v7, 0\n" \
+    "  v_mov_b32_e32 v39, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v8, 0\n" \
+    "  v_mov_b32_e32 v40, 0\n" \
+    "  v_mov_b32_e32 v9, 0\n" \
+    "  v_mov_b32_e32 v41, 0\n" \
+    "  v_mov_b32_e32 v10, 0\n" \
+    "  v_mov_b32_e32 v42, 0\n" \
+    "  v_mov_b32_e32 v11, 0\n" \
+    "  v_mov_b32_e32 v43, 0\n" \
+    "  v_mov_b32_e32 v12, 0\n" \
+    "  v_mov_b32_e32 v44, 0\n" \
+    "  v_mov_b32_e32 v13, 0\n" \
+    "  v_mov_b32_e32 v45, 0\n" \
+    "  v_mov_b32_e32 v14, 0\n" \
+    "  v_mov_b32_e32 v46, 0\n" \
+    "  v_mov_b32_e32 v15, 0\n" \
+    "  v_mov_b32_e32 v47, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v16, 0\n" \
+    "  v_mov_b32_e32 v48, 0\n" \
+    "  v_mov_b32_e32 v17, 0\n" \
+    "  v_mov_b32_e32 v49, 0\n" \
+    "  v_mov_b32_e32 v18, 0\n" \
+    "  v_mov_b32_e32 v50, 0\n" \
+    "  v_mov_b32_e32 v19, 0\n" \
+    "  v_mov_b32_e32 v51, 0\n" \
+    "  v_mov_b32_e32 v20, 0\n" \
+    "  v_mov_b32_e32 v52, 0\n" \
+    "  v_mov_b32_e32 v21, 0\n" \
+    "  v_mov_b32_e32 v53, 0\n" \
+    "  v_mov_b32_e32 v22, 0\n" \
+    "  v_mov_b32_e32 v54, 0\n" \
+    "  v_mov_b32_e32 v23, 0\n" \
+    "  v_mov_b32_e32 v55, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v24, 0\n" \
+    "  v_mov_b32_e32 v56, 0\n" \
+    "  v_mov_b32_e32 v25, 0\n" \
+    "  v_mov_b32_e32 v57, 0\n" \
+    "  v_mov_b32_e32 v26, 0\n" \
+    "  v_mov_b32_e32 v58, 0\n" \
+    "  v_mov_b32_e32 v27, 0\n" \
+    "  v_mov_b32_e32 v59, 0\n" \
+    "  v_mov_b32_e32 v28, 0\n" \
+    "  v_mov_b32_e32 v60, 0\n" \
+    "  v_mov_b32_e32 v29, 0\n" \
+    "  v_mov_b32_e32 v61, 0\n" \
+    "  v_mov_b32_e32 v30, 0\n" \
+    "  v_mov_b32_e32 v62, 0\n" \
+    "  v_mov_b32_e32 v31, 0\n" \
+    "  v_mov_b32_e32 v63, 0\n" \
+    "Lzr%=:\n" \
+    "  s_cmp_lg_u32 %[nsw], 0\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
+    "  v_mov_b32_e32 v96, 0\n" \
+    "  v_mov_b32_e32 v65, 0\n" \
+    "  v_mov_b32_e32 v97, 0\n" \
+    "  v_mov_b32_e32 v66, 0\n" \
+    "  v_mov_b32_e32 v98, 0\n" \
+    "  v_mov_b32_e32 v67, 0\n" \
+    "  v_mov_b32_e32 v99, 0\n" \
+    "  v_mov_b32_e32 v68, 0\n" \
+    "  v_mov_b32_e32 v100, 0\n" \
+    "  v_mov_b32_e32 v69, 0\n" \
+    "  v_mov_b32_e32 v101, 0\n" \
+    "  v_mov_b32_e32 v70, 0\n" \
+    "  v_mov_b32_e32 v102, 0\n" \
+    "  v_mov_b32_e32 v71, 0\n" \
+    "  v_mov_b32_e32 v103, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v72, 0\n" \
+    "  v_mov_b32_e32 v104, 0\n" \
+    "  v_mov_b32_e32 v73, 0\n" \
+    "  v_mov_b32_e32 v105, 0\n" \
+    "  v_mov_b32_e32 v74, 0\n" \
+    "  v_mov_b32_e32 v106, 0\n" \
+    "  v_mov_b32_e32 v75, 0\n" \
+    "  v_mov_b32_e32 v107, 0\n" \
+    "  v_mov_b32_e32 v76, 0\n" \
+    "  v_mov_b32_e32 v108, 0\n" \
+    "  v_mov_b32_e32 v77, 0\n" \
+    "  v_mov_b32_e32 v109, 0\n" \
+    "  v_mov_b32_e32 v78, 0\n" \
+    "  v_mov_b32_e32 v110, 0\n" \
+    "  v_mov_b32_e32 v79, 0\n" \
+    "  v_mov_b32_e32 v111, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v80, 0\n" \
+    "  v_mov_b32_e32 v112, 0\n" \
+    "  v_mov_b32_e32 v81, 0\n" \
+    "  v_mov_b32_e32 v113, 0\n" \
+    "  v_mov_b32_e32 v82, 0\n" \
+    "  v_mov_b32_e32 v114, 0\n" \
+    "  v_mov_b32_e32 v83, 0\n" \
+    "  v_mov_b32_e32 v115, 0\n" \
+    "  v_mov_b32_e32 v84, 0\n" \
+    "  v_mov_b32_e32 v116, 0\n" \
+    "  v_mov_b32_e32 v85, 0\n" \
+    "  v_mov_b32_e32 v117, 0\n" \
+    "  v_mov_b32_e32 v86, 0\n" \
+    "  v_mov_b32_e32 v118, 0\n" \
+    "  v_mov_b32_e32 v87, 0\n" \
+    "  v_mov_b32_e32 v119, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v88, 0\n" \
+    "  v_mov_b32_e32 v120, 0\n" \
+    "  v_mov_b32_e32 v89, 0\n" \
+    "  v_mov_b32_e32 v121, 0\n" \
+    "  v_mov_b32_e32 v90, 0\n" \
+    "  v_mov_b32_e32 v122, 0\n" \
+    "  v_mov_b32_e32 v91, 0\n" \
+    "  v_mov_b32_e32 v123, 0\n" \
+    "  v_mov_b32_e32 v92, 0\n" \
+    "  v_mov_b32_e32 v124, 0\n" \
+    "  v_mov_b32_e32 v93, 0\n" \
+    "  v_mov_b32_e32 v125, 0\n" \
+    "  v_mov_b32_e32 v94, 0\n" \
+    "  v_mov_b32_e32 v126, 0\n" \
+    "  v_mov_b32_e32 v95, 0\n" \
+    "  v_mov_b32_e32 v127, 0\n" \
+    "Lzw%=:\n" \
+    "  s_lshl_b32 s41, %[ni], 2\n" \
+    "  v_mul_u32_u24_e32 v136, s41, %[lane]\n" \
+    "  v_add_u32_e32 v136, %[dm0], v136\n" \
+    "  s_lshl_b32 s41, %[ni], 8\n" \
+    "  v_add_u32_e32 v137, s41, v136\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_cmp_eq_u32 %[ni], 0\n" \
+    "  s_cbranch_scc1 Lpl_done%=\n" \
+    "Lpl%=:\n" \
+    "  ds_read2_b32 v[128:129], v136 offset0:0 offset1:1\n" \
+    "  ds_read2_b32 v[130:131], v136 offset0:2 offset1:3\n" \
+    "  ds_read2_b32 v[132:133], v137 offset0:0 offset1:1\n" \
+    "  ds_read2_b32 v[134:135], v137 offset0:2 offset1:3\n" \
+    "  v_add_u32_e32 v136, 16, v136\n" \
+    "  v_add_u32_e32 v137, 16, v137\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v128\n" \
+    "  v_mov_b32_e32 v1, v129\n" \
+    "  v_mov_b32_e32 v2, v130\n" \
+    "  v_mov_b32_e32 v3, v131\n" \
+    "  v_mov_b32_e32 v64, v128\n" \
+    "  v_mov_b32_e32 v65, v129\n" \
+    "  v_mov_b32_e32 v66, v130\n" \
+    "  v_mov_b32_e32 v67, v131\n" \
+    "  v_mov_b32_e32 v32, v132\n" \
+    "  v_mov_b32_e32 v33, v133\n" \
+    "  v_mov_b32_e32 v34, v134\n" \
+    "  v_mov_b32_e32 v35, v135\n" \
+    "  v_mov_b32_e32 v96, v132\n" \
+    "  v_mov_b32_e32 v97, v133\n" \
+    "  v_mov_b32_e32 v98, v134\n" \
+    "  v_mov_b32_e32 v99, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_add_u32 s40, s40, 4\n" \
+    "  s_cmp_lt_u32 s40, %[ni]\n" \
+    "  s_cbranch_scc1 Lpl%=\n" \
+    "Lpl_done%=:\n" \
+    "  s_mov_b32 s41, %[ni]\n" \
+    "Lcl%=:\n" \
+    "  s_and_b32 s40, s41, 3\n" \
+    "  s_cbranch_scc0 Lcl_done%=\n" \
+    "  s_set_gpr_idx_on s41, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v32, 0\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
+    "  v_mov_b32_e32 v96, 0\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_add_u32 s41, s41, 1\n" \
+    "  s_branch Lcl%=\n" \
+    "Lcl_done%=:\n" \
+    "  s_set_gpr_idx_on %[zs], gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v1, 1.0\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
+    "  v_mov_b32_e32 v65, 1.0\n" \
+    "  v_mov_b32_e32 v32, 0\n" \
+    "  v_mov_b32_e32 v33, 1.0\n" \
+    "  v_mov_b32_e32 v96, 0\n" \
+    "  v_mov_b32_e32 v97, 1.0\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 %[dn], 0\n" \
+    "  s_cbranch_scc1 Ldma_done%=\n" \
+    "  s_mov_b64 s[42:43], exec\n" \
+    "  s_cmp_eq_u32 %[dvec], 0\n" \
+    "  s_cselect_b32 s41, 2, 4\n" \
+    "  v_lshlrev_b32_e32 v138, s41, %[lane]\n" \
+    "  v_mov_b32_e32 v139, 0\n" \
+    "  v_lshl_add_u64 v[138:139], v[138:139], 0, %[dsrc]\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_mov_b32 m0, %[dm0]\n" \
+    "  s_cmp_eq_u32 %[dvec], 0\n" \
+    "  s_cbranch_scc1 Ldma1%=\n" \
+    "  s_mov_b64 s[46:47], 1024\n" \
+    "Ldl4%=:\n" \
+    "  s_sub_u32 s41, %[dn], s40\n" \
+    "  v_cmp_gt_u32_e64 s[44:45], s41, %[lane]\n" \
+    "  s_and_b64 exec, s[42:43], s[44:45]\n" \
+    "  s_nop 0\n" \
+    "  global_load_lds_dwordx4 v[138:139], off nt\n" \
+    "  s_mov_b64 exec, s[42:43]\n" \
+    "  v_lshl_add_u64 v[138:139], v[138:139], 0, s[46:47]\n" \
+    "  s_add_u32 m0, m0, 1024\n" \
+    "  s_add_u32 s40, s40, 64\n" \
+    "  s_cmp_lt_u32 s40, %[dn]\n" \
+    "  s_cbranch_scc1 Ldl4%=\n" \
+    "  s_branch Ldma_done%=\n" \
+    "Ldma1%=:\n" \
+    "  s_mov_b64 s[46:47], 256\n" \
+    "Ldl1%=:\n" \
+    "  s_sub_u32 s41, %[dn], s40\n" \
+    "  v_cmp_gt_u32_e64 s[44:45], s41, %[lane]\n" \
+    "  s_and_b64 exec, s[42:43], s[44:45]\n" \
+    "  s_nop 0\n" \
+    "  global_load_lds_dword v[138:139], off nt\n" \
+    "  s_mov_b64 exec, s[42:43]\n" \
+    "  v_lshl_add_u64 v[138:139], v[138:139], 0, s[46:47]\n" \
+    "  s_add_u32 m0, m0, 256\n" \
+    "  s_add_u32 s40, s40, 64\n" \
+    "  s_cmp_lt_u32 s40, %[dn]\n" \
+    "  s_cbranch_scc1 Ldl1%=\n" \
+    "  s_branch Ldma_done%=\n" \
+    "Ldma_done%=:\n" \
+    "  s_mov_b32 s91, %[nsw]\n" \
+    "Lsw%=:\n" \
+    "  s_cmp_eq_u32 s91, 0\n" \
+    "  s_cbranch_scc1 Lsw_done%=\n" \
+    "  s_mov_b64 s[80:81], %[rec]\n" \
+    "  s_mov_b64 s[84:85], %[edg]\n" \
+    "  s_mov_b32 s86, 0\n" \
+    "  v_mov_b32_e32 v136, 0x2f309231\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], 0x0\n" \
+    "  s_getpc_b64 s[92:93]\n" \
+    "Lpc%=:\n" \
+    "  s_add_u32 s94, s92, Ltab_B%= - Lpc%=\n" \
+    "  s_addc_u32 s95, s93, 0\n" \
+    "  s_add_u32 s92, s92, Ltab_A%= - Lpc%=\n" \
+    "  s_addc_u32 s93, s93, 0\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v134\n" \
+    "  v_mov_b32_e32 v96, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v132\n" \
+    "  v_mov_b32_e32 v96, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s41\n" \
+    "  v_mov_b32_e32 v135, s41\n" \
+    "  v_fmac_f32_e64 v134, s42, v128\n" \
+    "  v_fmac_f32_e64 v135, s42, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_branch Ldone%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  v_mov_b32_e32 v128, 0\n" \
+    "  v_mov_b32_e32 v129, 0\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v128, v0, s47\n" \
+    "  v_fmac_f32_e64 v129, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v128, v0, s47\n" \
+    "  v_fmac_f32_e64 v129, v32, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v128, v0, s49\n" \
+    "  v_fmac_f32_e64 v129, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v128, v0, s51\n" \
+    "  v_fmac_f32_e64 v129, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v128, v0, s47\n" \
+    "  v_fmac_f32_e64 v129, v32, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v128, v0, s49\n" \
+    "  v_fmac_f32_e64 v129, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v128, v0, s51\n" \
+    "  v_fmac_f32_e64 v129, v32, s51\n" \
+    "  s_set_gpr_idx_idx s52\n" \
+    "  v_fmac_f32_e64 v128, v0, s53\n" \
+    "  v_fmac_f32_e64 v129, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_fmac_f32_e64 v128, v0, s55\n" \
+    "  v_fmac_f32_e64 v129, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v128, v0, s47\n" \
+    "  v_fmac_f32_e64 v129, v32, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v128, v0, s49\n" \
+    "  v_fmac_f32_e64 v129, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v128, v0, s51\n" \
+    "  v_fmac_f32_e64 v129, v32, s51\n" \
+    "  s_set_gpr_idx_idx s52\n" \
+    "  v_fmac_f32_e64 v128, v0, s53\n" \
+    "  v_fmac_f32_e64 v129, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_fmac_f32_e64 v128, v0, s55\n" \
+    "  v_fmac_f32_e64 v129, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_branch Lovs_A%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s53\n" \
+    "  v_mul_f32_e64 v131, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v132, v0, s55\n" \
+    "  v_mul_f32_e64 v133, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s45\n" \
+    "  v_mul_f32_e64 v129, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s53\n" \
+    "  v_mul_f32_e64 v131, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v132, v0, s55\n" \
+    "  v_mul_f32_e64 v133, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_branch Lovp_A%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s45\n" \
+    "  v_mul_f32_e64 v131, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s45\n" \
+    "  v_mul_f32_e64 v131, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s45\n" \
+    "  v_mul_f32_e64 v131, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s53\n" \
+    "  v_mul_f32_e64 v131, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v132, v0, s55\n" \
+    "  v_mul_f32_e64 v133, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s45\n" \
+    "  v_mul_f32_e64 v131, v32, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v132, v0, s47\n" \
+    "  v_mul_f32_e64 v133, v32, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s49\n" \
+    "  v_mul_f32_e64 v131, v32, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v132, v0, s51\n" \
+    "  v_mul_f32_e64 v133, v32, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s53\n" \
+    "  v_mul_f32_e64 v131, v32, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v132, v0, s55\n" \
+    "  v_mul_f32_e64 v133, v32, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v134\n" \
+    "  v_mov_b32_e32 v96, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v132\n" \
+    "  v_mov_b32_e32 v96, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s41, v128\n" \
+    "  v_add_f32_e32 v135, s41, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovs_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Los_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v128, v0, s73\n" \
+    "  v_fmac_f32_e64 v129, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_fmac_f32_e64 v128, v0, s75\n" \
+    "  v_fmac_f32_e64 v129, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovds_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v128, v0, s77\n" \
+    "  v_fmac_f32_e64 v129, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_fmac_f32_e64 v128, v0, s79\n" \
+    "  v_fmac_f32_e64 v129, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovds_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Los_A%=\n" \
+    "Lovds_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovp_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lop_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s73\n" \
+    "  v_mul_f32_e64 v131, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v132, v0, s75\n" \
+    "  v_mul_f32_e64 v133, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdp_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s77\n" \
+    "  v_mul_f32_e64 v131, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v132, v0, s79\n" \
+    "  v_mul_f32_e64 v133, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdp_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lop_A%=\n" \
+    "Lovdp_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovm_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lom_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s73\n" \
+    "  v_mul_f32_e64 v131, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v132, v0, s75\n" \
+    "  v_mul_f32_e64 v133, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdm_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s77\n" \
+    "  v_mul_f32_e64 v131, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v132, v0, s79\n" \
+    "  v_mul_f32_e64 v133, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdm_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lom_A%=\n" \
+    "Lovdm_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v134\n" \
+    "  v_mov_b32_e32 v96, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v132\n" \
+    "  v_mov_b32_e32 v96, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v134, s57\n" \
+    "  v_mov_b32_e32 v135, s57\n" \
+    "  v_fmac_f32_e64 v134, s58, v128\n" \
+    "  v_fmac_f32_e64 v135, s58, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_branch Ldone%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  v_mov_b32_e32 v128, 0\n" \
+    "  v_mov_b32_e32 v129, 0\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v128, v0, s63\n" \
+    "  v_fmac_f32_e64 v129, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v128, v0, s63\n" \
+    "  v_fmac_f32_e64 v129, v32, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v128, v0, s65\n" \
+    "  v_fmac_f32_e64 v129, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v128, v0, s67\n" \
+    "  v_fmac_f32_e64 v129, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v128, v0, s63\n" \
+    "  v_fmac_f32_e64 v129, v32, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v128, v0, s65\n" \
+    "  v_fmac_f32_e64 v129, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v128, v0, s67\n" \
+    "  v_fmac_f32_e64 v129, v32, s67\n" \
+    "  s_set_gpr_idx_idx s68\n" \
+    "  v_fmac_f32_e64 v128, v0, s69\n" \
+    "  v_fmac_f32_e64 v129, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_fmac_f32_e64 v128, v0, s71\n" \
+    "  v_fmac_f32_e64 v129, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v128, v0, s63\n" \
+    "  v_fmac_f32_e64 v129, v32, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v128, v0, s65\n" \
+    "  v_fmac_f32_e64 v129, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v128, v0, s67\n" \
+    "  v_fmac_f32_e64 v129, v32, s67\n" \
+    "  s_set_gpr_idx_idx s68\n" \
+    "  v_fmac_f32_e64 v128, v0, s69\n" \
+    "  v_fmac_f32_e64 v129, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_fmac_f32_e64 v128, v0, s71\n" \
+    "  v_fmac_f32_e64 v129, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_branch Lovs_B%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s69\n" \
+    "  v_mul_f32_e64 v131, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v132, v0, s71\n" \
+    "  v_mul_f32_e64 v133, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v128, v0, s61\n" \
+    "  v_mul_f32_e64 v129, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s69\n" \
+    "  v_mul_f32_e64 v131, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v132, v0, s71\n" \
+    "  v_mul_f32_e64 v133, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_branch Lovp_B%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s61\n" \
+    "  v_mul_f32_e64 v131, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s61\n" \
+    "  v_mul_f32_e64 v131, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s61\n" \
+    "  v_mul_f32_e64 v131, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s69\n" \
+    "  v_mul_f32_e64 v131, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v132, v0, s71\n" \
+    "  v_mul_f32_e64 v133, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s61\n" \
+    "  v_mul_f32_e64 v131, v32, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v132, v0, s63\n" \
+    "  v_mul_f32_e64 v133, v32, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v130, v132, v132\n" \
+    "  v_maximum3_f32 v129, v131, v133, v133\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s65\n" \
+    "  v_mul_f32_e64 v131, v32, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v132, v0, s67\n" \
+    "  v_mul_f32_e64 v133, v32, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s69\n" \
+    "  v_mul_f32_e64 v131, v32, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v132, v0, s71\n" \
+    "  v_mul_f32_e64 v133, v32, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v134\n" \
+    "  v_mov_b32_e32 v96, v135\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, 0x4038aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0x4038aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v132, v132\n" \
+    "  v_rcp_f32_e32 v133, v133\n" \
+    "  v_fma_f32 v130, v132, -2.0, 1.0\n" \
+    "  v_fma_f32 v131, v133, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v134\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v135\n" \
+    "  v_exp_f32_e32 v130, v130\n" \
+    "  v_exp_f32_e32 v131, v131\n" \
+    "  v_add_f32_e32 v132, 1.0, v130\n" \
+    "  v_add_f32_e32 v133, 1.0, v131\n" \
+    "  v_rcp_f32_e32 v130, v132\n" \
+    "  v_rcp_f32_e32 v131, v133\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_maximum3_f32 v130, v134, 0, 0\n" \
+    "  v_maximum3_f32 v131, v135, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v132, 0x3ea2f983, v134\n" \
+    "  v_mul_f32_e32 v133, 0x3ea2f983, v135\n" \
+    "  v_rndne_f32_e32 v132, v132\n" \
+    "  v_rndne_f32_e32 v133, v133\n" \
+    "  v_fmamk_f32 v128, v132, 0xc0490fdb, v134\n" \
+    "  v_fmamk_f32 v129, v133, 0xc0490fdb, v135\n" \
+    "  v_fmac_f32_e32 v128, 0x33bbbd2e, v132\n" \
+    "  v_fmac_f32_e32 v129, 0x33bbbd2e, v133\n" \
+    "  v_cvt_i32_f32_e32 v132, v132\n" \
+    "  v_cvt_i32_f32_e32 v133, v133\n" \
+    "  v_mul_f32_e32 v134, v128, v128\n" \
+    "  v_mul_f32_e32 v135, v129, v129\n" \
+    "  v_fmaak_f32 v137, v134, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v138, v135, v136, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xb9500d01\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xb9500d01\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0x3c088889\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0x3c088889\n" \
+    "  v_fmaak_f32 v137, v134, v137, 0xbe2aaaab\n" \
+    "  v_fmaak_f32 v138, v135, v138, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v130, v128, v134\n" \
+    "  v_mul_f32_e32 v131, v129, v135\n" \
+    "  v_fmac_f32_e32 v128, v130, v137\n" \
+    "  v_fmac_f32_e32 v129, v131, v138\n" \
+    "  v_lshl_add_u32 v130, v132, 31, v128\n" \
+    "  v_lshl_add_u32 v131, v133, 31, v129\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_mul_f32_e32 v130, v134, v134\n" \
+    "  v_mul_f32_e32 v131, v135, v135\n" \
+    "  v_mul_f32_e32 v130, 0xbfb8aa3b, v130\n" \
+    "  v_mul_f32_e32 v131, 0xbfb8aa3b, v131\n" \
+    "  v_exp_f32_e32 v132, v130\n" \
+    "  v_exp_f32_e32 v133, v131\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v132\n" \
+    "  v_mov_b32_e32 v96, v133\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v134, s57, v128\n" \
+    "  v_add_f32_e32 v135, s57, v129\n" \
+    "  v_maximum3_f32 v130, v134, -v134, -v134\n" \
+    "  v_maximum3_f32 v131, v135, -v135, -v135\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v64, v130\n" \
+    "  v_mov_b32_e32 v96, v131\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovs_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Los_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v128, v0, s73\n" \
+    "  v_fmac_f32_e64 v129, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_fmac_f32_e64 v128, v0, s75\n" \
+    "  v_fmac_f32_e64 v129, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovds_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v128, v0, s77\n" \
+    "  v_fmac_f32_e64 v129, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_fmac_f32_e64 v128, v0, s79\n" \
+    "  v_fmac_f32_e64 v129, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovds_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Los_B%=\n" \
+    "Lovds_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovp_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lop_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s73\n" \
+    "  v_mul_f32_e64 v131, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v132, v0, s75\n" \
+    "  v_mul_f32_e64 v133, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdp_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s77\n" \
+    "  v_mul_f32_e64 v131, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v132, v0, s79\n" \
+    "  v_mul_f32_e64 v133, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v128, v128, v130\n" \
+    "  v_mul_f32_e32 v129, v129, v131\n" \
+    "  v_mul_f32_e32 v128, v128, v132\n" \
+    "  v_mul_f32_e32 v129, v129, v133\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdp_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lop_B%=\n" \
+    "Lovdp_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovm_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lom_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s73\n" \
+    "  v_mul_f32_e64 v131, v32, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v132, v0, s75\n" \
+    "  v_mul_f32_e64 v133, v32, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdm_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v130, v0, s77\n" \
+    "  v_mul_f32_e64 v131, v32, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v132, v0, s79\n" \
+    "  v_mul_f32_e64 v133, v32, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v128, v128, v130, v132\n" \
+    "  v_maximum3_f32 v129, v129, v131, v133\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdm_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lom_B%=\n" \
+    "Lovdm_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Ldone%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_sub_u32 s91, s91, 1\n" \
+    "  s_cmp_eq_u32 s91, 0\n" \
+    "  s_cbranch_scc1 Lsw_done%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v0, v64\n" \
+    "  v_mov_b32_e32 v32, v96\n" \
+    "  v_mov_b32_e32 v1, v65\n" \
+    "  v_mov_b32_e32 v33, v97\n" \
+    "  v_mov_b32_e32 v2, v66\n" \
+    "  v_mov_b32_e32 v34, v98\n" \
+    "  v_mov_b32_e32 v3, v67\n" \
+    "  v_mov_b32_e32 v35, v99\n" \
+    "  v_mov_b32_e32 v4, v68\n" \
+    "  v_mov_b32_e32 v36, v100\n" \
+    "  v_mov_b32_e32 v5, v69\n" \
+    "  v_mov_b32_e32 v37, v101\n" \
+    "  v_mov_b32_e32 v6, v70\n" \
+    "  v_mov_b32_e32 v38, v102\n" \
+    "  v_mov_b32_e32 v7, v71\n" \
+    "  v_mov_b32_e32 v39, v103\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v8, v72\n" \
+    "  v_mov_b32_e32 v40, v104\n" \
+    "  v_mov_b32_e32 v9, v73\n" \
+    "  v_mov_b32_e32 v41, v105\n" \
+    "  v_mov_b32_e32 v10, v74\n" \
+    "  v_mov_b32_e32 v42, v106\n" \
+    "  v_mov_b32_e32 v11, v75\n" \
+    "  v_mov_b32_e32 v43, v107\n" \
+    "  v_mov_b32_e32 v12, v76\n" \
+    "  v_mov_b32_e32 v44, v108\n" \
+    "  v_mov_b32_e32 v13, v77\n" \
+    "  v_mov_b32_e32 v45, v109\n" \
+    "  v_mov_b32_e32 v14, v78\n" \
+    "  v_mov_b32_e32 v46, v110\n" \
+    "  v_mov_b32_e32 v15, v79\n" \
+    "  v_mov_b32_e32 v47, v111\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v16, v80\n" \
+    "  v_mov_b32_e32 v48, v112\n" \
+    "  v_mov_b32_e32 v17, v81\n" \
+    "  v_mov_b32_e32 v49, v113\n" \
+    "  v_mov_b32_e32 v18, v82\n" \
+    "  v_mov_b32_e32 v50, v114\n" \
+    "  v_mov_b32_e32 v19, v83\n" \
+    "  v_mov_b32_e32 v51, v115\n" \
+    "  v_mov_b32_e32 v20, v84\n" \
+    "  v_mov_b32_e32 v52, v116\n" \
+    "  v_mov_b32_e32 v21, v85\n" \
+    "  v_mov_b32_e32 v53, v117\n" \
+    "  v_mov_b32_e32 v22, v86\n" \
+    "  v_mov_b32_e32 v54, v118\n" \
+    "  v_mov_b32_e32 v23, v87\n" \
+    "  v_mov_b32_e32 v55, v119\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v24, v88\n" \
+    "  v_mov_b32_e32 v56, v120\n" \
+    "  v_mov_b32_e32 v25, v89\n" \
+    "  v_mov_b32_e32 v57, v121\n" \
+    "  v_mov_b32_e32 v26, v90\n" \
+    "  v_mov_b32_e32 v58, v122\n" \
+    "  v_mov_b32_e32 v27, v91\n" \
+    "  v_mov_b32_e32 v59, v123\n" \
+    "  v_mov_b32_e32 v28, v92\n" \
+    "  v_mov_b32_e32 v60, v124\n" \
+    "  v_mov_b32_e32 v29, v93\n" \
+    "  v_mov_b32_e32 v61, v125\n" \
+    "  v_mov_b32_e32 v30, v94\n" \
+    "  v_mov_b32_e32 v62, v126\n" \
+    "  v_mov_b32_e32 v31, v95\n" \
+    "  v_mov_b32_e32 v63, v127\n" \
+    "Lcp%=:\n" \
+    "  s_branch Lsw%=\n" \
+    "Lsw_done%=:\n" \
+    "  s_mov_b64 s[44:45], %[outs]\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_lshl_b32 s41, %[no], 2\n" \
+    "  v_mul_u32_u24_e32 v136, s41, %[lane]\n" \
+    "  v_add_u32_e32 v136, %[om0], v136\n" \
+    "  s_lshl_b32 s41, %[no], 8\n" \
+    "  v_add_u32_e32 v137, s41, v136\n" \
+    "Lout%=:\n" \
+    "  s_load_dwordx8 s[48:55], s[44:45], 0x0\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v128, v64\n" \
+    "  v_mov_b32_e32 v132, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v128 offset:0\n" \
+    "  ds_write_b32 v137, v132 offset:0\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s49, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v129, v64\n" \
+    "  v_mov_b32_e32 v133, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v129 offset:4\n" \
+    "  ds_write_b32 v137, v133 offset:4\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s50, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v130, v64\n" \
+    "  v_mov_b32_e32 v134, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v130 offset:8\n" \
+    "  ds_write_b32 v137, v134 offset:8\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s51, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v131, v64\n" \
+    "  v_mov_b32_e32 v135, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v131 offset:12\n" \
+    "  ds_write_b32 v137, v135 offset:12\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v128, v64\n" \
+    "  v_mov_b32_e32 v132, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v128 offset:16\n" \
+    "  ds_write_b32 v137, v132 offset:16\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s53, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v129, v64\n" \
+    "  v_mov_b32_e32 v133, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v129 offset:20\n" \
+    "  ds_write_b32 v137, v133 offset:20\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s54, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v130, v64\n" \
+    "  v_mov_b32_e32 v134, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v130 offset:24\n" \
+    "  ds_write_b32 v137, v134 offset:24\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s55, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v131, v64\n" \
+    "  v_mov_b32_e32 v135, v96\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v136, v131 offset:28\n" \
+    "  ds_write_b32 v137, v135 offset:28\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  v_add_u32_e32 v136, 32, v136\n" \
+    "  v_add_u32_e32 v137, 32, v137\n" \
+    "  s_add_u32 s44, s44, 32\n" \
+    "  s_addc_u32 s45, s45, 0\n" \
+    "  s_branch Lout%=\n" \
+    "Lout_done%=:\n" \
+    "  s_mov_b32 m0, s90\n"
+
+#define NEAT_CLOB_S2_32R \
+    "v0", "v1", "v2", "v3", "v4", "v5", "v6", "v7", "v8", "v9", "v10", "v11", \
+    "v12", "v13", "v14", "v15", "v16", "v17", "v18", "v19", "v20", "v21", "v22", "v23", \
+    "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33", "v34", "v35", \
+    "v36", "v37", "v38", "v39", "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", \
+    "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", \
+    "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", "v69", "v70", "v71", \
+    "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81", "v82", "v83", \
+    "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95", \
+    "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
+    "v108", "v109", "v110", "v111", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", \
+    "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "v128", "v129", "v130", "v131", \
+    "v132", "v133", "v134", "v135", "v136", "v137", "v138", "v139", "s40", "s41", "s42", "s43", \
+    "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", \
+    "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", \
+    "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", \
+    "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", \
+    "s92", "s93", "s94", "s95", "vcc", "scc"
+
+#define NEAT_SCRATCH_S2_32R 128
+
+
+// S1_52R: 1 sample(s) per lane, value vectors at v0, scratch v104..v111
+
+#define NEAT_TILE_S1_52R \
+    "  s_mov_b32 s90, m0\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v1, 0\n" \
+    "  v_mov_b32_e32 v2, 0\n" \
+    "  v_mov_b32_e32 v3, 0\n" \
+    "  v_mov_b32_e32 v4, 0\n" \
+    "  v_mov_b32_e32 v5, 0\n" \
+    "  v_mov_b32_e32 v6, 0\n" \
+    "  v_mov_b32_e32 v7, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v8, 0\n" \
+    "  v_mov_b32_e32 v9, 0\n" \
+    "  v_mov_b32_e32 v10, 0\n" \
+    "  v_mov_b32_e32 v11, 0\n" \
+    "  v_mov_b32_e32 v12, 0\n" \
+    "  v_mov_b32_e32 v13, 0\n" \
+    "  v_mov_b32_e32 v14, 0\n" \
+    "  v_mov_b32_e32 v15, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v16, 0\n" \
+    "  v_mov_b32_e32 v17, 0\n" \
+    "  v_mov_b32_e32 v18, 0\n" \
+    "  v_mov_b32_e32 v19, 0\n" \
+    "  v_mov_b32_e32 v20, 0\n" \
+    "  v_mov_b32_e32 v21, 0\n" \
+    "  v_mov_b32_e32 v22, 0\n" \
+    "  v_mov_b32_e32 v23, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v24, 0\n" \
+    "  v_mov_b32_e32 v25, 0\n" \
+    "  v_mov_b32_e32 v26, 0\n" \
+    "  v_mov_b32_e32 v27, 0\n" \
+    "  v_mov_b32_e32 v28, 0\n" \
+    "  v_mov_b32_e32 v29, 0\n" \
+    "  v_mov_b32_e32 v30, 0\n" \
+    "  v_mov_b32_e32 v31, 0\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v32, 0\n" \
+    "  v_mov_b32_e32 v33, 0\n" \
+    "  v_mov_b32_e32 v34, 0\n" \
+    "  v_mov_b32_e32 v35, 0\n" \
+    "  v_mov_b32_e32 v36, 0\n" \
+    "  v_mov_b32_e32 v37, 0\n" \
+    "  v_mov_b32_e32 v38, 0\n" \
+    "  v_mov_b32_e32 v39, 0\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v40, 0\n" \
+    "  v_mov_b32_e32 v41, 0\n" \
+    "  v_mov_b32_e32 v42, 0\n" \
+    "  v_mov_b32_e32 v43, 0\n" \
+    "  v_mov_b32_e32 v44, 0\n" \
+    "  v_mov_b32_e32 v45, 0\n" \
+    "  v_mov_b32_e32 v46, 0\n" \
+    "  v_mov_b32_e32 v47, 0\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lzr%=\n" \
+    "  v_mov_b32_e32 v48, 0\n" \
+    "  v_mov_b32_e32 v49, 0\n" \
+    "  v_mov_b32_e32 v50, 0\n" \
+    "  v_mov_b32_e32 v51, 0\n" \
+    "Lzr%=:\n" \
+    "  s_cmp_lg_u32 %[nsw], 0\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v52, 0\n" \
+    "  v_mov_b32_e32 v53, 0\n" \
+    "  v_mov_b32_e32 v54, 0\n" \
+    "  v_mov_b32_e32 v55, 0\n" \
+    "  v_mov_b32_e32 v56, 0\n" \
+    "  v_mov_b32_e32 v57, 0\n" \
+    "  v_mov_b32_e32 v58, 0\n" \
+    "  v_mov_b32_e32 v59, 0\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v60, 0\n" \
+    "  v_mov_b32_e32 v61, 0\n" \
+    "  v_mov_b32_e32 v62, 0\n" \
+    "  v_mov_b32_e32 v63, 0\n" \
+    "  v_mov_b32_e32 v64, 0\n" \
+    "  v_mov_b32_e32 v65, 0\n" \
+    "  v_mov_b32_e32 v66, 0\n" \
+    "  v_mov_b32_e32 v67, 0\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v68, 0\n" \
+    "  v_mov_b32_e32 v69, 0\n" \
+    "  v_mov_b32_e32 v70, 0\n" \
+    "  v_mov_b32_e32 v71, 0\n" \
+    "  v_mov_b32_e32 v72, 0\n" \
+    "  v_mov_b32_e32 v73, 0\n" \
+    "  v_mov_b32_e32 v74, 0\n" \
+    "  v_mov_b32_e32 v75, 0\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v76, 0\n" \
+    "  v_mov_b32_e32 v77, 0\n" \
+    "  v_mov_b32_e32 v78, 0\n" \
+    "  v_mov_b32_e32 v79, 0\n" \
+    "  v_mov_b32_e32 v80, 0\n" \
+    "  v_mov_b32_e32 v81, 0\n" \
+    "  v_mov_b32_e32 v82, 0\n" \
+    "  v_mov_b32_e32 v83, 0\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v84, 0\n" \
+    "  v_mov_b32_e32 v85, 0\n" \
+    "  v_mov_b32_e32 v86, 0\n" \
+    "  v_mov_b32_e32 v87, 0\n" \
+    "  v_mov_b32_e32 v88, 0\n" \
+    "  v_mov_b32_e32 v89, 0\n" \
+    "  v_mov_b32_e32 v90, 0\n" \
+    "  v_mov_b32_e32 v91, 0\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v92, 0\n" \
+    "  v_mov_b32_e32 v93, 0\n" \
+    "  v_mov_b32_e32 v94, 0\n" \
+    "  v_mov_b32_e32 v95, 0\n" \
+    "  v_mov_b32_e32 v96, 0\n" \
+    "  v_mov_b32_e32 v97, 0\n" \
+    "  v_mov_b32_e32 v98, 0\n" \
+    "  v_mov_b32_e32 v99, 0\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lzw%=\n" \
+    "  v_mov_b32_e32 v100, 0\n" \
+    "  v_mov_b32_e32 v101, 0\n" \
+    "  v_mov_b32_e32 v102, 0\n" \
+    "  v_mov_b32_e32 v103, 0\n" \
+    "Lzw%=:\n" \
+    "  s_lshl_b32 s41, %[ni], 2\n" \
+    "  v_mul_u32_u24_e32 v108, s41, %[lane]\n" \
+    "  v_add_u32_e32 v108, %[dm0], v108\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_cmp_eq_u32 %[ni], 0\n" \
+    "  s_cbranch_scc1 Lpl_done%=\n" \
+    "Lpl%=:\n" \
+    "  ds_read2_b32 v[104:105], v108 offset0:0 offset1:1\n" \
+    "  ds_read2_b32 v[106:107], v108 offset0:2 offset1:3\n" \
+    "  v_add_u32_e32 v108, 16, v108\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, v104\n" \
+    "  v_mov_b32_e32 v1, v105\n" \
+    "  v_mov_b32_e32 v2, v106\n" \
+    "  v_mov_b32_e32 v3, v107\n" \
+    "  v_mov_b32_e32 v52, v104\n" \
+    "  v_mov_b32_e32 v53, v105\n" \
+    "  v_mov_b32_e32 v54, v106\n" \
+    "  v_mov_b32_e32 v55, v107\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_add_u32 s40, s40, 4\n" \
+    "  s_cmp_lt_u32 s40, %[ni]\n" \
+    "  s_cbranch_scc1 Lpl%=\n" \
+    "Lpl_done%=:\n" \
+    "  s_mov_b32 s41, %[ni]\n" \
+    "Lcl%=:\n" \
+    "  s_and_b32 s40, s41, 3\n" \
+    "  s_cbranch_scc0 Lcl_done%=\n" \
+    "  s_set_gpr_idx_on s41, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v52, 0\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_add_u32 s41, s41, 1\n" \
+    "  s_branch Lcl%=\n" \
+    "Lcl_done%=:\n" \
+    "  s_set_gpr_idx_on %[zs], gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v0, 0\n" \
+    "  v_mov_b32_e32 v1, 1.0\n" \
+    "  v_mov_b32_e32 v52, 0\n" \
+    "  v_mov_b32_e32 v53, 1.0\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 %[dn], 0\n" \
+    "  s_cbranch_scc1 Ldma_done%=\n" \
+    "  s_mov_b64 s[42:43], exec\n" \
+    "  s_cmp_eq_u32 %[dvec], 0\n" \
+    "  s_cselect_b32 s41, 2, 4\n" \
+    "  v_lshlrev_b32_e32 v110, s41, %[lane]\n" \
+    "  v_mov_b32_e32 v111, 0\n" \
+    "  v_lshl_add_u64 v[110:111], v[110:111], 0, %[dsrc]\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_mov_b32 m0, %[dm0]\n" \
+    "  s_cmp_eq_u32 %[dvec], 0\n" \
+    "  s_cbranch_scc1 Ldma1%=\n" \
+    "  s_mov_b64 s[46:47], 1024\n" \
+    "Ldl4%=:\n" \
+    "  s_sub_u32 s41, %[dn], s40\n" \
+    "  v_cmp_gt_u32_e64 s[44:45], s41, %[lane]\n" \
+    "  s_and_b64 exec, s[42:43], s[44:45]\n" \
+    "  s_nop 0\n" \
+    "  global_load_lds_dwordx4 v[110:111], off nt\n" \
+    "  s_mov_b64 exec, s[42:43]\n" \
+    "  v_lshl_add_u64 v[110:111], v[110:111], 0, s[46:47]\n" \
+    "  s_add_u32 m0, m0, 1024\n" \
+    "  s_add_u32 s40, s40, 64\n" \
+    "  s_cmp_lt_u32 s40, %[dn]\n" \
+    "  s_cbranch_scc1 Ldl4%=\n" \
+    "  s_branch Ldma_done%=\n" \
+    "Ldma1%=:\n" \
+    "  s_mov_b64 s[46:47], 256\n" \
+    "Ldl1%=:\n" \
+    "  s_sub_u32 s41, %[dn], s40\n" \
+    "  v_cmp_gt_u32_e64 s[44:45], s41, %[lane]\n" \
+    "  s_and_b64 exec, s[42:43], s[44:45]\n" \
+    "  s_nop 0\n" \
+    "  global_load_lds_dword v[110:111], off nt\n" \
+    "  s_mov_b64 exec, s[42:43]\n" \
+    "  v_lshl_add_u64 v[110:111], v[110:111], 0, s[46:47]\n" \
+    "  s_add_u32 m0, m0, 256\n" \
+    "  s_add_u32 s40, s40, 64\n" \
+    "  s_cmp_lt_u32 s40, %[dn]\n" \
+    "  s_cbranch_scc1 Ldl1%=\n" \
+    "  s_branch Ldma_done%=\n" \
+    "Ldma_done%=:\n" \
+    "  s_mov_b32 s91, %[nsw]\n" \
+    "Lsw%=:\n" \
+    "  s_cmp_eq_u32 s91, 0\n" \
+    "  s_cbranch_scc1 Lsw_done%=\n" \
+    "  s_mov_b64 s[80:81], %[rec]\n" \
+    "  s_mov_b64 s[84:85], %[edg]\n" \
+    "  s_mov_b32 s86, 0\n" \
+    "  v_mov_b32_e32 v108, 0x2f309231\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], 0x0\n" \
+    "  s_getpc_b64 s[92:93]\n" \
+    "Lpc%=:\n" \
+    "  s_add_u32 s94, s92, Ltab_B%= - Lpc%=\n" \
+    "  s_addc_u32 s95, s93, 0\n" \
+    "  s_add_u32 s92, s92, Ltab_A%= - Lpc%=\n" \
+    "  s_addc_u32 s93, s93, 0\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "Ltab_A%=:\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v107\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_mul_f32_e32 v105, 0x4038aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v106, v106\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v105, v106, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v105, v106\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_maximum3_f32 v105, v107, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_mul_f32_e32 v106, 0x3ea2f983, v107\n" \
+    "  v_rndne_f32_e32 v106, v106\n" \
+    "  v_fmamk_f32 v104, v106, 0xc0490fdb, v107\n" \
+    "  v_fmac_f32_e32 v104, 0x33bbbd2e, v106\n" \
+    "  v_cvt_i32_f32_e32 v106, v106\n" \
+    "  v_mul_f32_e32 v107, v104, v104\n" \
+    "  v_fmaak_f32 v109, v107, v108, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xb9500d01\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3c088889\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v105, v104, v107\n" \
+    "  v_fmac_f32_e32 v104, v105, v109\n" \
+    "  v_lshl_add_u32 v105, v106, 31, v104\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_mul_f32_e32 v105, v107, v107\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v105\n" \
+    "  v_exp_f32_e32 v106, v105\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v106\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s41\n" \
+    "  v_fmac_f32_e64 v107, s42, v104\n" \
+    "  v_maximum3_f32 v105, v107, -v107, -v107\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_branch Ldone%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  v_mov_b32_e32 v104, 0\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v104, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v104, v0, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v104, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v104, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v104, v0, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v104, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v104, v0, s51\n" \
+    "  s_set_gpr_idx_idx s52\n" \
+    "  v_fmac_f32_e64 v104, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_fmac_f32_e64 v104, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_fmac_f32_e64 v104, v0, s47\n" \
+    "  s_set_gpr_idx_idx s48\n" \
+    "  v_fmac_f32_e64 v104, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_fmac_f32_e64 v104, v0, s51\n" \
+    "  s_set_gpr_idx_idx s52\n" \
+    "  v_fmac_f32_e64 v104, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_fmac_f32_e64 v104, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_branch Lovs_A%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v106, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v106, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_branch Lovp_A%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v106, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[56:71], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s44, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s45\n" \
+    "  s_set_gpr_idx_idx s46\n" \
+    "  v_mul_f32_e64 v106, v0, s47\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s49\n" \
+    "  s_set_gpr_idx_idx s50\n" \
+    "  v_mul_f32_e64 v106, v0, s51\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s53\n" \
+    "  s_set_gpr_idx_idx s54\n" \
+    "  v_mul_f32_e64 v106, v0, s55\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_branch Lovm_A%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v107\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_mul_f32_e32 v105, 0x4038aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v106, v106\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v105, v106, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v105, v106\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_maximum3_f32 v105, v107, 0, 0\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_mul_f32_e32 v106, 0x3ea2f983, v107\n" \
+    "  v_rndne_f32_e32 v106, v106\n" \
+    "  v_fmamk_f32 v104, v106, 0xc0490fdb, v107\n" \
+    "  v_fmac_f32_e32 v104, 0x33bbbd2e, v106\n" \
+    "  v_cvt_i32_f32_e32 v106, v106\n" \
+    "  v_mul_f32_e32 v107, v104, v104\n" \
+    "  v_fmaak_f32 v109, v107, v108, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xb9500d01\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3c088889\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v105, v104, v107\n" \
+    "  v_fmac_f32_e32 v104, v105, v109\n" \
+    "  v_lshl_add_u32 v105, v106, 31, v104\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_mul_f32_e32 v105, v107, v107\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v105\n" \
+    "  v_exp_f32_e32 v106, v105\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v106\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s41, v104\n" \
+    "  v_maximum3_f32 v105, v107, -v107, -v107\n" \
+    "  s_set_gpr_idx_on s40, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s59, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovs_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Los_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v104, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_fmac_f32_e64 v104, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovds_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v104, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_fmac_f32_e64 v104, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovds_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Los_A%=\n" \
+    "Lovds_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovp_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lop_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v106, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdp_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v106, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdp_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lop_A%=\n" \
+    "Lovdp_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovm_A%=:\n" \
+    "  s_and_b32 s87, s43, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lom_A%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v106, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdm_A%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v106, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdm_A%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lom_A%=\n" \
+    "Lovdm_A%=:\n" \
+    "  s_lshr_b32 s88, s40, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "Ltab_B%=:\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v107\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_mul_f32_e32 v105, 0x4038aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v106, v106\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v105, v106, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v105, v106\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_maximum3_f32 v105, v107, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_mul_f32_e32 v106, 0x3ea2f983, v107\n" \
+    "  v_rndne_f32_e32 v106, v106\n" \
+    "  v_fmamk_f32 v104, v106, 0xc0490fdb, v107\n" \
+    "  v_fmac_f32_e32 v104, 0x33bbbd2e, v106\n" \
+    "  v_cvt_i32_f32_e32 v106, v106\n" \
+    "  v_mul_f32_e32 v107, v104, v104\n" \
+    "  v_fmaak_f32 v109, v107, v108, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xb9500d01\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3c088889\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v105, v104, v107\n" \
+    "  v_fmac_f32_e32 v104, v105, v109\n" \
+    "  v_lshl_add_u32 v105, v106, 31, v104\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_mul_f32_e32 v105, v107, v107\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v105\n" \
+    "  v_exp_f32_e32 v106, v105\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v106\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_mov_b32_e32 v107, s57\n" \
+    "  v_fmac_f32_e64 v107, s58, v104\n" \
+    "  v_maximum3_f32 v105, v107, -v107, -v107\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_branch Ldone%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  v_mov_b32_e32 v104, 0\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v104, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v104, v0, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v104, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v104, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v104, v0, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v104, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v104, v0, s67\n" \
+    "  s_set_gpr_idx_idx s68\n" \
+    "  v_fmac_f32_e64 v104, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_fmac_f32_e64 v104, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_fmac_f32_e64 v104, v0, s63\n" \
+    "  s_set_gpr_idx_idx s64\n" \
+    "  v_fmac_f32_e64 v104, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_fmac_f32_e64 v104, v0, s67\n" \
+    "  s_set_gpr_idx_idx s68\n" \
+    "  v_fmac_f32_e64 v104, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_fmac_f32_e64 v104, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_branch Lovs_B%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v106, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v104, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v106, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_branch Lovp_B%=\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v106, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  s_add_u32 s86, s86, 64\n" \
+    "  s_load_dwordx16 s[40:55], s[80:81], s86\n" \
+    "  s_load_dwordx8 s[72:79], s[84:85], 0x0\n" \
+    "  s_set_gpr_idx_on s60, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s61\n" \
+    "  s_set_gpr_idx_idx s62\n" \
+    "  v_mul_f32_e64 v106, v0, s63\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v105, v106, v106\n" \
+    "  s_set_gpr_idx_on s64, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s65\n" \
+    "  s_set_gpr_idx_idx s66\n" \
+    "  v_mul_f32_e64 v106, v0, s67\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_set_gpr_idx_on s68, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s69\n" \
+    "  s_set_gpr_idx_idx s70\n" \
+    "  v_mul_f32_e64 v106, v0, s71\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_branch Lovm_B%=\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v107\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_mul_f32_e32 v105, 0x4038aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v106, v106\n" \
+    "  s_nop 0\n" \
+    "  v_fma_f32 v105, v106, -2.0, 1.0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v107\n" \
+    "  v_exp_f32_e32 v105, v105\n" \
+    "  s_nop 0\n" \
+    "  v_add_f32_e32 v106, 1.0, v105\n" \
+    "  v_rcp_f32_e32 v105, v106\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_maximum3_f32 v105, v107, 0, 0\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_mul_f32_e32 v106, 0x3ea2f983, v107\n" \
+    "  v_rndne_f32_e32 v106, v106\n" \
+    "  v_fmamk_f32 v104, v106, 0xc0490fdb, v107\n" \
+    "  v_fmac_f32_e32 v104, 0x33bbbd2e, v106\n" \
+    "  v_cvt_i32_f32_e32 v106, v106\n" \
+    "  v_mul_f32_e32 v107, v104, v104\n" \
+    "  v_fmaak_f32 v109, v107, v108, 0xb2d7322b\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3638ef1d\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xb9500d01\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0x3c088889\n" \
+    "  v_fmaak_f32 v109, v107, v109, 0xbe2aaaab\n" \
+    "  v_mul_f32_e32 v105, v104, v107\n" \
+    "  v_fmac_f32_e32 v104, v105, v109\n" \
+    "  v_lshl_add_u32 v105, v106, 31, v104\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_mul_f32_e32 v105, v107, v107\n" \
+    "  v_mul_f32_e32 v105, 0xbfb8aa3b, v105\n" \
+    "  v_exp_f32_e32 v106, v105\n" \
+    "  s_nop 1\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v106\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "  .p2align 8\n" \
+    "  v_add_f32_e32 v107, s57, v104\n" \
+    "  v_maximum3_f32 v105, v107, -v107, -v107\n" \
+    "  s_set_gpr_idx_on s56, gpr_idx(DST)\n" \
+    "  v_mov_b32_e32 v52, v105\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_lshr_b32 s88, s43, 16\n" \
+    "  s_add_u32 s88, s88, s92\n" \
+    "  s_addc_u32 s89, s93, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovs_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Los_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v104, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_fmac_f32_e64 v104, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovds_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_fmac_f32_e64 v104, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_fmac_f32_e64 v104, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovds_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Los_B%=\n" \
+    "Lovds_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovp_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lop_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v106, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdp_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v106, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_mul_f32_e32 v104, v104, v105\n" \
+    "  v_mul_f32_e32 v104, v104, v106\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdp_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lop_B%=\n" \
+    "Lovdp_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Lovm_B%=:\n" \
+    "  s_and_b32 s87, s59, 0x3fff\n" \
+    "  s_sub_u32 s87, s87, 3\n" \
+    "  s_mov_b64 s[82:83], s[84:85]\n" \
+    "  s_lshl_b32 s89, s87, 4\n" \
+    "  s_add_u32 s84, s84, s89\n" \
+    "  s_addc_u32 s85, s85, 0\n" \
+    "Lom_B%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s72, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s73\n" \
+    "  s_set_gpr_idx_idx s74\n" \
+    "  v_mul_f32_e64 v106, v0, s75\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_cmp_eq_u32 s87, 1\n" \
+    "  s_cbranch_scc1 Lovdm_B%=\n" \
+    "  s_set_gpr_idx_on s76, gpr_idx(SRC0)\n" \
+    "  v_mul_f32_e64 v105, v0, s77\n" \
+    "  s_set_gpr_idx_idx s78\n" \
+    "  v_mul_f32_e64 v106, v0, s79\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  v_maximum3_f32 v104, v104, v105, v106\n" \
+    "  s_sub_u32 s87, s87, 2\n" \
+    "  s_cmp_eq_u32 s87, 0\n" \
+    "  s_cbranch_scc1 Lovdm_B%=\n" \
+    "  s_add_u32 s82, s82, 32\n" \
+    "  s_addc_u32 s83, s83, 0\n" \
+    "  s_load_dwordx8 s[72:79], s[82:83], 0x0\n" \
+    "  s_branch Lom_B%=\n" \
+    "Lovdm_B%=:\n" \
+    "  s_lshr_b32 s88, s56, 16\n" \
+    "  s_add_u32 s88, s88, s94\n" \
+    "  s_addc_u32 s89, s95, 0\n" \
+    "  s_setpc_b64 s[88:89]\n" \
+    "Ldone%=:\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_sub_u32 s91, s91, 1\n" \
+    "  s_cmp_eq_u32 s91, 0\n" \
+    "  s_cbranch_scc1 Lsw_done%=\n" \
+    "  s_add_u32 s41, %[n], %[ni]\n" \
+    "  v_mov_b32_e32 v0, v52\n" \
+    "  v_mov_b32_e32 v1, v53\n" \
+    "  v_mov_b32_e32 v2, v54\n" \
+    "  v_mov_b32_e32 v3, v55\n" \
+    "  v_mov_b32_e32 v4, v56\n" \
+    "  v_mov_b32_e32 v5, v57\n" \
+    "  v_mov_b32_e32 v6, v58\n" \
+    "  v_mov_b32_e32 v7, v59\n" \
+    "  s_cmp_le_u32 s41, 8\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v8, v60\n" \
+    "  v_mov_b32_e32 v9, v61\n" \
+    "  v_mov_b32_e32 v10, v62\n" \
+    "  v_mov_b32_e32 v11, v63\n" \
+    "  v_mov_b32_e32 v12, v64\n" \
+    "  v_mov_b32_e32 v13, v65\n" \
+    "  v_mov_b32_e32 v14, v66\n" \
+    "  v_mov_b32_e32 v15, v67\n" \
+    "  s_cmp_le_u32 s41, 16\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v16, v68\n" \
+    "  v_mov_b32_e32 v17, v69\n" \
+    "  v_mov_b32_e32 v18, v70\n" \
+    "  v_mov_b32_e32 v19, v71\n" \
+    "  v_mov_b32_e32 v20, v72\n" \
+    "  v_mov_b32_e32 v21, v73\n" \
+    "  v_mov_b32_e32 v22, v74\n" \
+    "  v_mov_b32_e32 v23, v75\n" \
+    "  s_cmp_le_u32 s41, 24\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v24, v76\n" \
+    "  v_mov_b32_e32 v25, v77\n" \
+    "  v_mov_b32_e32 v26, v78\n" \
+    "  v_mov_b32_e32 v27, v79\n" \
+    "  v_mov_b32_e32 v28, v80\n" \
+    "  v_mov_b32_e32 v29, v81\n" \
+    "  v_mov_b32_e32 v30, v82\n" \
+    "  v_mov_b32_e32 v31, v83\n" \
+    "  s_cmp_le_u32 s41, 32\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v32, v84\n" \
+    "  v_mov_b32_e32 v33, v85\n" \
+    "  v_mov_b32_e32 v34, v86\n" \
+    "  v_mov_b32_e32 v35, v87\n" \
+    "  v_mov_b32_e32 v36, v88\n" \
+    "  v_mov_b32_e32 v37, v89\n" \
+    "  v_mov_b32_e32 v38, v90\n" \
+    "  v_mov_b32_e32 v39, v91\n" \
+    "  s_cmp_le_u32 s41, 40\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v40, v92\n" \
+    "  v_mov_b32_e32 v41, v93\n" \
+    "  v_mov_b32_e32 v42, v94\n" \
+    "  v_mov_b32_e32 v43, v95\n" \
+    "  v_mov_b32_e32 v44, v96\n" \
+    "  v_mov_b32_e32 v45, v97\n" \
+    "  v_mov_b32_e32 v46, v98\n" \
+    "  v_mov_b32_e32 v47, v99\n" \
+    "  s_cmp_le_u32 s41, 48\n" \
+    "  s_cbranch_scc1 Lcp%=\n" \
+    "  v_mov_b32_e32 v48, v100\n" \
+    "  v_mov_b32_e32 v49, v101\n" \
+    "  v_mov_b32_e32 v50, v102\n" \
+    "  v_mov_b32_e32 v51, v103\n" \
+    "Lcp%=:\n" \
+    "  s_branch Lsw%=\n" \
+    "Lsw_done%=:\n" \
+    "  s_mov_b64 s[44:45], %[outs]\n" \
+    "  s_mov_b32 s40, 0\n" \
+    "  s_lshl_b32 s41, %[no], 2\n" \
+    "  v_mul_u32_u24_e32 v108, s41, %[lane]\n" \
+    "  v_add_u32_e32 v108, %[om0], v108\n" \
+    "Lout%=:\n" \
+    "  s_load_dwordx8 s[48:55], s[44:45], 0x0\n" \
+    "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v104, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v104 offset:0\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s49, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v105, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v105 offset:4\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s50, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v106, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v106 offset:8\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s51, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v107, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v107 offset:12\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v104, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v104 offset:16\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s53, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v105, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v105 offset:20\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s54, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v106, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v106 offset:24\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  s_set_gpr_idx_on s55, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v107, v52\n" \
+    "  s_set_gpr_idx_off\n" \
+    "  ds_write_b32 v108, v107 offset:28\n" \
+    "  s_add_u32 s40, s40, 1\n" \
+    "  s_cmp_ge_u32 s40, %[no]\n" \
+    "  s_cbranch_scc1 Lout_done%=\n" \
+    "  v_add_u32_e32 v108, 32, v108\n" \
+    "  s_add_u32 s44, s44, 32\n" \
+    "  s_addc_u32 s45, s45, 0\n" \
+    "  s_branch Lout%=\n" \
+    "Lout_done%=:\n" \
+    "  s_mov_b32 m0, s90\n"
+
+#define NEAT_CLOB_S1_52R \
+    "v0", "v1", "v2", "v3", "v4", "v5", "v6", "v7", "v8", "v9", "v10", "v11", \
+    "v12", "v13", "v14", "v15", "v16", "v17", "v18", "v19", "v20", "v21", "v22", "v23", \
+    "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33", "v34", "v35", \
+    "v36", "v37", "v38", "v39", "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", \
+    "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", \
+    "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", "v69", "v70", "v71", \
+    "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81", "v82", "v83", \
+    "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95", \
+    "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", \
+    "v108", "v109", "v110", "v111", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", \
+    "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", \
+    "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", \
+    "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", \
+    "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", \
+    "vcc", "scc"
+
+#define NEAT_SCRATCH_S1_52R 104
+

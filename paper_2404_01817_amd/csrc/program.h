@@ -16,7 +16,8 @@
 // hold slots 0..I-1; outputs are never freed.  That number decides the
 // genome's SLOT CLASS and where the two constant slots (0 and 1) sit:
 //   R64   <= 62 values: 64 register slots, constants at 62 and 63 (at 30 and
-//         31 for N_max <= 30, whose values all fit 32 slots);
+//         31 for N_max <= 30, whose values all fit 32 slots, at 50 and 51 for
+//         N_max <= 50);
 //   R128  <= 126 values: 128 register slots, constants at 126 and 127;
 //   R224  <= 222 values: 224 register slots, constants at 222 and 223;
 //   LDS   otherwise: N_max + 2 LDS rows, constants at N_max and N_max + 1.
@@ -67,9 +68,12 @@ __host__ __device__ constexpr int class_slots(int cls, int N) {
     return cls == CLS_R64 ? 64 : (cls == CLS_R128 ? 128 : (cls == CLS_R224 ? 224 : N + 2));
 }
 // slot of the constant 0 (the constant 1 is the next slot)
-constexpr int SMALL_ROWS = 30;  // N_max of the populations that fit 32 slots
+constexpr int SMALL_ROWS = 30;   // N_max of the populations that fit 32 slots
+constexpr int MEDIUM_ROWS = 50;  // and 52 slots
 __host__ __device__ constexpr int zero_slot(int cls, int N) {
-    return cls == CLS_R64 && N <= SMALL_ROWS ? SMALL_ROWS : class_slots(cls, N) - 2;
+    return cls == CLS_R64 && N <= SMALL_ROWS    ? SMALL_ROWS
+           : cls == CLS_R64 && N <= MEDIUM_ROWS ? MEDIUM_ROWS
+                                                : class_slots(cls, N) - 2;
 }
 
 // node record (16 words), record k describes position I + k:

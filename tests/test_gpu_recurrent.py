@@ -175,3 +175,38 @@ def test_recurrent_full_size_sampled():
     y64, beta = oracle.forward_recurrent(pop.nodes[sample], pop.conns[sample],
                                          pop.inputs[sample], pop.I, pop.O, K)
     stats = assert_parity(y[sample], y64, beta, "")
+
+
+# both sides of the rules for the register stores: 30 rows with more than 3072
+# tiles of 64 samples and more than 64 samples (32 slots, two samples per lane),
+# 50 rows (52 slots), 62; ragged tiles, no sweep and odd and even numbers of them
+@pytest.mark.parametrize("P,N,I,O,B,K", [(1600, 30, 5, 2, 65, 3), (1100, 30, 29, 1, 129, 2),
+                                         (1600, 31, 7, 3, 128, 0), (1100, 50, 17, 6, 191, 1),
+                                         (1600, 50, 49, 1, 127, 4), (1600, 51, 17, 6, 65, 3),
+                                         (1100, 62, 20, 6, 130, 2), (3200, 12, 3, 2, 64, 2)])
+def test_register_stores_by_rows(P, N, I, O, B, K):
+    print("case", P, N, I, O, B, K, flush=True)
+    import paper_2404_01817_amd as neat
+    rng = np.random.default_rng(P + N + B)
+    base = synth.make_population(rng, 20, N, 4 * N, I, O, N - I - O, synth._k_uniform(4 * N),
+                                 range(7), synth.ALL_AGGS, recurrent=True)
+    who = np.arange(P) % base.P
+    nodes, conns = base.nodes[who], base.conns[who]
+    x = rng.standard_normal((P, B, I), dtype=np.float32)
+
+    def run(n, c, x):
+        tn, tc = torch.from_numpy(n).cuda(), torch.from_numpy(c).cuda()
+        _, _, _, prog = neat.topo_sort(tn, tc, I, O, want_order=False, recurrent=True)
+        y = neat.forward_recurrent(neat.dims_of(tn, tc, I, O), prog, torch.from_numpy(x).cuda(),
+                                   B, K)
+        return y.cpu().numpy()
+
+    y = run(nodes, conns, x)
+    few = base.P
+    one = run(nodes[:few], conns[:few], x[:few])  # few tiles: one sample per lane
+    nan = np.isnan(one)
+    assert np.array_equal(nan, np.isnan(y[:few]))
+    assert np.array_equal(one[~nan].view(np.uint32), y[:few][~nan].view(np.uint32))
+    for part in (slice(0, few), slice(P - few, P)):
+        y64, beta = oracle.forward_recurrent(nodes[part], conns[part], x[part], I, O, K)
+        assert_parity(y[part], y64, beta, "P%d N%d B%d K%d" % (P, N, B, K))
