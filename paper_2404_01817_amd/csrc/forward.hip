@@ -103,12 +103,14 @@ using LdsStore = LdsStoreT<WAVE>;
         [outs] "s"(outs), [no] "s"(no), [om0] "s"(om0)
 // EXTRA: more operands (the recurrent block's sweep count), or nothing
 #define NEAT_NSW_OPERAND , [nsw] "s"(nsw)
+#define NEAT_OUT_OPERANDS , [outp] "s"(outp), [nb] "s"(nb)
 #define NEAT_TILE_FN(TILE, CLOB, EXTRA)                                                   \
     __device__ __forceinline__ static void tile(const int32_t *rec, const int32_t *edg,   \
                                                 int n, int zs, int ni, unsigned dm0,      \
                                                 int dn, int dvec, const float *dsrc,      \
                                                 unsigned lane, const int32_t *outs, int no, \
-                                                unsigned om0, int nsw) {                  \
+                                                unsigned om0, int nsw, float *outp,       \
+                                                int nb) {                                 \
         n = __builtin_amdgcn_readfirstlane(n);                                            \
         zs = __builtin_amdgcn_readfirstlane(zs);                                          \
         ni = __builtin_amdgcn_readfirstlane(ni);                                          \
@@ -118,49 +120,60 @@ using LdsStore = LdsStoreT<WAVE>;
         dn = __builtin_amdgcn_readfirstlane(dn);                                          \
         dvec = __builtin_amdgcn_readfirstlane(dvec);                                      \
         nsw = __builtin_amdgcn_readfirstlane(nsw);                                        \
+        nb = __builtin_amdgcn_readfirstlane(nb);                                          \
         asm volatile(TILE : : NEAT_TILE_OPERANDS EXTRA : CLOB, "memory");               \
     }
 
+// SPL: samples per lane.  DIRECT: the block stores its outputs from registers
+// (no LDS output area).
 template <int K>
 struct AsmTile;
 template <>
 struct AsmTile<KIND_R64> {
     static constexpr int SPL = 1;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S1_64, NEAT_CLOB_S1_64, )
 };
 template <>
 struct AsmTile<KIND_R64X2> {
     static constexpr int SPL = 2;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S2_64, NEAT_CLOB_S2_64, )
 };
 template <>
 struct AsmTile<KIND_R128> {
     static constexpr int SPL = 1;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S1_128, NEAT_CLOB_S1_128, )
 };
 template <>
 struct AsmTile<KIND_R224> {
     static constexpr int SPL = 1;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S1_224, NEAT_CLOB_S1_224, )
 };
 template <>
 struct AsmTile<KIND_R32X4> {
     static constexpr int SPL = 4;
-    NEAT_TILE_FN(NEAT_TILE_S4_32, NEAT_CLOB_S4_32, )
+    static constexpr bool DIRECT = true;
+    NEAT_TILE_FN(NEAT_TILE_S4_32, NEAT_CLOB_S4_32, NEAT_OUT_OPERANDS)
 };
 template <>
 struct AsmTile<KIND_R64REC> {
     static constexpr int SPL = 1;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S1_64R, NEAT_CLOB_S1_64R, NEAT_NSW_OPERAND)
 };
 template <>
 struct AsmTile<KIND_R32REC> {
     static constexpr int SPL = 2;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S2_32R, NEAT_CLOB_S2_32R, NEAT_NSW_OPERAND)
 };
 template <>
 struct AsmTile<KIND_R52REC> {
     static constexpr int SPL = 1;
+    static constexpr bool DIRECT = false;
     NEAT_TILE_FN(NEAT_TILE_S1_52R, NEAT_CLOB_S1_52R, NEAT_NSW_OPERAND)
 };
 
@@ -297,6 +310,18 @@ __device__ __forceinline__ void wait_dma() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Wait for this wave's DMA, issued before the last `later` memory operations
+// (a wave's loads and stores retire in order), without waiting for those.
+__device__ __forceinline__ void wait_dma_before(int later) {
+    if (later >= 8) __builtin_amdgcn_s_waitcnt(0x0F78);       // vmcnt(8)
+    else if (later >= 4) __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
+    else if (later >= 2) __builtin_amdgcn_s_waitcnt(0x0F72);  // vmcnt(2)
+    else if (later == 1) __builtin_amdgcn_s_waitcnt(0x0F71);  // vmcnt(1)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Grid-point coordinate -1 + 2 i / (side - 1).
 __device__ __forceinline__ float grid_coord(int i, int side) {
     return (float)(2 * i - (side - 1)) / (float)(side - 1);
@@ -381,6 +406,7 @@ template <int K, bool GRID>
 __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int t1, float *area,
                                                  int stage_floats) {
     constexpr int SPL = AsmTile<K>::SPL;
+    constexpr bool DIRECT = AsmTile<K>::DIRECT;
     constexpr int TS = WAVE * SPL;  // samples per tile
     const unsigned lane = threadIdx.x & (WAVE - 1);
     const int N = it->N, I = it->I, O = it->O, B = it->B, side = GRID ? it->side : 0;
@@ -464,10 +490,13 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
             if (x2_0 >= uside) x2_0 -= uside, ++y2_0;
             if (y2_0 >= uside) y2_0 -= uside, ++x1_0;
             while (x1_0 >= uside) x1_0 -= uside, ++y1_0;
+        } else if (DIRECT && t > t0) {
+            // the stores of the last tile follow this tile's DMA
+            wait_dma_before(SPL * ((O >> 2) + ((O >> 1) & 1) + (O & 1)));
         } else {
             wait_dma();
         }
-        if (t > t0) flush_outputs(ostage, out_g + (size_t)(t - 1) * TS * O, TS * O);
+        if (!DIRECT && t > t0) flush_outputs(ostage, out_g + (size_t)(t - 1) * TS * O, TS * O);
         int dn = 0, dvec = 0;
         const float *dsrc = in_g;
         if (!GRID && t + 1 < t1) {
@@ -477,8 +506,9 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
             dsrc = in_g + (size_t)(t + 1) * TS * I;
         }
         AsmTile<K>::tile(rec, edg, ncomp, zs, I, ibase, dn, dvec, dsrc, lane, outs, O, obase,
-                         it->sweeps);
+                         it->sweeps, out_g + (size_t)t * TS * O, min(TS, B - t * TS));
     }
+    if (DIRECT) return;
     flush_outputs(ostage, out_g + (size_t)(t1 - 1) * TS * O, (min(B, t1 * TS) - (t1 - 1) * TS) * O);
 }
 
@@ -1009,7 +1039,7 @@ constexpr int min_waves(int kind) {
            : (kind == KIND_R64X2 || kind == KIND_R32X4 || kind == KIND_R128 ||
               kind == KIND_R64REC || kind == KIND_R32REC)
                ? 3
-           : kind == KIND_R52REC                     ? 4
+           : kind == KIND_R52REC ? 4
            : kind == KIND_R224 || kind == KIND_ANY ? 2
                                                    : 1;
 }
@@ -1112,6 +1142,8 @@ int tile_samples(int kind) {
                                 : (kind == KIND_LDS32 ? WAVE / 2 : WAVE);
 }
 
+bool direct_kind(int kind) { return kind == KIND_R32X4; }
+
 bool lds_kind(int kind) { return kind == KIND_LDS || kind == KIND_LDS32; }
 
 // kernel of class c under a variant
@@ -1178,7 +1210,8 @@ static int recurrent_kind(const FwdJob &J) {
 // samples per SIMD as with two per lane and 64 slots: CPPN grid queries, P =
 // 1000, N = 30, 65536 queries: 508 us with two samples per lane and 64 slots,
 // 414 us with two and 32 slots (five waves per SIMD instead of three), 395 us
-// with four (the vector pipe 79 % busy).
+// with four (the vector pipe 79 % busy), 384 us with outputs stored straight
+// from registers.
 static bool four_samples(const FwdJob &J) {
     return J.N <= SMALL_ROWS && J.I + J.O <= 12 && J.B > 2 * WAVE &&
            (long long)J.P * ((J.B + 2 * WAVE - 1) / (2 * WAVE)) > 3072;
@@ -1302,7 +1335,9 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             // samples' offsets after the staged inputs
             if (!J.side || !lds_kind(kind))
                 stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE + TS : 0));
-            if (!lds_kind(kind)) ostage_max[x] = std::max(ostage_max[x], TS * J.O);
+            // outputs stored from registers leave only what touch_lines writes
+            if (!lds_kind(kind))
+                ostage_max[x] = std::max(ostage_max[x], direct_kind(kind) ? WAVE : TS * J.O);
             if (kind == KIND_ANY) {
                 // the values of a genome past the register classes, in the same area
                 const int rows = class_slots(top, J.N), sh = level_tile(rows, J.B, 0);
@@ -1342,7 +1377,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         // keep each item's own target: their short-B items are latency-bound
         // and gain from spreading tiles over waves (a launch-wide target made
         // the uneven batch's calculation up to 32 % slower).
-        const int shared_tpw = (kind == KIND_R64X2 || kind == KIND_R32X4) && K.items.size() > 1
+        const int shared_tpw = tile_samples(kind) > WAVE && K.items.size() > 1
                                    ? launch_tiles_per_wave(K.items) : 0;
         long long units = 0;
         for (FwdItem &it : K.items) {

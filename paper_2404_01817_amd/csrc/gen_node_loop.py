@@ -24,6 +24,7 @@ Variants (name: samples per lane, value slots, VGPRs of the value vectors):
           recurrent calculation, %[nsw] synchronous sweeps of the node loop
 and in node_loop_wide.h, for populations of few node rows:
   S4_32   4 samples, 32 slots,  v0..v31, v32..v63, v64..v95, v96..v127
+          (outputs stored straight from registers)
   S2_32R  2 samples, 32 slots, recurrent: v0..v63 read, v64..v127 written
   S1_52R  1 sample, 52 slots, recurrent: v0..v51 read, v52..v103 written
 Scratch VGPRs follow the value vectors.
@@ -46,11 +47,12 @@ VARIANTS = [
     ("S1_64R", 1, (0,), 128, (64,)),
 ]
 
-# the variants of node_loop_wide.h, and the input buffers per sample
+# the variants of node_loop_wide.h: also the input buffers per sample, and
+# whether the outputs go straight to memory
 VARIANTS_WIDE = [
-    ("S4_32", 4, (0, 32, 64, 96), 128, None, 4),
-    ("S2_32R", 2, (0, 32), 128, (64, 96), 4),
-    ("S1_52R", 1, (0,), 104, (52,), 4),
+    ("S4_32", 4, (0, 32, 64, 96), 128, None, 4, True),
+    ("S2_32R", 2, (0, 32), 128, (64, 96), 4, False),
+    ("S1_52R", 1, (0,), 104, (52,), 4, False),
 ]
 
 # scalar register map (shared by all variants)
@@ -110,6 +112,7 @@ class Regs:
     def __init__(self, spl, bases, scratch, wbases=None, group=8):
         self.spl = spl
         self.unit_response = False  # set while those blocks are generated
+        self.direct = False  # outputs straight to memory, not through LDS
         self.bases = ["v%d" % b for b in bases]
         # recurrent: reads from v[bases], writes to v[wbases]
         self.rec = wbases is not None
@@ -609,6 +612,68 @@ def write_outputs(R):
     return out
 
 
+def store_outputs(R):
+    """Output j of the lane's sample s -> memory, %[outp] + 4 (s O + j), for
+    the samples below %[nb]; slots from %[outs], O = %[no].  Four outputs of a
+    sample per store, then two and one: a lane's outputs are contiguous, and
+    the stores of a wave cover whole lines between them, so they are left to
+    the cache to combine (non-temporal ones are not: 17 inputs, 6 outputs and
+    1000 samples took 257 us that way, 203 us like this, 197 us through LDS)."""
+    out = ["s_mov_b64 s[46:47], exec",
+           "s_mov_b64 s[44:45], %[outs]",
+           "s_lshl_b32 s41, %[no], 2",
+           "v_mul_u32_u24_e32 %s, s41, %%[lane]" % R.addr[0]]
+    if R.spl > 1:
+        out += ["s_lshl_b32 s41, %[no], 8"]
+        out += ["v_add_u32_e32 %s, s41, %s" % (R.addr[h], R.addr[h - 1])
+                for h in range(1, R.spl)]
+    for h in range(R.spl):
+        out += ["s_sub_u32 s41, %%[nb], %d" % (64 * h),
+                "v_cmp_gt_i32_e64 s[%d:%d], s41, %%[lane]" % (56 + 2 * h, 57 + 2 * h)]
+
+    def put(k0, n):
+        """Outputs k0 .. k0 + n - 1 of the loaded slots."""
+        o = []
+        for k in range(k0, k0 + n):
+            o += ["s_set_gpr_idx_on s%d, gpr_idx(SRC0)" % (48 + k)]
+            o += ["v_mov_b32_e32 %s, %s" % (R.buf[h][k], R.bases[h]) for h in range(R.spl)]
+            o += ["s_set_gpr_idx_off"]
+        for h in range(R.spl):
+            b = int(R.buf[h][k0][1:])
+            data = "v%d" % b if n == 1 else "v[%d:%d]" % (b, b + n - 1)
+            o += ["s_mov_b64 exec, s[%d:%d]" % (56 + 2 * h, 57 + 2 * h),
+                  "global_store_dword%s %s, %s, %%[outp]%s"
+                  % ("x%d" % n if n > 1 else "", R.addr[h], data,
+                     " offset:%d" % (4 * k0) if k0 else "")]
+        return o + ["s_mov_b64 exec, s[46:47]"]
+
+    out += ["s_mov_b32 s41, %[no]",
+            "Lst%=:",
+            "s_load_dwordx4 s[48:51], s[44:45], 0x0",
+            "s_waitcnt lgkmcnt(0)",
+            "s_cmp_lt_u32 s41, 4",
+            "s_cbranch_scc1 Lst_part%="]
+    out += put(0, 4)
+    out += ["v_add_u32_e32 %s, 16, %s" % (R.addr[h], R.addr[h]) for h in range(R.spl)]
+    out += ["s_add_u32 s44, s44, 16",
+            "s_addc_u32 s45, s45, 0",
+            "s_sub_u32 s41, s41, 4",
+            "s_cmp_eq_u32 s41, 0",
+            "s_cbranch_scc1 Lst_done%=",
+            "s_branch Lst%=",
+            "Lst_part%=:",
+            "s_cmp_lt_u32 s41, 2",
+            "s_cbranch_scc1 Lst_one%="]
+    out += put(0, 2)
+    out += ["s_cmp_eq_u32 s41, 2",
+            "s_cbranch_scc1 Lst_done%="]
+    out += put(2, 1)
+    out += ["s_branch Lst_done%=",
+            "Lst_one%=:"]
+    out += put(0, 1)
+    return out + ["Lst_done%=:"]
+
+
 def vector_blocks(R, tag, line):
     """line(h, k) for every sample h and slot k below %[n] + %[ni] (rounded up
     to a block of eight): the slots that the genome's nodes hold.  s40, s41 are
@@ -677,7 +742,7 @@ def tile(R):
         return (["s_mov_b32 s90, m0"] + zero_values(R) + pl[:k] + clear_past_inputs(R)
                 + pl[k:] + dma_next(R) + sweeps(R) + write_outputs(R) + ["s_mov_b32 m0, s90"])
     return (["s_mov_b32 s90, m0"] + place_inputs(R) + dma_next(R) + node_loop(R)
-            + write_outputs(R) + ["s_mov_b32 m0, s90"])
+            + (store_outputs(R) if R.direct else write_outputs(R)) + ["s_mov_b32 m0, s90"])
 
 
 HEADER = """\
@@ -750,12 +815,15 @@ WIDE_HEADER = """\
 //
 // Tile blocks as in node_loop_asm.h (which describes them) for populations
 // of few node rows, with more samples per lane or fewer value registers.
+// NEAT_TILE_S4_32 stores its outputs straight from registers: output j of
+// sample s to %[outp] + 4 (s O + j) for the %[nb] samples of the tile.
 #pragma once
 """
 
 
-def variant_text(name, spl, bases, scratch, wbases, group=8):
+def variant_text(name, spl, bases, scratch, wbases, group=8, direct=False):
     R = Regs(spl, bases, scratch, wbases, group)
+    R.direct = direct
     body = tile(R)
     parts = ["// %s: %d sample(s) per lane, value vectors at %s, scratch v%d..v%d\n"
              % (name, spl, ", ".join("v%d" % b for b in bases), scratch, R.last)]

@@ -2,6 +2,8 @@
 //
 // Tile blocks as in node_loop_asm.h (which describes them) for populations
 // of few node rows, with more samples per lane or fewer value registers.
+// NEAT_TILE_S4_32 stores its outputs straight from registers: output j of
+// sample s to %[outp] + 4 (s O + j) for the %[nb] samples of the tile.
 #pragma once
 
 // S4_32: 4 sample(s) per lane, value vectors at v0, v32, v64, v96, scratch v128..v149
@@ -2354,130 +2356,130 @@
     "  s_setpc_b64 s[88:89]\n" \
     "Ldone%=:\n" \
     "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_mov_b64 s[46:47], exec\n" \
     "  s_mov_b64 s[44:45], %[outs]\n" \
-    "  s_mov_b32 s40, 0\n" \
     "  s_lshl_b32 s41, %[no], 2\n" \
     "  v_mul_u32_u24_e32 v144, s41, %[lane]\n" \
-    "  v_add_u32_e32 v144, %[om0], v144\n" \
     "  s_lshl_b32 s41, %[no], 8\n" \
     "  v_add_u32_e32 v145, s41, v144\n" \
     "  v_add_u32_e32 v146, s41, v145\n" \
     "  v_add_u32_e32 v147, s41, v146\n" \
-    "Lout%=:\n" \
-    "  s_load_dwordx8 s[48:55], s[44:45], 0x0\n" \
+    "  s_sub_u32 s41, %[nb], 0\n" \
+    "  v_cmp_gt_i32_e64 s[56:57], s41, %[lane]\n" \
+    "  s_sub_u32 s41, %[nb], 64\n" \
+    "  v_cmp_gt_i32_e64 s[58:59], s41, %[lane]\n" \
+    "  s_sub_u32 s41, %[nb], 128\n" \
+    "  v_cmp_gt_i32_e64 s[60:61], s41, %[lane]\n" \
+    "  s_sub_u32 s41, %[nb], 192\n" \
+    "  v_cmp_gt_i32_e64 s[62:63], s41, %[lane]\n" \
+    "  s_mov_b32 s41, %[no]\n" \
+    "Lst%=:\n" \
+    "  s_load_dwordx4 s[48:51], s[44:45], 0x0\n" \
     "  s_waitcnt lgkmcnt(0)\n" \
+    "  s_cmp_lt_u32 s41, 4\n" \
+    "  s_cbranch_scc1 Lst_part%=\n" \
     "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v128, v0\n" \
     "  v_mov_b32_e32 v132, v32\n" \
     "  v_mov_b32_e32 v136, v64\n" \
     "  v_mov_b32_e32 v140, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v128 offset:0\n" \
-    "  ds_write_b32 v145, v132 offset:0\n" \
-    "  ds_write_b32 v146, v136 offset:0\n" \
-    "  ds_write_b32 v147, v140 offset:0\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s49, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v129, v0\n" \
     "  v_mov_b32_e32 v133, v32\n" \
     "  v_mov_b32_e32 v137, v64\n" \
     "  v_mov_b32_e32 v141, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v129 offset:4\n" \
-    "  ds_write_b32 v145, v133 offset:4\n" \
-    "  ds_write_b32 v146, v137 offset:4\n" \
-    "  ds_write_b32 v147, v141 offset:4\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s50, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v130, v0\n" \
     "  v_mov_b32_e32 v134, v32\n" \
     "  v_mov_b32_e32 v138, v64\n" \
     "  v_mov_b32_e32 v142, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v130 offset:8\n" \
-    "  ds_write_b32 v145, v134 offset:8\n" \
-    "  ds_write_b32 v146, v138 offset:8\n" \
-    "  ds_write_b32 v147, v142 offset:8\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
     "  s_set_gpr_idx_on s51, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v131, v0\n" \
     "  v_mov_b32_e32 v135, v32\n" \
     "  v_mov_b32_e32 v139, v64\n" \
     "  v_mov_b32_e32 v143, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v131 offset:12\n" \
-    "  ds_write_b32 v145, v135 offset:12\n" \
-    "  ds_write_b32 v146, v139 offset:12\n" \
-    "  ds_write_b32 v147, v143 offset:12\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
-    "  s_set_gpr_idx_on s52, gpr_idx(SRC0)\n" \
+    "  s_mov_b64 exec, s[56:57]\n" \
+    "  global_store_dwordx4 v144, v[128:131], %[outp]\n" \
+    "  s_mov_b64 exec, s[58:59]\n" \
+    "  global_store_dwordx4 v145, v[132:135], %[outp]\n" \
+    "  s_mov_b64 exec, s[60:61]\n" \
+    "  global_store_dwordx4 v146, v[136:139], %[outp]\n" \
+    "  s_mov_b64 exec, s[62:63]\n" \
+    "  global_store_dwordx4 v147, v[140:143], %[outp]\n" \
+    "  s_mov_b64 exec, s[46:47]\n" \
+    "  v_add_u32_e32 v144, 16, v144\n" \
+    "  v_add_u32_e32 v145, 16, v145\n" \
+    "  v_add_u32_e32 v146, 16, v146\n" \
+    "  v_add_u32_e32 v147, 16, v147\n" \
+    "  s_add_u32 s44, s44, 16\n" \
+    "  s_addc_u32 s45, s45, 0\n" \
+    "  s_sub_u32 s41, s41, 4\n" \
+    "  s_cmp_eq_u32 s41, 0\n" \
+    "  s_cbranch_scc1 Lst_done%=\n" \
+    "  s_branch Lst%=\n" \
+    "Lst_part%=:\n" \
+    "  s_cmp_lt_u32 s41, 2\n" \
+    "  s_cbranch_scc1 Lst_one%=\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v128, v0\n" \
     "  v_mov_b32_e32 v132, v32\n" \
     "  v_mov_b32_e32 v136, v64\n" \
     "  v_mov_b32_e32 v140, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v128 offset:16\n" \
-    "  ds_write_b32 v145, v132 offset:16\n" \
-    "  ds_write_b32 v146, v136 offset:16\n" \
-    "  ds_write_b32 v147, v140 offset:16\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
-    "  s_set_gpr_idx_on s53, gpr_idx(SRC0)\n" \
+    "  s_set_gpr_idx_on s49, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v129, v0\n" \
     "  v_mov_b32_e32 v133, v32\n" \
     "  v_mov_b32_e32 v137, v64\n" \
     "  v_mov_b32_e32 v141, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v129 offset:20\n" \
-    "  ds_write_b32 v145, v133 offset:20\n" \
-    "  ds_write_b32 v146, v137 offset:20\n" \
-    "  ds_write_b32 v147, v141 offset:20\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
-    "  s_set_gpr_idx_on s54, gpr_idx(SRC0)\n" \
+    "  s_mov_b64 exec, s[56:57]\n" \
+    "  global_store_dwordx2 v144, v[128:129], %[outp]\n" \
+    "  s_mov_b64 exec, s[58:59]\n" \
+    "  global_store_dwordx2 v145, v[132:133], %[outp]\n" \
+    "  s_mov_b64 exec, s[60:61]\n" \
+    "  global_store_dwordx2 v146, v[136:137], %[outp]\n" \
+    "  s_mov_b64 exec, s[62:63]\n" \
+    "  global_store_dwordx2 v147, v[140:141], %[outp]\n" \
+    "  s_mov_b64 exec, s[46:47]\n" \
+    "  s_cmp_eq_u32 s41, 2\n" \
+    "  s_cbranch_scc1 Lst_done%=\n" \
+    "  s_set_gpr_idx_on s50, gpr_idx(SRC0)\n" \
     "  v_mov_b32_e32 v130, v0\n" \
     "  v_mov_b32_e32 v134, v32\n" \
     "  v_mov_b32_e32 v138, v64\n" \
     "  v_mov_b32_e32 v142, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v130 offset:24\n" \
-    "  ds_write_b32 v145, v134 offset:24\n" \
-    "  ds_write_b32 v146, v138 offset:24\n" \
-    "  ds_write_b32 v147, v142 offset:24\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
-    "  s_set_gpr_idx_on s55, gpr_idx(SRC0)\n" \
-    "  v_mov_b32_e32 v131, v0\n" \
-    "  v_mov_b32_e32 v135, v32\n" \
-    "  v_mov_b32_e32 v139, v64\n" \
-    "  v_mov_b32_e32 v143, v96\n" \
+    "  s_mov_b64 exec, s[56:57]\n" \
+    "  global_store_dword v144, v130, %[outp] offset:8\n" \
+    "  s_mov_b64 exec, s[58:59]\n" \
+    "  global_store_dword v145, v134, %[outp] offset:8\n" \
+    "  s_mov_b64 exec, s[60:61]\n" \
+    "  global_store_dword v146, v138, %[outp] offset:8\n" \
+    "  s_mov_b64 exec, s[62:63]\n" \
+    "  global_store_dword v147, v142, %[outp] offset:8\n" \
+    "  s_mov_b64 exec, s[46:47]\n" \
+    "  s_branch Lst_done%=\n" \
+    "Lst_one%=:\n" \
+    "  s_set_gpr_idx_on s48, gpr_idx(SRC0)\n" \
+    "  v_mov_b32_e32 v128, v0\n" \
+    "  v_mov_b32_e32 v132, v32\n" \
+    "  v_mov_b32_e32 v136, v64\n" \
+    "  v_mov_b32_e32 v140, v96\n" \
     "  s_set_gpr_idx_off\n" \
-    "  ds_write_b32 v144, v131 offset:28\n" \
-    "  ds_write_b32 v145, v135 offset:28\n" \
-    "  ds_write_b32 v146, v139 offset:28\n" \
-    "  ds_write_b32 v147, v143 offset:28\n" \
-    "  s_add_u32 s40, s40, 1\n" \
-    "  s_cmp_ge_u32 s40, %[no]\n" \
-    "  s_cbranch_scc1 Lout_done%=\n" \
-    "  v_add_u32_e32 v144, 32, v144\n" \
-    "  v_add_u32_e32 v145, 32, v145\n" \
-    "  v_add_u32_e32 v146, 32, v146\n" \
-    "  v_add_u32_e32 v147, 32, v147\n" \
-    "  s_add_u32 s44, s44, 32\n" \
-    "  s_addc_u32 s45, s45, 0\n" \
-    "  s_branch Lout%=\n" \
-    "Lout_done%=:\n" \
+    "  s_mov_b64 exec, s[56:57]\n" \
+    "  global_store_dword v144, v128, %[outp]\n" \
+    "  s_mov_b64 exec, s[58:59]\n" \
+    "  global_store_dword v145, v132, %[outp]\n" \
+    "  s_mov_b64 exec, s[60:61]\n" \
+    "  global_store_dword v146, v136, %[outp]\n" \
+    "  s_mov_b64 exec, s[62:63]\n" \
+    "  global_store_dword v147, v140, %[outp]\n" \
+    "  s_mov_b64 exec, s[46:47]\n" \
+    "Lst_done%=:\n" \
     "  s_mov_b32 m0, s90\n"
 
 #define NEAT_CLOB_S4_32 \
