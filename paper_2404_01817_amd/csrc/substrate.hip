@@ -9,13 +9,27 @@
 // input planes X [B][S] to Y[g] = tanh(X W'[g]) [B][S].
 //
 // Y[g] = X W'[g] is a dense contraction (M = B, N = K = S), so it runs on
-// the matrix cores: v_mfma_f32_16x16x4_f32, fp32 in and fp32 accumulation
+// the matrix cores: v_mfma_f32_32x32x2_f32, fp32 in and fp32 accumulation
 // (the precision of the rest of the path).  A workgroup of four waves owns
-// a 64 x 64 tile of one genome's Y; K advances in chunks of 32 staged in
-// LDS (the threshold is applied as W enters LDS); each wave owns a 32 x 32
-// quarter, four 16 x 16 MFMA blocks.  Operand layout of the 16x16x4 MFMA:
-// lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives
-// D[4 (l / 16) + r][l % 16] in its r-th accumulator register.
+// a 128 x 64 tile of one genome's Y (64 x 64 for up to 64 input planes); K
+// advances in chunks of 32 staged in LDS (the threshold is applied as W
+// enters LDS); each wave owns a 64 x 32 quarter, two 32 x 32 MFMA blocks.
+// Operand layout of the 32x32x2 MFMA: lane l supplies A[l % 32][l / 32] and
+// B[l / 32][l % 32] and receives D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] in
+// its r-th accumulator register.
+//
+// Both tiles lie in LDS with k contiguous (W transposed as it is stored), and
+// lane half l / 32 takes k = 4 (l / 32) .. + 3 of every 8 for both operands,
+// one of them per MFMA: any pairing of k serves, and a fragment of four MFMAs
+// is one 16-byte read.
+//
+// What bounds it: the matrix cores.  P = 500, S = B = 256 (16.8 GFLOP): 153 us
+// (110 TFLOP/s); the MFMAs alone, without loads or stores, take 120 us in this
+// launch.  16x16x4 blocks with 4-byte LDS reads took 165 us (LDS busy two
+// thirds of the time; 16-byte reads halve that), 32x32x2 blocks 158 us, two of
+// them per wave 153 us, four 168 us; the next chunk's loads issued ahead of
+// the MFMAs 162 us (their registers cost waves); plain instead of
+// non-temporal stores no difference.
 #include <hip/hip_runtime.h>
 
 #include "act.h"
@@ -24,90 +38,109 @@
 namespace neat {
 namespace {
 
-constexpr int ST_M = 64, ST_N = 64, ST_KC = 32;
-constexpr int XS_LD = ST_KC + 1;  // padded LDS row strides
-constexpr int WS_LD = ST_N + 4;
+constexpr int ST_N = 64, ST_KC = 32;
+// LDS row stride: 16-byte aligned, and the rows of eight lanes that a 16-byte
+// access serves together start four banks apart
+constexpr int ST_LD = ST_KC + 4;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// MT: 32-row blocks of a wave (a workgroup's tile has 64 MT rows)
+template <int MT>
 __global__ __launch_bounds__(256) void substrate_kernel(SubLaunch L) {
-    __shared__ float xs[ST_M * XS_LD];
-    __shared__ float ws[ST_KC * WS_LD];
+    constexpr int ST_M = 64 * MT;
+    __shared__ __align__(16) float xs[ST_M * ST_LD];  // X tile [m][k]
+    __shared__ __align__(16) float ws[ST_N * ST_LD];  // W' tile [n][k]
     const int S = L.S, B = L.B;
     const int tiles_m = (B + ST_M - 1) / ST_M, tiles_n = S / ST_N;
-    const long long blk = blockIdx.x;
+    // workgroups are dealt to the 8 XCDs round robin; a genome's go to one, so
+    // that its weights are fetched into one L2
+    const unsigned bx = blockIdx.x & 7u, per = gridDim.x >> 3, rem = gridDim.x & 7u;
+    const long long blk = (long long)(bx * per + min(bx, rem) + (blockIdx.x >> 3));
     const int tn = (int)(blk % tiles_n);
     const long long rest = blk / tiles_n;
     const int tm = (int)(rest % tiles_m);
     const long long g = rest / tiles_m;
     const int m0 = tm * ST_M, n0 = tn * ST_N;
     const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = 32 * (wave >> 1), wn = 32 * (wave & 1);
+    const int wm = 32 * MT * (wave >> 1), wn = 32 * (wave & 1);
     const float *Wg = L.W + (size_t)g * S * S;
     const float theta = L.theta;
 
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x16 acc[MT] = {};
 
-    // staging assignment: X rows r = t / 4, columns 8 (t % 4) ..; W rows
-    // k = t / 8, columns 8 (t % 8) ..
+    // staging assignment: X row t / 4, columns 8 (t % 4) ..; W column t % 64,
+    // rows 4 (t / 64) .. and 16 further
     const int xr = t >> 2, xc = 8 * (t & 3);
-    const int wr = t >> 3, wc = 8 * (t & 7);
-    const bool xrow_ok = m0 + xr < B;
+    const int wk = 4 * wave;
+    const int li = lane & 31, lk = lane >> 5;
     for (int k0 = 0; k0 < S; k0 += ST_KC) {
-        f32x4 xa = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, xb = xa;
-        if (xrow_ok) {
-            const f32x4 *src = (const f32x4 *)(L.X + (size_t)(m0 + xr) * S + k0 + xc);
-            xa = src[0];
-            xb = src[1];
-        }
-        const f32x4 *wsrc = (const f32x4 *)(Wg + (size_t)(k0 + wr) * S + n0 + wc);
-        f32x4 wa = wsrc[0], wb = wsrc[1];
+        f32x4 x[MT][2] = {};
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+            if (m0 + 64 * i + xr < B) {
+                const f32x4 *src = (const f32x4 *)(L.X + (size_t)(m0 + 64 * i + xr) * S + k0 + xc);
+                x[i][0] = src[0];
+                x[i][1] = src[1];
+            }
+        f32x4 w[2];
+        const float *wsrc = Wg + (size_t)(k0 + wk) * S + n0 + lane;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[h][q] = wsrc[(size_t)(16 * h + q) * S];
         __syncthreads();  // the previous chunk's reads are done
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            xs[xr * XS_LD + xc + q] = xa[q];
-            xs[xr * XS_LD + xc + 4 + q] = xb[q];
+        for (int i = 0; i < MT; ++i) {
+            *(f32x4 *)(xs + (64 * i + xr) * ST_LD + xc) = x[i][0];
+            *(f32x4 *)(xs + (64 * i + xr) * ST_LD + xc + 4) = x[i][1];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
             // expression threshold: |w| < theta -> 0 (NaN is kept)
-            ws[wr * WS_LD + wc + q] = fabsf(wa[q]) < theta ? 0.0f : wa[q];
-            ws[wr * WS_LD + wc + 4 + q] = fabsf(wb[q]) < theta ? 0.0f : wb[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[h][q] = fabsf(w[h][q]) < theta ? 0.0f : w[h][q];
+            *(f32x4 *)(ws + lane * ST_LD + wk + 16 * h) = w[h];
         }
         __syncthreads();
-        const int li = lane & 15, lk = lane >> 4;
 #pragma unroll
-        for (int kk = 0; kk < ST_KC; kk += 4) {
-            const float a0 = xs[(wm + li) * XS_LD + kk + lk];
-            const float a1 = xs[(wm + 16 + li) * XS_LD + kk + lk];
-            const float b0 = ws[(kk + lk) * WS_LD + wn + li];
-            const float b1 = ws[(kk + lk) * WS_LD + wn + 16 + li];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
+        for (int kk = 0; kk < ST_KC; kk += 8) {
+            f32x4 a[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                a[i] = *(const f32x4 *)(xs + (wm + 32 * i + li) * ST_LD + kk + 4 * lk);
+            const f32x4 b = *(const f32x4 *)(ws + (wn + li) * ST_LD + kk + 4 * lk);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q], b[q], acc[i], 0, 0, 0);
         }
     }
     float *Yg = L.Y + (size_t)g * B * S;
+    const int n = n0 + wn + li;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-                const int n = n0 + wn + 16 * j + (lane & 15);
-                if (m < B) __builtin_nontemporal_store(act_tanh(acc[i][j][r]), Yg + (size_t)m * S + n);
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * lk + (r & 3);
+            if (m < B) __builtin_nontemporal_store(act_tanh(acc[i][r]), Yg + (size_t)m * S + n);
+        }
 }
 
 }  // namespace
 
 hipError_t substrate_launch(const SubLaunch &L, hipStream_t stream) {
-    const long long blocks = (long long)L.P * ((L.B + ST_M - 1) / ST_M) * (L.S / ST_N);
+    // two blocks of rows per wave halve the staging of W per product, but a
+    // call of up to 64 planes would leave the second one empty
+    const int mt = L.B > 64 ? 2 : 1;
+    const long long blocks = (long long)L.P * ((L.B + 64 * mt - 1) / (64 * mt)) * (L.S / ST_N);
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(substrate_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, L);
+    if (mt == 2)
+        hipLaunchKernelGGL(substrate_kernel<2>, dim3((unsigned)blocks), dim3(256), 0, stream, L);
+    else
+        hipLaunchKernelGGL(substrate_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream, L);
     return hipGetLastError();
 }
 

@@ -122,3 +122,24 @@ def test_substrate_full_size_sampled():
                              [0, pop.P - 1]])
     Y64, bound = substrate.forward(pop.nodes[sample], pop.conns[sample], 16, X)
     stats = assert_parity(y[sample], Y64, bound, "")
+
+
+@pytest.mark.parametrize("side,B", [(8, 63), (8, 65), (16, 64), (16, 127), (24, 129), (8, 257)])
+def test_layer_row_tiles(side, B):
+    """Input planes on both sides of a workgroup's 64 and 128 rows, against
+    the contraction in 64 bits of the weights that the call returns."""
+    import paper_2404_01817_amd as neat
+    print("case side=%d B=%d" % (side, B), flush=True)
+    pop = synth.cppn(seed=side + B, P=5)
+    tn, tc = torch.from_numpy(pop.nodes).cuda(), torch.from_numpy(pop.conns).cuda()
+    _, _, _, prog = neat.topo_sort(tn, tc, pop.I, pop.O, want_order=False)
+    S = side * side
+    x = torch.from_numpy(np.random.default_rng(B).uniform(-1, 1, (B, S)).astype(np.float32)).cuda()
+    y, w = neat.substrate_forward(neat.dims_of(tn, tc, pop.I, pop.O), prog, side, x, 0.2)
+    w64 = torch.where(w.abs() < 0.2, torch.zeros_like(w), w).double().view(-1, S, S)
+    for g in range(pop.P):
+        z = x.double() @ w64[g]
+        # a sum of S products in fp32, then tanh (slope at most 1)
+        u = 2.0 ** -24
+        bound = S * u / (1 - S * u) * (x.double().abs() @ w64[g].abs()) + 1e-6
+        assert ((y[g].double() - torch.tanh(z)).abs() <= bound).all()
