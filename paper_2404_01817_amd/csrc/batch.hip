@@ -146,7 +146,8 @@ struct HostPlan {
     int launches() const { return (int)topo.size() + (n_topo ? 1 : 0) + (int)fw.size(); }
 };
 
-int plan_host(const neat_batch_item *items, int32_t n, HostPlan &hp) {
+// in_order: the launches will follow one another on one stream.
+int plan_host(const neat_batch_item *items, int32_t n, bool in_order, HostPlan &hp) {
     // transformations bucketed by workgroup size (64 x (b + 1) threads): each
     // genome runs with the waves its N_max needs, and a launch reserves the
     // LDS of its own genomes only
@@ -192,9 +193,13 @@ int plan_host(const neat_batch_item *items, int32_t n, HostPlan &hp) {
             neat::tuned_variant(it.dims.N_max, it.dims.C_max, it.B, it.grid_side > 0, 1));
     }
     // every item with the variant tuned for its bucket's throughput (the
-    // batch fills the GPU; FWD_AUTO while none is), one launch per kernel
-    // kind over all of them
-    for (size_t j = 0; j < jobs.size(); ++j) jobs[j].variant = job_variant[j];
+    // batch fills the GPU), or the one its sizes suggest while none is; one
+    // launch per kernel kind over all of them
+    for (size_t j = 0; j < jobs.size(); ++j) {
+        jobs[j].variant = job_variant[j];
+        if (jobs.size() > 1 && jobs[j].variant == neat::FWD_AUTO)
+            jobs[j].variant = neat::shared_variant(jobs[j], in_order, max_lds_bytes());
+    }
     if (!jobs.empty()) {
         char err[256] = "";
         const int rc = neat::forward_plan(jobs.data(), (int)jobs.size(), neat::FWD_AUTO,
@@ -243,7 +248,7 @@ int build(const neat_batch_item *items, int32_t n, neat_batch_plan **out) {
     (void)hipGetDevice(&p->device);
     p->tune_gen = neat::tune_generation();
     HostPlan hp;
-    int rc = plan_host(items, n, hp);
+    int rc = plan_host(items, n, false, hp);
     if (rc != NEAT_OK) {
         destroy(p);
         return rc;
@@ -441,7 +446,7 @@ int neat_forward_batch_noalloc(const neat_batch_item *items, int32_t n, void *st
     int rc = scratch_ptr(dev, &base);
     if (rc != NEAT_OK) return rc;
     HostPlan hp;
-    rc = plan_host(items, n, hp);
+    rc = plan_host(items, n, true, hp);
     if (rc != NEAT_OK) return rc;
     const size_t topo_bytes = hp.topo_host.size() * sizeof(neat::TopoItem);
     const size_t fw_bytes = hp.fw_host.size() * sizeof(neat::FwdItem);

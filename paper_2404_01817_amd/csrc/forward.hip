@@ -1217,15 +1217,36 @@ static bool four_samples(const FwdJob &J) {
            (long long)J.P * ((J.B + 2 * WAVE - 1) / (2 * WAVE)) > 3072;
 }
 
+// Whether a job can leave the launches per class: more than one class, and
+// nothing that those would refuse (it stays refused).
+static bool classes_may_merge(const FwdJob &J, size_t max_lds) {
+    const int top = max_class(J.N);
+    if (J.side || J.recurrent || top == CLS_R64) return false;
+    const size_t stage = sizeof(float) * (size_t)(2 * WAVE) * (J.I + J.O);
+    const size_t lds32 = sizeof(float) * (size_t)(WAVE / 2) * (J.I + class_slots(top, J.N));
+    return stage <= max_lds && (top != CLS_LDS || lds32 <= max_lds);
+}
+
+int shared_variant(const FwdJob &J, bool in_order, size_t max_lds) {
+    if (!classes_may_merge(J, max_lds)) return FWD_AUTO;
+    // The GPU is full, so only total work counts: the level mapping where a
+    // 64-sample tile would be three quarters empty and the nodes many, and one
+    // launch for every class where the launches per class spend most of
+    // their time at two waves per SIMD.  Seven batches of 6 to 24 populations
+    // (N up to 120 .. 400, B up to 16 .. 512), launches per class / this, us:
+    // as parallel branches 537 / 461, 264 / 222, 196 / 201, 129 / 127, 147 /
+    // 147, 203 / 206, 177 / 162 (one launch from 251 rows on: 461, 222, 219 ..;
+    // from 223 on: 500, 222, 187 ..); one after another, where every launch
+    // also ends in its own tail, 804 / 660, 378 / 302, 286 / 216, 187 / 168,
+    // 162 / 162, 311 / 246, 275 / 236.
+    if (J.N > 222 && J.B <= 16) return FWD_LVL;
+    return J.N > (in_order ? 126 : 300) ? FWD_ANY : FWD_AUTO;
+}
+
 // The mapping of a call's only population of more than 62 node rows where
 // the caller left it open (FWD_AUTO, or registers of either kind).
 static int resolve_variant(const FwdJob &J, int variant, int n_jobs, size_t max_lds) {
-    const int top = max_class(J.N);
-    if (n_jobs != 1 || J.side || J.recurrent || top == CLS_R64) return variant;
-    // a call that the launches per class refuse stays refused
-    const size_t stage = sizeof(float) * (size_t)(2 * WAVE) * (J.I + J.O);
-    const size_t lds32 = sizeof(float) * (size_t)(WAVE / 2) * (J.I + class_slots(top, J.N));
-    if (stage > max_lds || (top == CLS_LDS && lds32 > max_lds)) return variant;
+    if (n_jobs != 1 || !classes_may_merge(J, max_lds)) return variant;
     const long long units = (long long)J.P * ((J.B + WAVE - 1) / WAVE);
     if (variant == FWD_AUTO) {
         // Few samples: the level mapping, whose lanes share a genome's nodes,

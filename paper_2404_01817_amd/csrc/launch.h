@@ -135,6 +135,10 @@ const char *kind_name(int kind);
 // NEAT_OK or an error code with a message in err.
 int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
                  std::vector<FwdKernelLaunch> &out, char *err, size_t errlen);
+// The variant of one of several jobs that share the GPU, where none is tuned
+// for its bucket: in_order when the plan's launches follow one another on a
+// stream instead of running side by side.
+int shared_variant(const FwdJob &job, bool in_order, size_t max_lds);
 // Launch one planned kernel.  dev_items: the launch's items in device memory
 // (may be nullptr when the launch has a single item, passed inline).
 hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hipStream_t stream,

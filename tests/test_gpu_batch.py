@@ -208,3 +208,37 @@ def test_items_of_the_two_samples_kernel_share_the_wave_target():
                                    p.pop.I, p.pop.O)
         assert_parity(y[pick], y64, beta, "item %d" % k)
     plan.free()
+
+
+# populations on both sides of the rules for several at once: the level mapping
+# past 222 rows up to 16 inputs, one launch for every class past 300 rows (126
+# when the launches follow one another), and the launches per class
+@pytest.mark.parametrize("no_alloc", [False, True], ids=["graph", "in order"])
+def test_mappings_of_shared_populations(no_alloc):
+    import paper_2404_01817_amd as neat
+    rng = np.random.default_rng(5)
+    items, outs, refs, keep = [], [], [], []
+    for P, N, B in [(30, 126, 70), (30, 127, 70), (30, 222, 16), (30, 223, 16), (30, 223, 17),
+                    (30, 300, 130), (30, 301, 130), (700, 301, 200), (40, 50, 300)]:
+        pop = synth.uneven_population(rng, (20, 20), (N, N), (1, 1), with_inputs=False)
+        who = np.arange(P) % pop.P
+        tn, tc = torch.from_numpy(pop.nodes[who]).cuda(), torch.from_numpy(pop.conns[who]).cuda()
+        x = torch.from_numpy(rng.standard_normal((P, B, pop.I), dtype=np.float32)).cuda()
+        d = neat.dims_of(tn, tc, pop.I, pop.O)
+        _, _, _, prog = neat.topo_sort(tn, tc, pop.I, pop.O, want_order=False)
+        refs.append(neat.forward(d, prog, x, B, variant=neat.FWD_LDS))
+        outs.append(torch.empty_like(refs[-1]))
+        own = torch.empty_like(prog)  # written by the batch's transformation
+        items.append(neat.batch_item(d, own, outs[-1], inputs=x, B=B, nodes=tn, conns=tc))
+        keep.append((tn, tc, x, own))  # items hold addresses only
+    plan = neat.BatchPlan()
+    for _ in range(3):
+        for y in outs:
+            y.fill_(7.0)
+        neat.forward_batch_noalloc(items) if no_alloc else plan.run(items)
+        torch.cuda.synchronize()
+        for y, r in zip(outs, refs):
+            assert torch.equal(y.isnan(), r.isnan())
+            assert torch.equal(y.nan_to_num(0.0).view(torch.int32),
+                               r.nan_to_num(0.0).view(torch.int32))
+    del keep
