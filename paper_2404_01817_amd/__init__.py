@@ -425,14 +425,19 @@ class Server:
 
     def wait(self, ticket: int, timeout_s: float = 60.0):
         import time
+        res = Result()
+        slot = ctypes.byref(res)
+        fn = lib().neat_wait
+        if check(fn(self._h, ticket, 0, slot)) == 0:
+            return res
         t_end = time.monotonic() + timeout_s
         while True:
-            r = self.poll(ticket)
-            if r is not None:
-                return r
+            # blocks without the interpreter lock, in slices that let signals in
+            left = t_end - time.monotonic()
+            if check(fn(self._h, ticket, int(1e6 * min(max(left, 0.0), 0.05)), slot)) == 0:
+                return res
             if time.monotonic() > t_end:
                 raise TimeoutError("ticket %d not done after %.1fs" % (ticket, timeout_s))
-            time.sleep(20e-6)
 
     def stats(self) -> Stats:
         st = Stats()

@@ -113,6 +113,7 @@ SIGNATURES = {
     "neat_submit_many": (_i32, [_vp, ctypes.POINTER(Request), _i32,
                                 ctypes.POINTER(ctypes.c_uint64)]),
     "neat_poll": (_i32, [_vp, ctypes.c_uint64, ctypes.POINTER(Result)]),
+    "neat_wait": (_i32, [_vp, ctypes.c_uint64, _i64, ctypes.POINTER(Result)]),
     "neat_server_stats": (_i32, [_vp, ctypes.POINTER(Stats)]),
     "neat_server_reset_stats": (_i32, [_vp]),
     "neat_last_error": (ctypes.c_char_p, []),

@@ -103,6 +103,7 @@ class Scheduler {
             }
         }
         cv_.notify_all();
+        done_cv_.notify_all();
         if (worker_.joinable()) worker_.join();
     }
 
@@ -159,6 +160,31 @@ class Scheduler {
     // NEAT_E_UNKNOWN_TICKET.  Never blocks on the device.
     int poll(uint64_t ticket, Result *res) {
         std::lock_guard<std::mutex> lk(m_);
+        auto it = reqs_.find(ticket);
+        if (it == reqs_.end()) return NEAT_E_UNKNOWN_TICKET;
+        if (it->second.state != DONE) return NEAT_PENDING;
+        if (res) *res = it->second.res;
+        reqs_.erase(it);
+        return NEAT_OK;
+    }
+
+    // As poll, after sleeping until the request is done or timeout_us passed:
+    // a client that polls with sleeps of its own wakes tens of microseconds
+    // late for every result.
+    int wait(uint64_t ticket, int64_t timeout_us, Result *res) {
+        std::unique_lock<std::mutex> lk(m_);
+        auto pending = [&] {
+            auto it = reqs_.find(ticket);
+            return it != reqs_.end() && it->second.state != DONE;
+        };
+        if (timeout_us > 0 && pending()) {
+            // (a system-clock deadline, as in loop)
+            const auto until =
+                std::chrono::system_clock::now() + std::chrono::microseconds(timeout_us);
+            waiters_++;
+            done_cv_.wait_until(lk, until, [&] { return !pending(); });
+            waiters_--;
+        }
         auto it = reqs_.find(ticket);
         if (it == reqs_.end()) return NEAT_E_UNKNOWN_TICKET;
         if (it->second.state != DONE) return NEAT_PENDING;
@@ -244,6 +270,7 @@ class Scheduler {
         sl.tickets.clear();
         sl.bytes = sl.genome_inputs = 0;
         sl.busy = false;
+        if (waiters_ > 0) done_cv_.notify_all();
     }
 
     // Caller holds the lock.  Nothing queued and no slot busy: the worker is
@@ -399,7 +426,9 @@ class Scheduler {
     std::vector<Slot> slots_;
     const std::chrono::steady_clock::time_point t0_;
     std::mutex m_;
-    std::condition_variable cv_;
+    std::condition_variable cv_;       // the worker: something to admit or to poll
+    std::condition_variable done_cv_;  // waiters: requests ended
+    int waiters_ = 0;
     bool stop_ = false;
     std::unordered_map<uint64_t, Req> reqs_;
     std::deque<uint64_t> queue_;

@@ -319,10 +319,7 @@ int neat_submit_many(neat_server *s, const neat_request *reqs, int32_t n, uint64
     return NEAT_OK;
 }
 
-int neat_poll(neat_server *s, uint64_t ticket, neat_result *res) {
-    if (!s) return fail(NEAT_E_INVALID, "server is NULL");
-    neat::sched::Result r;
-    const int rc = s->sched->poll(ticket, &r);
+static int report(int rc, uint64_t ticket, const neat::sched::Result &r, neat_result *res) {
     if (rc == NEAT_E_UNKNOWN_TICKET)
         return fail(rc, "unknown ticket %llu", (unsigned long long)ticket);
     if (rc == NEAT_OK && res) {
@@ -333,6 +330,20 @@ int neat_poll(neat_server *s, uint64_t ticket, neat_result *res) {
         res->t_done_ns = r.t_done_ns;
     }
     return rc;
+}
+
+int neat_poll(neat_server *s, uint64_t ticket, neat_result *res) {
+    if (!s) return fail(NEAT_E_INVALID, "server is NULL");
+    neat::sched::Result r;
+    const int rc = s->sched->poll(ticket, &r);
+    return report(rc, ticket, r, res);
+}
+
+int neat_wait(neat_server *s, uint64_t ticket, int64_t timeout_us, neat_result *res) {
+    if (!s) return fail(NEAT_E_INVALID, "server is NULL");
+    neat::sched::Result r;
+    const int rc = s->sched->wait(ticket, timeout_us, &r);
+    return report(rc, ticket, r, res);
 }
 
 int neat_server_stats(neat_server *s, neat_stats *st) {

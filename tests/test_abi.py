@@ -124,3 +124,8 @@ def test_invalid_dims_are_refused_before_any_access():
         assert field in lib.neat_last_error().decode(), (dims, lib.neat_last_error())
         rc = lib.neat_forward(ctypes.byref(d), p, p, 0, 1, p, None)
         assert rc == -1, dims
+
+
+def test_wait_refuses_a_null_server():
+    import paper_2404_01817_amd._lib as binding
+    assert binding.lib().neat_wait(None, 1, 1000, None) == -1

@@ -239,3 +239,45 @@ def test_poll_unknown_ticket_and_shutdown():
     server.close()  # queued requests are cancelled, running ones finish
     torch.cuda.synchronize()
     assert keep
+
+
+def test_wait_blocks_until_done_and_times_out():
+    """Server.wait from several threads at once, a deadline that passes while
+    the request runs (its result is still there afterwards), and a ticket that
+    was already reported."""
+    import threading
+
+    import paper_2404_01817_amd as neat
+    pop = synth.control(seed=3, P=4000, B=1)
+    tn, tc = torch.from_numpy(pop.nodes).cuda(), torch.from_numpy(pop.conns).cuda()
+    B = 1000
+    x = torch.randn((pop.P, B, pop.I), device="cuda")
+    d = neat.dims_of(tn, tc, pop.I, pop.O)
+    _, _, _, prog = neat.topo_sort(tn, tc, pop.I, pop.O, want_order=False)
+    ref = neat.forward(d, prog, x, B)
+    outs = [torch.full_like(ref, 7.0) for _ in range(6)]
+    torch.cuda.synchronize()
+    srv = neat.Server(cap_bytes=32 << 30, max_inflight=2)
+    pid = srv.register(tn, tc, pop.I, pop.O)
+    reqs = [srv.request(pid, y, inputs=x, B=B, I=pop.I, tag=k) for k, y in enumerate(outs)]
+    tickets = srv.submit_many(reqs)
+    with pytest.raises(TimeoutError):
+        srv.wait(tickets[-1], timeout_s=0.0)
+    tags = []
+
+    def client(t):
+        tags.append(srv.wait(t, timeout_s=30.0).tag)
+
+    threads = [threading.Thread(target=client, args=(t,)) for t in tickets]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert sorted(tags) == list(range(6))
+    for y in outs:
+        assert torch.equal(y.isnan(), ref.isnan()) and torch.equal(y.nan_to_num(0.0),
+                                                                   ref.nan_to_num(0.0))
+    with pytest.raises(neat.NeatError) as e:
+        srv.wait(tickets[0])
+    assert e.value.code == -5  # NEAT_E_UNKNOWN_TICKET
+    srv.close()
