@@ -260,3 +260,53 @@ def test_edits_fill_and_overflow():
     assert np.array_equal(ga, oa) and np.array_equal(_bits(gn), _bits(on))
     assert np.all(~np.isnan(gn[[1, 4], :, 0]))
     assert np.array_equal(_bits(gn[[0, 2, 3, 5]]), _bits(pop.nodes[[0, 2, 3, 5]]))
+
+
+# windows and shares of the positions: fewer edits than a window, many more than
+# one per genome, all of them in few genomes (the window misses the run), rows
+# past one chunk of 64 and past the chunks in registers
+@pytest.mark.parametrize("P,N,C,n,skew", [(50, 20, 30, 40, 0), (3, 64, 256, 2000, 0),
+                                          (900, 30, 100, 900, 3), (900, 30, 100, 20000, 6),
+                                          (7, 65, 200, 700, 0), (40, 20, 300, 4000, 2),
+                                          (1, 10, 0, 100, 0)])
+@pytest.mark.parametrize("pad", ["none", "after", "both"])
+def test_edit_runs_and_out_of_range_genomes(P, N, C, n, skew, pad):
+    print("case", P, N, C, n, skew, pad, flush=True)
+    rng = np.random.default_rng(P + n + len(pad))
+    pop = synth.make_population(rng, P, N, C, 3, 2, N - 5, synth._k_uniform(max(C, 1)),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    e = _random_edits(rng, P, N, C, n)
+    if skew:  # most edits in a few genomes
+        e["genome"] = np.sort((P * rng.random(n) ** skew).astype(np.int32))
+    if pad != "none":  # a fixed-size list padded with genomes that do not exist
+        e["genome"][-(n // 3):] = P + 5
+    if pad == "both":
+        e["genome"][:n // 4] = -2
+    gn, gc, ga = _gpu_edit(pop.nodes, pop.conns, e)
+    on, oc, oa = oracle.edit(pop.nodes, pop.conns, e)
+    assert np.array_equal(ga, oa)
+    assert np.array_equal(_bits(gn), _bits(on)) and np.array_equal(_bits(gc), _bits(oc))
+
+
+@pytest.mark.parametrize("P,n", [(1, 150), (300, 5000), (4000, 3000)])
+def test_unsorted_edits_report_what_they_did(P, n):
+    """Edits that are not sorted by genome may not apply, but every entry of
+    applied is written, and exactly the edits reported applied changed the
+    tensors (attribute writes to places of their own)."""
+    print("case", P, n, flush=True)
+    N, C = 30, 100
+    rng = np.random.default_rng(n)
+    pop = synth.make_population(rng, P, N, C, 3, 2, N - 5, synth._k_uniform(C),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    place = rng.choice(P * C * 2, n, replace=False)
+    e = np.zeros(n, oracle.EDIT_DTYPE)
+    e["op"], e["genome"] = oracle.CONN_SET, place // (2 * C)
+    e["row"], e["column"] = place // 2 % C, 2 + place % 2
+    e["v"][:, 0] = 1000.0 + np.arange(n)
+    e["genome"][::7] = -1
+    gn, gc, ga = _gpu_edit(pop.nodes, pop.conns, e)
+    assert set(np.unique(ga)) <= {0, 1} and np.all(ga[::7] == 0)
+    want = pop.conns.copy()
+    for k in np.flatnonzero(ga):
+        want[e["genome"][k], e["row"][k], e["column"][k]] = e["v"][k, 0]
+    assert np.array_equal(_bits(gc), _bits(want)) and np.array_equal(_bits(gn), _bits(pop.nodes))
