@@ -73,7 +73,7 @@ int check_topo_args(const neat_dims *d, const float *nodes, const float *conns,
     if (conns && !aligned(conns, 16)) return fail(NEAT_E_INVALID, "conns must be 16-byte aligned");
     if (program && !aligned(program, 16))
         return fail(NEAT_E_INVALID, "program must be 16-byte aligned");
-    const size_t lds = topo_lds_bytes(d->N_max, d->C_max);
+    const size_t lds = topo_admission_bytes(d->N_max, d->C_max);
     if (lds > max_lds_bytes())
         return fail(NEAT_E_INVALID,
                     "N_max=%d, C_max=%d needs %zu B of LDS per genome, device allows %zu",

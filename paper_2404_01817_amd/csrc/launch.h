@@ -13,6 +13,9 @@ namespace neat {
 
 // Dynamic LDS bytes the transformation kernel needs for one genome.
 size_t topo_lds_bytes(int N, int C);
+// The bound that decides which sizes are admitted (at least the above for
+// sizes near the device's limit).
+size_t topo_admission_bytes(int N, int C);
 // Threads per block of the transformation kernel (one thread per node row).
 int topo_block_threads(int N);
 

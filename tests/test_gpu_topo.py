@@ -63,3 +63,50 @@ def test_keys_at_the_end_of_the_key_map(N):
     assert (status[:P // 2] == 0).all()
     y64, beta = oracle.forward(pop.nodes, pop.conns, x, I, O)
     _assert_outputs(y, y64, beta, "keys N=%d" % N)
+
+
+def _connect(pop, g, pairs, rng):
+    """Genome g's connections replaced by the pairs, in random rows."""
+    pop.conns[g] = np.nan
+    rows = rng.choice(pop.conns.shape[1], len(pairs), replace=False)
+    pop.conns[g, rows, :2] = pairs
+    pop.conns[g, rows, 2] = 1.0
+    pop.conns[g, rows, 3] = rng.standard_normal(len(pairs)) * 0.5
+
+
+# connection rows in registers only and beyond them, lists of every length modulo
+# eight, in-degrees and depths up to the number of rows
+@pytest.mark.parametrize("N,C", [(65, 256), (65, 700), (128, 513), (129, 2000), (300, 1200),
+                                 (512, 4000), (1000, 2100)])
+def test_graphs_of_larger_groups(N, C):
+    print("case", N, C, flush=True)
+    rng = np.random.default_rng(N + C)
+    P, I, O = 28, 3, 2
+    pop = synth.make_population(rng, P, N, C, I, O, N - 5, synth._k_density(C),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    for g in range(P):
+        keys = pop.nodes[g, :, 0]
+        hidden = rng.permutation(keys[keys >= I + O])
+        kind = g % 7
+        chain = [[a, b] for a, b in zip(np.r_[0, hidden], np.r_[hidden, I])]
+        on = np.nonzero(pop.conns[g, :, 2] == 1.0)[0]
+        if kind == 1:                     # one long chain
+            _connect(pop, g, chain, rng)
+        elif kind == 2:                   # the widest fan-in, and a second output fed by g nodes
+            _connect(pop, g, [[k % I, h] for k, h in enumerate(hidden)] +
+                     [[h, I] for h in hidden[:C - 2 * len(hidden)]] +
+                     [[h, I + 1] for h in hidden[:g % 8][:max(0, C - 2 * len(hidden))]], rng)
+        elif kind == 3 and len(on) > 1:   # an edge twice: first and last row in use
+            pop.conns[g, on[-1], :2] = pop.conns[g, on[0], :2]
+        elif kind == 4 and len(hidden):   # a cycle through every hidden node
+            _connect(pop, g, chain + [[hidden[-1], hidden[0]]], rng)
+        elif kind == 5 and len(on):       # a self-loop at an output, nothing else wrong
+            pop.conns[g, on[-1], :2] = I
+        elif kind == 6 and len(hidden) > 2:   # a chain whose first node also reads its third
+            _connect(pop, g, chain + [[hidden[2], hidden[0]]], rng)
+    x = rng.standard_normal((P, 33, I), dtype=np.float32)
+    order, level, status, y = _gpu(pop.nodes, pop.conns, I, O, x)
+    _assert_transform_exact(pop.nodes, pop.conns, I, O, order, level, status)
+    assert (status[0::7] == 0).all() and (status[1::7] == 0).all() and (status[2::7] == 0).all()
+    y64, beta = oracle.forward(pop.nodes, pop.conns, x, I, O)
+    _assert_outputs(y, y64, beta, "graphs N=%d C=%d" % (N, C))
