@@ -201,6 +201,16 @@ __device__ __forceinline__ void pair_vals(float &acc, bool first, float x0, floa
     }
 }
 
+// The same where the lanes' classes differ: every class's value, and a select.
+__device__ __forceinline__ float pair_lanes(bool prod, bool mx, float acc, bool first, float x0,
+                                            float w0, float x1, float w1) {
+    float s = acc, p = acc, m = acc;
+    pair_vals<ACLS_SUM>(s, first, x0, w0, x1, w1);
+    pair_vals<ACLS_PROD>(p, first, x0, w0, x1, w1);
+    pair_vals<ACLS_MAX>(m, first, x0, w0, x1, w1);
+    return prod ? p : mx ? m : s;
+}
+
 template <int ACLS, class Store>
 __device__ __forceinline__ void pair(float &acc, bool first, int s0, float w0, int s1, float w1,
                                      const Store &v) {
@@ -571,6 +581,18 @@ __device__ __forceinline__ void forward_unit_lds(citem_t *it, int g, int t0, int
 // in registers), and a slot the program reuses after its last reader
 // (liveness) is taken only by a later position, so no value is overwritten
 // before it is read.
+//
+// What bounds it: a step is a chain of some 2000 cycles (record, sources,
+// aggregation, activation), and few waves share a SIMD.  At 700 genomes of up
+// to 365 nodes on 18 samples: 25.8 us; 36.3 when overflow pairs were read one
+// by one (30.2 with four requested together), every lane loaded its whole
+// record and pairs (the 64 bytes x 64 lanes of a step hold the vector cache's
+// return path for 64 cycles; 27.9 with a quarter per lane), and each
+// aggregation class took a branch per pair.  Requests two steps ahead, selects
+// for the activations, twice the waves with half as wide tiles: 28.3, 26.2 and
+// 37.2 us.
+constexpr int LVL_AHEAD = 1;
+
 struct LvlStore {
     float *v;
     int sh;  // log2 BW
@@ -582,7 +604,8 @@ struct LvlStore {
 };
 
 typedef const __attribute__((address_space(1))) int32_t gint_t;
-typedef const __attribute__((address_space(1))) i32x16 gint16_t;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) i32x4 gint4_t;
 
 // Order this wave's LDS accesses (the hardware keeps a wave's LDS
 // operations in order; this stops the compiler from moving them).
@@ -592,73 +615,174 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Advance (l, kb, k1) to the next step: the next npw records of level l,
-// or the first records of the next level that has computed nodes (l =
-// nlev when none is left).  Start with l = -1.
-__device__ __forceinline__ void lvl_advance(cprog_t *lvl, int nlev, int I, int npw, int *l,
-                                            int *kb, int *k1) {
-    if (*l >= 0 && *kb + npw < *k1) {
-        *kb += npw;
-        return;
+// The steps of every level in order: records kb .. kb + npw - 1 below k1 of
+// level l (l = nlev when none is left).  The level starts are held a lane
+// each, 64 at a time: reading one is no memory access.
+struct LvlSteps {
+    gint_t *lvl;
+    int nlev, I, npw;
+    int l, kb, k1;
+    int base, start;  // lane i: the start of level base + i
+    __device__ __forceinline__ void begin() {
+        l = -1, kb = 0, k1 = 0;
+        hold(0);
     }
-    for (++*l; *l < nlev; ++*l) {
-        *kb = max(lvl[*l], I) - I, *k1 = lvl[*l + 1] - I;
-        if (*kb < *k1) return;
+    __device__ __forceinline__ void hold(int b) {
+        base = b;
+        start = lvl[min(b + (int)(threadIdx.x & (WAVE - 1)), nlev)];
     }
-}
+    __device__ __forceinline__ void next() {
+        if (l >= 0 && kb + npw < k1) {
+            kb += npw;
+            return;
+        }
+        if (l >= nlev) return;
+        for (++l; l < nlev; ++l) {
+            if (l + 1 - base >= WAVE) hold(l);
+            kb = max(__builtin_amdgcn_readlane(start, l - base), I) - I;
+            k1 = __builtin_amdgcn_readlane(start, l + 1 - base) - I;
+            if (kb < k1) return;
+        }
+    }
+};
 
-// Request the record (and its first overflow edge) of this lane's node in
-// step (l, kb, k1).
-__device__ __forceinline__ void lvl_load(gint16_t *recs, gint_t *ebeg, int nlev, int node, int l,
-                                         int kb, int k1, i32x16 *r, int *e) {
-    const int k = kb + node;
-    if (l < nlev && k < k1) {
-        *r = recs[k];
-        *e = ebeg[k];
+// Sixteen words (a record, or four overflow pairs) of this lane's node, as
+// requested.  QUAD (tiles of four samples and more): a quad of lanes has one
+// node, each lane loads one quarter, and the quad's lanes exchange them by DPP;
+// else every lane loads all of it.
+template <bool QUAD>
+struct LvlWords {
+    i32x4 w[QUAD ? 1 : 4];
+    // quarter q lies at at(q)
+    template <class At>
+    __device__ __forceinline__ void load(At at) {
+        if constexpr (QUAD) {
+            w[0] = *at((int)(threadIdx.x & 3u));
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q] = *at(q);
+        }
     }
-}
+    template <int Q>
+    __device__ __forceinline__ i32x4 quarter() const {
+        if constexpr (QUAD) {
+            i32x4 r;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)  // quad_perm: lane Q's to all four
+                r[c] = __builtin_amdgcn_update_dpp(0, w[0][c], Q * 0x55, 0xf, 0xf, true);
+            return r;
+        } else {
+            return w[Q];
+        }
+    }
+};
 
-// One step: this lane's node (record r, first overflow edge e) on its
-// sample, when active; then the write of every active lane's result once
-// all lanes of the step have read their sources.
-__device__ __forceinline__ void lvl_step(const i32x16 &r, int e, bool active, gint_t *edges,
+// A step's request: this lane's record and its first overflow edge.
+template <bool QUAD>
+struct LvlReq {
+    LvlWords<QUAD> rec;
+    int e;
+    bool some, active;  // the step has records; this lane has one
+    __device__ __forceinline__ void load(LvlSteps &s, gint_t *recs, gint_t *ebeg, int node) {
+        s.next();
+        const int k = s.kb + node;
+        some = s.l < s.nlev;
+        active = some && k < s.k1;
+        // (a lane without a node reads record 0: loads without branches can be
+        // counted, so a wait for older ones leaves these in flight)
+        gint4_t *r = (gint4_t *)(recs + REC_WORDS * (active ? k : 0));
+        rec.load([&](int q) { return r + q; });
+        e = ebeg[active ? k : 0];
+    }
+};
+
+// One step: this lane's node (request q) on its sample; the next step is
+// requested by next() once this one's overflow pairs are (a wait for them then
+// leaves the later requests in flight).  Every active lane's result is written
+// once all lanes of the step have read their sources.
+template <bool QUAD, class Next>
+__device__ __forceinline__ void lvl_step(const LvlReq<QUAD> &q, gint_t *edges, Next next,
                                          const LvlStore &src, float *v, int sh, int j) {
     // the sources of this step were written by earlier steps
     wave_lds_sync();
+    const i32x4 head = q.rec.template quarter<0>();
+    const unsigned code = (unsigned)head[REC_CODE], np = (unsigned)head[REC_NPAIRS];
+    const int pairs = (int)(np & (unsigned)REC_NPAIRS_MASK);
+    const int over = pairs - REC_INLINE_PAIRS;
+    // overflow pairs four at a time (lists begin at a multiple of two edges:
+    // 16-byte loads; past the end the last pair again, or what follows an
+    // empty list)
+    gint4_t *ov = (gint4_t *)(edges + EDGE_WORDS * q.e);
+    LvlWords<QUAD> o;
+    o.load([&](int i) { return ov + max(min(i, over - 1), 0); });
+    const i32x4 in[REC_INLINE_PAIRS] = {q.rec.template quarter<1>(), q.rec.template quarter<2>(),
+                                        q.rec.template quarter<3>()};
+    const bool active = q.active;
+    next();
     float y = 0.0f;
     int slot = -1;
     if (active) {
-        const unsigned code = (unsigned)r[REC_CODE], np = (unsigned)r[REC_NPAIRS];
-        const int pairs = (int)(np & (unsigned)REC_NPAIRS_MASK);
         const int acls = slot_class((int)(np >> REC_FIELD_SHIFT));
-        const int act = rec_act(code);
         slot = (int)(code & (unsigned)REC_DST_MASK);
         // the six inline sources at once (unused inline edges name the
         // constant slot with weight 0)
         float x[2 * REC_INLINE_PAIRS];
 #pragma unroll
-        for (int q = 0; q < 2 * REC_INLINE_PAIRS; ++q) x[q] = src.get<0>(r[REC_PAIRS + 2 * q]);
+        for (int p = 0; p < REC_INLINE_PAIRS; ++p) {
+            x[2 * p] = src.get<0>(in[p].x);
+            x[2 * p + 1] = src.get<0>(in[p].z);
+        }
         float a = 0.0f;
-        const int inl = min(pairs, REC_INLINE_PAIRS);
-        gint_t *ov = edges + EDGE_WORDS * e;
-#define NEAT_LVL_AGG(ACLS)                                                                   \
-    {                                                                                        \
-        _Pragma("unroll") for (int q = 0; q < REC_INLINE_PAIRS; ++q) if (q < inl)            \
-            pair_vals<ACLS>(a, q == 0, x[2 * q], fbits(r[REC_PAIRS + 4 * q + 1]), x[2 * q + 1], \
-                            fbits(r[REC_PAIRS + 4 * q + 3]));                                \
-        for (int p = 0; p < pairs - REC_INLINE_PAIRS; ++p)                                   \
-            pair<ACLS>(a, false, ov[4 * p], fbits(ov[4 * p + 1]), ov[4 * p + 2],             \
-                       fbits(ov[4 * p + 3]), src);                                           \
-    }
-        if (acls == ACLS_PROD) NEAT_LVL_AGG(ACLS_PROD)
-        else if (acls == ACLS_MAX) NEAT_LVL_AGG(ACLS_MAX)
-        else NEAT_LVL_AGG(ACLS_SUM)
-#undef NEAT_LVL_AGG
-        y = activation(act, fmaf(fbits(r[REC_RESP]), a, fbits(r[REC_BIAS])));
+        const bool prod = acls == ACLS_PROD, mx = acls == ACLS_MAX;
+#pragma unroll
+        for (int p = 0; p < REC_INLINE_PAIRS; ++p)
+            a = p < pairs ? pair_lanes(prod, mx, a, p == 0, x[2 * p], fbits(in[p].y), x[2 * p + 1],
+                                       fbits(in[p].w))
+                          : a;
+        for (int p0 = 0; p0 < over; p0 += 4) {
+            const i32x4 c[4] = {o.template quarter<0>(), o.template quarter<1>(),
+                                o.template quarter<2>(), o.template quarter<3>()};
+            float z[8];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                z[2 * p] = src.get<0>(c[p].x);
+                z[2 * p + 1] = src.get<0>(c[p].z);
+            }
+            if (p0 + 4 < over) o.load([&](int i) { return ov + min(p0 + 4 + i, over - 1); });
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                a = p0 + p < over ? pair_lanes(prod, mx, a, false, z[2 * p], fbits(c[p].y),
+                                               z[2 * p + 1], fbits(c[p].w))
+                                  : a;
+        }
+        y = activation(rec_act(code), fmaf(fbits(head[REC_RESP]), a, fbits(head[REC_BIAS])));
     }
     // every lane of the step has read its sources
     wave_lds_sync();
     if (slot >= 0) v[(slot << sh) + j] = y;
+}
+
+// Every step of a tile, the records (and overflow offsets) requested LVL_AHEAD
+// steps before they are used.
+template <bool QUAD>
+__device__ __forceinline__ void lvl_walk(LvlSteps &steps, gint_t *recs, gint_t *ebeg,
+                                         gint_t *edges, int node, const LvlStore &src, float *v,
+                                         int sh, int j) {
+    LvlReq<QUAD> q[LVL_AHEAD + 1];
+#pragma unroll
+    for (int d = 0; d < LVL_AHEAD; ++d) q[d].load(steps, recs, ebeg, node);
+    for (bool more = q[0].some; more;) {
+#pragma unroll
+        for (int d = 0; d <= LVL_AHEAD; ++d) {
+            if (!more) continue;
+            lvl_step<QUAD>(q[d], edges,
+                           [&] {
+                               q[(d + LVL_AHEAD) % (LVL_AHEAD + 1)].load(steps, recs, ebeg, node);
+                           },
+                           src, v, sh, j);
+            more = q[(d + 1) % (LVL_AHEAD + 1)].some;  // requested before
+        }
+    }
 }
 
 // Tiles [t0, t1) of BW samples.
@@ -676,10 +800,9 @@ __device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int t0, int
     const float *in_g = it->inputs + (size_t)g * it->gstride;
     const int nlev = prog[HDR_NLEVELS];
     const int zs = zero_slot(prog[HDR_CLASS], N);
-    cprog_t *lvl = prog + lvl_off(N, C, O);
     gint_t *ebeg = gp + ebeg_off(N, C, O);
     gint_t *edges = gp + edge_off(N, O);
-    gint16_t *recs = (gint16_t *)(gp + rec_off(O));
+    gint_t *recs = gp + rec_off(O);
     const int j = lane & (BW - 1), node = lane >> sh, npw = WAVE >> sh;
     const LvlStore src{v, sh, j};
     for (int t = t0; t < t1; ++t) {
@@ -695,27 +818,10 @@ __device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int t0, int
             v[(zs << sh) + lane] = 0.0f;
             v[((zs + 1) << sh) + lane] = 1.0f;
         }
-        // the steps of every level in order: (level l, records kb ..
-        // kb + npw - 1 below k1), alternating two record buffers: the next
-        // step's records (and overflow offsets) are requested before the
-        // current step is aggregated
-        int l = -1, kb = 0, k1 = 0;
-        lvl_advance(lvl, nlev, I, npw, &l, &kb, &k1);
-        i32x16 ra = {}, rb = {};
-        int ea = 0, eb = 0;
-        lvl_load(recs, ebeg, nlev, node, l, kb, k1, &ra, &ea);
-        while (l < nlev) {
-            int l2 = l, kb2 = kb, k12 = k1;
-            lvl_advance(lvl, nlev, I, npw, &l2, &kb2, &k12);
-            lvl_load(recs, ebeg, nlev, node, l2, kb2, k12, &rb, &eb);
-            lvl_step(ra, ea, kb + node < k1, edges, src, v, sh, j);
-            l = l2, kb = kb2, k1 = k12;
-            if (l >= nlev) break;
-            lvl_advance(lvl, nlev, I, npw, &l2, &kb2, &k12);
-            lvl_load(recs, ebeg, nlev, node, l2, kb2, k12, &ra, &ea);
-            lvl_step(rb, eb, kb + node < k1, edges, src, v, sh, j);
-            l = l2, kb = kb2, k1 = k12;
-        }
+        LvlSteps steps{gp + lvl_off(N, C, O), nlev, I, npw, 0, 0, 0, 0, 0};
+        steps.begin();
+        if (sh >= 2) lvl_walk<true>(steps, recs, ebeg, edges, node, src, v, sh, j);
+        else lvl_walk<false>(steps, recs, ebeg, edges, node, src, v, sh, j);
         wave_lds_sync();
         // outputs of the tile: y[s0 + j][o] = v[out slot o][j]
         float *o_t = out_g + (size_t)s0 * O;

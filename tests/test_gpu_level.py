@@ -220,3 +220,39 @@ def test_one_population_mappings_agree_bitwise(P, N, B):
     few = min(P, 12)
     y64, beta = oracle.forward(pop.nodes[:few], pop.conns[:few], pop.inputs[:few], pop.I, pop.O)
     assert_parity(ref[:few], y64, beta, "P%d N%d B%d" % (P, N, B))
+
+
+# tiles of 1, 2, 4, 8 and 32 samples: lanes that load whole records and quads that share one
+@pytest.mark.parametrize("P,B", [(30, 5), (2000, 4), (1300, 12), (1500, 9), (3000, 30)])
+def test_level_mapping_in_edge_lists_of_every_length(P, B):
+    """25 genomes whose nodes have 0 to 24 in-edges (records hold six, the rest comes four
+    pairs at a time) with every aggregation and activation, repeated P times."""
+    print("case", P, B, flush=True)
+    neat = _neat()
+    rng = np.random.default_rng(P + B)
+    I, O, H, N, C, G = 24, 4, 31, 60, 600, 25
+    nodes = np.full((G, N, 5), np.nan, np.float32)
+    conns = np.full((G, C, 4), np.nan, np.float32)
+    for g in range(G):
+        nodes[g, :I + O + H, 0] = np.arange(I + O + H)
+        nodes[g, :I + O + H, 1:3] = rng.standard_normal((I + O + H, 2))
+        nodes[g, :I + O + H, 3] = rng.integers(0, 7, I + O + H)
+        nodes[g, :I + O + H, 4] = rng.choice(synth.ALL_AGGS, I + O + H)
+        edges = [(s, I + O + h) for h in range(H) for s in rng.permutation(I)[:(h + g) % 25]]
+        edges += [(I + O + h, I + o) for o in range(O) for h in rng.permutation(H)[:(6 * o + g) % 25]]
+        rows = rng.permutation(C)[:len(edges)]
+        conns[g, rows, :2], conns[g, rows, 2] = edges, 1.0
+        conns[g, rows, 3] = rng.standard_normal(len(edges)) * 0.5
+    x = rng.standard_normal((B, I), dtype=np.float32)
+    dev = torch.device("cuda:0")
+    copies = np.arange(P) % G
+    tn, tc = torch.from_numpy(nodes[copies]).to(dev), torch.from_numpy(conns[copies]).to(dev)
+    _, _, status, prog = neat.topo_sort(tn, tc, I, O, want_order=False)
+    d = neat.dims_of(tn, tc, I, O)
+    tx = torch.from_numpy(x).to(dev)
+    y, want = (neat.forward(d, prog, tx, B, shared_inputs=True, variant=v).cpu().numpy()
+               for v in (neat.FWD_LVL, neat.FWD_LDS))
+    assert (status.cpu().numpy() == 0).all()
+    assert _same_bits(y, want)
+    y64, beta = oracle.forward(nodes, conns, x, I, O, shared_inputs=True)
+    assert_parity(y[:G], y64, beta, "in-edge lists P=%d B=%d" % (P, B))
