@@ -11,7 +11,7 @@
 // Y[g] = X W'[g] is a dense contraction (M = B, N = K = S), so it runs on
 // the matrix cores: v_mfma_f32_32x32x2_f32, fp32 in and fp32 accumulation
 // (the precision of the rest of the path).  A workgroup of four waves owns
-// a 128 x 64 tile of one genome's Y (64 x 64 for up to 64 input planes); K
+// a 128 x 64 tile of one genome's Y (64 x 64 in smaller launches); K
 // advances in chunks of 32 staged in LDS (the threshold is applied as W
 // enters LDS); each wave owns a 64 x 32 quarter, two 32 x 32 MFMA blocks.
 // Operand layout of the 32x32x2 MFMA: lane l supplies A[l % 32][l / 32] and
@@ -132,9 +132,17 @@ __global__ __launch_bounds__(256) void substrate_kernel(SubLaunch L) {
 }  // namespace
 
 hipError_t substrate_launch(const SubLaunch &L, hipStream_t stream) {
-    // two blocks of rows per wave halve the staging of W per product, but a
-    // call of up to 64 planes would leave the second one empty
-    const int mt = L.B > 64 ? 2 : 1;
+    // Two blocks of rows per wave halve the staging of W per product, but hold
+    // twice the registers, and an odd number of 64 rows leaves one empty (one
+    // part in 32 more work is what they are worth).  So they are taken for
+    // launches of at least 800,000 chunk rows (tiles times S): 1,024,000 (P =
+    // 500, side 16, B = 256) 265 us against 270 with one, 1,016,000 (P = 31,
+    // side 32, B = 256) 289 against 295; 614,000 (P = 300, side 16, B = 256)
+    // 173 against 172, 410,000 (P = 200) 126 against 123, 311,000 (P = 60, side
+    // 24, B = 128) 152 against 143.  B = 192: 264 against 233 (P = 500).
+    const long long rows = ((long long)L.B + 63) / 64;  // of 64
+    const bool filled = rows % 2 == 0 || rows > 32;
+    const int mt = filled && L.P * ((rows + 1) / 2) * (L.S / ST_N) * L.S >= 800000 ? 2 : 1;
     const long long blocks = (long long)L.P * ((L.B + 64 * mt - 1) / (64 * mt)) * (L.S / ST_N);
     if (blocks == 0) return hipSuccess;
     if (mt == 2)

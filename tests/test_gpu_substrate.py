@@ -143,3 +143,22 @@ def test_layer_row_tiles(side, B):
         u = 2.0 ** -24
         bound = S * u / (1 - S * u) * (x.double().abs() @ w64[g].abs()) + 1e-6
         assert ((y[g].double() - torch.tanh(z)).abs() <= bound).all()
+
+
+# the largest launches take two blocks of rows per wave where the planes fill them
+@pytest.mark.parametrize("B", [192, 200, 256])
+def test_layer_rows_of_large_launches(B):
+    import paper_2404_01817_amd as neat
+    print("case side=32 P=25 B=%d" % B, flush=True)
+    pop = synth.cppn(seed=B, P=25)
+    tn, tc = torch.from_numpy(pop.nodes).cuda(), torch.from_numpy(pop.conns).cuda()
+    _, _, _, prog = neat.topo_sort(tn, tc, pop.I, pop.O, want_order=False)
+    S = 1024
+    x = torch.from_numpy(np.random.default_rng(B).uniform(-1, 1, (B, S)).astype(np.float32)).cuda()
+    y, w = neat.substrate_forward(neat.dims_of(tn, tc, pop.I, pop.O), prog, 32, x, 0.2)
+    w = w.view(-1, S, S)
+    for g in (0, 12, 24):
+        w64 = torch.where(w[g].abs() < 0.2, torch.zeros_like(w[g]), w[g]).double()
+        u = 2.0 ** -24  # as above
+        bound = S * u / (1 - S * u) * (x.double().abs() @ w64.abs()) + 1e-6
+        assert ((y[g].double() - torch.tanh(x.double() @ w64)).abs() <= bound).all()
