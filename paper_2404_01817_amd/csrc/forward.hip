@@ -590,7 +590,9 @@ __device__ __forceinline__ void forward_unit_lds(citem_t *it, int g, int t0, int
 // return path for 64 cycles; 27.9 with a quarter per lane), and each
 // aggregation class took a branch per pair.  Requests two steps ahead, selects
 // for the activations, twice the waves with half as wide tiles: 28.3, 26.2 and
-// 37.2 us.
+// 37.2 us.  Calculation alone, before / now: N = 300, P = 100, B = 16: 20.6 /
+// 18.0; N = 200, P = 700, B = 16: 18.1 / 16.9; N = 140, P = 100 .. 3000, whose
+// levels are short, B = 4 .. 16: 14.0 - 30.2 / 14.1 - 30.0.
 constexpr int LVL_AHEAD = 1;
 
 struct LvlStore {
@@ -625,7 +627,7 @@ struct LvlSteps {
     int base, start;  // lane i: the start of level base + i
     __device__ __forceinline__ void begin() {
         l = -1, kb = 0, k1 = 0;
-        hold(0);
+        if (base != 0) hold(0);
     }
     __device__ __forceinline__ void hold(int b) {
         base = b;
@@ -805,6 +807,8 @@ __device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int t0, int
     gint_t *recs = gp + rec_off(O);
     const int j = lane & (BW - 1), node = lane >> sh, npw = WAVE >> sh;
     const LvlStore src{v, sh, j};
+    LvlSteps steps{gp + lvl_off(N, C, O), nlev, I, npw, 0, 0, 0, 0, 0};
+    steps.hold(0);  // requested before the inputs are
     for (int t = t0; t < t1; ++t) {
         const int s0 = t * BW, nb = min(BW, B - s0);
         // inputs of the tile (contiguous [nb][I] floats): v[i][j] = x[s0 + j][i];
@@ -818,7 +822,6 @@ __device__ __forceinline__ void forward_unit_lvl(citem_t *it, int g, int t0, int
             v[(zs << sh) + lane] = 0.0f;
             v[((zs + 1) << sh) + lane] = 1.0f;
         }
-        LvlSteps steps{gp + lvl_off(N, C, O), nlev, I, npw, 0, 0, 0, 0, 0};
         steps.begin();
         if (sh >= 2) lvl_walk<true>(steps, recs, ebeg, edges, node, src, v, sh, j);
         else lvl_walk<false>(steps, recs, ebeg, edges, node, src, v, sh, j);
