@@ -839,7 +839,7 @@ def bench_substrate(args, torch, neat, synth):
             "ms": round(ms, 4), "ms_cppn_weights": round(ms_cppn, 4),
             "ms_substrate_layer": round(ms_layer, 4),
             "value": round(pop.P * X.shape[0] / (ms / 1e3), 1), "unit": "genome-inputs/s",
-            "roofline": {"kernel": "substrate layer, fp32 MFMA 16x16x4", "bound": "mfma",
+            "roofline": {"kernel": "substrate layer, fp32 MFMA 32x32x2", "bound": "mfma",
                          "achieved": round(tflops, 2), "peak": MFMA_F32_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": round(tflops / MFMA_F32_PEAK_TFLOPS, 4),
                          "flops_per_launch": flops}}
@@ -1008,7 +1008,7 @@ def bench_recurrent(args, torch, neat, synth):
             "forward_ms": round(fwd_ms, 4),
             "value": round(units / (step_ms / 1e3), 1), "unit": "genome-inputs/s",
             "rejected_genomes": int((hdr[:, 2] != 0).sum()),
-            "roofline": {"kernel": "recurrent forward, 64-slot register store (read and "
+            "roofline": {"kernel": "recurrent forward, 52-slot register store (read and "
                                    "write vectors)", "bound": "alu",
                          "achieved": round(tflops, 2), "peak": VALU_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": round(tflops / VALU_PEAK_TFLOPS, 4),
