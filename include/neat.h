@@ -162,7 +162,8 @@ int neat_forward(const neat_dims *dims, const void *program, const float *inputs
  * The program build gives every genome a slot class from its largest set of
  * simultaneously live values (<= 62, <= 126, <= 222 values in registers,
  * more in LDS rows); NEAT_FWD_AUTO runs each class's genomes with that
- * class's kernel, two samples per lane for the smallest class when B > 64.
+ * class's kernel, two or four samples per lane for the smallest class when
+ * B > 64 (one while a call's only population leaves the GPU unfilled).
  * A call over one population that can need more than the smallest class may
  * run every class in one launch instead (NEAT_FWD_AUTO, _REG and _REG2;
  * genomes past the register classes then as by NEAT_FWD_LVL), and

@@ -1352,9 +1352,25 @@ int shared_variant(const FwdJob &J, bool in_order, size_t max_lds) {
     return J.N > (in_order ? 126 : 300) ? FWD_ANY : FWD_AUTO;
 }
 
-// The mapping of a call's only population of more than 62 node rows where
-// the caller left it open (FWD_AUTO, or registers of either kind).
+// One sample per lane where a call's only population, of 31 to 62 node rows,
+// has more than 64 inputs: two per lane share the scalar work of a node, but a
+// wave's chain is longer, and nothing is shared while every one-sample wave is
+// resident.  Calculation, two samples per lane / one, us: N = 50, P = 157, B =
+// 128: 8.7 / 7.3; N = 62, P = 157, B = 200: 8.8 / 7.5; N = 37, P = 1000, B =
+// 256 (4000 waves): 8.6 / 8.3; N = 45, P = 2500, B = 65 (5000): 9.7 / 10.4.
+// Three tiles of 64 leave a quarter of two-sample tiles empty (B = 192, P =
+// 5000: N = 45: 24.8 / 23.2, N = 62: 31.3 / 28.2).  Up to 30 rows nothing is
+// gained (N = 20, P = 1500, B = 192: 6.6 / 7.1).
+static bool one_sample(const FwdJob &J) {
+    const int tiles = (J.B + WAVE - 1) / WAVE;
+    return !J.side && !J.recurrent && J.N > SMALL_ROWS && max_class(J.N) == CLS_R64 &&
+           ((long long)J.P * tiles <= 4096 || tiles == 3);
+}
+
+// The mapping of a call's only population where the caller left it open
+// (FWD_AUTO, or registers of either kind).
 static int resolve_variant(const FwdJob &J, int variant, int n_jobs, size_t max_lds) {
+    if (n_jobs == 1 && variant == FWD_AUTO && one_sample(J)) return FWD_REG;
     if (n_jobs != 1 || !classes_may_merge(J, max_lds)) return variant;
     const long long units = (long long)J.P * ((J.B + WAVE - 1) / WAVE);
     if (variant == FWD_AUTO) {

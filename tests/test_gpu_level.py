@@ -256,3 +256,28 @@ def test_level_mapping_in_edge_lists_of_every_length(P, B):
     assert _same_bits(y, want)
     y64, beta = oracle.forward(nodes, conns, x, I, O, shared_inputs=True)
     assert_parity(y[:G], y64, beta, "in-edge lists P=%d B=%d" % (P, B))
+
+
+# on both sides of 4096 one-sample waves, of 30 and 62 rows, and of three tiles of 64
+@pytest.mark.parametrize("P,N,B", [(16, 62, 1000), (2048, 31, 128), (2049, 31, 128), (30, 30, 130),
+                                   (1500, 50, 192), (1500, 62, 193), (40, 33, 65), (20, 63, 129)])
+def test_samples_per_lane_agree_bitwise(P, N, B):
+    """The mapping chosen for one population and two samples per lane, bit for bit; a sample of
+    genomes against the oracle."""
+    print("case", P, N, B, flush=True)
+    neat = _neat()
+    rng = np.random.default_rng(P + N + B)
+    I, O = 7, 3
+    pop = synth.make_population(rng, P, N, 3 * N, I, O, N - 10, synth._k_density(3 * N),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    x = rng.standard_normal((P, B, I), dtype=np.float32)
+    dev = torch.device("cuda:0")
+    tn, tc = torch.from_numpy(pop.nodes).to(dev), torch.from_numpy(pop.conns).to(dev)
+    tx = torch.from_numpy(x).to(dev)
+    _, _, _, prog = neat.topo_sort(tn, tc, I, O, want_order=False)
+    d = neat.dims_of(tn, tc, I, O)
+    y, want = (neat.forward(d, prog, tx, B, variant=v).cpu().numpy()
+               for v in (neat.FWD_AUTO, neat.FWD_REG2))
+    assert _same_bits(y, want)
+    y64, beta = oracle.forward(pop.nodes[:8], pop.conns[:8], x[:8], I, O)
+    assert_parity(y[:8], y64, beta, "samples per lane P=%d N=%d B=%d" % (P, N, B))
