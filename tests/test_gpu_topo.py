@@ -1,4 +1,5 @@
-"""Where the transformation changes its way of working: keys on both sides of the key map's end.
+"""Where the transformation changes its way of working: keys on both sides of the key map's end,
+and the graphs of groups of more than one wave.
 
 The oracle gives order, level and status bit for bit; outputs follow the parity rule."""
 from __future__ import annotations
