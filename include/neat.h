@@ -597,8 +597,8 @@ int neat_submit_many(neat_server *server, const neat_request *requests, int32_t 
  * NEAT_E_UNKNOWN_TICKET.  Never blocks. */
 int neat_poll(neat_server *server, uint64_t ticket, neat_result *result);
 /* As neat_poll, after blocking until the request is done or timeout_us
- * microseconds passed (NEAT_PENDING then; at once when timeout_us <= 0).  The
- * caller must not destroy the server while a thread waits in it. */
+ * microseconds passed (NEAT_PENDING then; at once when timeout_us <= 0; the
+ * largest number waits as long as it takes).  The caller must not destroy the server while a thread waits in it. */
 int neat_wait(neat_server *server, uint64_t ticket, int64_t timeout_us, neat_result *result);
 /* Counters and latency percentiles since creation or the last reset. */
 int neat_server_stats(neat_server *server, neat_stats *stats);

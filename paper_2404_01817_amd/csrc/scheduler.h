@@ -178,9 +178,9 @@ class Scheduler {
             return it != reqs_.end() && it->second.state != DONE;
         };
         if (timeout_us > 0 && pending()) {
-            // (a system-clock deadline, as in loop)
-            const auto until =
-                std::chrono::system_clock::now() + std::chrono::microseconds(timeout_us);
+            // (no further ahead than the clock can count: 10^15 us are 31 years)
+            const auto until = WaitClock::now() +
+                               std::chrono::microseconds(std::min<int64_t>(timeout_us, MAX_WAIT_US));
             waiters_++;
             done_cv_.wait_until(lk, until, [&] { return !pending(); });
             waiters_--;
@@ -223,6 +223,15 @@ class Scheduler {
     }
 
   private:
+    // A waiter's deadline does not follow changes of the system's time, but
+    // thread checkers do not follow the wait on the steady clock.
+#ifdef __SANITIZE_THREAD__
+    using WaitClock = std::chrono::system_clock;
+#else
+    using WaitClock = std::chrono::steady_clock;
+#endif
+    static constexpr int64_t MAX_WAIT_US = 1000000000000000;
+
     enum State { QUEUED = 0, ADMITTED = 1, DONE = 2 };
     struct Req {
         Payload payload{};
