@@ -598,7 +598,10 @@ int neat_submit_many(neat_server *server, const neat_request *requests, int32_t 
 int neat_poll(neat_server *server, uint64_t ticket, neat_result *result);
 /* As neat_poll, after blocking until the request is done or timeout_us
  * microseconds passed (NEAT_PENDING then; at once when timeout_us <= 0; the
- * largest number waits as long as it takes).  The caller must not destroy the server while a thread waits in it. */
+ * largest number waits as long as it takes).  Destroying the server ends the
+ * waits in it first: a queued request's with NEAT_E_SHUTDOWN in its result, a
+ * running one's when it is done.  No call may begin once the destruction has
+ * (as for every call of a server). */
 int neat_wait(neat_server *server, uint64_t ticket, int64_t timeout_us, neat_result *result);
 /* Counters and latency percentiles since creation or the last reset. */
 int neat_server_stats(neat_server *server, neat_stats *stats);

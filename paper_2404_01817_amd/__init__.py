@@ -9,10 +9,11 @@ device memory and the current HIP stream; nothing is computed in Python.
 from __future__ import annotations
 
 import ctypes
+import threading
 from typing import Optional, Tuple
 
 from ._lib import (FWD_AUTO, FWD_LDS, FWD_LVL, FWD_REG, FWD_REG2, FWD_SEG, FWD_TUNED,
-                   TUNE_CANDIDATES,
+                   NEAT_E_SHUTDOWN, TUNE_CANDIDATES,
                    INPUT_GRID, INPUT_TENSOR,
                    BatchItem, Dims, NeatError, Request, Result, ServerCfg, Stats, check, lib)
 
@@ -352,6 +353,9 @@ class Server:
         cfg = ServerCfg(device, max_inflight, cap_bytes,
                         tune_cache_path.encode() if tune_cache_path else None)
         self._h = ctypes.c_void_p(None)
+        self._guard = threading.Condition()
+        self._waiting = []  # threads in wait
+        self._closing = False
         check(lib().neat_server_create(ctypes.byref(cfg), ctypes.byref(self._h)))
 
     def register(self, nodes, conns, I: int, O: int) -> int:
@@ -424,6 +428,9 @@ class Server:
         return None if rc == 1 else res
 
     def wait(self, ticket: int, timeout_s: float = 60.0):
+        """The Result of a ticket, which is then forgotten; TimeoutError after
+        timeout_s, NeatError (NEAT_E_SHUTDOWN) when another thread closes the
+        server meanwhile."""
         import time
         res = Result()
         slot = ctypes.byref(res)
@@ -431,13 +438,23 @@ class Server:
         if check(fn(self._h, ticket, 0, slot)) == 0:
             return res
         t_end = time.monotonic() + timeout_s
-        while True:
-            # blocks without the interpreter lock, in slices that let signals in
-            left = t_end - time.monotonic()
-            if check(fn(self._h, ticket, int(1e6 * min(max(left, 0.0), 0.05)), slot)) == 0:
-                return res
-            if time.monotonic() > t_end:
-                raise TimeoutError("ticket %d not done after %.1fs" % (ticket, timeout_s))
+        # close destroys the server once no thread is listed
+        me = threading.get_ident()
+        with self._guard:
+            self._waiting.append(me)
+        try:
+            while not self._closing:
+                # blocks without the interpreter lock, in slices that let signals in
+                left = t_end - time.monotonic()
+                if check(fn(self._h, ticket, int(1e6 * min(max(left, 0.0), 0.05)), slot)) == 0:
+                    return res
+                if time.monotonic() > t_end:
+                    raise TimeoutError("ticket %d not done after %.1fs" % (ticket, timeout_s))
+        finally:
+            with self._guard:
+                self._waiting.remove(me)
+                self._guard.notify_all()
+        raise NeatError(NEAT_E_SHUTDOWN, "the server was closed while ticket %d waited" % ticket)
 
     def stats(self) -> Stats:
         st = Stats()
@@ -448,9 +465,15 @@ class Server:
         check(lib().neat_server_reset_stats(self._h))
 
     def close(self):
-        if self._h.value:
-            check(lib().neat_server_destroy(self._h))
-            self._h = ctypes.c_void_p(None)
+        """Destroy the server, after other threads in wait have left it (at
+        most one of their slices of 50 ms)."""
+        me = threading.get_ident()  # in wait itself when a signal's handler closes
+        with self._guard:
+            self._closing = True
+            self._guard.wait_for(lambda: all(t == me for t in self._waiting))
+            if self._h.value:
+                check(lib().neat_server_destroy(self._h))
+                self._h = ctypes.c_void_p(None)
 
     def __del__(self):
         try:

@@ -15,6 +15,7 @@ LIB_PATH = os.path.join(PKG, "libneat.so")
 
 NEAT_OK = 0
 NEAT_PENDING = 1
+NEAT_E_SHUTDOWN = -6
 FWD_AUTO, FWD_REG, FWD_LDS, FWD_REG2, FWD_TUNED, FWD_LVL, FWD_SEG = 0, 1, 2, 3, 4, 5, 6
 TUNE_CANDIDATES = 5  # REG, REG2, LDS, LVL, SEG
 

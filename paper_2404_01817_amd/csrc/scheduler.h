@@ -88,7 +88,7 @@ class Scheduler {
     ~Scheduler() { shutdown(); }
 
     // Queued requests end with NEAT_E_SHUTDOWN; running batches finish; the
-    // worker exits.  Idempotent.
+    // worker exits and the threads in wait leave.  Idempotent.
     void shutdown() {
         {
             std::lock_guard<std::mutex> lk(m_);
@@ -105,6 +105,9 @@ class Scheduler {
         cv_.notify_all();
         done_cv_.notify_all();
         if (worker_.joinable()) worker_.join();
+        // every request is done, so every waiter was woken
+        std::unique_lock<std::mutex> lk(m_);
+        left_cv_.wait(lk, [this] { return waiters_ == 0; });
     }
 
     // Hold `bytes` of resident data against the cap for good; NEAT_E_TOO_LARGE
@@ -183,7 +186,7 @@ class Scheduler {
                                std::chrono::microseconds(std::min<int64_t>(timeout_us, MAX_WAIT_US));
             waiters_++;
             done_cv_.wait_until(lk, until, [&] { return !pending(); });
-            waiters_--;
+            if (--waiters_ == 0) left_cv_.notify_all();
         }
         auto it = reqs_.find(ticket);
         if (it == reqs_.end()) return NEAT_E_UNKNOWN_TICKET;
@@ -437,6 +440,7 @@ class Scheduler {
     std::mutex m_;
     std::condition_variable cv_;       // the worker: something to admit or to poll
     std::condition_variable done_cv_;  // waiters: requests ended
+    std::condition_variable left_cv_;  // shutdown: no waiter left
     int waiters_ = 0;
     bool stop_ = false;
     std::unordered_map<uint64_t, Req> reqs_;

@@ -1,7 +1,8 @@
 // Scheduler::wait (paper_2404_01817_amd/csrc/scheduler.h) on the CPU, with an
 // executor whose batches end after a fixed time: timeouts from none to the
-// largest number, several waiters and launch errors.  Argument: which check to
-// run.  Exit status 0 when it held.
+// largest number, several waiters, launch errors, requests cancelled by a
+// shutdown, and a scheduler destroyed under its waiters.  Argument: which
+// check to run.  Exit status 0 when it held.
 #include <atomic>
 #include <chrono>
 #include <cstdint>
@@ -122,12 +123,41 @@ void waiters() {
     CHECK(got.load() == 1 && gone.load() == 7);
 }
 
+// Waiters of running and queued requests when the scheduler is shut down and
+// destroyed: each leaves with its result or NEAT_E_SHUTDOWN in it, and before
+// the memory goes.
+void destroyed() {
+    for (int round = 0; round < 20; ++round) {
+        constexpr int W = 48;
+        TimedExec ex(1, 4.0);
+        auto *s = new Scheduler<int>(&ex, 1, 1000, 4, 5);
+        std::vector<uint64_t> tk;
+        for (int i = 0; i < W; ++i) tk.push_back(submit(*s, (uint64_t)i));
+        std::atomic<int> in{0}, done{0}, cancelled{0};
+        std::vector<std::thread> th;
+        for (int i = 0; i < W; ++i)
+            th.emplace_back([&, i] {
+                Result r;
+                in++;
+                CHECK(s->wait(tk[i], std::numeric_limits<int64_t>::max(), &r) == NEAT_OK);
+                CHECK(r.tag == (uint64_t)i);
+                (r.status == NEAT_E_SHUTDOWN ? cancelled : done)++;
+            });
+        while (in.load() < W) std::this_thread::yield();
+        std::this_thread::sleep_for(std::chrono::milliseconds(2));  // all of them in wait
+        delete s;
+        for (auto &x : th) x.join();
+        CHECK(done.load() + cancelled.load() == W && cancelled.load() > 0);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "timeouts")) timeouts();
     else if (!std::strcmp(what, "waiters")) waiters();
+    else if (!std::strcmp(what, "destroyed")) destroyed();
     else return 2;
     if (g_fail.load() == 0) std::printf("%s: checks passed\n", what);
     return g_fail.load();

@@ -26,7 +26,7 @@ def program(request, tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["timeouts", "waiters"])
+@pytest.mark.parametrize("check", ["timeouts", "waiters", "destroyed"])
 def test_wait(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "checks passed" in r.stdout, r.stdout + r.stderr
