@@ -277,9 +277,11 @@ static int forward_common(const neat_dims *d, const void *program, const float *
     if (rc != NEAT_OK || d->P == 0 || B == 0) return rc;
     const neat::FwdJob job =
         make_job(d, program, inputs, stride, B, outputs, grid ? side : 0, first);
+    const size_t lds = max_lds_bytes();
+    if (variant == NEAT_FWD_AUTO) variant = neat::alone_variant(job, lds);
     std::vector<neat::FwdKernelLaunch> plan;
     char err[256] = "";
-    rc = neat::forward_plan(&job, 1, variant, max_lds_bytes(), plan, err, sizeof(err));
+    rc = neat::forward_plan(&job, 1, variant, lds, plan, err, sizeof(err));
     if (rc != NEAT_OK) return fail(rc, "%s", err);
     for (const neat::FwdKernelLaunch &k : plan) {
         hipError_t e = neat::forward_launch(k, nullptr, (hipStream_t)stream);

@@ -197,8 +197,10 @@ int plan_host(const neat_batch_item *items, int32_t n, bool in_order, HostPlan &
     // launch per kernel kind over all of them
     for (size_t j = 0; j < jobs.size(); ++j) {
         jobs[j].variant = job_variant[j];
-        if (jobs.size() > 1 && jobs[j].variant == neat::FWD_AUTO)
-            jobs[j].variant = neat::shared_variant(jobs[j], in_order, max_lds_bytes());
+        if (jobs[j].variant == neat::FWD_AUTO)
+            jobs[j].variant = jobs.size() > 1
+                                  ? neat::shared_variant(jobs[j], in_order, max_lds_bytes())
+                                  : neat::alone_variant(jobs[j], max_lds_bytes());
     }
     if (!jobs.empty()) {
         char err[256] = "";

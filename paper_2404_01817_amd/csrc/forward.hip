@@ -1367,31 +1367,24 @@ static bool one_sample(const FwdJob &J) {
            ((long long)J.P * tiles <= 4096 || tiles == 3);
 }
 
-// The mapping of a call's only population where the caller left it open
-// (FWD_AUTO, or registers of either kind).
-static int resolve_variant(const FwdJob &J, int variant, int n_jobs, size_t max_lds) {
-    if (n_jobs == 1 && variant == FWD_AUTO && one_sample(J)) return FWD_REG;
-    if (n_jobs != 1 || !classes_may_merge(J, max_lds)) return variant;
+int alone_variant(const FwdJob &J, size_t max_lds) {
+    if (one_sample(J)) return FWD_REG;
+    if (!classes_may_merge(J, max_lds)) return FWD_AUTO;
     const long long units = (long long)J.P * ((J.B + WAVE - 1) / WAVE);
-    if (variant == FWD_AUTO) {
-        // Few samples: the level mapping, whose lanes share a genome's nodes,
-        // has the shorter chain while its waves fit the GPU (N = 300, P =
-        // 700: 24.5 us against 28.9 at B = 18, 37.6 against 28.9 at B = 48),
-        // and past 2048 genomes up to 8 samples (N = 160, P = 4000: 19.9 us
-        // against 32.0 at B = 4, 38.4 against 31.7 at B = 12).  Below 127 rows
-        // the chains are short and only the second holds (N = 126, P = 200,
-        // B = 12: 13.3 us against 12.8).
-        if (J.P > 2048 ? J.B <= 8 : J.N > 126 && (long long)J.P * J.B <= 16384) return FWD_LVL;
-    }
-    if (variant == FWD_AUTO || variant == FWD_REG || variant == FWD_REG2) {
-        // One launch for every class (figures at run_any): up to 126 rows while
-        // every wave is resident at once, up to 150 rows for four times as
-        // many, and always past that, where the launches per class leave the
-        // two largest at two waves per SIMD anyway.
-        const long long most = J.N <= 126 ? 2048 : (J.N <= 150 ? 8192 : units);
-        if (units <= most) return FWD_ANY;
-    }
-    return variant;
+    // Few samples: the level mapping, whose lanes share a genome's nodes,
+    // has the shorter chain while its waves fit the GPU (N = 300, P =
+    // 700: 24.5 us against 28.9 at B = 18, 37.6 against 28.9 at B = 48),
+    // and past 2048 genomes up to 8 samples (N = 160, P = 4000: 19.9 us
+    // against 32.0 at B = 4, 38.4 against 31.7 at B = 12).  Below 127 rows
+    // the chains are short and only the second holds (N = 126, P = 200,
+    // B = 12: 13.3 us against 12.8).
+    if (J.P > 2048 ? J.B <= 8 : J.N > 126 && (long long)J.P * J.B <= 16384) return FWD_LVL;
+    // One launch for every class (figures at run_any): up to 126 rows while
+    // every wave is resident at once, up to 150 rows for four times as
+    // many, and always past that, where the launches per class leave the
+    // two largest at two waves per SIMD anyway.
+    const long long most = J.N <= 126 ? 2048 : (J.N <= 150 ? 8192 : units);
+    return units <= most ? FWD_ANY : FWD_AUTO;
 }
 
 int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
@@ -1412,7 +1405,7 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const FwdJob &J = jobs[j];
         if (J.P == 0 || J.B == 0) continue;
         const int top = max_class(J.N);
-        const int variant = resolve_variant(J, J.variant >= 0 ? J.variant : plan_variant, n, max_lds);
+        const int variant = J.variant >= 0 ? J.variant : plan_variant;
         if ((variant == FWD_LVL || variant == FWD_SEG) && !J.side && !J.recurrent) {
             // the level and segment mappings: every genome, one launch per
             // mapping over all items (the segment mapping also keeps N_max + 1

@@ -48,6 +48,7 @@ hipError_t launch_classify_batch(const TopoItem *dev_items, int n, hipStream_t s
 
 // Forward variants (value stores of the lane-per-sample mapping).
 constexpr int FWD_AUTO = 0;  // per slot class: registers, R64 with two samples per lane when B > 64
+                             // (four for populations of at most 30 rows that fill the GPU)
 constexpr int FWD_REG = 1;   // registers, one sample per lane (LDS rows for the LDS class)
 constexpr int FWD_LDS = 2;   // every genome in LDS rows
 constexpr int FWD_REG2 = 3;  // as FWD_REG, R64 genomes two samples per lane
@@ -138,9 +139,11 @@ const char *kind_name(int kind);
 // NEAT_OK or an error code with a message in err.
 int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
                  std::vector<FwdKernelLaunch> &out, char *err, size_t errlen);
-// The variant of one of several jobs that share the GPU, where none is tuned
-// for its bucket: in_order when the plan's launches follow one another on a
-// stream instead of running side by side.
+// What FWD_AUTO stands for, by a job's sizes (the plan takes a variant as it
+// is: FWD_AUTO itself is a launch per class there): for a call's only job,
+int alone_variant(const FwdJob &job, size_t max_lds);
+// and for one of several that share the GPU, in_order when the plan's launches
+// follow one another on a stream instead of running side by side.
 int shared_variant(const FwdJob &job, bool in_order, size_t max_lds);
 // Launch one planned kernel.  dev_items: the launch's items in device memory
 // (may be nullptr when the launch has a single item, passed inline).

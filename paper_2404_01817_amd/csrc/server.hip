@@ -96,8 +96,8 @@ class HipExec : public neat::sched::Executor<Payload> {
                                       grid ? r.grid_side : 0, r.grid_first);
             j.variant = neat::tuned_variant(q->pop->d.N_max, q->pop->d.C_max, r.B, grid, tp);
             // other slots' launches run beside this one's
-            if (tp && j.variant == neat::FWD_AUTO)
-                j.variant = neat::shared_variant(j, false, lds);
+            if (j.variant == neat::FWD_AUTO)
+                j.variant = tp ? neat::shared_variant(j, false, lds) : neat::alone_variant(j, lds);
             jobs.push_back(j);
         }
         std::vector<neat::FwdKernelLaunch> fw;

@@ -1,0 +1,71 @@
+"""CPU: the forward planner (forward_plan and the rules of NEAT_FWD_AUTO,
+csrc/forward.hip), called from a small host program linked against libneat.so
+(tests/plan_probe.cpp): what each call launches, without a GPU."""
+from __future__ import annotations
+
+import json
+import os
+import subprocess
+
+import pytest
+
+import paper_2404_01817_amd as neat
+from paper_2404_01817_amd._lib import LIB_PATH
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LDS = 163840
+AS_IS, GRAPH, IN_ORDER = -1, 0, 1
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    if not os.path.exists(LIB_PATH):
+        from paper_2404_01817_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_probe")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", rocm + "/include",
+                        "-I", os.path.join(ROOT, "include"),
+                        "-I", os.path.join(ROOT, "paper_2404_01817_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "plan_probe.cpp"), LIB_PATH,
+                        "-Wl,-rpath," + os.path.dirname(LIB_PATH) + ":" + rocm + "/lib", "-L", rocm + "/lib",
+                        "-lamdhip64", "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(plans):
+        """plans: (how, jobs); job: dict of P, N, B, and optionally C, I, O, side, variant,
+        recurrent, aligned."""
+        text = ""
+        for how, jobs in plans:
+            text += "%d %d %d\n" % (how, LDS, len(jobs))
+            for j in jobs:
+                full = dict(dict(C=4 * j["N"], I=5, O=2, side=0, variant=neat.FWD_AUTO, recurrent=0,
+                                 aligned=1), **j)
+                text += " ".join(str(full[k]) for k in ("P", "N", "C", "I", "O", "B", "side",
+                                                        "variant", "recurrent", "aligned")) + "\n"
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        out = [json.loads(l) for l in r.stdout.splitlines()]
+        assert len(out) == len(plans)
+        return out
+    return run
+
+
+def kinds(p):
+    return [l["kind"] for l in p["launches"]]
+
+
+PER_CLASS = {50: [], 100: ["r128"], 200: ["r128", "r224"], 300: ["r128", "r224", "lds"]}
+
+
+@pytest.mark.parametrize("how", [AS_IS, GRAPH, IN_ORDER])
+@pytest.mark.parametrize("N", sorted(PER_CLASS))
+@pytest.mark.parametrize("P,B", [(3, 1), (50, 65), (4000, 300)])
+def test_explicit_variants_are_launches_per_class(plan, how, N, P, B):
+    """NEAT_FWD_REG and NEAT_FWD_REG2 mean the stores that their names say,
+    alone and beside other populations, whatever the sizes."""
+    for variant, first in ((neat.FWD_REG, "r64"), (neat.FWD_REG2, "r64x2")):
+        for others in ([], [dict(P=7, N=60, B=3, variant=neat.FWD_SEG)]):
+            got, = plan([(how, [dict(P=P, N=N, B=B, variant=variant)] + others)])
+            assert got["rc"] == 0
+            assert kinds(got) == [first] + PER_CLASS[N] + (["seg"] if others else [])
