@@ -196,6 +196,12 @@ class Scheduler {
         return NEAT_OK;
     }
 
+    // Threads asleep in wait.
+    int waiting() {
+        std::lock_guard<std::mutex> lk(m_);
+        return waiters_;
+    }
+
     Stats stats() {
         std::lock_guard<std::mutex> lk(m_);
         Stats s;
