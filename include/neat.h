@@ -207,7 +207,8 @@ int neat_forward_ex(const neat_dims *dims, const void *program, const float *inp
  * NEAT_TUNE_CANDIDATES mappings -- NEAT_FWD_REG, NEAT_FWD_REG2, NEAT_FWD_LDS
  * (lane per sample, three value stores), NEAT_FWD_LVL (lanes over a level's
  * nodes) and NEAT_FWD_SEG (lanes over a level's in-edges, segmented
- * reduction) -- on the caller's buffers, one warm-up and `reps`
+ * reduction) -- and NEAT_FWD_AUTO's choice where it launches none of these
+ * (its time is not reported) on the caller's buffers, one warm-up and `reps`
  * launches each, with HIP events on `stream`, in two ways: the population
  * alone (latency), and as many copies of it in one launch as fill the GPU
  * (about 16 waves per CU, at most 64 copies; throughput per copy).  It
@@ -229,8 +230,9 @@ int neat_forward_ex(const neat_dims *dims, const void *program, const float *inp
  *   arguments as neat_forward_ex (outputs are overwritten; they end with the
  *                latency winner's result);
  *   reps         launches timed per variant, 1..1000
- *   variant_out  (host, written) the latency winner; NEAT_FWD_AUTO when
- *                P = 0 or B = 0 (nothing is timed or recorded)
+ *   variant_out  (host, written) the latency winner (NEAT_FWD_AUTO when its
+ *                own choice is it); NEAT_FWD_AUTO when P = 0 or B = 0 (nothing
+ *                is timed or recorded)
  *   ms_out       [2 * NEAT_TUNE_CANDIDATES] (host, written, nullable): mean
  *                ms per launch of REG, REG2, LDS, LVL and SEG alone, then mean
  *                ms per copy of the same five on a full GPU (-1 when untimed)
@@ -248,7 +250,7 @@ int neat_autotune_forward(const neat_dims *dims, const void *program, const floa
  * The variant the autotuner recorded for the bucket of (dims->N_max,
  * dims->C_max, B, grid != 0): the latency winner (throughput = 0) or the
  * throughput winner (throughput != 0); NEAT_FWD_AUTO for a bucket never
- * tuned.  Host only, thread-safe.  Errors: NEAT_E_INVALID (bad dims or
+ * tuned, and for one where the automatic choice was fastest.  Host only, thread-safe.  Errors: NEAT_E_INVALID (bad dims or
  * B < 0).
  */
 int32_t neat_tuned_variant(const neat_dims *dims, int32_t B, int32_t grid, int32_t throughput);

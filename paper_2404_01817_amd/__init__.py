@@ -138,8 +138,9 @@ def autotune_forward(dims: Dims, program, inputs, B: int, outputs=None, reps: in
     """Time the forward variants on these buffers and record the fastest for
     the call's bucket (neat_autotune_forward); returns (latency winner, [ms
     of FWD_REG, FWD_REG2, FWD_LDS, FWD_LVL, FWD_SEG alone, then per copy on
-    a full GPU]).  Later calls with variant=FWD_TUNED, and
-    batches, use the recorded variant."""
+    a full GPU]).  FWD_AUTO is the winner when its own choice is none of these
+    and faster (its time is not returned).  Later calls with
+    variant=FWD_TUNED, and batches, use the recorded variant."""
     stride, outputs = _io(dims, inputs, B, False, outputs)
     v = ctypes.c_int32(0)
     ms = (ctypes.c_float * (2 * TUNE_CANDIDATES))()

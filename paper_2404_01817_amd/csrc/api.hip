@@ -212,6 +212,35 @@ unsigned tune_generation() {
     tune_env_locked();
     return g_tune_gen;
 }
+// Whether two plans launch the same kernels over the same tiles.
+static bool same_launches(const std::vector<FwdKernelLaunch> &a,
+                          const std::vector<FwdKernelLaunch> &b) {
+    if (a.size() != b.size()) return false;
+    for (size_t k = 0; k < a.size(); ++k) {
+        if (a[k].kind != b[k].kind || a[k].grid != b[k].grid || a[k].block != b[k].block ||
+            a[k].items.size() != b[k].items.size())
+            return false;
+        for (size_t i = 0; i < a[k].items.size(); ++i) {
+            const FwdItem &x = a[k].items[i], &y = b[k].items[i];
+            if (x.cls != y.cls || x.tiles != y.tiles || x.tpw != y.tpw || x.lvl_sh != y.lvl_sh)
+                return false;
+        }
+    }
+    return true;
+}
+int tune_auto(const FwdJob &job, int copies, bool throughput, size_t max_lds) {
+    const int own = throughput ? shared_variant(job, true, max_lds) : alone_variant(job, max_lds);
+    const std::vector<FwdJob> jobs(copies, job);
+    std::vector<FwdKernelLaunch> mine, other;
+    char err[256] = "";
+    if (forward_plan(jobs.data(), copies, own, max_lds, mine, err, sizeof(err)) != NEAT_OK)
+        return -1;
+    for (int v : TUNE_CANDIDATES)
+        if (forward_plan(jobs.data(), copies, v, max_lds, other, err, sizeof(err)) == NEAT_OK &&
+            same_launches(mine, other))
+            return -1;
+    return own;
+}
 int tune_cache_use(const char *path) {
     if (!path || !*path) return NEAT_OK;
     std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -364,16 +393,14 @@ int neat_autotune_forward(const neat_dims *d, const void *program, const float *
     rc = check_forward_args(d, program, inputs, input_genome_stride, B, outputs, false, 0, 0);
     if (rc != NEAT_OK) return rc;
     constexpr int NC = NEAT_TUNE_CANDIDATES;
-    const int cand[NC] = {NEAT_FWD_REG, NEAT_FWD_REG2, NEAT_FWD_LDS, NEAT_FWD_LVL,
-                          NEAT_FWD_SEG};
     float ms[2 * NC];
     for (float &m : ms) m = -1.0f;
-    int best = NEAT_FWD_AUTO, best_tp = NEAT_FWD_AUTO;
+    int best[2] = {NEAT_FWD_AUTO, NEAT_FWD_AUTO};  // alone, on a full GPU
     if (d->P > 0 && B > 0) {
         // copies of the population that fill the GPU (about 16 waves per CU
         // of lane-per-sample tiles), for the throughput timing
         const long long waves = (long long)d->P * ((B + 63) / 64);
-        const int copies = (int)std::max(1ll, std::min(64ll, (16384 + waves - 1) / waves));
+        const int full = (int)std::max(1ll, std::min(64ll, (16384 + waves - 1) / waves));
         const neat::FwdJob job =
             make_job(d, program, inputs, input_genome_stride, B, outputs, 0, 0);
         hipEvent_t e0, e1;
@@ -383,15 +410,24 @@ int neat_autotune_forward(const neat_dims *d, const void *program, const float *
             return hip_fail(hipGetLastError(), "event");
         }
         const hipStream_t s = (hipStream_t)stream;
-        float best_ms = 0.0f, best_tp_ms = 0.0f;
-        for (int i = 0; i < NC && rc == NEAT_OK; ++i) {
-            rc = time_copies(job, 1, cand[i], reps, e0, e1, s, &ms[i]);
-            if (rc == NEAT_OK) rc = time_copies(job, copies, cand[i], reps, e0, e1, s, &ms[NC + i]);
-            if (rc != NEAT_OK) break;
-            ms[NC + i] /= (float)copies;
-            if (best == NEAT_FWD_AUTO || ms[i] < best_ms) best = cand[i], best_ms = ms[i];
-            if (best_tp == NEAT_FWD_AUTO || ms[NC + i] < best_tp_ms)
-                best_tp = cand[i], best_tp_ms = ms[NC + i];
+        for (int w = 0; w < 2 && rc == NEAT_OK; ++w) {
+            const int copies = w ? full : 1;
+            float best_ms = 0.0f;
+            for (int i = 0; i < NC && rc == NEAT_OK; ++i) {
+                float &t = ms[w * NC + i];
+                rc = time_copies(job, copies, neat::TUNE_CANDIDATES[i], reps, e0, e1, s, &t);
+                if (rc != NEAT_OK) break;
+                t /= (float)copies;
+                if (i == 0 || t < best_ms) best[w] = neat::TUNE_CANDIDATES[i], best_ms = t;
+            }
+            // the automatic choice, where it launches none of these: recorded
+            // as NEAT_FWD_AUTO when it is the fastest
+            const int own = neat::tune_auto(job, copies, w == 1, max_lds_bytes());
+            if (rc == NEAT_OK && own >= 0) {
+                float t = 0.0f;
+                rc = time_copies(job, copies, own, reps, e0, e1, s, &t);
+                if (rc == NEAT_OK && t / (float)copies < best_ms) best[w] = NEAT_FWD_AUTO;
+            }
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
@@ -401,18 +437,18 @@ int neat_autotune_forward(const neat_dims *d, const void *program, const float *
         const unsigned long long key = tune_key(d->N_max, d->C_max, B, 0);
         int &slot = g_tune[key];
         int &slot_tp = g_tune_tp[key];
-        if (slot != best || slot_tp != best_tp) ++g_tune_gen;
-        slot = best;
-        slot_tp = best_tp;
+        if (slot != best[0] || slot_tp != best[1]) ++g_tune_gen;
+        slot = best[0];
+        slot_tp = best[1];
         tune_write_locked();
     }
     // the outputs end with the recorded latency winner's result
     if (d->P > 0 && B > 0) {
-        rc = forward_common(d, program, inputs, input_genome_stride, B, outputs, best, false, 0, 0,
-                            stream);
+        rc = forward_common(d, program, inputs, input_genome_stride, B, outputs, best[0], false, 0,
+                            0, stream);
         if (rc != NEAT_OK) return rc;
     }
-    *variant_out = best;
+    *variant_out = best[0];
     if (ms_out)
         for (int i = 0; i < 2 * NC; ++i) ms_out[i] = ms[i];
     return NEAT_OK;

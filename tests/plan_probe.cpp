@@ -2,13 +2,16 @@
 // GPU: linked against libneat.so, whose planner is host code.  Standard input,
 // one plan per line: "how max_lds n", then n times "P N C I O B side variant
 // recurrent aligned".  how: -1 takes every job's variant as it is, 0 resolves
-// FWD_AUTO as a batch recorded into a graph does, 1 as one launched in order.
+// FWD_AUTO as a batch recorded into a graph does, 1 as one launched in order, 2
+// and 3 plan n copies of the (first) job with what the autotuner times for
+// FWD_AUTO alone and on a full GPU ("tune": that variant; no launches for -1).
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
 
 #include "launch.h"
 #include "neat.h"
+#include "tune.h"
 
 int main() {
     int how, n;
@@ -23,14 +26,22 @@ int main() {
             j.inputs = (const float *)(size_t)(aligned ? 4096 : 4100);
             j.gstride = 4 * (((long long)j.B * j.I + 3) / 4);
             j.sweeps = j.recurrent ? 3 : 0;
-            if (how >= 0 && j.variant == neat::FWD_AUTO)
+            if (how >= 0 && how < 2 && j.variant == neat::FWD_AUTO)
                 j.variant = n > 1 ? neat::shared_variant(j, how == 1, lds)
                                   : neat::alone_variant(j, lds);
         }
+        int tune = -2;
+        if (how >= 2) {
+            jobs[0].variant = -1;
+            tune = neat::tune_auto(jobs[0], n, how == 3, lds);
+            for (neat::FwdJob &j : jobs) j.variant = tune;
+        }
         std::vector<neat::FwdKernelLaunch> out;
         char err[256] = "";
-        const int rc = neat::forward_plan(jobs.data(), n, neat::FWD_AUTO, lds, out, err, sizeof(err));
-        std::printf("{\"rc\": %d, \"launches\": [", rc);
+        int rc = NEAT_OK;
+        if (tune != -1)
+            rc = neat::forward_plan(jobs.data(), n, neat::FWD_AUTO, lds, out, err, sizeof(err));
+        std::printf("{\"rc\": %d, \"tune\": %d, \"launches\": [", rc, tune);
         for (size_t k = 0; k < out.size(); ++k) {
             const neat::FwdKernelLaunch &L = out[k];
             std::printf("%s{\"kind\": \"%s\", \"grid_mode\": %d, \"grid\": %u, \"block\": %u, \"lds\": "

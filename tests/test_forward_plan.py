@@ -14,7 +14,7 @@ from paper_2404_01817_amd._lib import LIB_PATH
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LDS = 163840
-AS_IS, GRAPH, IN_ORDER = -1, 0, 1
+AS_IS, GRAPH, IN_ORDER, TUNE_ALONE, TUNE_FULL = -1, 0, 1, 2, 3
 
 
 @pytest.fixture(scope="module")
@@ -69,3 +69,37 @@ def test_explicit_variants_are_launches_per_class(plan, how, N, P, B):
             got, = plan([(how, [dict(P=P, N=N, B=B, variant=variant)] + others)])
             assert got["rc"] == 0
             assert kinds(got) == [first] + PER_CLASS[N] + (["seg"] if others else [])
+
+
+CANDIDATES = [neat.FWD_REG, neat.FWD_REG2, neat.FWD_LDS, neat.FWD_LVL, neat.FWD_SEG]
+
+
+@pytest.mark.parametrize("N", [8, 30, 31, 62, 63, 126, 140, 151, 222, 223, 300, 500, 1000])
+def test_the_autotuner_times_what_untuned_calls_launch(plan, N):
+    """For every population the launches of NEAT_FWD_AUTO, alone and beside others on one
+    stream, are those of a timed candidate, or timed beside them."""
+    plans, sizes = [], []
+    for P in (1, 40, 700, 5000, 40000):
+        for B in (1, 9, 64, 65, 192, 1000):
+            job = dict(P=P, N=N, B=B, I=4, O=2)
+            full = max(1, min(64, -(-16384 // (P * -(-B // 64)))))
+            for copies, how, tune in ((1, IN_ORDER, TUNE_ALONE), (full, IN_ORDER, TUNE_FULL)):
+                if copies == 1 and tune == TUNE_FULL:
+                    continue
+                sizes.append((P, B, copies))
+                plans.append((how, [job] * copies))
+                plans.append((tune, [job] * copies))
+                plans += [(AS_IS, [dict(job, variant=v)] * copies) for v in CANDIDATES]
+    out = plan(plans)
+    step = 2 + len(CANDIDATES)
+    own = 0
+    for k, size in enumerate(sizes):
+        untuned, tuned, *cands = out[step * k:step * k + step]
+        if tuned["tune"] == -1:
+            assert any(c["launches"] == untuned["launches"] for c in cands), size
+        else:
+            own += 1
+            assert tuned["launches"] == untuned["launches"], size
+            assert all(c["launches"] != untuned["launches"] for c in cands), size
+    # four samples per lane, and one launch for every class, are no candidate's
+    assert (own > 0) == (N <= 30 or N > 62)
