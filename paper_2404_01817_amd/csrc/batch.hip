@@ -182,30 +182,22 @@ int plan_host(const neat_batch_item *items, int32_t n, bool in_order, HostPlan &
     hp.topo_host.insert(hp.topo_host.end(), all_topo.begin(), all_topo.end());
     hp.n_topo = (int)all_topo.size();
 
+    // every item with the variant tuned for its bucket's throughput (the
+    // batch fills the GPU), or the one its sizes suggest while none is; one
+    // launch per kernel kind over all of them
     std::vector<neat::FwdJob> jobs;
-    std::vector<int> job_variant;
     for (int32_t k = 0; k < n; ++k) {
         const neat_batch_item &it = items[k];
         if (it.dims.P == 0 || it.B == 0) continue;
         jobs.push_back(make_job(&it.dims, it.program, it.inputs, it.input_genome_stride, it.B,
                                 it.outputs, it.grid_side, it.grid_first));
-        job_variant.push_back(
-            neat::tuned_variant(it.dims.N_max, it.dims.C_max, it.B, it.grid_side > 0, 1));
-    }
-    // every item with the variant tuned for its bucket's throughput (the
-    // batch fills the GPU), or the one its sizes suggest while none is; one
-    // launch per kernel kind over all of them
-    for (size_t j = 0; j < jobs.size(); ++j) {
-        jobs[j].variant = job_variant[j];
-        if (jobs[j].variant == neat::FWD_AUTO)
-            jobs[j].variant = jobs.size() > 1
-                                  ? neat::shared_variant(jobs[j], in_order, max_lds_bytes())
-                                  : neat::alone_variant(jobs[j], max_lds_bytes());
+        jobs.back().variant =
+            neat::tuned_variant(it.dims.N_max, it.dims.C_max, it.B, it.grid_side > 0, 1);
     }
     if (!jobs.empty()) {
         char err[256] = "";
-        const int rc = neat::forward_plan(jobs.data(), (int)jobs.size(), neat::FWD_AUTO,
-                                          max_lds_bytes(), hp.fw, err, sizeof(err));
+        const int rc = neat::forward_plan_auto(jobs, in_order, max_lds_bytes(), hp.fw, err,
+                                               sizeof(err));
         if (rc != NEAT_OK) return fail(rc, "%s", err);
     }
     // work-unit tables of the launches with more than one item

@@ -1552,6 +1552,41 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
     return NEAT_OK;
 }
 
+int forward_plan_auto(std::vector<FwdJob> &jobs, bool in_order, size_t max_lds,
+                      std::vector<FwdKernelLaunch> &out, char *err, size_t errlen) {
+    std::vector<size_t> own;  // jobs that a rule takes off the launches per class
+    int I = 0, O = 0, rows = 0;
+    for (size_t k = 0; k < jobs.size(); ++k) {
+        FwdJob &J = jobs[k];
+        I = std::max(I, J.I), O = std::max(O, J.O);
+        rows = std::max(rows, class_slots(max_class(J.N), J.N));
+        if (J.variant != FWD_AUTO) continue;
+        J.variant = jobs.size() > 1 ? shared_variant(J, in_order, max_lds)
+                                    : alone_variant(J, max_lds);
+        if (J.variant != FWD_AUTO) own.push_back(k);
+    }
+    // A launch over several jobs reserves the largest input staging and the
+    // largest output staging or rows of any of them, which need not belong to
+    // one job: only while even their sum fits, all jobs taken together, can no
+    // plan be refused.  Else what is refused is what the launches per class
+    // refuse, and they are the plan where the other one does not fit.
+    const bool roomy =
+        sizeof(float) * ((size_t)(2 * WAVE) * (I + O + 1) + GRID_MAX_SIDE) <= max_lds &&
+        sizeof(float) * (size_t)WAVE * (I + rows) <= max_lds;
+    std::vector<FwdKernelLaunch> by_class;
+    if (!roomy && jobs.size() > 1 && !own.empty()) {
+        std::vector<FwdJob> plain = jobs;
+        for (size_t k : own) plain[k].variant = FWD_AUTO;
+        const int rc = forward_plan(plain.data(), (int)plain.size(), FWD_AUTO, max_lds, by_class,
+                                    err, errlen);
+        if (rc != NEAT_OK) return rc;
+    }
+    const int rc = forward_plan(jobs.data(), (int)jobs.size(), FWD_AUTO, max_lds, out, err, errlen);
+    if (rc == NEAT_OK || by_class.empty()) return rc;
+    out.swap(by_class);
+    return NEAT_OK;
+}
+
 size_t recurrent_lds_bytes(int N, int I, int ld) {
     return sizeof(float) * (size_t)ld * ((size_t)I + 2 * (size_t)class_slots(max_class(N), N));
 }

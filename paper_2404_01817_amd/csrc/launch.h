@@ -145,6 +145,10 @@ int alone_variant(const FwdJob &job, size_t max_lds);
 // and for one of several that share the GPU, in_order when the plan's launches
 // follow one another on a stream instead of running side by side.
 int shared_variant(const FwdJob &job, bool in_order, size_t max_lds);
+// The plan of a call's jobs, every one with a variant; FWD_AUTO among them is
+// replaced by what it stands for.
+int forward_plan_auto(std::vector<FwdJob> &jobs, bool in_order, size_t max_lds,
+                      std::vector<FwdKernelLaunch> &out, char *err, size_t errlen);
 // Launch one planned kernel.  dev_items: the launch's items in device memory
 // (may be nullptr when the launch has a single item, passed inline).
 hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hipStream_t stream,

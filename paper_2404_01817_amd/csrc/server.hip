@@ -87,7 +87,6 @@ class HipExec : public neat::sched::Executor<Payload> {
         std::vector<neat::FwdJob> jobs;
         jobs.reserve(batch.size());
         const int tp = batch.size() > 1 ? 1 : 0;
-        const size_t lds = max_lds_bytes();
         for (const Payload *q : batch) {
             const neat_request &r = q->r;
             const bool grid = r.input_mode == NEAT_INPUT_GRID;
@@ -95,15 +94,12 @@ class HipExec : public neat::sched::Executor<Payload> {
                                       r.input_genome_stride, r.B, r.outputs,
                                       grid ? r.grid_side : 0, r.grid_first);
             j.variant = neat::tuned_variant(q->pop->d.N_max, q->pop->d.C_max, r.B, grid, tp);
-            // other slots' launches run beside this one's
-            if (j.variant == neat::FWD_AUTO)
-                j.variant = tp ? neat::shared_variant(j, false, lds) : neat::alone_variant(j, lds);
             jobs.push_back(j);
         }
         std::vector<neat::FwdKernelLaunch> fw;
         char err[256] = "";
-        int rc = neat::forward_plan(jobs.data(), (int)jobs.size(), neat::FWD_AUTO, lds, fw, err,
-                                    sizeof(err));
+        // (other slots' launches run beside this one's)
+        int rc = neat::forward_plan_auto(jobs, false, max_lds_bytes(), fw, err, sizeof(err));
         if (rc != NEAT_OK) return rc;
         // only launches of several items read a table; a launch of one item
         // takes it inline in its arguments, so a batch of single-item

@@ -26,9 +26,6 @@ int main() {
             j.inputs = (const float *)(size_t)(aligned ? 4096 : 4100);
             j.gstride = 4 * (((long long)j.B * j.I + 3) / 4);
             j.sweeps = j.recurrent ? 3 : 0;
-            if (how >= 0 && how < 2 && j.variant == neat::FWD_AUTO)
-                j.variant = n > 1 ? neat::shared_variant(j, how == 1, lds)
-                                  : neat::alone_variant(j, lds);
         }
         int tune = -2;
         if (how >= 2) {
@@ -39,7 +36,9 @@ int main() {
         std::vector<neat::FwdKernelLaunch> out;
         char err[256] = "";
         int rc = NEAT_OK;
-        if (tune != -1)
+        if (how == 0 || how == 1)
+            rc = neat::forward_plan_auto(jobs, how == 1, lds, out, err, sizeof(err));
+        else if (tune != -1)
             rc = neat::forward_plan(jobs.data(), n, neat::FWD_AUTO, lds, out, err, sizeof(err));
         std::printf("{\"rc\": %d, \"tune\": %d, \"launches\": [", rc, tune);
         for (size_t k = 0; k < out.size(); ++k) {

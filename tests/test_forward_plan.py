@@ -7,6 +7,7 @@ import json
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 import paper_2404_01817_amd as neat
@@ -103,3 +104,28 @@ def test_the_autotuner_times_what_untuned_calls_launch(plan, N):
             assert all(c["launches"] != untuned["launches"] for c in cands), size
     # four samples per lane, and one launch for every class, are no candidate's
     assert (own > 0) == (N <= 30 or N > 62)
+
+
+def test_batches_are_refused_exactly_when_their_launches_per_class_are(plan):
+    """Populations whose inputs and outputs fit a wave's LDS one by one and not together, and
+    others near that limit: what a batch launches for them by size changes nothing in what is
+    accepted."""
+    rng = np.random.default_rng(5)
+    lists = [[dict(P=100, N=400, I=300, O=10, B=64), dict(P=100, N=400, I=10, O=300, B=1000)],
+             [dict(P=100, N=310, I=300, O=10, B=100), dict(P=100, N=310, I=10, O=300, B=100)]]
+    for _ in range(400):
+        jobs = []
+        for _ in range(rng.integers(2, 5)):
+            N = int(rng.choice([130, 200, 320, 400, 640, 1000]))
+            I = int(rng.integers(1, min(N - 1, 340)))
+            jobs.append(dict(P=int(rng.choice([1, 100, 5000])), N=N, I=I,
+                             O=int(rng.integers(1, min(N - I, 340) + 1)),
+                             B=int(rng.choice([5, 64, 65, 1000]))))
+        lists.append(jobs)
+    for how in (GRAPH, IN_ORDER):
+        out = plan([(AS_IS, l) for l in lists] + [(how, l) for l in lists])
+        n = len(lists)
+        codes = [(a["rc"], b["rc"]) for a, b in zip(out[:n], out[n:])]
+        assert all(a == b for a, b in codes), [l for l, (a, b) in zip(lists, codes) if a != b][:3]
+        assert len(set(codes)) == 2  # some are accepted and some refused
+        assert all(l["lds"] <= LDS for p in out for l in p["launches"])
