@@ -435,21 +435,27 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
     const float *in_g = GRID ? nullptr : it->inputs + (size_t)g * it->gstride;
     const int vec4 = it->vec4;
     if (!GRID) dma_inputs(in_g + (size_t)t0 * TS * I, istage, min(TS, B - t0 * TS) * I, vec4);
-    // grid queries: the side coordinates and every sample's offset in the
-    // tile as digits (x, y, points past them), once per unit, after the staging
+    // grid queries: the side coordinates and (where LDS has room for the table,
+    // else in every tile) each sample's offset in the tile as digits (x, y,
+    // points past them), once per unit, after the staging
     float *ctab = istage + TS * I;
     unsigned *otab = (unsigned *)(ctab + GRID_MAX_SIDE);
     const unsigned uside = (unsigned)side, pts = uside * uside;
     const float rside = GRID ? 1.0f / (float)side : 0.0f;
     // digits of the tile's first query (points p1, p2) and of a tile's length
     unsigned x1_0 = 0, y1_0 = 0, x2_0 = 0, y2_0 = 0, tx = 0, ty = 0, tk = 0;
+    const bool tabulated = GRID && it->grid_table != 0;
+    auto digits = [&](unsigned o) {
+        const unsigned k = o / pts;
+        unsigned oy, ox;
+        divmod_small(o - k * pts, uside, rside, &oy, &ox);
+        return ox | (oy << 8) | (k << 16);
+    };
     if (GRID) {
         for (int i = (int)lane; i < side; i += WAVE) ctab[i] = grid_coord(i, side);
         for (int h = 0; h < SPL; ++h) {
-            const unsigned o = (unsigned)(h * WAVE) + lane, k = o / pts;
-            unsigned oy, ox;
-            divmod_small(o - k * pts, uside, rside, &oy, &ox);
-            otab[o] = ox | (oy << 8) | (k << 16);
+            const unsigned o = (unsigned)(h * WAVE) + lane;
+            if (tabulated) otab[o] = digits(o);
             istage[o * 5 + 4] = 1.0f;
         }
         const unsigned q0 = (unsigned)(it->first + (long long)t0 * TS);
@@ -475,7 +481,8 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
             const bool target = t == t0 || (tx | ty) != 0;
             for (int h = 0; h < SPL; ++h) {
                 float *x = istage + (h * WAVE + lane) * 5;
-                const unsigned o = otab[h * WAVE + lane];
+                const unsigned s = (unsigned)(h * WAVE) + lane;
+                const unsigned o = tabulated ? otab[s] : digits(s);
                 unsigned x2 = x2_0 + (o & 0xffu), y2 = y2_0 + ((o >> 8) & 0xffu);
                 unsigned x1 = x1_0 + (o >> 16), y1 = y1_0;
                 if (x2 >= uside) x2 -= uside, ++y2;
@@ -1464,16 +1471,16 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             it.P = J.P, it.N = J.N, it.C = J.C, it.I = J.I, it.O = J.O, it.B = J.B;
             it.side = J.side;
             it.prog_words = prog_words(J.N, J.C, J.O);
-            it.sweeps = J.recurrent ? J.sweeps : 0;
+            if (J.recurrent) it.sweeps = J.sweeps;
             const int TS = kind == KIND_ANY ? any_tile(J) : tile_samples(kind);
             it.tiles = (J.B + TS - 1) / TS;
             it.vec4 = (!J.side && ((uintptr_t)J.inputs % 16 == 0) && (J.gstride % 4 == 0)) ? 1 : 0;
             const int x = 2 * kind + (J.side ? 1 : 0);
             k[x].items.push_back(it);
-            // register kernels on grid queries keep the coordinates and the
-            // samples' offsets after the staged inputs
+            // register kernels on grid queries keep the coordinates after the
+            // staged inputs
             if (!J.side || !lds_kind(kind))
-                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE + TS : 0));
+                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE : 0));
             // outputs stored from registers leave only what touch_lines writes
             if (!lds_kind(kind))
                 ostage_max[x] = std::max(ostage_max[x], direct_kind(kind) ? WAVE : TS * J.O);
@@ -1494,6 +1501,13 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const size_t rows = (kind == KIND_LVL || kind == KIND_SEG) ? (size_t)rows_max[x]
                             : lds_kind(kind) ? (size_t)rows_max[x] * tile_samples(kind)
                                              : (size_t)ostage_max[x];
+        // and the samples' offsets where they fit beside the outputs (a table
+        // of them must not make a call too large)
+        if (K.grid_mode && !lds_kind(kind) &&
+            sizeof(float) * ((size_t)stage_max[x] + tile_samples(kind) + rows) <= max_lds) {
+            stage_max[x] += tile_samples(kind);
+            for (FwdItem &it : K.items) it.grid_table = 1;
+        }
         size_t wave_floats = (size_t)stage_max[x] + rows;
         if (kind == KIND_ANY) wave_floats = std::max(wave_floats, (size_t)rows_max[x]);
         const size_t wave_bytes = wave_floats * sizeof(float);

@@ -100,7 +100,10 @@ struct FwdItem {
     long long gstride, first, unit0;
     int P, N, I, O, B, side, vec4, cls;
     int tiles, tpw, chunks, prog_words;
-    int sweeps;  // recurrent kernel: sweeps per sample
+    union {
+        int sweeps;      // recurrent kernel: sweeps per sample
+        int grid_table;  // grid queries: the samples' offsets in a tile are tabulated in LDS
+    };
     int C;         // C_max (program layout)
     int lvl_sh;    // level and segment mappings: log2 of the samples per tile
     int lvl_rows;  // segment mapping: value rows before the edge offsets; any class: samples

@@ -129,3 +129,22 @@ def test_batches_are_refused_exactly_when_their_launches_per_class_are(plan):
         assert all(a == b for a, b in codes), [l for l, (a, b) in zip(lists, codes) if a != b][:3]
         assert len(set(codes)) == 2  # some are accepted and some refused
         assert all(l["lds"] <= LDS for p in out for l in p["launches"])
+
+
+@pytest.mark.parametrize("B,samples", [(64, 64), (65, 128), (5000, 128)])
+@pytest.mark.parametrize("N", [1000, 1024])
+def test_grid_queries_up_to_the_lds_of_their_staging(plan, N, B, samples):
+    """A wave holds a tile's five inputs, 256 coordinates and a tile's outputs: every O for
+    which these fit is accepted, and the table of offsets only where it fits too."""
+    floats = LDS // 4 - 256 - 5 * samples
+    top = floats // samples  # outputs
+    outs = [1, 100, top - 2, top - 1, top, top + 1]
+    got = plan([(AS_IS, [dict(P=3, N=N, I=5, O=O, B=B, side=16)]) for O in outs])
+    for O, g in zip(outs, got):
+        assert (g["rc"] == 0) == (O <= top), O
+        for l in g["launches"]:
+            s = {"r64x2": 128, "lds": 0, "lds32": 0}.get(l["kind"], 64)
+            for it in l["items"]:
+                assert it["table"] == (s > 0 and 4 * (s * (6 + O) + 256) <= LDS)
+            if s:
+                assert l["wave_floats"] == s * (5 + O + it["table"]) + 256
