@@ -1509,7 +1509,10 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             for (FwdItem &it : K.items) it.grid_table = 1;
         }
         size_t wave_floats = (size_t)stage_max[x] + rows;
-        if (kind == KIND_ANY) wave_floats = std::max(wave_floats, (size_t)rows_max[x]);
+        // (the waves' staging areas start at 16 bytes: their loads and stores are
+        // that wide, while a level mapping's rows may end anywhere)
+        if (kind == KIND_ANY)
+            wave_floats = std::max(wave_floats, (size_t)round_up(rows_max[x], 4));
         const size_t wave_bytes = wave_floats * sizeof(float);
         int waves = FWD_MAX_WAVES;
         while (waves > 1 && wave_bytes * waves > max_lds) --waves;

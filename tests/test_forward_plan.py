@@ -148,3 +148,20 @@ def test_grid_queries_up_to_the_lds_of_their_staging(plan, N, B, samples):
                 assert it["table"] == (s > 0 and 4 * (s * (6 + O) + 256) <= LDS)
             if s:
                 assert l["wave_floats"] == s * (5 + O + it["table"]) + 256
+
+
+def test_wave_areas_start_at_16_bytes(plan):
+    """Inputs arrive in LDS and outputs leave it 16 bytes at a time: every wave's area and its
+    output staging start at a multiple of that, whatever the rows of the level mapping that
+    may share them."""
+    plans = [(how, [dict(P=P, N=N, I=I, O=O, B=B, variant=v)])
+             for how in (AS_IS, IN_ORDER) for v in (neat.FWD_AUTO, neat.FWD_REG)
+             for N in (31, 63, 127, 223, 365, 511, 512, 513, 601, 1022, 1023, 1024)
+             for I, O in ((1, 1), (3, 2), (9, 4)) for P in (3, 2500)
+             for B in (1, 2, 3, 30, 70, 300)]
+    for (_, (job,)), got in zip(plans, plan(plans)):
+        assert got["rc"] == 0
+        for l in got["launches"]:
+            if l["kind"] in ("lvl", "seg"):
+                continue  # words only
+            assert l["wave_floats"] % 4 == 0 and l["stage_floats"] % 4 == 0, (job, l)
