@@ -1343,6 +1343,37 @@ static bool classes_may_merge(const FwdJob &J, size_t max_lds) {
     return stage <= max_lds && (top != CLS_LDS || lds32 <= max_lds);
 }
 
+// Past 510 rows the level mapping's tiles hold two samples or one, and a genome
+// past the register classes walks its levels 32 or 64 times for every 64
+// samples of a launch for every class: some 500 us for a wave, whatever the
+// size of the call.  The level mapping alone spreads those walks over its own
+// waves, and LDS rows take them in one.  Calculation in us, launches per class /
+// one launch for every class / levels (a call's only population):
+//   N = 515, P = 700, B = 64: 342 / 476 / 169; B = 130: 346 / 941 / 399
+//   N = 515, P = 100, B = 300: 254 / 500 / 89; P = 1500, B = 64: 448 / 515 / 398
+//   N = 590, P = 700, B = 64: 330 / 491 / 180; P = 2500, B = 64: 779 / 597 / 512
+//   N = 590, P = 1500, B = 200: 689 / 1093 / 786; P = 5000, B = 64: 1044 / 733 / 1152
+//   N = 680, P = 700, B = 300: 960 / 1188 / 709; P = 5000, B = 64: 1596 / 1004 / 1430
+//   N = 780, P = 700, B = 130: 1190 / 1329 / 315; N = 850, P = 2500, B = 130: 4789 /
+//   2558 / 1330; N = 1000, P = 5000, B = 64: 5721 / 2070 / 1488
+// So the level mapping past 740 rows, where few genomes fit the registers, and
+// below while the call is small; else launches per class up to 660 rows where
+// most of a 64-sample tile is used.  Up to 530 rows genomes past the registers
+// are so rare that a population may have none, and the launches per class may
+// take half their time (N = 511: P = 700, B = 64: 114 / 48 / 162; P = 100, B =
+// 300: 115 / 48 / 77): lower lines.  Of several populations, on a GPU that is
+// full anyway, levels past 660 rows (4 of 700 .. 1000 rows, B = 20 .. 200: 2479 /
+// 1267 / 632; 4 of 515 .. 640, B = 100 .. 300: 1453 / 1558 / 1976).
+constexpr int NARROW_ROWS = 510;
+static int narrow_variant(const FwdJob &J, bool alone) {
+    const long long all = (long long)J.P * J.B;
+    if (J.N > 740) return FWD_LVL;
+    if (J.N > 660) return !alone || all <= 300000 ? FWD_LVL : FWD_ANY;
+    const bool rare = J.N <= 530;
+    if (alone && all <= (rare ? 30000 : 90000)) return FWD_LVL;
+    return J.B > (rare ? WAVE / 2 : WAVE) ? FWD_AUTO : FWD_ANY;
+}
+
 int shared_variant(const FwdJob &J, bool in_order, size_t max_lds) {
     if (!classes_may_merge(J, max_lds)) return FWD_AUTO;
     // The GPU is full, so only total work counts: the level mapping where a
@@ -1356,22 +1387,26 @@ int shared_variant(const FwdJob &J, bool in_order, size_t max_lds) {
     // also ends in its own tail, 804 / 660, 378 / 302, 286 / 216, 187 / 168,
     // 162 / 162, 311 / 246, 275 / 236.
     if (J.N > 222 && J.B <= 16) return FWD_LVL;
+    if (J.N > NARROW_ROWS) return narrow_variant(J, false);
     return J.N > (in_order ? 126 : 300) ? FWD_ANY : FWD_AUTO;
 }
 
 // One sample per lane where a call's only population, of 31 to 62 node rows,
 // has more than 64 inputs: two per lane share the scalar work of a node, but a
-// wave's chain is longer, and nothing is shared while every one-sample wave is
-// resident.  Calculation, two samples per lane / one, us: N = 50, P = 157, B =
-// 128: 8.7 / 7.3; N = 62, P = 157, B = 200: 8.8 / 7.5; N = 37, P = 1000, B =
-// 256 (4000 waves): 8.6 / 8.3; N = 45, P = 2500, B = 65 (5000): 9.7 / 10.4.
-// Three tiles of 64 leave a quarter of two-sample tiles empty (B = 192, P =
-// 5000: N = 45: 24.8 / 23.2, N = 62: 31.3 / 28.2).  Up to 30 rows nothing is
-// gained (N = 20, P = 1500, B = 192: 6.6 / 7.1).
+// wave's chain is longer, and nothing is shared while three one-sample waves
+// per SIMD are all that there are.  Calculation, two samples per lane / one,
+// us: N = 50, P = 157, B = 128 (314 waves): 7.7 / 7.2; P = 1500, B = 128
+// (3000): 9.1 / 8.5; P = 1000, B = 200 (4000): 8.9 / 9.5; N = 31, P = 1500, B =
+// 128: 7.0 / 6.8; P = 1000, B = 200: 7.0 / 7.5.  Three tiles of 64 leave a
+// quarter of two-sample tiles empty, which counts once the waves are many (N =
+// 62, B = 192: P = 1500, 4500 waves: 11.5 / 12.8; P = 3000: 19.4 / 19.4; P =
+// 8000: 43.4 / 40.7).  Up to 30 rows nothing is gained (N = 20, P = 1500, B =
+// 192: 6.6 / 7.1).
 static bool one_sample(const FwdJob &J) {
     const int tiles = (J.B + WAVE - 1) / WAVE;
+    const long long waves = (long long)J.P * tiles;
     return !J.side && !J.recurrent && J.N > SMALL_ROWS && max_class(J.N) == CLS_R64 &&
-           ((long long)J.P * tiles <= 4096 || tiles == 3);
+           (waves <= 3072 || (tiles == 3 && waves > 8192));
 }
 
 int alone_variant(const FwdJob &J, size_t max_lds) {
@@ -1382,15 +1417,24 @@ int alone_variant(const FwdJob &J, size_t max_lds) {
     // has the shorter chain while its waves fit the GPU (N = 300, P =
     // 700: 24.5 us against 28.9 at B = 18, 37.6 against 28.9 at B = 48),
     // and past 2048 genomes up to 8 samples (N = 160, P = 4000: 19.9 us
-    // against 32.0 at B = 4, 38.4 against 31.7 at B = 12).  Below 127 rows
-    // the chains are short and only the second holds (N = 126, P = 200,
-    // B = 12: 13.3 us against 12.8).
-    if (J.P > 2048 ? J.B <= 8 : J.N > 126 && (long long)J.P * J.B <= 16384) return FWD_LVL;
-    // One launch for every class (figures at run_any): up to 126 rows while
-    // every wave is resident at once, up to 150 rows for four times as
-    // many, and always past that, where the launches per class leave the
-    // two largest at two waves per SIMD anyway.
-    const long long most = J.N <= 126 ? 2048 : (J.N <= 150 ? 8192 : units);
+    // against 32.0 at B = 4, 38.4 against 31.7 at B = 12).  The chains of
+    // up to 130 rows are short and only the second holds (N = 127, P = 2000, B
+    // = 4: levels 18.5, one launch for every class 15.1), from 121 rows on (P =
+    // 5000, B = 2, launches per class / levels: N = 80: 17.6 / 19.0; N = 113:
+    // 21.9 / 25.5; N = 126: 27.6 / 25.0).
+    if (J.P > 2048 ? J.B <= 8 && J.N > 120 : J.N > 130 && (long long)J.P * J.B <= 16384)
+        return FWD_LVL;
+    if (J.N > NARROW_ROWS) return narrow_variant(J, true);
+    // One launch for every class (figures at run_any): up to 130 rows, where
+    // next to no genome needs the 224-register class and its launch ends at
+    // once, while every wave is resident (N = 127, P = 5000, B = 64: 27.1 us
+    // with launches per class against 36.0), up to 150 rows for four times as
+    // many (N = 133: 47.1 against 39.8; N = 140, P = 5000, B = 130: 78.9 against
+    // 81.7, B = 300: 104 against 113; N = 150: 143 against 123), and always past
+    // that, where the launches per class leave the two largest at two waves per
+    // SIMD anyway (P = 5000, B = 300: N = 151: 127 against 120; N = 160: 179
+    // against 128).
+    const long long most = J.N <= 130 ? 2048 : (J.N <= 150 ? 8192 : units);
     return units <= most ? FWD_ANY : FWD_AUTO;
 }
 

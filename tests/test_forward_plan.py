@@ -102,8 +102,9 @@ def test_the_autotuner_times_what_untuned_calls_launch(plan, N):
             own += 1
             assert tuned["launches"] == untuned["launches"], size
             assert all(c["launches"] != untuned["launches"] for c in cands), size
-    # four samples per lane, and one launch for every class, are no candidate's
-    assert (own > 0) == (N <= 30 or N > 62)
+    # four samples per lane, and one launch for every class, are no candidate's (past 740 rows
+    # every population goes by levels)
+    assert (own > 0) == (N <= 30 or 62 < N <= 740)
 
 
 def test_batches_are_refused_exactly_when_their_launches_per_class_are(plan):
@@ -165,3 +166,40 @@ def test_wave_areas_start_at_16_bytes(plan):
             if l["kind"] in ("lvl", "seg"):
                 continue  # words only
             assert l["wave_floats"] % 4 == 0 and l["stage_floats"] % 4 == 0, (job, l)
+
+
+# (P, N, B), what a call's only population launches: both sides of every line of the rule
+ALONE = [
+    ((3072, 31, 64), ["r64"]), ((1536, 50, 100), ["r64"]), ((1537, 50, 100), ["r64x2"]),
+    ((1024, 62, 192), ["r64"]), ((1025, 62, 192), ["r64x2"]), ((2731, 62, 192), ["r64"]),
+    ((2730, 62, 192), ["r64x2"]), ((100, 30, 100), ["r64x2"]),
+    ((3000, 120, 4), ["r64", "r128"]), ((3000, 121, 4), ["lvl"]), ((3000, 121, 9), ["r64", "r128"]),
+    ((2000, 130, 4), ["any"]), ((2000, 131, 4), ["lvl"]),
+    ((2048, 130, 64), ["any"]), ((2049, 130, 64), ["r64", "r128", "r224"]),
+    ((2049, 131, 64), ["any"]), ((8192, 150, 64), ["any"]),
+    ((8193, 150, 64), ["r64", "r128", "r224"]), ((8193, 151, 64), ["any"]),
+    ((512, 200, 32), ["lvl"]), ((513, 200, 32), ["any"]), ((2000, 510, 300), ["any"]),
+    ((100, 530, 300), ["lvl"]), ((101, 530, 300), ["r64x2", "r128", "r224", "lds"]),
+    ((2000, 530, 32), ["any"]), ((2000, 530, 33), ["r64", "r128", "r224", "lds"]),
+    ((300, 531, 300), ["lvl"]), ((301, 660, 300), ["r64x2", "r128", "r224", "lds32"]),
+    ((2000, 640, 64), ["any"]), ((2000, 640, 65), ["r64x2", "r128", "r224", "lds32"]),
+    ((1000, 661, 300), ["lvl"]), ((1001, 740, 300), ["any"]), ((9000, 741, 300), ["lvl"]),
+]
+
+
+def test_a_lone_population_takes_the_mapping_measured_best(plan):
+    out = plan([(GRAPH, [dict(P=P, N=N, B=B)]) for (P, N, B), _ in ALONE])
+    got = {k: kinds(o) for (k, _), o in zip(ALONE, out)}
+    assert got == dict(ALONE)
+
+
+def test_several_populations_past_510_rows(plan):
+    other = dict(P=9, N=20, B=5)
+    for how in (GRAPH, IN_ORDER):
+        for (P, N, B), want in [((500, 530, 32), ["any"]),
+                                ((500, 530, 33), ["r128", "r224", "lds"]),
+                                ((500, 640, 64), ["any"]), ((500, 640, 16), ["lvl"]),
+                                ((500, 640, 300), ["r64x2", "r128", "r224", "lds32"]),
+                                ((500, 661, 300), ["lvl"]), ((50000, 900, 300), ["lvl"])]:
+            got, = plan([(how, [dict(P=P, N=N, B=B), other])])
+            assert [k for k in kinds(got) if k != "r64"] == want, (how, P, N, B)
