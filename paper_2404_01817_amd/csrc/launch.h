@@ -126,11 +126,11 @@ struct FwdLaunch {
 };
 
 struct FwdKernelLaunch {
-    int kind;
-    int grid_mode;  // items generate CPPN grid queries
-    unsigned grid, block;
-    size_t lds;
-    FwdLaunch args;
+    int kind = 0;
+    int grid_mode = 0;  // items generate CPPN grid queries
+    unsigned grid = 0, block = 0;
+    size_t lds = 0;
+    FwdLaunch args{};
     std::vector<FwdItem> items;
 };
 

@@ -203,3 +203,15 @@ def test_several_populations_past_510_rows(plan):
                                 ((500, 661, 300), ["lvl"]), ((50000, 900, 300), ["lvl"])]:
             got, = plan([(how, [dict(P=P, N=N, B=B), other])])
             assert [k for k in kinds(got) if k != "r64"] == want, (how, P, N, B)
+
+
+def test_launches_come_in_the_order_of_the_kernels(plan):
+    """Whatever the order of the jobs (in-order batches run them so)."""
+    jobs = [dict(P=10, N=300, B=300, variant=neat.FWD_REG2), dict(P=10, N=20, B=5),
+            dict(P=10, N=40, I=5, O=1, B=50, side=16), dict(P=9, N=100, B=3, variant=neat.FWD_SEG),
+            dict(P=9, N=100, B=3, variant=neat.FWD_LVL), dict(P=3000, N=30, B=500)]
+    a, b = plan([(AS_IS, jobs), (AS_IS, jobs[::-1])])
+    order = [(l["kind"], l["grid_mode"]) for l in a["launches"]]
+    assert order == [("r64", 0), ("r64", 1), ("r64x2", 0), ("r128", 0), ("r224", 0), ("lds", 0),
+                     ("lvl", 0), ("seg", 0), ("r32x4", 0)]
+    assert [(l["kind"], l["grid_mode"]) for l in b["launches"]] == order
