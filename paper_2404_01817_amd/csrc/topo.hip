@@ -51,8 +51,8 @@ __device__ __forceinline__ bool is_int_in(float x, float lo, float hi_excl) {
 
 // Key -> row table: open addressing with linear probing in H = hash_size(N)
 // slots (a power of two, at least twice the rows, so probes end at an empty
-// slot).  Every well-formed key is inserted with the smallest row holding it.
-constexpr int HASH_EMPTY = -1;
+// slot).  Slots hold key + 1, empty ones 0 as the key map before it is filled.
+constexpr int HASH_EMPTY = 0;
 __host__ __device__ constexpr int hash_size(int N) {
     int h = 64;
     while (h < 2 * N) h *= 2;
@@ -61,15 +61,12 @@ __host__ __device__ constexpr int hash_size(int N) {
 __device__ __forceinline__ int hash_slot(int key, int H) {
     return (int)(((unsigned)key * 2654435761u) >> 8) & (H - 1);
 }
-// Returns the key's slot.
-__device__ __forceinline__ int hash_insert(int *hkey, int *hrow, int H, int key, int row) {
+// Returns the key's slot (its row is written once its rank is known).
+__device__ __forceinline__ int hash_insert(int *hkey, int H, int key) {
     int h = hash_slot(key, H);
     for (;;) {
-        const int old = atomicCAS(&hkey[h], HASH_EMPTY, key);
-        if (old == HASH_EMPTY || old == key) {
-            atomicMin(&hrow[h], row);
-            return h;
-        }
+        const int old = atomicCAS(&hkey[h], HASH_EMPTY, key + 1);
+        if (old == HASH_EMPTY || old == key + 1) return h;
         h = (h + 1) & (H - 1);
     }
 }
@@ -81,15 +78,14 @@ __device__ __forceinline__ int key_of(float k) {
     return ((float)i == k && (unsigned)i < (1u << 24)) ? i : -1;
 }
 
-// Table word of the well-formed key equal to k, or -1.  The word's low 16
-// bits are the first row among duplicates; one-wave groups later add the
-// key's rank above them.
+// Table word of the well-formed key equal to k, or -1: a row that holds it in
+// the low 16 bits, its rank above them.
 __device__ __forceinline__ int find_row(float k, const int *hkey, const int *hrow, int H) {
     if (!is_int_in(k, 0.0f, KEY_LIMIT)) return -1;
     const int key = (int)k;
     for (int h = hash_slot(key, H);; h = (h + 1) & (H - 1)) {
         const int kk = hkey[h];
-        if (kk == key) return hrow[h];
+        if (kk == key + 1) return hrow[h];
         if (kk == HASH_EMPTY) return -1;
     }
 }
@@ -407,20 +403,30 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
     // Keys below 32 H (evolution numbers its nodes from 0) are bits of a map:
     // a rank is a population count, a bit found set is a duplicate, and a
     // lookup is two dependent reads without a loop.  Measured against the
-    // table and the compared words, which keys past the map still take: 24.5
-    // against 30 us at 10,000 genomes of 50 node and 200 connection rows, 33.4
-    // against 39 us at 700 of 365 and 1460.  (A genome with a
-    // duplicate is rejected; its other status bits depend on keys only, and
+    // table and the compared words, which genomes with a key past the map still
+    // take: 24.5 against 30 us at 10,000 genomes of 50 node and 200 connection
+    // rows, 33.4 against 39 us at 700 of 365 and 1460.  Those genomes pay little
+    // for the question (16 of 50 and 200: 9.3 us, 9.0 without the map; 700 of 365
+    // and 1460: 40 us, 44.5 with the other steps of that time): one wave asks a
+    // ballot before it touches the zeros that both start from.  (A genome with
+    // a duplicate is rejected; its other status bits depend on keys only, and
     // the number of its rows is not used.)
     int rank = -1;
     int n_map = 0;  // keys in the map
     const unsigned bit = 1u << (key & 31);
     gsync(G);
-    bool dup = false;
-    if (key >= 32 * H) G.sh[SH_WIDE] = 1;
-    else if (key >= 0) dup = (unsigned)atomicOr(&k_map[key >> 5].x, (int)bit) & bit;
-    gsync(G);
-    const bool mapped = G.sh[SH_WIDE] == 0;
+    bool dup = false, mapped = true;
+    if constexpr (ONE) {
+        // known before the map is touched: the table starts from its zeros
+        mapped = __ballot(key >= 32 * H) == 0ull;
+        if (mapped && key >= 0) dup = (unsigned)atomicOr(&k_map[key >> 5].x, (int)bit) & bit;
+        gsync(G);
+    } else {
+        if (key >= 32 * H) G.sh[SH_WIDE] = 1;
+        else if (key >= 0) dup = (unsigned)atomicOr(&k_map[key >> 5].x, (int)bit) & bit;
+        gsync(G);
+        mapped = G.sh[SH_WIDE] == 0;
+    }
     if (mapped) {
         if (dup) st |= NEAT_ST_DUP_KEY;
         // keys below every word: a run of words per thread, at most four (H is
@@ -446,21 +452,20 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
     } else {
         const int rb = N <= 256 ? 8 : 10;  // row bits of the packed (key, row) words
         int my_h = -1;
-        gsync(G);  // SH_WIDE and the map have been read
-        if (t == 0) G.sh[SH_WIDE] = 0;
+        if constexpr (!ONE) {
+            gsync(G);  // SH_WIDE and the map have been read
+            if (t == 0) G.sh[SH_WIDE] = 0;
+            for (int i = t; i < H; i += W) h_key[i] = HASH_EMPTY;
+        }
         for (int i = t; i < N; i += W) {
             s_curi[i] = 0;
             s_skey[i] = -1;
-        }
-        for (int i = t; i < H; i += W) {
-            h_key[i] = HASH_EMPTY;
-            h_row[i] = 0x7fffffff;
         }
         if (!merge && t >= N && t < NS) s_stack[t] = -1;
         gsync(G);
         if (t < N) {
             if (key != -1) atomicAdd(&s_nvalid, 1);
-            if (key >= 0) my_h = hash_insert(h_key, h_row, H, key, t);
+            if (key >= 0) my_h = hash_insert(h_key, H, key);
             // (key, row) in one word: rows take rb bits, keys the rest (always
             // room when rows fit in 8 bits, keys being below 2^24; with 10 row
             // bits a key of 2^22 or more marks the genome as wide)
@@ -575,9 +580,6 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
         }
         return true;
     };
-    auto row_of = [&](float k) {
-        return mapped ? map_row(k, k_map, s_srow, H) : find_row(k, h_key, h_row, H);
-    };
     int sdp[CPRE];
     int lp[CPRE];  // larger groups: the edge's place in its in-list
     {
@@ -629,7 +631,7 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
                 bool more = false;
 #pragma unroll
                 for (int i = 0; i < 2 * CPRE; ++i) {
-                    const bool go = key2[i] >= 0 && hk[i] != key2[i] && hk[i] != HASH_EMPTY;
+                    const bool go = key2[i] >= 0 && hk[i] != key2[i] + 1 && hk[i] != HASH_EMPTY;
                     if (go) hs[i] = (hs[i] + 1) & (H - 1);
                     more |= go;
                 }
@@ -643,7 +645,7 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
             for (int i = 0; i < 2 * CPRE; ++i) asm volatile("" : "+v"(r2[i]));
 #pragma unroll
             for (int i = 0; i < 2 * CPRE; ++i)
-                r2[i] = (key2[i] >= 0 && hk[i] == key2[i]) ? r2[i] : -1;
+                r2[i] = (key2[i] >= 0 && hk[i] == key2[i] + 1) ? r2[i] : -1;
         }
         // the updates of all four rows in flight together; in one-wave groups a
         // row without an edge ORs 0 into row 0's mask
@@ -672,14 +674,18 @@ __device__ __forceinline__ void topo_genome(const TopoItem &a, size_t g, const G
                 if (old[k] & bits[k]) st |= NEAT_ST_DUP_EDGE;
         }
     }
-    for (int c = t + CPRE * W; c < C; c += W) {
-        const float4 row = conns4[c];
-        int sd = -1;
-        if (enabled(row))
-            sd = resolved(row_of(row.x), row_of(row.y),
-                          is_int_in(row.y, 0.0f, KEY_LIMIT) ? (int)row.y : -1);
-        e_sd[c] = sd;
-    }
+    auto further = [&](auto row_of) {
+        for (int c = t + CPRE * W; c < C; c += W) {
+            const float4 row = conns4[c];
+            int sd = -1;
+            if (enabled(row))
+                sd = resolved(row_of(row.x), row_of(row.y),
+                              is_int_in(row.y, 0.0f, KEY_LIMIT) ? (int)row.y : -1);
+            e_sd[c] = sd;
+        }
+    };
+    if (mapped) further([&](float k) { return map_row(k, k_map, s_srow, H); });
+    else further([&](float k) { return find_row(k, h_key, h_row, H); });
     gsync(G);
 
     // ---- 4. every edge's index among its destination's in-edges by source

@@ -111,3 +111,33 @@ def test_graphs_of_larger_groups(N, C):
     assert (status[0::7] == 0).all() and (status[1::7] == 0).all() and (status[2::7] == 0).all()
     y64, beta = oracle.forward(pop.nodes, pop.conns, x, I, O)
     _assert_outputs(y, y64, beta, "graphs N=%d C=%d" % (N, C))
+
+
+@pytest.mark.parametrize("N,C", [(7, 20), (62, 248), (64, 900), (65, 260), (200, 3000)])
+def test_rejected_genomes_with_keys_past_the_map(N, C):
+    """The key table's path: repeated keys, keys that no node holds, repeated edges and missing
+    outputs in genomes that all have keys past the map, beside sound ones."""
+    print("case", N, C, flush=True)
+    rng = np.random.default_rng(N + C)
+    P, I, O, end = 20, 3, 2, _map_end(N)
+    pop = synth.make_population(rng, P, N, C, I, O, N - 5, synth._k_density(C),
+                                synth.CONTROL_ACTS, synth.ALL_AGGS)
+    for g in range(P):
+        h = N - 5
+        _rekey(pop, g, np.sort(rng.choice((1 << 24) - end - h, h, replace=False)) + end + np.arange(h))
+        hidden = np.nonzero(pop.nodes[g, :, 0] >= I + O)[0]
+        on = np.nonzero(pop.conns[g, :, 2] == 1.0)[0]
+        if g % 5 == 1 and len(hidden) > 1:
+            pop.nodes[g, hidden[0], 0] = pop.nodes[g, hidden[-1], 0]
+        elif g % 5 == 2 and len(on):
+            pop.conns[g, on[-1], 0] = (1 << 24) - 1
+        elif g % 5 == 3 and len(on) > 1:
+            pop.conns[g, on[0], :2] = pop.conns[g, on[-1], :2]
+        elif g % 5 == 4:
+            pop.nodes[g, pop.nodes[g, :, 0] == I, 0] = np.nan
+    x = rng.standard_normal((P, 9, I), dtype=np.float32)
+    order, level, status, y = _gpu(pop.nodes, pop.conns, I, O, x)
+    _assert_transform_exact(pop.nodes, pop.conns, I, O, order, level, status)
+    assert (status[0::5] == 0).all()
+    y64, beta = oracle.forward(pop.nodes, pop.conns, x, I, O)
+    _assert_outputs(y, y64, beta, "rejected N=%d" % N)
