@@ -12,8 +12,8 @@ namespace neat {
 // out [P][Q] = distance of genome p (nodes/conns [P][N][5] / [P][C][4]) to
 // representative q (rnodes/rconns [Q][N][5] / [Q][C][4]).  The fields from hn
 // on are set by distance_launch: hash table sizes, representatives per group,
-// genomes per workgroup, workgroups per group, and whether the connection
-// tensors are 16-byte aligned.
+// genomes per workgroup, workgroups per group, whether the connection tensors
+// are 16-byte aligned, and the launch's first representative.
 struct DistLaunch {
     const float *nodes;
     const float *conns;
@@ -23,7 +23,7 @@ struct DistLaunch {
     int P, Q, N, C;
     float cd, ch;
     int hn, hc, hn_log2, hc_log2;
-    int rq, per_block, blocks_per_group, vec;
+    int rq, per_block, blocks_per_group, vec, q_first;
 };
 
 // LDS of the two gene hash tables of one genome (what crossover uses, and

@@ -233,9 +233,9 @@ __global__ __launch_bounds__(1024) void distance_dict_kernel(DistLaunch L) {
     const int t = (int)threadIdx.x, T = (int)blockDim.x;
     const int lane = t & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(t / WAVE), waves = T / WAVE;
-    const int group = (int)blockIdx.x / L.blocks_per_group;
-    const int part = (int)blockIdx.x - group * L.blocks_per_group;
-    const int q0 = group * rq, nq = min(rq, L.Q - q0);
+    const int in_launch = (int)(blockIdx.x / (unsigned)L.blocks_per_group);
+    const int part = (int)(blockIdx.x - (unsigned)in_launch * (unsigned)L.blocks_per_group);
+    const int q0 = L.q_first + in_launch * rq, nq = min(rq, L.Q - q0);
     const int sn = 32 - L.hn_log2, sc = 32 - L.hc_log2;  // hash shifts
     const bool vec = L.vec != 0;
 
@@ -317,8 +317,8 @@ __global__ __launch_bounds__(1024) void distance_dict_kernel(DistLaunch L) {
     const int my_b = cnt[(conn_half ? R : 0) + my_r];
 
     // ---- genomes, one per wave
-    const int g1 = min(L.P, (part + 1) * L.per_block);
-    for (int g = part * L.per_block + wave; g < g1; g += waves) {
+    const long long g0 = (long long)part * L.per_block, g1 = min((long long)L.P, g0 + L.per_block);
+    for (long long g = g0 + wave; g < g1; g += waves) {
         const float *An = L.nodes + (size_t)g * N * 5;
         const float *Ac = L.conns + (size_t)g * C * 4;
         int na = 0, ca = 0;
@@ -1039,15 +1039,16 @@ hipError_t distance_launch(DistLaunch L, size_t max_lds, hipStream_t stream) {
     if (rq == 0) {
         L.hn = pow2_at_least(2 * L.N);
         L.hc = pow2_at_least(2 * L.C);
-        const dim3 grid((unsigned)((L.P + DIST_GENOMES - 1) / DIST_GENOMES));
+        const dim3 grid((unsigned)(((long long)L.P + DIST_GENOMES - 1) / DIST_GENOMES));
         hipLaunchKernelGGL(distance_kernel, grid, dim3(WAVE * DIST_WAVES),
                            gene_tables_lds_bytes(L.N, L.C), stream, L);
         return hipGetLastError();
     }
     constexpr int CUS = 256;
-    while (rq > 4 && (long long)((L.Q + rq - 1) / rq) * ((L.P + 15) / 16) < CUS) rq = (rq + 1) / 2;
-    const int groups = (L.Q + rq - 1) / rq;
-    L.rq = (L.Q + groups - 1) / groups;
+    auto parts = [](long long x, int by) { return (x + by - 1) / by; };
+    while (rq > 4 && parts(L.Q, rq) * parts(L.P, 16) < CUS) rq = (rq + 1) / 2;
+    const int groups = (int)parts(L.Q, rq);
+    L.rq = (int)parts(L.Q, groups);
     const size_t lds = dict_shape(L.N, L.C, L.rq, row_bytes, &L.hn, &L.hc);
     L.hn_log2 = log2_of(L.hn), L.hc_log2 = log2_of(L.hc);
     L.vec = ((uintptr_t)L.conns % 16) == 0 && ((uintptr_t)L.rconns % 16) == 0;
@@ -1057,21 +1058,29 @@ hipError_t distance_launch(DistLaunch L, size_t max_lds, hipStream_t stream) {
     const int waves = 2 * lds > max_lds ? 16 : 8;
     const int per_cu = waves == 16 ? 1 : (int)std::min<size_t>(small ? 4 : 2, max_lds / lds);
     const int target = std::max(1, CUS * per_cu / groups);  // workgroups per group
-    const int least = (L.P + target - 1) / target;
-    L.per_block = (least + waves - 1) / waves * waves;
-    L.blocks_per_group = (L.P + L.per_block - 1) / L.per_block;
-    const dim3 grid((unsigned)(groups * L.blocks_per_group)), block((unsigned)(WAVE * waves));
+    const long long least = ((long long)L.P + target - 1) / target;
+    L.per_block = (int)std::min<long long>((least + waves - 1) / waves * waves, 1 << 30);
+    L.blocks_per_group = (int)(((long long)L.P + L.per_block - 1) / L.per_block);
+    // a launch holds fewer than 2^32 threads
+    const int most = (int)std::min<long long>(groups, 0xffffffffll / (WAVE * waves) / L.blocks_per_group);
+    for (int first = 0; first < groups; first += most) {
+        L.q_first = first * L.rq;
+        const dim3 grid((unsigned)std::min(most, groups - first) * (unsigned)L.blocks_per_group);
+        const dim3 block((unsigned)(WAVE * waves));
 #define NEAT_DICT(W, R, RB)                                                                 \
     hipLaunchKernelGGL((distance_dict_kernel<W, R, RB>), grid, block, lds, stream, L)
-    if (row_bytes == 1) {
-        if (small) NEAT_DICT(1, 4, 1);
-        else NEAT_DICT(1, 16, 4);
-    } else {
-        if (small) NEAT_DICT(2, 4, 1);
-        else NEAT_DICT(2, 8, 4);
+        if (row_bytes == 1) {
+            if (small) NEAT_DICT(1, 4, 1);
+            else NEAT_DICT(1, 16, 4);
+        } else {
+            if (small) NEAT_DICT(2, 4, 1);
+            else NEAT_DICT(2, 8, 4);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
 #undef NEAT_DICT
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace neat
