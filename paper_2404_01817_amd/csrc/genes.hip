@@ -666,41 +666,60 @@ __global__ __launch_bounds__(WAVE *CROSS_WAVES) void crossover_kernel(CrossLaunc
 // What bounds it: the latency of the wave's loads, so they are few and
 // independent: the list is sorted by genome, and a window of 64 whole records
 // around the place where evenly spread edits would put the genome's run
-// usually holds it; the rows' keys are requested beside it.  Where the window
-// misses, a 64-way search finds the run.  Every entry of `applied` is written
-// in one pass: a record inside its genome's run by that genome's wave, and
-// records of genomes out of range by the wave whose share of the positions
-// they lie in.  A record outside its genome's run (the list is not sorted)
-// lies either between some genome's begin and the next one's, whose wave
-// writes its 0, or before the first begin or past the last, where the wave
-// whose share it is does.
+// usually holds it; the rows' keys are requested beside it, and 64-way searches
+// find where the run and the next genome's begin.  Every entry of `applied` is
+// written in one pass.  The begins never fall from one genome to the next,
+// whatever the order of the list (a probe that is below one genome is below
+// the next), so they cut it into one part per genome: a wave applies the records
+// of its genome at its part's front and writes 0 for the rest (none when the
+// list is sorted).  Records of genomes out of range, and others before the first
+// part or past the last, belong to the wave whose share of the positions they
+// lie in.
 // Measured at 10,000 genomes of 50 node and 200 connection rows, 80,000 edits:
 // 18.9 us, before 25.2 us and 4.8 us for clearing `applied` (one genome per
-// workgroup, a search of three dependent steps, keys staged in LDS, edits one
-// by one); of the 18.9 us, 6 are the records and the launch, 5.5 the 50 MB of
-// key lines, the rest the edits.  One genome per workgroup: 23.8 against 22.9
-// with four, both with edits one by one.
+// workgroup, keys staged in LDS, edits one by one); of the 18.9 us, 6 are the
+// records and the launch, 5.5 the 50 MB of key lines, the rest the edits.  One
+// genome per workgroup: 23.8 against 22.9 with four, both with edits one by one.
+// The same list shuffled: 21 us (15 ms while begins came from the windows, fell
+// and rose with the list, and every record beside a run had its genome's run
+// looked up).
 constexpr int EDIT_WAVES = 4;      // genomes per workgroup
 constexpr int EDIT_CHUNKS = 4;     // 64-row chunks of connection rows kept in registers
 
-// First index whose genome is >= g in edits sorted by genome: each step
-// lets every lane probe one of 64 evenly spaced positions and narrows the
-// range to the gap the ballot points at (about three steps for 10^5 edits,
-// against seventeen dependent loads of a binary search).  Every probe
-// stays inside [0, n) whatever the order of the edits.
-__device__ __forceinline__ int edits_search(const EditRec *e, int n, int g, int lane) {
-    int lo = 0, hi = n;  // the answer lies in [lo, hi]
-    while (hi - lo > WAVE) {
-        const int step = (hi - lo + WAVE - 1) / WAVE;
-        const long long p = lo + (long long)(lane + 1) * step - 1;
-        const bool less = p < hi && e[p].genome < g;
-        const int cnt = __popcll(__ballot(less));
-        const long long top = lo + (long long)(cnt + 1) * step - 1;  // first probe >= g
-        if (top < hi) hi = (int)top;
-        lo += cnt * step;
+// First indexes whose genomes are >= ga and >= gb in edits sorted by genome: each
+// step lets every lane probe one of 64 evenly spaced positions and narrows a
+// range to the gap that the ballot points at (about three steps for 10^5 edits,
+// against seventeen dependent loads of a binary search), both ranges side by
+// side.  Every probe stays inside [0, n) whatever the order of the edits, and
+// more genomes below never give a smaller index.
+__device__ __forceinline__ void edits_search(const EditRec *e, int n, int ga, int gb, int lane,
+                                             int *first_a, int *first_b) {
+    int lo[2] = {0, 0}, hi[2] = {n, n};  // the answers lie in [lo, hi]
+    const int key[2] = {ga, gb};
+    while (max(hi[0] - lo[0], hi[1] - lo[1]) > WAVE) {
+        int step[2], genome[2];
+        bool in[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            step[k] = (hi[k] - lo[k] + WAVE - 1) / WAVE;
+            const long long p = lo[k] + (long long)(lane + 1) * step[k] - 1;
+            in[k] = p < hi[k];
+            genome[k] = in[k] ? e[p].genome : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (step[k] <= 1) continue;  // narrow enough: the last step's
+            const int cnt = __popcll(__ballot(in[k] && genome[k] < key[k]));
+            const long long top = lo[k] + (long long)(cnt + 1) * step[k] - 1;  // first probe >= key
+            if (top < hi[k]) hi[k] = (int)top;
+            lo[k] += cnt * step[k];
+        }
     }
-    const bool less = lo + lane < hi && e[lo + lane].genome < g;
-    return lo + __popcll(__ballot(less));
+    int genome[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) genome[k] = lo[k] + lane < hi[k] ? e[lo[k] + lane].genome : 0;
+    *first_a = lo[0] + __popcll(__ballot(lo[0] + lane < hi[0] && genome[0] < ga));
+    *first_b = lo[1] + __popcll(__ballot(lo[1] + lane < hi[1] && genome[1] < gb));
 }
 
 // The window of genome g: 64 positions around g n / P.
@@ -708,34 +727,8 @@ __device__ __forceinline__ int edits_window(int n, int P, int g) {
     const long long mid = (long long)g * n / P;
     return (int)max(0ll, min((long long)n - WAVE, mid - WAVE / 2 + 4));
 }
-// First index whose genome is >= g, given the genomes at the window's
-// positions (lane l: p + l); a search where the window does not show it.
-__device__ __forceinline__ int edits_begin(const EditRec *e, int n, int g, int p, int genome,
-                                           int lane) {
-    const unsigned long long less = __ballot(p + lane < n && genome < g);
-    const int cnt = __popcll(less);
-    const bool shown = (p == 0 || (less & 1ull)) && (p + WAVE >= n || cnt < WAVE);
-    return shown ? p + cnt : edits_search(e, n, g, lane);
-}
-__device__ __forceinline__ int edits_begin_of(const EditRec *e, int n, int P, int g, int lane) {
-    const int p = edits_window(n, P, g);
-    return edits_begin(e, n, g, p, p + lane < n ? e[p + lane].genome : 0, lane);
-}
-// Whether record at (of genome g) lies inside g's run.
-__device__ __forceinline__ bool edits_inside(const EditRec *e, int n, int P, int at, int g,
-                                             int lane) {
-    const int b = edits_begin_of(e, n, P, g, lane);
-    bool inside = b <= at;
-    for (int q = b; inside && q <= at; q += WAVE)
-        inside = __ballot(q + lane <= at && e[q + lane].genome != g) == 0ull;
-    return inside;
-}
 
 __device__ __forceinline__ int lane_int(int v, int i) { return __builtin_amdgcn_readlane(v, i); }
-__device__ __forceinline__ float lane_float(float v, int i) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
-
 // One bit per row of a tensor whose key is NaN, 64 rows per chunk: in scalar
 // registers (CH chunks), or in LDS (CH = 0).
 template <int CH>
@@ -813,18 +806,6 @@ struct EditLanes {
     }
 };
 
-// Records s + i for the bits i of odd (genome x in lane i): 0 where they lie
-// outside their genome's run.
-__device__ __forceinline__ void zero_outside(const EditLaunch &L, int s, unsigned long long odd,
-                                             int x, int lane) {
-    while (odd) {
-        const int i = __ffsll((long long)odd) - 1;
-        odd &= odd - 1;
-        if (!edits_inside(L.edits, L.n, L.P, s + i, lane_int(x, i), lane) && lane == 0)
-            L.applied[s + i] = 0;
-    }
-}
-
 // CN, CC: chunks of node and connection rows in registers (0: in LDS)
 template <int CN, int CC>
 __global__ __launch_bounds__(WAVE *EDIT_WAVES) void edit_kernel(EditLaunch L) {
@@ -840,33 +821,40 @@ __global__ __launch_bounds__(WAVE *EDIT_WAVES) void edit_kernel(EditLaunch L) {
     nn.lds = edit_lds + (size_t)wave * L.mask_words;
     nc.lds = nn.lds + (N + WAVE - 1) / WAVE;
     EditLanes rec;
-    int at = edits_window(n, L.P, g);  // the position of lane 0's record
-    rec.load(L.edits, at, n, lane);
-    const int at1 = edits_window(n, L.P, g + 1);
-    const int genome1 = at1 + lane < n ? L.edits[at1 + lane].genome : 0;
-    // the rows' keys, beside the records where most genomes have edits
+    int at = -WAVE;  // the position of lane 0's record
+    const int front = L.edits[0].genome, back = L.edits[n - 1].genome;
+    // records and the rows' keys, requested beside the search where most
+    // genomes have edits
     if (L.prefetch) {
+        at = edits_window(n, L.P, g);
+        rec.load(L.edits, at, n, lane);
         nn.load(gn, 5, N, lane);
         if (C > 0) nc.load(gc, 4, C, lane);
     }
-    const int lo = edits_begin(L.edits, n, g, at, rec.genome, lane);
-    // the first genome's begin and the one past the last (without a search
-    // where the list's ends show them)
-    const int lo0 = L.edits[0].genome >= 0 ? 0 : edits_begin_of(L.edits, n, L.P, 0, lane);
-    const int loP = L.edits[n - 1].genome < L.P ? n : edits_begin_of(L.edits, n, L.P, L.P, lane);
-    const int lo1 = g + 1 < L.P ? edits_begin(L.edits, n, g + 1, at1, genome1, lane) : loP;
+    // this genome's part [lo, lo1) of the list, and all genomes' [lo0, loP): whole
+    // unless its ends are out of range
+    int lo, lo1, lo0 = 0, loP = n;
+    edits_search(L.edits, n, g, g + 1, lane, &lo, &lo1);
+    if (front < 0 || back >= L.P) {
+        int a, b;
+        edits_search(L.edits, n, 0, L.P, lane, &a, &b);
+        lo0 = front < 0 ? a : 0, loP = back >= L.P ? b : n;
+    }
+    if (g == 0) lo = lo0;
+    if (g == L.P - 1) lo1 = loP;
     int e = lo;  // the genome's run continues at e
     bool masks = L.prefetch != 0;
     for (;;) {
+        if (e >= lo1) break;
         if (e < at || e >= at + WAVE) {
-            if (e >= n) break;
             at = e;
             rec.load(L.edits, at, n, lane);
         }
         // records e .. e + cnt - 1, in lanes i0 ..
         const int i0 = e - at;
         const unsigned long long same = __ballot(at + lane < n && rec.genome == g) >> i0;
-        const int cnt = ~same ? __ffsll((long long)~same) - 1 : WAVE;
+        const int run = ~same ? __ffsll((long long)~same) - 1 : WAVE;
+        const int cnt = min(run, lo1 - e);
         if (cnt == 0) break;
         if (!masks) {
             nn.load(gn, 5, N, lane);
@@ -935,20 +923,13 @@ __global__ __launch_bounds__(WAVE *EDIT_WAVES) void edit_kernel(EditLaunch L) {
         e += cnt;
         if (e < at + WAVE) break;  // the run ended inside the lanes
     }
-    // this wave's share of the positions: records of genomes out of range, and
-    // others before the first begin or past the last
-    const int s0 = (int)((long long)g * n / L.P), s1 = (int)((long long)(g + 1) * n / L.P);
-    for (int s = s0; s < s1; s += WAVE) {
-        const int i = s + lane, x = i < s1 ? L.edits[i].genome : 0;
-        const bool in = x >= 0 && x < L.P;
-        if (i < s1 && !in) L.applied[i] = 0;
-        zero_outside(L, s, __ballot(i < s1 && in && (i < lo0 || i >= loP)), x, lane);
-    }
-    // and records between this run's end and the next genome's begin
-    for (int s = g == 0 ? lo0 : e; s < lo1; s += WAVE) {
-        const int i = s + lane, x = i < lo1 ? L.edits[i].genome : -1;
-        const bool mine = g == 0 && i >= lo && i < e;
-        zero_outside(L, s, __ballot(x >= 0 && x < L.P && !mine), x, lane);
+    // what is left of its part, and its share of the positions before the first
+    // part and past the last
+    for (int i = e + lane; i < lo1; i += WAVE) L.applied[i] = 0;
+    if (lo0 > 0 || loP < n) {
+        const int s0 = (int)((long long)g * n / L.P), s1 = (int)((long long)(g + 1) * n / L.P);
+        for (int i = s0 + lane; i < s1; i += WAVE)
+            if (i < lo0 || i >= loP) L.applied[i] = 0;
     }
 }
 
