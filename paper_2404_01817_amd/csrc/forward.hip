@@ -435,36 +435,59 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
     const float *in_g = GRID ? nullptr : it->inputs + (size_t)g * it->gstride;
     const int vec4 = it->vec4;
     if (!GRID) dma_inputs(in_g + (size_t)t0 * TS * I, istage, min(TS, B - t0 * TS) * I, vec4);
-    // grid queries: the side coordinates and (where LDS has room for the table,
-    // else in every tile) each sample's offset in the tile as digits (x, y,
-    // points past them), once per unit, after the staging
+    // grid queries: the side coordinates and every sample's offset in the
+    // tile as digits (x, y, points past them), once per unit, after the staging
     float *ctab = istage + TS * I;
     unsigned *otab = (unsigned *)(ctab + GRID_MAX_SIDE);
     const unsigned uside = (unsigned)side, pts = uside * uside;
     const float rside = GRID ? 1.0f / (float)side : 0.0f;
     // digits of the tile's first query (points p1, p2) and of a tile's length
-    unsigned x1_0 = 0, y1_0 = 0, x2_0 = 0, y2_0 = 0, tx = 0, ty = 0, tk = 0;
-    const bool tabulated = GRID && it->grid_table != 0;
-    auto digits = [&](unsigned o) {
-        const unsigned k = o / pts;
-        unsigned oy, ox;
-        divmod_small(o - k * pts, uside, rside, &oy, &ox);
-        return ox | (oy << 8) | (k << 16);
+    unsigned x1_0 = 0, y1_0 = 0, x2_0 = 0, y2_0 = 0;
+    const unsigned step = GRID ? (unsigned)it->grid_step : 0u;
+    const unsigned tx = step & 0xffu, ty = (step >> 8) & 0xffu, tk = (step >> 16) & 0xffu;
+    // grid queries: the inputs of the lane's sample h (the fifth, 1, stays), by
+    // adding its offset to the tile's first query digit by digit.  Where whole
+    // rows of targets fit the tile (tx = ty = 0) the target point stays from tile
+    // to tile.
+    auto place = [&](int h, unsigned o, bool target) {
+        float *x = istage + (h * WAVE + lane) * 5;
+        unsigned x2 = x2_0 + (o & 0xffu), y2 = y2_0 + ((o >> 8) & 0xffu);
+        unsigned x1 = x1_0 + (o >> 16), y1 = y1_0;
+        if (x2 >= uside) x2 -= uside, ++y2;
+        if (y2 >= uside) y2 -= uside, ++x1;
+        if (pts >= (unsigned)TS) {
+            if (x1 >= uside) x1 -= uside, ++y1;
+        } else {
+            unsigned c;
+            divmod_small(x1, uside, rside, &c, &x1);
+            y1 += c;
+        }
+        y1 = min(y1, uside - 1u);  // lanes past the last query
+        x[0] = ctab[x1];
+        x[1] = ctab[y1];
+        if (target) {
+            x[2] = ctab[x2];
+            x[3] = ctab[y2];
+        }
     };
     if (GRID) {
         for (int i = (int)lane; i < side; i += WAVE) ctab[i] = grid_coord(i, side);
-        for (int h = 0; h < SPL; ++h) {
-            const unsigned o = (unsigned)(h * WAVE) + lane;
-            if (tabulated) otab[o] = digits(o);
-            istage[o * 5 + 4] = 1.0f;
-        }
         const unsigned q0 = (unsigned)(it->first + (long long)t0 * TS);
         const unsigned p1 = q0 / pts, p2 = q0 - p1 * pts;
-        y1_0 = p1 / uside, x1_0 = p1 - y1_0 * uside;
-        y2_0 = p2 / uside, x2_0 = p2 - y2_0 * uside;
-        tk = (unsigned)TS / pts;
-        ty = (unsigned)TS % pts / uside, tx = (unsigned)TS % pts % uside;
+        divmod_small(p1, uside, rside, &y1_0, &x1_0);
+        divmod_small(p2, uside, rside, &y2_0, &x2_0);
         __builtin_amdgcn_wave_barrier();
+        // the first tile's inputs, and the offsets for the others
+        for (int h = 0; h < SPL; ++h) {
+            const unsigned o = (unsigned)(h * WAVE) + lane;
+            const unsigned k = pts >= (unsigned)TS ? 0u : o / pts;
+            unsigned oy, ox;
+            divmod_small(o - k * pts, uside, rside, &oy, &ox);
+            const unsigned d = ox | (oy << 8) | (k << 16);
+            otab[o] = d;
+            istage[o * 5 + 4] = 1.0f;
+            place(h, d, true);
+        }
     }
     // the records and overflow edges the node loop will read, in one burst
     // (the first tile's wait covers it)
@@ -474,39 +497,14 @@ __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int
 
     for (int t = t0; t < t1; ++t) {
         if (GRID) {
-            // grid queries: the inputs of each of the lane's samples (the
-            // fifth, 1, stays), by adding the sample's offset to the tile's
-            // first query digit by digit.  Where whole rows of targets fit the
-            // tile (tx = ty = 0) the target point stays from tile to tile.
-            const bool target = t == t0 || (tx | ty) != 0;
-            for (int h = 0; h < SPL; ++h) {
-                float *x = istage + (h * WAVE + lane) * 5;
-                const unsigned s = (unsigned)(h * WAVE) + lane;
-                const unsigned o = tabulated ? otab[s] : digits(s);
-                unsigned x2 = x2_0 + (o & 0xffu), y2 = y2_0 + ((o >> 8) & 0xffu);
-                unsigned x1 = x1_0 + (o >> 16), y1 = y1_0;
-                if (x2 >= uside) x2 -= uside, ++y2;
-                if (y2 >= uside) y2 -= uside, ++x1;
-                if (pts >= (unsigned)TS) {
-                    if (x1 >= uside) x1 -= uside, ++y1;
-                } else {
-                    unsigned c;
-                    divmod_small(x1, uside, rside, &c, &x1);
-                    y1 += c;
-                }
-                y1 = min(y1, uside - 1u);  // lanes past the last query
-                x[0] = ctab[x1];
-                x[1] = ctab[y1];
-                if (target) {
-                    x[2] = ctab[x2];
-                    x[3] = ctab[y2];
-                }
+            if (t > t0) {
+                // this tile's first query
+                x2_0 += tx, y2_0 += ty, x1_0 += tk;
+                if (x2_0 >= uside) x2_0 -= uside, ++y2_0;
+                if (y2_0 >= uside) y2_0 -= uside, ++x1_0;
+                while (x1_0 >= uside) x1_0 -= uside, ++y1_0;
+                for (int h = 0; h < SPL; ++h) place(h, otab[h * WAVE + lane], (tx | ty) != 0);
             }
-            // the next tile's first query
-            x2_0 += tx, y2_0 += ty, x1_0 += tk;
-            if (x2_0 >= uside) x2_0 -= uside, ++y2_0;
-            if (y2_0 >= uside) y2_0 -= uside, ++x1_0;
-            while (x1_0 >= uside) x1_0 -= uside, ++y1_0;
         } else if (DIRECT && t > t0) {
             // the stores of the last tile follow this tile's DMA
             wait_dma_before(SPL * ((O >> 2) + ((O >> 1) & 1) + (O & 1)));
@@ -1262,6 +1260,14 @@ bool direct_kind(int kind) { return kind == KIND_R32X4; }
 
 bool lds_kind(int kind) { return kind == KIND_LDS || kind == KIND_LDS32; }
 
+// Whether a register kernel's wave holds five inputs and O outputs of a tile of
+// grid queries and the coordinates, but not the samples' offsets as well.
+bool grid_table_too_large(int kind, int O, size_t max_lds) {
+    const size_t TS = (size_t)tile_samples(kind);
+    const size_t floats = TS * 5 + GRID_MAX_SIDE + (direct_kind(kind) ? WAVE : TS * O);
+    return sizeof(float) * floats <= max_lds && sizeof(float) * (floats + TS) > max_lds;
+}
+
 // kernel of class c under a variant
 int kind_of(int variant, int cls, int B) {
     if (variant == FWD_LDS) return KIND_LDS;
@@ -1462,7 +1468,9 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const FwdJob &J = jobs[j];
         if (J.P == 0 || J.B == 0) continue;
         const int top = max_class(J.N);
-        const int variant = J.variant >= 0 ? J.variant : plan_variant;
+        int variant = J.variant >= 0 ? J.variant : plan_variant;
+        // (grid queries without that room in tiles of 64 samples: LDS rows)
+        if (J.side && grid_table_too_large(KIND_R64, J.O, max_lds)) variant = FWD_LDS;
         if ((variant == FWD_LVL || variant == FWD_SEG) && !J.side && !J.recurrent) {
             // the level and segment mappings: every genome, one launch per
             // mapping over all items (the segment mapping also keeps N_max + 1
@@ -1505,6 +1513,10 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
                        : any       ? KIND_ANY
                                    : kind_of(variant, c < 0 ? CLS_LDS : c, J.B);
             if (kind == KIND_R64X2 && variant == FWD_AUTO && four_samples(J)) kind = KIND_R32X4;
+            // grid queries whose outputs leave no room for the table of offsets
+            // beside them: half as many samples per tile
+            if (J.side && kind == KIND_R64X2 && grid_table_too_large(kind, J.O, max_lds))
+                kind = KIND_R64;
             // LDS rows too large for 64 columns per wave: half-wave tiles
             if (kind == KIND_LDS &&
                 sizeof(float) * (size_t)WAVE * (J.I + class_slots(top, J.N)) > max_lds)
@@ -1522,16 +1534,20 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             it.side = J.side;
             it.prog_words = prog_words(J.N, J.C, J.O);
             if (J.recurrent) it.sweeps = J.sweeps;
+            if (J.side) {
+                const int ts = tile_samples(kind), pts = J.side * J.side;
+                it.grid_step = ts % pts % J.side | (ts % pts / J.side) << 8 | (ts / pts) << 16;
+            }
             const int TS = kind == KIND_ANY ? any_tile(J) : tile_samples(kind);
             it.tiles = (J.B + TS - 1) / TS;
             it.vec4 = (!J.side && ((uintptr_t)J.inputs % 16 == 0) && (J.gstride % 4 == 0)) ? 1 : 0;
             const int x = 2 * kind + (J.side ? 1 : 0);
             std::vector<FwdItem> &items = items_of(x);
             items.push_back(it);
-            // register kernels on grid queries keep the coordinates after the
-            // staged inputs
+            // register kernels on grid queries keep the coordinates and the
+            // samples' offsets after the staged inputs
             if (!J.side || !lds_kind(kind))
-                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE : 0));
+                stage_max[x] = std::max(stage_max[x], TS * J.I + (J.side ? GRID_MAX_SIDE + TS : 0));
             // outputs stored from registers leave only what touch_lines writes
             if (!lds_kind(kind))
                 ostage_max[x] = std::max(ostage_max[x], direct_kind(kind) ? WAVE : TS * J.O);
@@ -1552,13 +1568,6 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
         const size_t rows = (kind == KIND_LVL || kind == KIND_SEG) ? (size_t)rows_max[x]
                             : lds_kind(kind) ? (size_t)rows_max[x] * tile_samples(kind)
                                              : (size_t)ostage_max[x];
-        // and the samples' offsets where they fit beside the outputs (a table
-        // of them must not make a call too large)
-        if (K.grid_mode && !lds_kind(kind) &&
-            sizeof(float) * ((size_t)stage_max[x] + tile_samples(kind) + rows) <= max_lds) {
-            stage_max[x] += tile_samples(kind);
-            for (FwdItem &it : K.items) it.grid_table = 1;
-        }
         size_t wave_floats = (size_t)stage_max[x] + rows;
         // (the waves' staging areas start at 16 bytes: their loads and stores are
         // that wide, while a level mapping's rows may end anywhere)
@@ -1689,6 +1698,8 @@ hipError_t forward_launch(const FwdKernelLaunch &k, const FwdItem *dev_items, hi
                           unsigned *counter) {
     FwdLaunch L = k.args;
     L.counter = L.persistent ? counter : nullptr;
+    // only one item goes inline
+    if (dev_items == nullptr && k.items.size() != 1) return hipErrorInvalidValue;
     if (k.items.size() == 1 && dev_items == nullptr) {
         L.items = nullptr;
         L.n_items = 1;

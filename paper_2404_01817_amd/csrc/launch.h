@@ -101,8 +101,9 @@ struct FwdItem {
     int P, N, I, O, B, side, vec4, cls;
     int tiles, tpw, chunks, prog_words;
     union {
-        int sweeps;      // recurrent kernel: sweeps per sample
-        int grid_table;  // grid queries: the samples' offsets in a tile are tabulated in LDS
+        int sweeps;     // recurrent kernel: sweeps per sample
+        int grid_step;  // grid queries: a tile's length as digits (x, y, points past them;
+                        // a byte each)
     };
     int C;         // C_max (program layout)
     int lvl_sh;    // level and segment mappings: log2 of the samples per tile

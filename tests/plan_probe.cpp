@@ -51,9 +51,9 @@ int main() {
             for (size_t i = 0; i < L.items.size(); ++i) {
                 const neat::FwdItem &it = L.items[i];
                 std::printf("%s{\"P\": %d, \"N\": %d, \"B\": %d, \"cls\": %d, \"tiles\": %d, \"tpw\": %d, "
-                            "\"lvl_sh\": %d, \"lvl_rows\": %d, \"vec4\": %d, \"table\": %d}",
+                            "\"lvl_sh\": %d, \"lvl_rows\": %d, \"vec4\": %d}",
                             i ? ", " : "", it.P, it.N, it.B, it.cls, it.tiles, it.tpw, it.lvl_sh,
-                            it.lvl_rows, it.vec4, L.grid_mode ? it.grid_table : 0);
+                            it.lvl_rows, it.vec4);
             }
             std::printf("]}");
         }

@@ -136,19 +136,23 @@ def test_batches_are_refused_exactly_when_their_launches_per_class_are(plan):
 @pytest.mark.parametrize("N", [1000, 1024])
 def test_grid_queries_up_to_the_lds_of_their_staging(plan, N, B, samples):
     """A wave holds a tile's five inputs, 256 coordinates and a tile's outputs: every O for
-    which these fit is accepted, and the table of offsets only where it fits too."""
-    floats = LDS // 4 - 256 - 5 * samples
-    top = floats // samples  # outputs
+    which these fit is accepted, with the table of the samples' offsets beside them, or where
+    that does not fit by tiles of half the samples or by LDS rows."""
+    top = (LDS // 4 - 256 - 5 * samples) // samples  # outputs
     outs = [1, 100, top - 2, top - 1, top, top + 1]
     got = plan([(AS_IS, [dict(P=3, N=N, I=5, O=O, B=B, side=16)]) for O in outs])
+    small = "r64" if samples == 64 else "r64x2"
     for O, g in zip(outs, got):
         assert (g["rc"] == 0) == (O <= top), O
+        if O < top:
+            assert kinds(g) == [small, "r128", "r224", "lds32"]
+        elif O == top:
+            assert kinds(g) == (["lds32"] if samples == 64 else ["r64", "r128", "r224", "lds32"])
+            assert [i["cls"] for l in g["launches"] for i in l["items"]] == \
+                ([-1] if samples == 64 else [0, 1, 2, 3])
         for l in g["launches"]:
             s = {"r64x2": 128, "lds": 0, "lds32": 0}.get(l["kind"], 64)
-            for it in l["items"]:
-                assert it["table"] == (s > 0 and 4 * (s * (6 + O) + 256) <= LDS)
-            if s:
-                assert l["wave_floats"] == s * (5 + O + it["table"]) + 256
+            assert not s or l["wave_floats"] == s * (6 + O) + 256
 
 
 def test_wave_areas_start_at_16_bytes(plan):
@@ -215,3 +219,19 @@ def test_launches_come_in_the_order_of_the_kernels(plan):
     assert order == [("r64", 0), ("r64", 1), ("r64x2", 0), ("r128", 0), ("r224", 0), ("lds", 0),
                      ("lvl", 0), ("seg", 0), ("r32x4", 0)]
     assert [(l["kind"], l["grid_mode"]) for l in b["launches"]] == order
+
+
+def test_one_population_is_one_item_of_every_launch(plan):
+    """A call over one population passes its items inline: no launch of it may hold two."""
+    sizes = [(N, O) for N in (8, 30, 31, 62, 63, 127, 223, 330, 700, 1000, 1024)
+             for O in (1, 2, 20, 312, 313, 314, 629, 630, 631, 900) if 5 + O <= N]
+    plans = [(how, [dict(P=P, N=N, O=O, B=B, side=side, variant=v)])
+             for N, O in sizes for side in (0, 3, 16) for P in (1, 5000) for B in (1, 64, 65, 300)
+             for how, v in ((AS_IS, neat.FWD_AUTO), (GRAPH, neat.FWD_AUTO), (AS_IS, neat.FWD_REG),
+                            (AS_IS, neat.FWD_REG2), (AS_IS, neat.FWD_LDS), (AS_IS, neat.FWD_LVL),
+                            (AS_IS, neat.FWD_SEG))]
+    accepted = 0
+    for (_, (job,)), got in zip(plans, plan(plans)):
+        accepted += got["rc"] == 0
+        assert all(len(l["items"]) == 1 for l in got["launches"]), (job, kinds(got))
+    assert accepted > len(plans) // 2
