@@ -380,7 +380,7 @@ int neat_crossover(const neat_dims *dims, const float *nodes, const float *conns
  *   outputs  [P][B][S] f32: y[g][b][p2] = tanh(sum_p1 w'[g][p1][p2] x[b][p1])
  *            with w' = 0 where |w| < threshold, else w (NaN kept); genomes
  *            with status != 0 give NaN rows.
- * The contraction runs on the matrix cores in fp32 (v_mfma_f32_16x16x4).
+ * The contraction runs on the matrix cores in fp32 (v_mfma_f32_32x32x2).
  * Requires 8 <= side <= 32 with side^2 a multiple of 64 (side 8, 16, 24,
  * 32), threshold >= 0, 16-byte aligned x, weights and outputs.
  * Errors: NEAT_E_INVALID, NEAT_E_HIP.

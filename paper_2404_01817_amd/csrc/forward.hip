@@ -1,7 +1,7 @@
 // forward.hip -- the calculation stage (Section 3.3) over population x inputs.
 //
 // Mapping "lane per sample": a 64-lane wave evaluates one genome on a run of
-// sample tiles, one or two samples per lane.  The genome's program is
+// sample tiles, one, two or four samples per lane.  The genome's program is
 // uniform across the wave, so it is read with scalar loads and every branch
 // on a node's activation or aggregation is a scalar branch.  A workgroup
 // holds up to four waves working on the same genome, so they share the
@@ -25,15 +25,14 @@
 //
 // Work units.  A launch covers one or more populations ("items"); item j
 // contributes P_j x chunks_j wave units (chunks_j from the item's wave
-// target, or the launch's for several items of the two-samples kernel),
-// unit (i, c) being run c of the
-// tiles of the i-th genome of the item's list for the kernel's class (the
-// class list the transformation wrote, or all genomes).  Each wave of a
-// workgroup takes its own unit, so consecutive waves share a genome when it
-// has several chunks and take different genomes when it has one.  Units
-// past the list's length exit at once.  Workgroups are remapped so
-// consecutive ones share an XCD (workgroups are dealt to the 8 XCDs round
-// robin).
+// target, or the launch's for several items of a kernel with more than one
+// sample per lane), unit (i, c) being run c of the tiles of the i-th genome of
+// the item's list for the kernel's class (the class list the transformation
+// wrote, or all genomes).  Each wave of a workgroup takes its own unit, so
+// consecutive waves share a genome when it has several chunks and take
+// different genomes when it has one.  Units past the list's length exit at
+// once.  Workgroups are remapped so consecutive ones share an XCD (workgroups
+// are dealt to the 8 XCDs round robin).
 //
 // Inputs of the next tile are copied HBM -> LDS by the DMA path of
 // global_load_lds (16-byte pieces when aligned) while the current tile
@@ -410,8 +409,10 @@ __device__ __forceinline__ void fill_nan(float *out_g, int first, int end, int O
     for (int e = first * O + lane; e < end * O; e += WAVE) out_g[e] = __builtin_nanf("");
 }
 
-// One unit with a register store: tiles [t0, t1) of genome g.  area: the wave's LDS (input staging TS x I floats, then output staging
-// TS x O floats).
+// One unit with a register store: tiles [t0, t1) of genome g.  area: the wave's
+// LDS: input staging (TS x I floats; for grid queries the coordinates and the
+// offsets too), then output staging (TS x O floats, or 64 that touch_lines writes
+// where outputs are stored from registers).
 template <int K, bool GRID>
 __device__ __forceinline__ void forward_unit_reg(citem_t *it, int g, int t0, int t1, float *area,
                                                  int stage_floats) {
@@ -1326,14 +1327,19 @@ static int recurrent_kind(const FwdJob &J) {
 }
 
 // Four samples per lane for the smallest class: where every value has one of
-// 32 slots, two-sample tiles fill the GPU (3072 waves of that kernel) and
-// 256 staged samples leave room for 12 waves per CU.  The node loop's scalar
-// work is shared by twice the samples, and the register file holds as many
-// samples per SIMD as with two per lane and 64 slots: CPPN grid queries, P =
-// 1000, N = 30, 65536 queries: 508 us with two samples per lane and 64 slots,
-// 414 us with two and 32 slots (five waves per SIMD instead of three), 395 us
-// with four (the vector pipe 79 % busy), 384 us with outputs stored straight
-// from registers.
+// 32 slots and two-sample tiles fill the GPU (3072 waves of that kernel).  The
+// node loop's scalar work is shared by twice the samples, and the register file
+// holds as many samples per SIMD as with two per lane and 64 slots: CPPN grid
+// queries, P = 1000, N = 30, 65536 queries: 508 us with two samples per lane and
+// 64 slots, 414 us with two and 32 slots (five waves per SIMD instead of three),
+// 395 us with four (the vector pipe 79 % busy), 384 us with outputs stored
+// straight from registers.  Both ends of a network limit it: 256 staged samples
+// of more than 12 inputs leave fewer than 12 waves per CU, and the stores of
+// many outputs from registers, four at a time, are not combined into lines.
+// N = 30, P = 3000, B = 500, two samples / four, us: I = 4, O = 1: 19.8 / 16.4;
+// 8, 4: 22.4 / 20.0; 11, 1: 21.0 / 18.0; 6, 6: 22.7 / 22.1; 13, 2: 21.7 / 23.1;
+// 4, 12: 28.3 / 29.2; 4, 20: 34.2 / 73.7 (12, 1 and 12, 4 would gain: 21.6 / 18.6,
+// 23.3 / 22.2).
 static bool four_samples(const FwdJob &J) {
     return J.N <= SMALL_ROWS && J.I + J.O <= 12 && J.B > 2 * WAVE &&
            (long long)J.P * ((J.B + 2 * WAVE - 1) / (2 * WAVE)) > 3072;
@@ -1585,8 +1591,8 @@ int forward_plan(const FwdJob *jobs, int n, int variant, size_t max_lds,
             out.clear();
             return NEAT_E_TOO_LARGE;
         }
-        // Several items of the two-samples kernel (the streaming one, taken
-        // for B > 64) share the launch's wave target: one tiles-per-wave
+        // Several items of a kernel with two or four samples per lane (the
+        // streaming ones, taken for B > 64) share the launch's wave target: one tiles-per-wave
         // count for all, the largest that still gives the target, so a
         // population split into items runs as it does whole and each wave
         // overlaps its next tile's input DMA with the current tile (the

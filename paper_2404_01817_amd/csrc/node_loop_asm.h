@@ -44,11 +44,12 @@
 // write of v[dst] and the jump to the next node.  The C++ node loop of the
 // LDS store performs the same operations in the same order.
 //
-// The recurrent block (NEAT_TILE_S1_64R) zeroes the read vector v0..v63,
-// places the inputs and constants in it and in the write vector v64..v127,
-// then runs the node loop %[nsw] times: every sweep reads v0.. and writes
-// v64.., and all but the last copy the %[n] + %[ni] nodes' slots back (s91
-// counts the sweeps); the outputs are read from v64...
+// The recurrent blocks (NEAT_TILE_S1_64R here, _S2_32R and _S1_52R in
+// node_loop_wide.h) zero the read vectors (v0..v63 here), place the inputs and
+// constants in them and in the write vectors (v64..v127), then run the node
+// loop %[nsw] times: every sweep reads the first and writes the second, and all
+// but the last copy the %[n] + %[ni] nodes' slots back (s91 counts the sweeps);
+// the outputs are read from the write vectors.
 //
 // Hazards: a transcendental's result is read no sooner than one instruction
 // later (with two samples the other sample's instruction sits between); a

@@ -24,7 +24,7 @@
 // is one 16-byte read.
 //
 // What bounds it: the matrix cores.  P = 500, S = B = 256 (16.8 GFLOP): 153 us
-// (110 TFLOP/s); the MFMAs alone, without loads or stores, take 120 us in this
+// (110 TFLOP/s; the layer alone, without the grid queries that make W); the MFMAs alone, without loads or stores, take 120 us in this
 // launch.  16x16x4 blocks with 4-byte LDS reads took 165 us (LDS busy two
 // thirds of the time; 16-byte reads halve that), 32x32x2 blocks 158 us, two of
 // them per wave 153 us, four 168 us; the next chunk's loads issued ahead of
@@ -135,11 +135,14 @@ hipError_t substrate_launch(const SubLaunch &L, hipStream_t stream) {
     // Two blocks of rows per wave halve the staging of W per product, but hold
     // twice the registers, and an odd number of 64 rows leaves one empty (one
     // part in 32 more work is what they are worth).  So they are taken for
-    // launches of at least 800,000 chunk rows (tiles times S): 1,024,000 (P =
-    // 500, side 16, B = 256) 265 us against 270 with one, 1,016,000 (P = 31,
-    // side 32, B = 256) 289 against 295; 614,000 (P = 300, side 16, B = 256)
-    // 173 against 172, 410,000 (P = 200) 126 against 123, 311,000 (P = 60, side
-    // 24, B = 128) 152 against 143.  B = 192: 264 against 233 (P = 500).
+    // launches of at least 800,000 chunk rows (tiles times S).  The layer alone in
+    // us, one block / two (runs differ by 3 percent): P = 500, side 16, B = 256
+    // (1,024,000 chunk rows) 178 / 164; P = 31, side 32, B = 256 (1,016,000) 163 /
+    // 155; P = 500, side 16, B = 512: 302 / 294; P = 400, side 16, B = 256 (819,000)
+    // 125 / 123; P = 300 (614,000) 96 / 96; P = 200 (410,000) 67.6 / 69.7; P = 60,
+    // side 24, B = 128 (311,000) 61 / 67.  Past that it is even or costs little
+    // where a genome's W is large (P = 100, side 24, B = 256: 161 / 165; P = 60, side
+    // 32: 284 / 291).  An odd number of 64 rows: P = 500, side 16, B = 192: 123 / 149.
     const long long rows = ((long long)L.B + 63) / 64;  // of 64
     const bool filled = rows % 2 == 0 || rows > 32;
     const int mt = filled && L.P * ((rows + 1) / 2) * (L.S / ST_N) * L.S >= 800000 ? 2 : 1;
