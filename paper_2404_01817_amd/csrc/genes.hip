@@ -317,8 +317,9 @@ __global__ __launch_bounds__(1024) void distance_dict_kernel(DistLaunch L) {
     const int my_b = cnt[(conn_half ? R : 0) + my_r];
 
     // ---- genomes, one per wave
-    const long long g0 = (long long)part * L.per_block, g1 = min((long long)L.P, g0 + L.per_block);
-    for (long long g = g0 + wave; g < g1; g += waves) {
+    const unsigned g0 = (unsigned)part * (unsigned)L.per_block;
+    const unsigned g1 = min((unsigned)L.P, g0 + (unsigned)L.per_block);
+    for (unsigned g = g0 + (unsigned)wave; g < g1; g += (unsigned)waves) {
         const float *An = L.nodes + (size_t)g * N * 5;
         const float *Ac = L.conns + (size_t)g * C * 4;
         int na = 0, ca = 0;
