@@ -60,15 +60,16 @@ struct EditRec {
 
 // edits [n] sorted by genome (application order within a genome) applied
 // in place to nodes/conns [P][N][5] / [P][C][4]; applied [n] written.
-// prefetch (rows' keys are requested before the edits are known) and
-// mask_words (8-byte words of LDS per wave) are set by edit_launch.
+// prefetch (rows' keys are requested before the edits are known), mask_words
+// (8-byte words of LDS per wave) and height (halvings of the list down to blocks
+// of 64) are set by edit_launch.
 struct EditLaunch {
     float *nodes;
     float *conns;
     const EditRec *edits;
     int32_t *applied;
     int n, P, N, C;
-    int prefetch, mask_words;
+    int prefetch, mask_words, height;
 };
 
 hipError_t edit_launch(EditLaunch L, hipStream_t stream);

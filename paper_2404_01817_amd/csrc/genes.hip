@@ -665,69 +665,77 @@ __global__ __launch_bounds__(WAVE *CROSS_WAVES) void crossover_kernel(CrossLaunc
 // where two of the wave's edits write one row.
 //
 // What bounds it: the latency of the wave's loads, so they are few and
-// independent: the list is sorted by genome, and a window of 64 whole records
-// around the place where evenly spread edits would put the genome's run
-// usually holds it; the rows' keys are requested beside it, and 64-way searches
-// find where the run and the next genome's begin.  Every entry of `applied` is
-// written in one pass.  The begins never fall from one genome to the next,
-// whatever the order of the list (a probe that is below one genome is below
-// the next), so they cut it into one part per genome: a wave applies the records
-// of its genome at its part's front and writes 0 for the rest (none when the
-// list is sorted).  Records of genomes out of range, and others before the first
-// part or past the last, belong to the wave whose share of the positions they
-// lie in.
+// independent: the list is sorted by genome, and the probes that lead a search to
+// where evenly spread edits would put the genome's run and the next one's, the 64
+// whole records there and the rows' keys are requested together.  Every entry of
+// `applied` is written in one pass.  The begins that the searches find never fall
+// from one genome to the next, whatever the order of the list (a probe that is
+// below one genome is below the next), so they cut it into one part per genome: a
+// wave applies the records of its genome at its part's front and writes 0 for the
+// rest (none when the list is sorted).  Records of genomes out of range, and
+// others before the first part or past the last, belong to the wave whose share of
+// the positions they lie in.
 // Measured at 10,000 genomes of 50 node and 200 connection rows, 80,000 edits:
 // 18.9 us, before 25.2 us and 4.8 us for clearing `applied` (one genome per
 // workgroup, keys staged in LDS, edits one by one); of the 18.9 us, 6 are the
 // records and the launch, 5.5 the 50 MB of key lines, the rest the edits.  One
 // genome per workgroup: 23.8 against 22.9 with four, both with edits one by one.
-// The same list shuffled: 21 us (15 ms while begins came from the windows, fell
+// The same list shuffled: 23 us (15 ms while begins came from the windows, fell
 // and rose with the list, and every record beside a run had its genome's run
 // looked up).
 constexpr int EDIT_WAVES = 4;      // genomes per workgroup
 constexpr int EDIT_CHUNKS = 4;     // 64-row chunks of connection rows kept in registers
 
-// First indexes whose genomes are >= ga and >= gb in edits sorted by genome: each
-// step lets every lane probe one of 64 evenly spaced positions and narrows a
-// range to the gap that the ballot points at (about three steps for 10^5 edits,
-// against seventeen dependent loads of a binary search), both ranges side by
-// side.  Every probe stays inside [0, n) whatever the order of the edits, and
-// more genomes below never give a smaller index.
-__device__ __forceinline__ void edits_search(const EditRec *e, int n, int ga, int gb, int lane,
-                                             int *first_a, int *first_b) {
-    int lo[2] = {0, 0}, hi[2] = {n, n};  // the answers lie in [lo, hi]
-    const int key[2] = {ga, gb};
-    while (max(hi[0] - lo[0], hi[1] - lo[1]) > WAVE) {
-        int step[2], genome[2];
-        bool in[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            step[k] = (hi[k] - lo[k] + WAVE - 1) / WAVE;
-            const long long p = lo[k] + (long long)(lane + 1) * step[k] - 1;
-            in[k] = p < hi[k];
-            genome[k] = in[k] ? e[p].genome : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            if (step[k] <= 1) continue;  // narrow enough: the last step's
-            const int cnt = __popcll(__ballot(in[k] && genome[k] < key[k]));
-            const long long top = lo[k] + (long long)(cnt + 1) * step[k] - 1;  // first probe >= key
-            if (top < hi[k]) hi[k] = (int)top;
-            lo[k] += cnt * step[k];
-        }
+// The list as a binary tree down to blocks of 64 records: at a block of 2 x 64 x
+// 2^k records a search goes right if the last record of the left half is below the
+// key, and counts the records below the key in the block of 64 that it comes to.
+// Every probe stays inside [0, n) whatever the order of the edits, and a larger key
+// never gives a smaller index.
+//
+// The probes on the way to positions to[0] and to[1], one per lane, and the blocks
+// of 64 there are requested before any of them is used: where evenly spread edits
+// put this genome's run and the next one's, so both searches cost one latency and
+// some twenty lines.  A search that leaves its way probes the 63 ends of six steps
+// at once.  80,000 edits of 10,000 genomes behind a crossover: 53.7 us for both,
+// 55.0 with steps of 64 parts (sixty-four lines each on the way).
+struct EditTree {
+    const EditRec *e;
+    int n, height, lane;  // steps from the whole list to a block
+    int to[2], block[2];  // genomes of the blocks there
+    int probe;            // lane 32 w + k: the genome at step k (of 2^k blocks) of way w
+    static __device__ __forceinline__ int start(int at) { return at & ~(WAVE - 1); }
+    __device__ __forceinline__ int load(long long p) const {
+        return p < n ? e[p].genome : 0x7fffffff;
     }
-    int genome[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) genome[k] = lo[k] + lane < hi[k] ? e[lo[k] + lane].genome : 0;
-    *first_a = lo[0] + __popcll(__ballot(lo[0] + lane < hi[0] && genome[0] < ga));
-    *first_b = lo[1] + __popcll(__ballot(lo[1] + lane < hi[1] && genome[1] < gb));
-}
-
-// The window of genome g: 64 positions around g n / P.
-__device__ __forceinline__ int edits_window(int n, int P, int g) {
-    const long long mid = (long long)g * n / P;
-    return (int)max(0ll, min((long long)n - WAVE, mid - WAVE / 2 + 4));
-}
+    __device__ __forceinline__ void request(int to0, int to1) {
+        to[0] = to0, to[1] = to1;
+        const long long t = lane < 32 ? to0 : to1;
+        const int k = lane & 31;
+        probe = 0x7fffffff;
+        if (k < height) probe = load((t >> (7 + k) << (7 + k)) + (64ll << k) - 1);
+    }
+    // first index whose genome is >= key
+    __device__ __forceinline__ int search(int w, int key) const {
+        const unsigned right = (unsigned)(__ballot(probe < key) >> (32 * w));
+        const unsigned off = right ^ (unsigned)(to[w] / WAVE);
+        if (!off) return start(to[w]) + __popcll(__ballot(block[w] < key));
+        int k = 31 - __clz((int)off);
+        long long lo = (long long)to[w] >> (7 + k) << (7 + k);
+        lo += (long long)((right >> k) & 1u) << (6 + k);
+        while (k > 0) {
+            const int steps = min(k, 6);
+            k -= steps;
+            const unsigned long long below =
+                __ballot(lane + 1 < 1 << steps &&
+                         load(lo + ((long long)(lane + 1) << (6 + k)) - 1) < key);
+            int s = 0;
+            for (int b = steps - 1; b >= 0; --b)
+                s += (int)((below >> (s + (1 << b) - 1)) & 1ull) << b;
+            lo += (long long)s << (6 + k);
+        }
+        return (int)lo + __popcll(__ballot(load(lo + lane) < key));
+    }
+};
 
 __device__ __forceinline__ int lane_int(int v, int i) { return __builtin_amdgcn_readlane(v, i); }
 // One bit per row of a tensor whose key is NaN, 64 rows per chunk: in scalar
@@ -821,26 +829,31 @@ __global__ __launch_bounds__(WAVE *EDIT_WAVES) void edit_kernel(EditLaunch L) {
     NanRows<CC> nc;
     nn.lds = edit_lds + (size_t)wave * L.mask_words;
     nc.lds = nn.lds + (N + WAVE - 1) / WAVE;
+    EditTree tree;
+    tree.e = L.edits, tree.n = n, tree.height = L.height, tree.lane = lane;
     EditLanes rec;
     int at = -WAVE;  // the position of lane 0's record
     const int front = L.edits[0].genome, back = L.edits[n - 1].genome;
     // records and the rows' keys, requested beside the search where most
     // genomes have edits
+    tree.request((int)((long long)g * n / L.P), min((int)((long long)(g + 1) * n / L.P), n - 1));
+    const int here = EditTree::start(tree.to[0]), next = EditTree::start(tree.to[1]);
     if (L.prefetch) {
-        at = edits_window(n, L.P, g);
+        at = here;
         rec.load(L.edits, at, n, lane);
+        tree.block[0] = at + lane < n ? rec.genome : 0x7fffffff;
+        tree.block[1] = next == here ? tree.block[0] : tree.load((long long)next + lane);
         nn.load(gn, 5, N, lane);
         if (C > 0) nc.load(gc, 4, C, lane);
+    } else {
+        tree.block[0] = tree.load((long long)here + lane);
+        tree.block[1] = next == here ? tree.block[0] : tree.load((long long)next + lane);
     }
     // this genome's part [lo, lo1) of the list, and all genomes' [lo0, loP): whole
     // unless its ends are out of range
-    int lo, lo1, lo0 = 0, loP = n;
-    edits_search(L.edits, n, g, g + 1, lane, &lo, &lo1);
-    if (front < 0 || back >= L.P) {
-        int a, b;
-        edits_search(L.edits, n, 0, L.P, lane, &a, &b);
-        lo0 = front < 0 ? a : 0, loP = back >= L.P ? b : n;
-    }
+    int lo = tree.search(0, g), lo1 = tree.search(1, g + 1), lo0 = 0, loP = n;
+    if (front < 0) lo0 = tree.search(0, 0);
+    if (back >= L.P) loP = tree.search(1, L.P);
     if (g == 0) lo = lo0;
     if (g == L.P - 1) lo1 = loP;
     int e = lo;  // the genome's run continues at e
@@ -976,6 +989,8 @@ hipError_t edit_launch(EditLaunch L, hipStream_t stream) {
         return hipGetLastError();
     }
     L.prefetch = L.n >= L.P;
+    L.height = 0;
+    while ((long long)L.n > (long long)WAVE << L.height) ++L.height;
     const dim3 grid((unsigned)(((long long)L.P + EDIT_WAVES - 1) / EDIT_WAVES));
     const dim3 block(WAVE * EDIT_WAVES);
     if (L.N <= WAVE && L.C <= WAVE * EDIT_CHUNKS) {
