@@ -355,7 +355,7 @@ class Server:
                         tune_cache_path.encode() if tune_cache_path else None)
         self._h = ctypes.c_void_p(None)
         self._guard = threading.Condition()
-        self._waiting = []  # threads in wait
+        self._waiting = []  # threads in wait (changed under the interpreter lock)
         self._closing = False
         check(lib().neat_server_create(ctypes.byref(cfg), ctypes.byref(self._h)))
 
@@ -436,14 +436,15 @@ class Server:
         res = Result()
         slot = ctypes.byref(res)
         fn = lib().neat_wait
-        if check(fn(self._h, ticket, 0, slot)) == 0:
-            return res
-        t_end = time.monotonic() + timeout_s
-        # close destroys the server once no thread is listed
+        # close says so first and destroys the server once no thread is listed; a
+        # look that comes after that meets its word or no server
         me = threading.get_ident()
-        with self._guard:
-            self._waiting.append(me)
+        self._waiting.append(me)
         try:
+            if not (self._closing and self._h.value):
+                if check(fn(self._h, ticket, 0, slot)) == 0:
+                    return res
+                t_end = time.monotonic() + timeout_s
             while not self._closing:
                 # blocks without the interpreter lock, in slices that let signals in
                 left = t_end - time.monotonic()
@@ -452,9 +453,10 @@ class Server:
                 if time.monotonic() > t_end:
                     raise TimeoutError("ticket %d not done after %.1fs" % (ticket, timeout_s))
         finally:
-            with self._guard:
-                self._waiting.remove(me)
-                self._guard.notify_all()
+            self._waiting.remove(me)
+            if self._closing:
+                with self._guard:
+                    self._guard.notify_all()
         raise NeatError(NEAT_E_SHUTDOWN, "the server was closed while ticket %d waited" % ticket)
 
     def stats(self) -> Stats:

@@ -96,3 +96,28 @@ def test_wait_times_out(monkeypatch):
     server = neat.Server()
     with pytest.raises(TimeoutError):
         server.wait(7, timeout_s=0.01)
+
+
+def test_close_waits_for_a_first_look(monkeypatch):
+    """A thread on its way through wait's first look at the ticket counts too."""
+    fake = FakeLib()
+    sleeping = fake.neat_wait
+    fake.neat_wait = lambda h, ticket, us, res: sleeping(h, ticket, max(us, 200000), res)
+    monkeypatch.setattr(neat, "lib", lambda: fake)
+    server = neat.Server()
+    errors = []
+
+    def wait():
+        try:
+            server.wait(7, timeout_s=30.0)
+        except neat.NeatError as e:
+            errors.append(e.code)
+
+    t = threading.Thread(target=wait)
+    t.start()
+    while fake.inside == 0:
+        time.sleep(0.001)
+    server.close()
+    t.join(5.0)
+    assert fake.inside_at_destroy == 0 and fake.after_destroy == []
+    assert errors == [neat.NEAT_E_SHUTDOWN]
