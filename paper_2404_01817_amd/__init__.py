@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import threading
+import time
 from typing import Optional, Tuple
 
 from ._lib import (FWD_AUTO, FWD_LDS, FWD_LVL, FWD_REG, FWD_REG2, FWD_SEG, FWD_TUNED,
@@ -432,7 +433,6 @@ class Server:
         """The Result of a ticket, which is then forgotten; TimeoutError after
         timeout_s, NeatError (NEAT_E_SHUTDOWN) when another thread closes the
         server meanwhile."""
-        import time
         res = Result()
         slot = ctypes.byref(res)
         fn = lib().neat_wait
